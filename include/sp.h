@@ -472,11 +472,12 @@ sp_status sp_pagerank_get_last_stats(sp_pagerank_stats *out);
  * The number of triangles of the graph, each counted once: the count the
  * paper's node iterator produces (for every vertex v, the adjacent pairs
  * (u, w) of neighbours with u < v < w).  The library counts every triangle
- * once at its lowest edge under the (degree, id) order, which bounds the
- * work by O(m^1.5); the number is the same.  The graph must be simple and
- * undirected (each edge stored in both rows once, no self-loops), else
- * SP_ERR_INVALID_ARGUMENT.  The oriented rows (8 bytes per undirected edge +
- * 4 per vertex) are built on the first call and kept with the graph.
+ * once at its lowest-degree vertex, which bounds the work by O(m^1.5); the
+ * number is the same.  The graph must be simple and undirected (each edge
+ * stored in both rows once, no self-loops), else SP_ERR_INVALID_ARGUMENT.
+ * The oriented rows and their index (18 bytes per undirected edge + 16 per
+ * vertex, up to 4 MB of work units) are built on the first call and kept
+ * with the graph.
  * ------------------------------------------------------------------------ */
 
 typedef struct sp_tc_stats {

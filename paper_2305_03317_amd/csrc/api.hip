@@ -816,9 +816,9 @@ sp_status sp_graph_release(sp_graph g) {
         dev_free(g->rp_in);
         dev_free(g->ci_in);
     }
+    dev_free(g->rank_new);  // holds rank_old too
     dev_free(g->tc_orp);
-    dev_free(g->tc_oci);
-    dev_free(g->tc_osrc);
+    dev_free(g->tc_entries);
     dev_free(g->hub_static);
     dev_free(g->owner_static);
     dev_free(g->pr_hubs);

@@ -101,11 +101,25 @@ struct sp_graph_s {
     int32_t *pr_owner = nullptr;         // device, pr_chunks (>= 1)
     int64_t pr_chunks = 0;
     int32_t pr_n_hubs = 0;               // entries of pr_hubs
-    // Triangle counting: rows oriented toward higher (degree, id) rank, built
-    // on first use (ensure_oriented): offsets, entries, and each entry's row.
-    int32_t *tc_orp = nullptr;       // device, n + 1
-    int32_t *tc_oci = nullptr;       // device, tc_m (>= 1)
-    int32_t *tc_osrc = nullptr;      // device, tc_m (>= 1)
+    // Vertices ranked by degree, highest first (ensure_rank_locked): rank of a
+    // vertex, vertex of a rank, and how many have degree >= kRankExact.
+    int32_t *rank_new = nullptr;     // device, n
+    int32_t *rank_old = nullptr;     // device, n
+    int32_t rank_heavy = 0;
+    // Triangle counting (ensure_oriented, on first use), vertices by rank: row
+    // v holds its neighbours of lower rank number (higher degree), ascending,
+    // as 32-bit ids and (where they fit) as 16-bit ones; each entry's row; and
+    // per vertex u the entries that name it, each as {row start, entry}.
+    int32_t *tc_orp = nullptr;       // device, n + 1; its allocation holds tc_iptr too
+    int32_t *tc_iptr = nullptr;      // device, n + 1
+    void *tc_entries = nullptr;      // device allocation of the five arrays below
+    int32_t *tc_oci = nullptr;       // tc_m (+ padding)
+    uint16_t *tc_olo = nullptr;      // tc_m (+ padding): low 16 bits of tc_oci
+    int32_t *tc_osrc = nullptr;      // tc_m (>= 1)
+    int2 *tc_inl = nullptr;          // tc_m (>= 1)
+    int4 *tc_units = nullptr;        // tc_units_n (>= 1): {u, first, end, 0} of tc_inl
+    int32_t tc_units_lo = 0;         // units of vertices below kTcLow, listed first
+    int32_t tc_units_n = 0;
     int64_t tc_m = 0;
     int32_t max_weight = 0;
     size_t weight_bytes = 0;

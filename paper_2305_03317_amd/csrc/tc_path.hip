@@ -5,167 +5,433 @@
 // in a sorted row; each triangle is counted once.  Its work at a vertex is
 // (neighbours below) x (neighbours above): quadratic in the degree of a
 // high-degree vertex.  Here each triangle is instead counted once at its
-// lowest-ranked edge, ranking vertices by (degree, id): N+(v) holds the
-// neighbours of higher rank (a subsequence of v's sorted row, so sorted
-// too), and for every v and u in N+(v) the triangles are the common entries
-// of N+(v) and N+(u).  A vertex has at most sqrt(2m) neighbours of higher
-// rank, so the work is bounded by O(m^1.5) whatever the degree mix.  The
-// count is the same number the paper's loops produce.
+// vertex of lowest degree.  Vertices are renumbered by rank, heaviest first
+// (rank.hip), and N(v) holds the neighbours of lower rank number, ascending; a
+// triangle {w < u < v} is a pair (w, u) of N(v) with w in N(u).  A vertex has
+// at most about sqrt(2m) heavier neighbours, so the work is bounded by
+// O(m^1.5) whatever the degree mix.  The count is the same number the paper's
+// loops produce.
 //
-// Kernels: the oriented rows are built once per graph (out-degree by rank,
-// a two-level scan, a filtering copy that also records each oriented entry's
-// row; rows longer than kHubDeg are counted and copied by a block each), then
-// each oriented entry (v, u) intersects N+(v) and N+(u) (both sorted) by
-// binary-searching the elements of the shorter list in the longer one: by
-// its own lane when the shorter list is short, else by the whole wave.
-// Lane counts are summed per block in a fixed order and added with one
-// 64-bit atomic.
+// Counting goes by the middle vertex u: its N(u) is marked in a bitmap in
+// LDS, and for every entry (v, u) that names it, the entries of N(v) before u
+// are streamed past the bitmap, one bit test each.  rmat-22: 7.2 G tests,
+// read as 16-bit ids (u < 65536: 97% of the tests), 15 GB, instead of 11.8 G
+// binary searches of about ten dependent loads each.
+//
+// The oriented rows are built once per graph: row lengths, a scan, a
+// compacting copy, each row sorted (in registers, through an LDS bitmap, or by
+// a bitonic network), the entries that name each vertex, and the work units.
+#include <utility>
+
 #include "common.h"
 #include "devutil.h"
 #include "levels.h"
+#include "rank.h"
 
 namespace sp {
 
 namespace {
-constexpr int kScanTile = 1024;  // vertices per scan tile (256 threads x 4)
-}
+constexpr int32_t kTcLow = 1 << 16;    // ids below stream as 16-bit values
+constexpr int32_t kTcBits = 1 << 18;   // ids below are counted with an LDS bitmap
+constexpr int32_t kTcLanes = 16;       // lanes per entry
+constexpr int32_t kTcUnit = 512;       // entries naming u per work unit
+constexpr int32_t kTcPosCap = 4096;    // per-vertex counts of N(u) kept in LDS up to this length
+constexpr int32_t kTcSortBits = 1 << 19;  // rows of lower ids are sorted through a bitmap of this size
+constexpr int32_t kTcHot = 4096;      // ids whose names are counted in LDS first
+constexpr int32_t kTcNamedTile = 1 << 15;
+constexpr int32_t kTcSortCap = 8192;   // bitonic rows (a row of a higher id holds under 4,400 entries)
+}  // namespace
 
 // rank(a) < rank(b): lower degree, ties broken by id.
 __device__ __forceinline__ bool rank_below(int32_t da, int32_t a, int32_t db, int32_t b) {
     return da < db || (da == db && a < b);
 }
 
-// Out-degree under the rank order of every vertex whose row is at most
-// kHubDeg long (a lane per vertex); longer rows are left to k_tc_hub_outdeg.
-__global__ void k_tc_outdeg(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci, int32_t n,
-                            int32_t *odeg) {
-    const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        const int32_t b = rp[v], e = rp[v + 1], dv = e - b;
-        if (dv > kHubDeg) continue;
+// Whether a vertex is counted with an LDS bitmap.  Marking and clearing one
+// costs a few microseconds of a block, so it takes some entries that name u
+// to pay (rmat-22: from 32 on 7.0 ms, from 16 6.5, from 8 6.2); the rest go
+// entry by entry (k_tc_light), as do ids whose bitmap would not fit.
+__device__ __forceinline__ bool tc_heavy(int32_t u, int32_t named) { return u < kTcBits && named >= 8; }
+
+// The heavier neighbours of the ranked vertices [first, n): calls
+// f(keep, v, w) for every entry, 16 lanes per row, or (BLOCK) a block per row.
+template <bool BLOCK, class F>
+__device__ __forceinline__ void tc_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                                        const int32_t *__restrict__ rank_new,
+                                        const int32_t *__restrict__ rank_old, int32_t first, int32_t n, F f) {
+    constexpr int per = BLOCK ? 256 : 16;
+    const int64_t stride = BLOCK ? gridDim.x : (int64_t)gridDim.x * (256 / per);
+    for (int64_t v = first + (BLOCK ? (int64_t)blockIdx.x
+                                    : (int64_t)blockIdx.x * (256 / per) + threadIdx.x / per);
+         v < n; v += stride) {
+        const int32_t old = rank_old[v];
+        const int32_t b = rp[old], e = rp[old + 1];
+        f((int32_t)v, old, b, e);
+    }
+}
+
+// Row lengths: odeg[v] = neighbours of v of lower rank number.  exact: how
+// many entries rise in the (degree, id) order, which is half of them exactly
+// when a graph is simple and undirected (the two orders differ only between
+// vertices of degree >= kRankExact).
+template <bool BLOCK>
+__global__ __launch_bounds__(256) void k_tc_outdeg(const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ ci,
+                                                   const int32_t *__restrict__ rank_new,
+                                                   const int32_t *__restrict__ rank_old, int32_t first,
+                                                   int32_t n, int32_t heavy, int32_t *odeg,
+                                                   unsigned long long *exact) {
+    __shared__ unsigned long long s_red[1];
+    __shared__ int32_t s_sum;
+    constexpr int per = BLOCK ? 256 : 16;
+    const int l = threadIdx.x % per;
+    unsigned long long ex = 0;
+    tc_rows<BLOCK>(rp, ci, rank_new, rank_old, first, n, [&](int32_t v, int32_t old, int32_t b, int32_t e) {
         int32_t d = 0;
-        for (int32_t k = b; k < e; ++k) {
-            const int32_t u = ci[k];
-            d += rank_below(dv, v, rp[u + 1] - rp[u], u);
+        for (int32_t k = b + l; k < e; k += per) {
+            const int32_t w = ci[k], r = rank_new[w];
+            d += r < v;
+            if (v < heavy && r < heavy) ex += rank_below(e - b, old, rp[w + 1] - rp[w], w);
+            else ex += r < v;
         }
-        odeg[v] = d;
-    }
-}
-
-// Out-degree of the hubs: a block per hub row.
-__global__ __launch_bounds__(256) void k_tc_hub_outdeg(const int32_t *__restrict__ rp,
-                                                       const int32_t *__restrict__ ci,
-                                                       const HubEntry *__restrict__ hubs, int32_t nh,
-                                                       int32_t *odeg) {
-    __shared__ int32_t s_scan[256 / kWave + 1];
-    for (int32_t j = blockIdx.x; j < nh; j += gridDim.x) {
-        const int32_t v = hubs[j].v;
-        const int32_t b = rp[v], e = rp[v + 1], dv = e - b;
-        int32_t d = 0;
-        for (int32_t k = b + threadIdx.x; k < e; k += 256) {
-            const int32_t u = ci[k];
-            d += rank_below(dv, v, rp[u + 1] - rp[u], u);
+        if (BLOCK) {
+            if (threadIdx.x == 0) s_sum = 0;
+            __syncthreads();
+            if (d) atomicAdd(&s_sum, d);
+            __syncthreads();
+            if (threadIdx.x == 0) odeg[v] = s_sum;
+            __syncthreads();
+        } else {
+            for (int o = 8; o > 0; o >>= 1) d += __shfl_xor(d, o, kWave);
+            if (l == 0) odeg[v] = d;
         }
-        int32_t total;
-        (void)block_excl_scan<256>(d, s_scan, &total);
-        if (threadIdx.x == 0) odeg[v] = total;
-        __syncthreads();
-    }
+    });
+    block_add_u64<256>(ex, s_red, exact);
 }
 
-// Exclusive scan of the out-degrees within tiles of kScanTile vertices:
-// odeg_off[v] = offset of v inside its tile; tile_sum[t] = the tile's total.
-__global__ __launch_bounds__(256) void k_tc_scan_local(const int32_t *__restrict__ odeg, int32_t n,
-                                                       int32_t *odeg_off, int32_t *tile_sum) {
-    __shared__ int32_t s_scan[256 / kWave + 1];
-    const int32_t v0 = blockIdx.x * kScanTile + threadIdx.x * 4;
-    int32_t d[4];
-    int32_t mine = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        d[q] = v0 + q < n ? odeg[v0 + q] : 0;
-        mine += d[q];
-    }
-    int32_t total;
-    int32_t off = block_excl_scan<256>(mine, s_scan, &total);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (v0 + q < n) odeg_off[v0 + q] = off;
-        off += d[q];
-    }
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
-}
-
-// Exclusive scan of the tile totals in place (one block), and the entry count.
-__global__ __launch_bounds__(256) void k_tc_scan_tiles(int32_t *tile_sum, int32_t ntiles,
-                                                       int32_t *orp, int32_t n) {
-    __shared__ int32_t s_scan[256 / kWave + 1];
-    int32_t carry = 0;
-    for (int32_t b = 0; b < ntiles; b += 256) {
-        const int32_t i = b + threadIdx.x;
-        const int32_t x = i < ntiles ? tile_sum[i] : 0;
-        int32_t total;
-        const int32_t off = block_excl_scan<256>(x, s_scan, &total);
-        if (i < ntiles) tile_sum[i] = carry + off;
-        carry += total;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) orp[n] = carry;
-}
-
-// Oriented rows of the vertices with rows of at most kHubDeg entries (a lane
-// per vertex): orp[v] = tile base + offset in tile; N+(v) copied in row
-// order, with each entry's row in osrc.
-__global__ void k_tc_fill(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci, int32_t n,
-                          const int32_t *__restrict__ odeg_off, const int32_t *__restrict__ tile_base,
-                          int32_t *orp, int32_t *oci, int32_t *osrc) {
-    const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        int32_t o = tile_base[v / kScanTile] + odeg_off[v];
-        orp[v] = o;
-        const int32_t b = rp[v], e = rp[v + 1], dv = e - b;
-        if (dv > kHubDeg) continue;
-        for (int32_t k = b; k < e; ++k) {
-            const int32_t u = ci[k];
-            if (rank_below(dv, v, rp[u + 1] - rp[u], u)) {
-                oci[o] = u;
-                osrc[o] = v;
-                ++o;
-            }
-        }
-    }
-}
-
-// Oriented rows of the hubs: a block per hub compacts the row's
-// higher-ranked entries in row order (block scan per 256 entries).
-__global__ __launch_bounds__(256) void k_tc_hub_fill(const int32_t *__restrict__ rp,
-                                                     const int32_t *__restrict__ ci,
-                                                     const HubEntry *__restrict__ hubs, int32_t nh,
-                                                     const int32_t *__restrict__ odeg_off,
-                                                     const int32_t *__restrict__ tile_base,
-                                                     int32_t *oci, int32_t *osrc) {
-    __shared__ int32_t s_scan[256 / kWave + 1];
-    for (int32_t j = blockIdx.x; j < nh; j += gridDim.x) {
-        const int32_t v = hubs[j].v;
-        const int32_t b = rp[v], e = rp[v + 1], dv = e - b;
-        int32_t o = tile_base[v / kScanTile] + odeg_off[v];
-        for (int32_t k0 = b; k0 < e; k0 += 256) {
-            const int32_t k = k0 + threadIdx.x;
-            int32_t u = 0;
-            bool keep = false;
-            if (k < e) {
-                u = ci[k];
-                keep = rank_below(dv, v, rp[u + 1] - rp[u], u);
-            }
-            int32_t total;
-            const int32_t off = block_excl_scan<256>((int32_t)keep, s_scan, &total);
-            if (keep) {
-                oci[o + off] = u;
-                osrc[o + off] = v;
-            }
-            o += total;
+// Rows in any order within a row (they are sorted next), each entry's row.
+template <bool BLOCK>
+__global__ __launch_bounds__(256) void k_tc_fill(const int32_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ ci,
+                                                 const int32_t *__restrict__ rank_new,
+                                                 const int32_t *__restrict__ rank_old, int32_t first,
+                                                 int32_t n, const int32_t *__restrict__ orp, int32_t *oci,
+                                                 int32_t *osrc) {
+    __shared__ int32_t s_at;
+    constexpr int per = BLOCK ? 256 : 16;
+    const int l = threadIdx.x % per;
+    const int lane = lane_id();
+    tc_rows<BLOCK>(rp, ci, rank_new, rank_old, first, n, [&](int32_t v, int32_t, int32_t b, int32_t e) {
+        int32_t at = orp[v];
+        if (BLOCK) {
+            if (threadIdx.x == 0) s_at = at;
             __syncthreads();
         }
+        for (int32_t k0 = b; k0 < e; k0 += per) {
+            const int32_t k = k0 + l;
+            const int32_t r = k < e ? rank_new[ci[k]] : INT32_MAX;
+            const bool keep = r < v;
+            const unsigned long long m = __ballot(keep);
+            int32_t p = 0;
+            if (BLOCK) {
+                if (m) {
+                    const int leader = __ffsll((long long)m) - 1;
+                    if (lane == leader) p = atomicAdd(&s_at, __popcll(m));
+                    p = shfl_i32(p, leader) + lanes_below(m);
+                }
+            } else {
+                const unsigned int g = (unsigned int)(m >> (lane & 48)) & 0xffffu;
+                p = at + __popc(g & ((1u << l) - 1u));
+                at += __popc(g);
+            }
+            if (keep) {
+                oci[p] = r;
+                osrc[p] = v;
+            }
+        }
+        if (BLOCK) __syncthreads();
+    });
+}
+
+// Rows of 2..64 entries sorted by a wave each (an entry's place is the number
+// of smaller ones); longer rows listed for the block kernels.
+__global__ __launch_bounds__(256) void k_tc_sort_small(const int32_t *__restrict__ orp, int32_t n, int32_t *oci,
+                                                       int32_t *big, int32_t *nbig) {
+    const int lane = lane_id();
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t v0 = (int64_t)blockIdx.x * 256 + threadIdx.x - lane; v0 < n; v0 += stride) {
+        const int64_t v = v0 + lane;
+        int32_t b = 0, len = 0;
+        if (v < n) {
+            b = orp[v];
+            len = orp[v + 1] - b;
+        }
+        const unsigned long long more = __ballot(len > kWave);
+        if (more) {
+            const int leader = __ffsll((long long)more) - 1;
+            int32_t at = 0;
+            if (lane == leader) at = atomicAdd(nbig, __popcll(more));
+            at = shfl_i32(at, leader);
+            if (len > kWave) big[at + lanes_below(more)] = (int32_t)v;
+        }
+        unsigned long long todo = __ballot(len >= 2 && len <= kWave);
+        while (todo) {
+            const int src = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int32_t rb = __builtin_amdgcn_readlane(b, src), rl = __builtin_amdgcn_readlane(len, src);
+            const int32_t x = lane < rl ? oci[rb + lane] : INT32_MAX;
+            int32_t place = 0;
+            for (int32_t j = 0; j < rl; ++j) {
+                const int32_t y = __builtin_amdgcn_readlane(x, j);
+                place += y < x || (y == x && j < lane);
+            }
+            if (lane < rl) oci[rb + place] = x;
+        }
+    }
+}
+
+// Rows of more than 64 entries and ids in [lo, hi), hi <= 32 * WORDS: marked
+// in a bitmap, read back in order.  Entries stored twice (not a simple graph)
+// leave a shorter row, whose tail repeats its last entry.
+template <int WORDS>
+__global__ __launch_bounds__(256) void k_tc_sort_bits(const int32_t *__restrict__ orp, int32_t *oci,
+                                                      const int32_t *__restrict__ big,
+                                                      const int32_t *__restrict__ nbig, int32_t lo, int32_t hi) {
+    __shared__ uint32_t s_bits[WORDS];
+    __shared__ int32_t s_scan[256 / kWave + 1], s_last;
+    const int32_t nb = *nbig;
+    for (int32_t j = blockIdx.x; j < nb; j += gridDim.x) {
+        const int32_t v = big[j];
+        if (v < lo || v >= hi) continue;
+        const int32_t b = orp[v], len = orp[v + 1] - b;
+        const int32_t words = (v + 31) >> 5;  // the row's ids are below v
+        for (int32_t i = threadIdx.x; i < words; i += 256) s_bits[i] = 0;
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < len; i += 256) {
+            const int32_t w = oci[b + i];
+            atomicOr(&s_bits[w >> 5], 1u << (w & 31));
+        }
+        __syncthreads();
+        const int32_t per = (words + 255) / 256;
+        const int32_t i0 = min(words, (int32_t)threadIdx.x * per), i1 = min(words, i0 + per);
+        int32_t mine = 0;
+        for (int32_t i = i0; i < i1; ++i) mine += __popc(s_bits[i]);
+        int32_t total;
+        int32_t at = b + block_excl_scan<256>(mine, s_scan, &total);
+        for (int32_t i = i0; i < i1; ++i)
+            for (uint32_t m = s_bits[i]; m; m &= m - 1) {
+                const int32_t w = i * 32 + __ffs(m) - 1;
+                oci[at++] = w;
+                if (at == b + total) s_last = w;
+            }
+        __syncthreads();
+        for (int32_t i = total + threadIdx.x; i < len; i += 256) oci[b + i] = s_last;
+        __syncthreads();
+    }
+}
+
+// Rows of more than 64 entries and ids from kTcSortBits up: such a vertex has
+// at least kTcSortBits heavier ones, so its degree, and its row, stays under
+// kTcSortCap (fewer than 2^31 entries in all).
+__global__ __launch_bounds__(256) void k_tc_sort_net(const int32_t *__restrict__ orp, int32_t *oci,
+                                                     const int32_t *__restrict__ big,
+                                                     const int32_t *__restrict__ nbig, int32_t lo) {
+    __shared__ int32_t s_x[kTcSortCap];
+    const int32_t nb = *nbig;
+    for (int32_t j = blockIdx.x; j < nb; j += gridDim.x) {
+        const int32_t v = big[j];
+        if (v < lo) continue;
+        const int32_t b = orp[v], len = min(orp[v + 1] - b, kTcSortCap);
+        int32_t size = 128;
+        while (size < len) size <<= 1;
+        for (int32_t i = threadIdx.x; i < size; i += 256) s_x[i] = i < len ? oci[b + i] : INT32_MAX;
+        __syncthreads();
+        for (int32_t k = 2; k <= size; k <<= 1)
+            for (int32_t d = k >> 1; d > 0; d >>= 1) {
+                for (int32_t i = threadIdx.x; i < size; i += 256) {
+                    const int32_t p = i ^ d;
+                    if (p > i) {
+                        const int32_t x = s_x[i], y = s_x[p];
+                        if ((x > y) == ((i & k) == 0)) {
+                            s_x[i] = y;
+                            s_x[p] = x;
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+        for (int32_t i = threadIdx.x; i < len; i += 256) oci[b + i] = s_x[i];
+        __syncthreads();
+    }
+}
+
+// 16-bit copies of the sorted entries, and each entry's place among those
+// that name the same vertex (any order: only sums are formed over them).  The
+// heaviest vertices are named by most rows, so a block first counts the names
+// of the ids below kTcHot in its tile in LDS and reserves each id's places
+// with one atomic (rmat-22: 41% of the entries; 7.1 ms with an atomic each).
+__global__ __launch_bounds__(256) void k_tc_named(const int32_t *__restrict__ oci, int64_t m, uint16_t *olo,
+                                                  int32_t *named, int32_t *slot) {
+    __shared__ int32_t s_at[kTcHot];
+    for (int64_t t0 = (int64_t)blockIdx.x * kTcNamedTile; t0 < m; t0 += (int64_t)gridDim.x * kTcNamedTile) {
+        const int64_t t1 = min(m, t0 + kTcNamedTile);
+        for (int32_t i = threadIdx.x; i < kTcHot; i += 256) s_at[i] = 0;
+        __syncthreads();
+        for (int64_t e = t0 + threadIdx.x; e < t1; e += 256) {
+            const int32_t u = oci[e];
+            olo[e] = (uint16_t)u;
+            if (u < kTcHot) atomicAdd(&s_at[u], 1);
+            else slot[e] = atomicAdd(&named[u], 1);
+        }
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < kTcHot; i += 256)
+            if (s_at[i]) s_at[i] = atomicAdd(&named[i], s_at[i]);
+        __syncthreads();
+        for (int64_t e = t0 + threadIdx.x; e < t1; e += 256) {
+            const int32_t u = oci[e];
+            if (u < kTcHot) slot[e] = atomicAdd(&s_at[u], 1);
+        }
+        __syncthreads();
+    }
+}
+
+__global__ void k_tc_inlist(const int32_t *__restrict__ oci, const int32_t *__restrict__ osrc,
+                            const int32_t *__restrict__ orp, const int32_t *__restrict__ iptr,
+                            const int32_t *__restrict__ slot, int64_t m, int2 *inl) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += stride)
+        inl[iptr[oci[e]] + slot[e]] = make_int2(orp[osrc[e]], (int32_t)e);
+}
+
+// Work units of the vertices counted with a bitmap.
+__global__ void k_tc_unit_count(const int32_t *__restrict__ iptr, int32_t nu, int32_t *cnt) {
+    const int32_t stride = gridDim.x * blockDim.x;
+    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nu; u += stride) {
+        const int32_t named = iptr[u + 1] - iptr[u];
+        cnt[u] = tc_heavy(u, named) ? (named + kTcUnit - 1) / kTcUnit : 0;
+    }
+}
+
+__global__ void k_tc_unit_fill(const int32_t *__restrict__ iptr, int32_t nu, const int32_t *__restrict__ first,
+                               int4 *units, int64_t cap) {
+    const int32_t stride = gridDim.x * blockDim.x;
+    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nu; u += stride) {
+        const int32_t b = iptr[u], e = iptr[u + 1];
+        for (int32_t k = first[u], j = b; k < first[u + 1] && k < cap; ++k, j += kTcUnit)
+            units[k] = make_int4(u, j, min(e, j + kTcUnit), 0);
+    }
+}
+
+// Triangles by their middle vertex.  A block takes a unit {u, entries naming
+// u}: N(u) goes into the bitmap, and 16 lanes per entry (v, u) stream N(v)'s
+// entries before u, four per lane and load (LO: 16-bit ids, 8 bytes a lane).
+// Bound by reading those entries (each row comes from L2 or the Infinity
+// Cache once per heavier neighbour); eight waves per SIMD and two loads a lane
+// in flight cover the latency, and 256 threads with a 8 KB bitmap leave room
+// for them.  PER: per-vertex counts; hits on w are counted at w's place in
+// N(u) (s_first: the row position of a bitmap word's first entry) and added
+// once per unit.
+template <int BITS, bool LO, bool PER>
+__global__ __launch_bounds__(256) void k_tc_heavy(const int32_t *__restrict__ orp,
+                                                  const int32_t *__restrict__ oci,
+                                                  const uint16_t *__restrict__ olo,
+                                                  const int32_t *__restrict__ osrc,
+                                                  const int2 *__restrict__ inl,
+                                                  const int4 *__restrict__ units, int32_t nunits,
+                                                  const int32_t *__restrict__ rank_old,
+                                                  unsigned long long *total, unsigned long long *per,
+                                                  unsigned long long *prof) {
+    constexpr int kWords = BITS / 32;
+    __shared__ uint32_t s_bits[kWords];
+    __shared__ uint16_t s_first[PER ? kWords : 1];
+    __shared__ uint32_t s_cnt[PER ? kTcPosCap : 1];
+    __shared__ int2 s_in[256];
+    __shared__ unsigned long long s_red[1];
+    const int l = threadIdx.x % kTcLanes, grp = threadIdx.x / kTcLanes;
+    unsigned long long hits = 0, tests = 0;
+    for (int32_t i = threadIdx.x; i < kWords; i += 256) s_bits[i] = 0;
+    for (int32_t k = blockIdx.x; k < nunits; k += gridDim.x) {
+        const int4 unit = units[k];
+        const int32_t ub = orp[unit.x], un = orp[unit.x + 1] - ub;
+        const bool pos = PER && un <= kTcPosCap;
+        __syncthreads();  // the bitmap is clear
+        for (int32_t i = threadIdx.x; i < un; i += 256) {
+            const int32_t w = oci[ub + i];
+            atomicOr(&s_bits[w >> 5], 1u << (w & 31));
+            if (PER && pos) {
+                if (i == 0 || (oci[ub + i - 1] >> 5) != (w >> 5)) s_first[w >> 5] = (uint16_t)i;
+                s_cnt[i] = 0;
+            }
+        }
+        unsigned long long unit_hits = 0;
+        for (int32_t j0 = unit.y; j0 < unit.z; j0 += 256) {
+            const int32_t nin = min(256, unit.z - j0);
+            if ((int32_t)threadIdx.x < nin) s_in[threadIdx.x] = inl[j0 + threadIdx.x];
+            __syncthreads();
+            for (int32_t q = grp; q < nin; q += 256 / kTcLanes) {
+                const int2 in = s_in[q];
+                const int32_t b = in.x, e = in.y;  // entries [b, e) of N(v)
+                uint32_t found = 0;
+                // one bit of the result per entry; entries outside [b, e) masked off
+                auto test4 = [&](const uint4 &x, int32_t at) {
+                    const uint32_t w4[4] = {x.x, x.y, x.z, x.w};
+                    uint32_t bits[4], hit = 0;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) bits[t] = s_bits[(w4[t] >> 5) & (kWords - 1)];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) hit |= ((bits[t] >> (w4[t] & 31)) & 1u) << t;
+                    hit &= (0xfu >> max(0, at + 4 - e)) & (0xfu << max(0, b - at));
+                    found += __popc(hit);
+                    if (PER) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if ((hit >> t) & 1u) {
+                                const uint32_t w = LO ? w4[t] & 0xffffu : w4[t];
+                                const int32_t p = s_first[w >> 5] + __popc(bits[t] & ((1u << (w & 31)) - 1u));
+                                if (pos && p < kTcPosCap) atomicAdd(&s_cnt[p], 1u);
+                                else atomicAdd(&per[rank_old[w]], 1ull);
+                            }
+                    }
+                };
+                auto load4 = [&](int32_t at) {  // LO: odd ids keep the next one above them (masked where used)
+                    if (LO) {
+                        const uint2 x = *reinterpret_cast<const uint2 *>(olo + at);
+                        return make_uint4(x.x, x.x >> 16, x.y, x.y >> 16);
+                    }
+                    return *reinterpret_cast<const uint4 *>(oci + at);
+                };
+                for (int32_t at = (b & ~3) + 4 * l; at < e; at += 8 * kTcLanes) {
+                    const int32_t at2 = at + 4 * kTcLanes < e ? at + 4 * kTcLanes : at;
+                    const uint4 x = load4(at), y = load4(at2);
+                    test4(x, at);
+                    if (at2 != at) test4(y, at2);
+                }
+                if (prof && l == 0) tests += (unsigned long long)(e - b);
+                if (PER) {
+                    uint32_t f = found;
+                    for (int o = kTcLanes / 2; o > 0; o >>= 1) f += __shfl_xor(f, o, kWave);
+                    if (l == 0 && f) atomicAdd(&per[rank_old[osrc[e]]], (unsigned long long)f);
+                }
+                unit_hits += found;
+            }
+            __syncthreads();
+        }
+        hits += unit_hits;
+        if (PER) {
+            unit_hits = wave_sum_u64(unit_hits);
+            if (lane_id() == 0 && unit_hits) atomicAdd(&per[rank_old[unit.x]], unit_hits);
+        }
+        for (int32_t i = threadIdx.x; i < un; i += 256) {
+            const int32_t w = oci[ub + i];
+            s_bits[w >> 5] = 0;
+            if (PER && pos && s_cnt[i]) atomicAdd(&per[rank_old[w]], (unsigned long long)s_cnt[i]);
+        }
+    }
+    __syncthreads();
+    block_add_u64<256>(hits, s_red, total);
+    if (prof) {
+        __syncthreads();
+        block_add_u64<256>(tests, s_red, prof + 1);
     }
 }
 
@@ -179,81 +445,76 @@ __device__ __forceinline__ int32_t lower_bound(const int32_t *__restrict__ a, in
     return lo;
 }
 
-// |N+(v) & N+(u)| for the oriented entries of a wave (64 consecutive
-// entries, one per lane).  An entry whose shorter list has at most
-// kTcLaneWork elements is intersected by its own lane, which walks the
-// shorter list and binary-searches each element in the longer one, the
-// window shrinking as the walk moves up.  Longer ones are taken by the whole
-// wave in turn: lane j searches elements j, j + 64, ... of the shorter list
-// in the whole longer one.  With `per` the three vertices of every triangle
-// found get one count each.
-constexpr int32_t kTcLaneWork = 32;
+// Triangles whose middle vertex u has no bitmap: a wave takes kTcLightIds
+// consecutive vertices, and 16 lanes per entry (v, u) that names one of them
+// search the elements of the shorter of N(u) and N(v)'s entries before u in
+// the longer.  Few entries and short lists, so it is a matter of latency: the
+// first form, an entry per lane and 64 vertices per wave, left a few waves
+// with thousands of dependent searches (rmat-22: 3.0 ms).
+constexpr int32_t kTcLightIds = 16;
 
-template <int BS>
-__global__ __launch_bounds__(BS) void k_tc_count(const int32_t *__restrict__ orp,
-                                                 const int32_t *__restrict__ oci,
-                                                 const int32_t *__restrict__ osrc, int64_t m,
-                                                 unsigned long long *total,
-                                                 unsigned long long *per, unsigned long long *prof) {
+__global__ __launch_bounds__(256) void k_tc_light(const int32_t *__restrict__ orp,
+                                                  const int32_t *__restrict__ oci,
+                                                  const int32_t *__restrict__ osrc,
+                                                  const int32_t *__restrict__ iptr,
+                                                  const int2 *__restrict__ inl, int32_t n,
+                                                  const int32_t *__restrict__ rank_old,
+                                                  unsigned long long *total, unsigned long long *per,
+                                                  unsigned long long *prof) {
     __shared__ unsigned long long s_red[1];
-    const int lane = lane_id();
-    unsigned long long mine = 0, probes = 0;
-    auto hit = [&](int32_t v, int32_t u, int32_t w) {
-        ++mine;
-        if (per) {
-            atomicAdd(&per[v], 1ull);
-            atomicAdd(&per[u], 1ull);
-            atomicAdd(&per[w], 1ull);
+    const int lane = lane_id(), l = lane & 15, grp = lane >> 4;
+    unsigned long long mine = 0, tests = 0;
+    constexpr int64_t per_block = kTcLightIds * (256 / kWave);
+    const int64_t stride = (int64_t)gridDim.x * per_block;
+    for (int64_t u0 = (int64_t)blockIdx.x * per_block + (threadIdx.x / kWave) * kTcLightIds; u0 < n; u0 += stride) {
+        // lane a (< kTcLightIds) holds vertex u0 + a: its row and where its entries begin and end
+        // in the wave's list
+        const int64_t uu = u0 + min(lane, kTcLightIds - 1);
+        int32_t named = 0, ib = 0, lb = 0, le = 0;
+        if (uu < n && lane < kTcLightIds) {
+            ib = iptr[uu];
+            named = iptr[uu + 1] - ib;
+            lb = orp[uu];
+            le = orp[uu + 1];
+            if (tc_heavy((int32_t)uu, named) || le == lb) named = 0;
         }
-    };
-    const int64_t stride = (int64_t)gridDim.x * BS;
-    for (int64_t e0 = (int64_t)blockIdx.x * BS + threadIdx.x - lane; e0 < m; e0 += stride) {
-        const int64_t e = e0 + lane;
-        int32_t v = 0, u = 0, sb = 0, se = 0, lb = 0, le = 0;
-        if (e < m) {
-            v = osrc[e];
-            u = oci[e];
-            sb = orp[v];
-            se = orp[v + 1];
-            lb = orp[u];
-            le = orp[u + 1];
-            if (se - sb > le - lb) {  // walk the shorter list
-                int32_t t = sb; sb = lb; lb = t;
-                t = se; se = le; le = t;
-            }
-        }
-        const bool alone = se - sb <= kTcLaneWork;
-        if (alone) {
-            int32_t pos = lb;
-            for (int32_t i = sb; i < se && pos < le; ++i) {
-                const int32_t w = oci[i];
-                pos = lower_bound(oci, pos, le, w);
-                ++probes;
-                if (pos < le && oci[pos] == w) {
-                    hit(v, u, w);
-                    ++pos;
+        const int32_t incl = wave_incl_scan(named);
+        const int32_t all = __builtin_amdgcn_readlane(incl, kWave - 1);
+        for (int32_t k0 = 0; k0 < all; k0 += 4) {
+            const int32_t k = k0 + grp;
+            int32_t a = 0;  // the owner: vertices whose entries all lie before k
+#pragma unroll
+            for (int j = 0; j < kTcLightIds - 1; ++j) a += __builtin_amdgcn_readlane(incl, j) <= k;
+            const int32_t end = __shfl(incl, a, kWave), cnt = __shfl(named, a, kWave);
+            const int32_t first = __shfl(ib, a, kWave);
+            int32_t lo = __shfl(lb, a, kWave), hi = __shfl(le, a, kWave);
+            if (k < all) {
+                const int2 in = inl[first + (k - (end - cnt))];
+                int32_t sb = in.x, se = in.y;
+                if (se - sb > hi - lo) {  // walk the shorter list
+                    int32_t t = sb; sb = lo; lo = t;
+                    t = se; se = hi; hi = t;
+                }
+                for (int32_t i = sb + l; i < se; i += 16) {
+                    const int32_t w = oci[i];
+                    const int32_t at = lower_bound(oci, lo, hi, w);
+                    ++tests;
+                    if (at < hi && oci[at] == w) {
+                        ++mine;
+                        if (per) {
+                            atomicAdd(&per[rank_old[osrc[in.y]]], 1ull);
+                            atomicAdd(&per[rank_old[u0 + a]], 1ull);
+                            atomicAdd(&per[rank_old[w]], 1ull);
+                        }
+                    }
                 }
             }
         }
-        unsigned long long big = __ballot(!alone);
-        while (big) {
-            const int src = __ffsll((long long)big) - 1;
-            big &= big - 1;
-            const int32_t bv = __shfl(v, src, kWave), bu = __shfl(u, src, kWave);
-            const int32_t bsb = __shfl(sb, src, kWave), bse = __shfl(se, src, kWave);
-            const int32_t blb = __shfl(lb, src, kWave), ble = __shfl(le, src, kWave);
-            for (int32_t i = bsb + lane; i < bse; i += kWave) {
-                const int32_t w = oci[i];
-                const int32_t pos = lower_bound(oci, blb, ble, w);
-                ++probes;
-                if (pos < ble && oci[pos] == w) hit(bv, bu, w);
-            }
-        }
     }
-    block_add_u64<BS>(mine, s_red, total);
+    block_add_u64<256>(mine, s_red, total);
     if (prof) {
         __syncthreads();
-        block_add_u64<BS>(probes, s_red, prof + 1);
+        block_add_u64<256>(tests, s_red, prof + 1);
     }
 }
 
@@ -265,87 +526,157 @@ __global__ void k_tc_zero(unsigned long long *p, int64_t n) {
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
+namespace {
+// Arrays carved from one device allocation each (an allocation or release
+// costs tens of microseconds, as much as building a small graph's rows);
+// freed unless kept.
+struct TcBlock {
+    void *base = nullptr;
+    size_t bytes = 0;
+    std::vector<std::pair<void **, size_t>> parts;
+    template <class T>
+    void add(T **p, size_t count) {
+        parts.emplace_back((void **)p, bytes);
+        bytes += (sizeof(T) * count + 255) & ~(size_t)255;
+    }
+    sp_status alloc() {
+        SP_TRY(dev_alloc(&base, bytes));
+        for (auto &x : parts) *x.first = (char *)base + x.second;
+        return SP_OK;
+    }
+    ~TcBlock() { dev_free(base); }
+};
+}  // namespace
+
 sp_status ensure_oriented(sp_graph g, hipStream_t s) {
-    SP_TRY(ensure_static_hubs(g, s));
     std::lock_guard<std::mutex> lk(g->mu);
     if (g->tc_orp) return SP_OK;
-    const int32_t n = g->n;
-    const int32_t ntiles = std::max(1, (n + kScanTile - 1) / kScanTile);
+    SP_TRY(ensure_rank_locked(g, s));
+    const int32_t n = g->n, heavy = g->rank_heavy;
     const int maxb = device_cu_count() * 8;
-    int32_t *orp = nullptr, *oci = nullptr, *osrc = nullptr, *odeg = nullptr, *off = nullptr,
-            *tiles = nullptr;
-    auto fail = [&](sp_status st) {
-        dev_free(orp);
-        dev_free(oci);
-        dev_free(osrc);
-        dev_free(odeg);
-        dev_free(off);
-        dev_free(tiles);
-        return st;
-    };
     const size_t vn = (size_t)std::max(n, 1);
-    sp_status st = dev_alloc((void **)&orp, sizeof(int32_t) * (vn + 1));
-    if (st == SP_OK) st = dev_alloc((void **)&odeg, sizeof(int32_t) * vn);
-    if (st == SP_OK) st = dev_alloc((void **)&off, sizeof(int32_t) * vn);
-    if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)ntiles);
-    if (st != SP_OK) return fail(st);
+    const int32_t *rp = g->row_ptr, *ci = g->col_idx, *rn = g->rank_new, *ro = g->rank_old;
+    TcBlock rows, entries, work, places;
+    int32_t *orp, *oci, *osrc, *iptr, *tiles, *big, *slot;
+    uint16_t *olo;
+    int2 *inl;
+    int4 *units;
+    unsigned long long *ctl;  // [0] entries that rise in (degree, id) order, [1] rows over 64
+    rows.add(&orp, vn + 1);
+    rows.add(&iptr, vn + 1);
+    SP_TRY(rows.alloc());
+    work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
+    work.add(&ctl, 2);
+    work.add(&big, vn + 1);
+    SP_TRY(work.alloc());
+    hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)2);
+    const int row_grid = grid_for((int64_t)n - heavy, 16, maxb);
     if (n > 0) {
-        hipLaunchKernelGGL(k_tc_outdeg, dim3(grid_for(n, 256, maxb)), dim3(256), 0, s,
-                           (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, n, odeg);
-        if (g->n_hubs > 0)
-            hipLaunchKernelGGL(k_tc_hub_outdeg, dim3(std::min(g->n_hubs, maxb)), dim3(256), 0, s,
-                               (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx,
-                               (const HubEntry *)g->hub_static, g->n_hubs, odeg);
-        hipLaunchKernelGGL(k_tc_scan_local, dim3(ntiles), dim3(256), 0, s, (const int32_t *)odeg, n, off,
-                           tiles);
+        if (heavy)
+            hipLaunchKernelGGL(k_tc_outdeg<true>, dim3(std::min(heavy, maxb)), dim3(256), 0, s, rp, ci, rn, ro, 0,
+                               heavy, heavy, orp, ctl);
+        hipLaunchKernelGGL(k_tc_outdeg<false>, dim3(row_grid), dim3(256), 0, s, rp, ci, rn, ro, heavy, n, heavy,
+                           orp, ctl);
     }
-    hipLaunchKernelGGL(k_tc_scan_tiles, dim3(1), dim3(256), 0, s, tiles, n > 0 ? ntiles : 0, orp, n);
+    launch_excl_scan(orp, n, orp, tiles, s);
     SP_HIP(hipGetLastError());
     int32_t m = 0;
+    unsigned long long exact = 0;
     SP_HIP(hipMemcpyAsync(&m, orp + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    SP_HIP(hipMemcpyAsync(&exact, ctl, sizeof(exact), hipMemcpyDeviceToHost, s));
     SP_HIP(hipStreamSynchronize(s));
-    if ((int64_t)m * 2 != g->nnz) {
+    if ((int64_t)exact * 2 != g->nnz) {
         // a simple symmetric graph orients exactly one entry of each pair
-        set_error("triangle counting needs a simple undirected CSR (%d oriented entries of %lld)", m,
-                  (long long)g->nnz);
-        return fail(SP_ERR_INVALID_ARGUMENT);
+        set_error("triangle counting needs a simple undirected CSR (%lld oriented entries of %lld)",
+                  (long long)exact, (long long)g->nnz);
+        return SP_ERR_INVALID_ARGUMENT;
     }
-    st = dev_alloc((void **)&oci, sizeof(int32_t) * (size_t)std::max(m, 1));
-    if (st == SP_OK) st = dev_alloc((void **)&osrc, sizeof(int32_t) * (size_t)std::max(m, 1));
-    if (st != SP_OK) return fail(st);
+    const size_t me = (size_t)std::max(m, 1), padded = me + 8;  // 4-entry loads may run past the last row
+    const int32_t nu = std::min(n, kTcBits);
+    const int64_t unit_cap = (int64_t)me / kTcUnit + nu + 1;
+    entries.add(&oci, padded);
+    entries.add(&olo, padded);
+    entries.add(&osrc, me);
+    entries.add(&inl, me);
+    entries.add(&units, (size_t)unit_cap);
+    SP_TRY(entries.alloc());
+    places.add(&slot, me);
+    SP_TRY(places.alloc());
+    const int ent_grid = grid_for(m, 256, 2 * maxb);
+    int32_t un[2] = {0, 0};
     if (n > 0) {
-        hipLaunchKernelGGL(k_tc_fill, dim3(grid_for(n, 256, maxb)), dim3(256), 0, s,
-                           (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, n, (const int32_t *)off,
-                           (const int32_t *)tiles, orp, oci, osrc);
-        if (g->n_hubs > 0)
-            hipLaunchKernelGGL(k_tc_hub_fill, dim3(std::min(g->n_hubs, maxb)), dim3(256), 0, s,
-                               (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx,
-                               (const HubEntry *)g->hub_static, g->n_hubs, (const int32_t *)off,
-                               (const int32_t *)tiles, oci, osrc);
+        if (heavy)
+            hipLaunchKernelGGL(k_tc_fill<true>, dim3(std::min(heavy, maxb)), dim3(256), 0, s, rp, ci, rn, ro, 0,
+                               heavy, (const int32_t *)orp, oci, osrc);
+        hipLaunchKernelGGL(k_tc_fill<false>, dim3(row_grid), dim3(256), 0, s, rp, ci, rn, ro, heavy, n,
+                           (const int32_t *)orp, oci, osrc);
+        int32_t *nbig = (int32_t *)(ctl + 1);
+        hipLaunchKernelGGL(k_tc_sort_small, dim3(grid_for(n, 256, maxb)), dim3(256), 0, s, (const int32_t *)orp, n,
+                           oci, big, nbig);
+        hipLaunchKernelGGL(k_tc_sort_bits<kTcLow / 32>, dim3(maxb), dim3(256), 0, s, (const int32_t *)orp, oci,
+                           (const int32_t *)big, (const int32_t *)nbig, 0, kTcLow);
+        if (n > kTcLow)
+            hipLaunchKernelGGL(k_tc_sort_bits<kTcSortBits / 32>, dim3(maxb), dim3(256), 0, s, (const int32_t *)orp,
+                               oci, (const int32_t *)big, (const int32_t *)nbig, kTcLow, kTcSortBits);
+        if (n > kTcSortBits)
+            hipLaunchKernelGGL(k_tc_sort_net, dim3(maxb), dim3(256), 0, s, (const int32_t *)orp, oci,
+                               (const int32_t *)big, (const int32_t *)nbig, kTcSortBits);
+        SP_TRY(launch_fill_i32(iptr, n, 0, s));
+        hipLaunchKernelGGL(k_tc_named, dim3(grid_for(m, kTcNamedTile, maxb)), dim3(256), 0, s, (const int32_t *)oci, (int64_t)m, olo, iptr,
+                           slot);
+        launch_excl_scan(iptr, n, iptr, tiles, s);
+        hipLaunchKernelGGL(k_tc_inlist, dim3(ent_grid), dim3(256), 0, s, (const int32_t *)oci, (const int32_t *)osrc,
+                           (const int32_t *)orp, (const int32_t *)iptr, (const int32_t *)slot, (int64_t)m, inl);
+        int32_t *first = big;  // nu + 1 <= vn + 1 values; the row list is done with
+        hipLaunchKernelGGL(k_tc_unit_count, dim3(grid_for(nu, 256, maxb)), dim3(256), 0, s, (const int32_t *)iptr, nu,
+                           first);
+        launch_excl_scan(first, nu, first, tiles, s);
+        hipLaunchKernelGGL(k_tc_unit_fill, dim3(grid_for(nu, 256, maxb)), dim3(256), 0, s, (const int32_t *)iptr, nu,
+                           (const int32_t *)first, units, unit_cap);
+        SP_HIP(hipGetLastError());
+        SP_HIP(hipMemcpyAsync(&un[0], first + std::min(nu, kTcLow), sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        SP_HIP(hipMemcpyAsync(&un[1], first + nu, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     }
-    SP_HIP(hipGetLastError());
     SP_HIP(hipStreamSynchronize(s));
-    dev_free(odeg);
-    dev_free(off);
-    dev_free(tiles);
-    g->tc_orp = orp;
+    g->bytes += rows.bytes + entries.bytes;
+    g->tc_entries = std::exchange(entries.base, nullptr);
     g->tc_oci = oci;
+    g->tc_olo = olo;
     g->tc_osrc = osrc;
+    g->tc_iptr = iptr;
+    g->tc_inl = inl;
+    g->tc_units = units;
+    g->tc_units_lo = un[0];
+    g->tc_units_n = (int32_t)std::min<int64_t>(un[1], unit_cap);
     g->tc_m = m;
-    g->bytes += sizeof(int32_t) * (vn + 1 + 2 * (size_t)std::max(m, 1));
+    g->tc_orp = (int32_t *)std::exchange(rows.base, nullptr);  // the rows' block begins with orp
     return SP_OK;
 }
 
-sp_status tc_run(sp_graph g, unsigned long long *d_total, unsigned long long *per, hipStream_t s) {
+template <bool PER>
+static void launch_tc_count(sp_graph g, unsigned long long *d_total, unsigned long long *per, hipStream_t s) {
     const int maxb = device_cu_count() * 8;
+    unsigned long long *prof = prof_counters(P_TC_COUNT);
+    const int32_t lo = g->tc_units_lo, hi = g->tc_units_n - lo;
+    auto heavy = [&](auto kernel, const int4 *units, int32_t count) {
+        hipLaunchKernelGGL(kernel, dim3(std::min(count, maxb)), dim3(256), 0, s, (const int32_t *)g->tc_orp,
+                           (const int32_t *)g->tc_oci, (const uint16_t *)g->tc_olo, (const int32_t *)g->tc_osrc,
+                           (const int2 *)g->tc_inl, units, count, (const int32_t *)g->rank_old, d_total, per, prof);
+    };
+    if (lo > 0) heavy(k_tc_heavy<kTcLow, true, PER>, g->tc_units, lo);
+    if (hi > 0) heavy(k_tc_heavy<kTcBits, false, PER>, g->tc_units + lo, hi);
+    hipLaunchKernelGGL(k_tc_light, dim3(grid_for(g->n, kTcLightIds * (256 / kWave), 2 * maxb)), dim3(256), 0, s, (const int32_t *)g->tc_orp,
+                       (const int32_t *)g->tc_oci, (const int32_t *)g->tc_osrc, (const int32_t *)g->tc_iptr,
+                       (const int2 *)g->tc_inl, g->n, (const int32_t *)g->rank_old, d_total, per, prof);
+}
+
+sp_status tc_run(sp_graph g, unsigned long long *d_total, unsigned long long *per, hipStream_t s) {
     hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, d_total, (int64_t)1);
     if (per) hipLaunchKernelGGL(k_tc_zero, dim3(grid_for(g->n, 256, 4096)), dim3(256), 0, s, per, (int64_t)g->n);
     if (g->tc_m > 0) {
         ProfScope ps(P_TC_COUNT, s);
-        hipLaunchKernelGGL(k_tc_count<256>, dim3(grid_for(g->tc_m, 256, maxb)), dim3(256), 0, s,
-                           (const int32_t *)g->tc_orp, (const int32_t *)g->tc_oci,
-                           (const int32_t *)g->tc_osrc, (int64_t)g->tc_m, d_total, per,
-                           prof_counters(P_TC_COUNT));
+        if (per) launch_tc_count<true>(g, d_total, per, s);
+        else launch_tc_count<false>(g, d_total, nullptr, s);
     }
     SP_HIP(hipGetLastError());
     return SP_OK;
