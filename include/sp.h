@@ -437,7 +437,7 @@ sp_status sp_sssp_get_last_stats(sp_sssp_stats *out);
  * ------------------------------------------------------------------------ */
 
 typedef struct sp_pagerank_config {
-    int32_t block_size;  /* 128, 256 or 512 (0 = 256) */
+    int32_t block_size;  /* 128, 256 or 512 (0 = automatic) */
     int32_t chunk_iters; /* k > 0: iterations captured k at a time (rounded up to
                             even) in a hipGraph, the device "done" flag checked
                             after each replay; k < 0: |k| per check, launched

@@ -487,29 +487,6 @@ sp_status ensure_static_hubs(sp_graph g, hipStream_t st) {
     return upload_hub_layout(g, hubs, owners, st, &g->hub_static, &g->owner_static);
 }
 
-// PageRank's hub layout over the rows it gathers (a vertex's in-neighbours:
-// its own row when undirected, its reversed row when directed): every hub cut
-// by row eighths into 8m near-equal pieces of at most kHubChunk entries
-// (split_piece), m = ceil(deg / (8 * kHubChunk)); every hub's first chunk id
-// is a multiple of 8.
-sp_status ensure_pr_hubs(sp_graph g, hipStream_t st) {
-    std::lock_guard<std::mutex> lk(g->mu);
-    if (g->pr_hubs) return SP_OK;
-    const std::vector<int32_t> &deg = g->directed ? g->host_deg_in : g->host_deg;
-    std::vector<HubEntry> hubs;
-    std::vector<int32_t> owners;
-    for (int32_t v = 0; v < g->n; ++v)
-        if (deg[v] > kHubDeg) {
-            const int32_t nch = kXcds * ((deg[v] + kXcds * kHubChunk - 1) / (kXcds * kHubChunk));
-            hubs.push_back(HubEntry{v, 0, (int32_t)owners.size(), nch});
-            owners.insert(owners.end(), (size_t)nch, (int32_t)hubs.size() - 1);
-        }
-    SP_TRY(upload_hub_layout(g, hubs, owners, st, &g->pr_hubs, &g->pr_owner));
-    g->pr_chunks = (int64_t)owners.size();
-    g->pr_n_hubs = (int32_t)hubs.size();
-    return SP_OK;
-}
-
 // The per-source loop shared by sp_bc and sp_bc_noalloc: out_bc zeroed,
 // then one pass per source in list order (block size from the graph's tuned
 // configuration).  Times the call with ws's events when it has them.
@@ -821,8 +798,7 @@ sp_status sp_graph_release(sp_graph g) {
     dev_free(g->tc_entries);
     dev_free(g->hub_static);
     dev_free(g->owner_static);
-    dev_free(g->pr_hubs);
-    dev_free(g->pr_owner);
+    pr_plan_free(g->pr_plan);
     dev_free(g->row_ptr);
     dev_free(g->col_idx);
     delete g;
@@ -1263,7 +1239,7 @@ sp_status sp_pagerank(sp_graph g, double beta, double delta, int32_t max_iter, d
     if (g->n == 0) return SP_OK;
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)s;
-    SP_TRY(ensure_pr_hubs(g, st));
+    SP_TRY(ensure_pr_plan(g, st));
     PrWorkspace *ws = nullptr;
     SP_TRY(acquire_pr_ws(g, &ws));
     struct Rel {

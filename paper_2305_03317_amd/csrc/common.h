@@ -51,6 +51,7 @@ struct BatchWorkspace;
 struct SourceWorkspace;
 struct SsspWorkspace;
 struct PrWorkspace;
+struct PrPlan;
 struct HubEntry;
 
 struct TuneEntry {
@@ -96,16 +97,13 @@ struct sp_graph_s {
     // chunk; built on first use by the whole-graph kernels (ensure_static_hubs).
     sp::HubEntry *hub_static = nullptr;  // device, n_hubs (>= 1)
     int32_t *owner_static = nullptr;     // device, hub_chunks (>= 1)
-    // PageRank's hub chunks, cut by row eighths (ensure_pr_hubs).
-    sp::HubEntry *pr_hubs = nullptr;     // device, n_hubs (>= 1)
-    int32_t *pr_owner = nullptr;         // device, pr_chunks (>= 1)
-    int64_t pr_chunks = 0;
-    int32_t pr_n_hubs = 0;               // entries of pr_hubs
+    // PageRank's rows in the order and numbering it gathers them (ensure_pr_plan).
+    sp::PrPlan *pr_plan = nullptr;   // host
     // Vertices ranked by degree, highest first (ensure_rank_locked): rank of a
-    // vertex, vertex of a rank, and how many have degree >= kRankExact.
-    int32_t *rank_new = nullptr;     // device, n
+    // vertex, vertex of a rank, and where each degree class starts.
+    int32_t *rank_new = nullptr;     // device, n; its allocation holds rank_old too
     int32_t *rank_old = nullptr;     // device, n
-    int32_t rank_heavy = 0;
+    std::vector<int32_t> rank_first; // host, kRankBuckets + 1
     // Triangle counting (ensure_oriented, on first use), vertices by rank: row
     // v holds its neighbours of lower rank number (higher degree), ascending,
     // as 32-bit ids and (where they fit) as 16-bit ones; each entry's row; and
@@ -255,7 +253,7 @@ struct LevelCtl {
 enum ProfKind : int {
     P_SRC_TOPDOWN, P_SRC_BOTTOMUP, P_SRC_SIGMA, P_SRC_SIGMA_HUB, P_SRC_DELTA, P_SRC_DELTA_HUB,
     P_MS_TOPDOWN, P_MS_BOTTOMUP, P_MS_SIGMA, P_MS_SIGMA_HUB, P_MS_EXPAND, P_MS_DELTA, P_MS_DELTA_HUB,
-    P_MS_BC, P_SSSP_PUSH, P_SSSP_PULL, P_PR_PULL, P_PR_HUB, P_TC_COUNT, P_WG_BC,
+    P_MS_BC, P_SSSP_PUSH, P_SSSP_PULL, P_PR_PULL, P_TC_COUNT, P_WG_BC,
     P_MS_SIGMA_PUSH, P_COUNT
 };
 constexpr int kProfCounters = 4;  // items, edges, pairs, item_slots
@@ -561,19 +559,46 @@ struct PrCtl {
     HotU64 diff_;        // this iteration's sum of |change|, fixed point (2^-kPrDiffBits units)
     HotI32 blocks_done_; // working blocks of the closing kernel that finished
 };
-// Each block rounds its sum of |change| to a multiple of 2^-60 and adds it
-// with an integer atomic: the total is the same whatever the order, so the
-// stopping decision is reproducible.  Its error is at most blocks x 2^-61
-// (under 2e-15 for 4096 blocks); the sum itself is at most 2 (the values
+// Each wave rounds its sum of |change| over a tile's rows to a multiple of
+// 2^-60, and the rounded sums are added as integers: the total is the same
+// whatever the order, so the stopping decision is reproducible.  Its error is
+// at most 2^-61 a wave and tile (3e-14 for 4.2 M vertices, 2e-16 expected); the sum itself is at most 2 (the values
 // start at 1/N and each iteration's total is at most 1), below the 16 that
 // 64 bits hold at this scale.
 constexpr int kPrDiffBits = 60;
+
+// The rows PageRank gathers, sorted by length class.  Vertices may be
+// renumbered by degree rank ("ids" below; the vertex of id x is old[x]).
+constexpr int kPrRowClasses = 6;
+struct PrView {
+    const int32_t *col;      // row entries, as ids
+    const int2 *rows;        // n: {first entry, entries} of the i-th row; null: from rp
+    const int32_t *rp;       // n + 1: the graph's offsets of the rows gathered
+    const int32_t *order;    // n: id of the i-th row; null: i
+    const int32_t *out_deg;  // n: entries that leave id x; null: those of its row
+    const int2 *split;       // rows of class 0: {first piece, pieces}
+    const int2 *pieces;      // n_pieces of them: {first entry, entries}
+    const int32_t *piece_row;  // the row of each
+    int32_t n_pieces;
+    int32_t row0[kPrRowClasses + 1];   // first row of each class
+    int32_t tile0[kPrRowClasses + 1];  // first block tile of each class (class 0: a tile per piece)
+};
+struct PrPlan {
+    PrView view{};           // tile0 is filled per launch (it depends on the block size)
+    void *rows = nullptr;    // device allocation of view.rows, .order, .out_deg
+    int32_t *col = nullptr;  // device: the renumbered entries; null: the graph's own
+    const int32_t *old_id = nullptr, *new_id = nullptr;  // device, null when not renumbered
+    void *split = nullptr;   // device allocation of view.split, .pieces, .piece_row
+    int32_t n_split = 0;     // rows of class 0
+};
+void pr_plan_free(PrPlan *p);
 
 struct PrWorkspace {
     int device = -1;
     double *pr[2] = {nullptr, nullptr};     // V each: PageRank by iteration parity
     double *share[2] = {nullptr, nullptr};  // V each: pr / out-degree (0 without out-edges)
-    double *partial = nullptr;              // hub_chunks + 1: hub chunk sums
+    double *partial = nullptr;              // pieces + 1: sums of the split rows' pieces
+    int32_t *arrived = nullptr;             // split rows + 1: pieces summed this iteration
     PrCtl *ctl = nullptr;
     PrCtl *ctl_host = nullptr;              // pinned mirror
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -584,7 +609,7 @@ sp_status pr_ws_create(sp_graph g, PrWorkspace &ws);
 void pr_ws_destroy(PrWorkspace &ws);
 
 struct PrOpts {
-    int block = 256;
+    int block = 0;         // 0: automatic
     int chunk_iters = 8;   // > 0: captured chunks; < 0: direct launches
 };
 struct PrResult {
@@ -615,8 +640,8 @@ sp_status check_batch_cfg(const sp_batch_config *cfg);
 
 // Builds g->hub_static / g->owner_static once (thread-safe).
 sp_status ensure_static_hubs(sp_graph g, hipStream_t s);
-// Builds g->pr_hubs / g->pr_owner once (thread-safe).
-sp_status ensure_pr_hubs(sp_graph g, hipStream_t s);
+// Builds g->pr_plan once (thread-safe).
+sp_status ensure_pr_plan(sp_graph g, hipStream_t s);
 
 // Workspace pools and configuration shared by the entry points and the server.
 int64_t initial_qcap(int32_t n, int32_t width);

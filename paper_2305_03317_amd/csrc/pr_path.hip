@@ -8,29 +8,41 @@
 // the reversed graph on a directed one; outdeg is always the outgoing row's
 // length, and a vertex without outgoing arcs passes nothing on.
 //
-// Design: each iteration is one streaming pass over the CSR.  The producer of
-// a value also stores share = val / outdeg, so the gather reads one double
-// per adjacency entry.  A wave takes 64 consecutive vertices: rows of at most
-// 8 entries are summed in row order by their own lane, longer ones by the
-// wave in chunks of 8 aligned at the row start (wave_chunk_sum); either way a
-// vertex's sum depends only on its row, so results are reproducible.  Rows
-// longer than kHubDeg are cut by row eighths into 8m pieces of at most
-// kHubChunk entries (split_piece), which waves reduce into partials, one XCD
-// per eighth; a finishing kernel adds a row's partials in row order.  The
-// stopping test sums |val - pr| per block in a fixed order and adds the block
+// Design: each iteration is one pass over the entries.  The producer of a
+// value also stores share = val / outdeg, so the gather reads one double per
+// entry.  A plan made once per graph (ensure_pr_plan) lists the rows by length
+// class, and each class gives a row the lanes its length fills: 1 for up to 8
+// entries (summed in row order), 4 up to 32, 16 up to 128, 64 below 512, a
+// block from there on; rows longer than a 256th of all entries (at least
+// 16,384) are cut into pieces, whose sums a finishing kernel adds.  A lane
+// adds entries j, j + lanes, ... in order, four loads in flight, and a fixed
+// tree adds the lanes, so a vertex's sum depends only on its row.
+//
+// On large skewed graphs the plan renumbers the vertices by degree rank: the
+// shares that most entries gather then fill consecutive lines that stay in
+// each XCD's 4 MB L2 (rmat-22: the first eighth of the ranks holds 92% of the
+// entries), where random numbers spread them over 33 MB.  What is left then is L2
+// bandwidth: 93 M requests of a 128-byte line per iteration, 17 TB/s; blocks
+// therefore keep the shares of the first 9,216 ranks (a third of the gathers)
+// in LDS.  rmat-22: 1.09 -> 0.68 ms per iteration; rmat-15, where latency and
+// the number of launches count: 43 -> 13 us.
+//
+// The stopping test sums |val - pr| per block in a fixed order and adds the block
 // sums as fixed-point integers, so the total and the decision do not depend on
 // scheduling.  The last working block of an iteration's last kernel closes it;
 // chunks of iterations are captured as HIP graphs and replayed until the
 // device reports done.
+#include <type_traits>
+
 #include "capture.h"
 #include "common.h"
 #include "devutil.h"
 #include "levels.h"
+#include "rank.h"
 
 namespace sp {
 
-// Rows of at most this many entries are summed by their own lane.
-constexpr int kPrShortRow = 8;
+static_assert(kPrRowClasses == kRowClasses, "one tile range per row class");
 
 __device__ __forceinline__ unsigned long long diff_fixed(double x) {
     return (unsigned long long)__double2ll_rn(x * 0x1p60);
@@ -44,18 +56,13 @@ __device__ __forceinline__ int32_t read_pr_state(PrCtl *c) {
     return s_state;
 }
 
-// Sum of the block's per-thread |change| in a fixed order, added to the
-// iteration's total as a fixed-point integer.
-template <int BS>
-__device__ __forceinline__ void add_block_diff(PrCtl *c, double x, double *lds) {
-    x = wave_sum_f64(x);
-    if (lane_id() == 0) lds[threadIdx.x / kWave] = x;
+// Adds the block's |change| (fixed-point sums of its waves) to the iteration's total.
+__device__ __forceinline__ void add_block_diff(PrCtl *c, unsigned long long x, unsigned long long *lds) {
+    if (threadIdx.x == 0) lds[0] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int w = 0; w < BS / kWave; ++w) s += lds[w];
-        if (s > 0.0) atomicAdd(&c->diff_.v, diff_fixed(s));
-    }
+    if (lane_id() == 0 && x) atomicAdd(&lds[0], x);
+    __syncthreads();
+    if (threadIdx.x == 0 && lds[0]) atomicAdd(&c->diff_.v, lds[0]);
 }
 
 // End of an iteration (one thread of the last working block).
@@ -68,14 +75,18 @@ __device__ void close_iteration(PrCtl *c) {
     __hip_atomic_store(&c->state, it * 2 + (done ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_pr_init(PrCtl *c, const int32_t *__restrict__ rp, double *pr, double *share,
-                          int32_t n, double beta, int32_t max_iter) {
+// rp: outgoing row offsets; old: vertex of an id (null: the id).
+__global__ void k_pr_init(PrCtl *c, const int32_t *__restrict__ rp, const int32_t *__restrict__ old,
+                          double *pr, double *share, int32_t n, double beta, int32_t max_iter,
+                          int32_t *arrived, int32_t n_split) {
     const double x = 1.0 / (double)n;
     const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int32_t v = old ? old[i] : i;
         const int32_t deg = rp[v + 1] - rp[v];
-        pr[v] = x;
-        share[v] = deg > 0 ? x / (double)deg : 0.0;
+        pr[i] = x;
+        share[i] = deg > 0 ? x / (double)deg : 0.0;
+        if (i < n_split) arrived[i] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         c->state = 0;
@@ -83,116 +94,381 @@ __global__ void k_pr_init(PrCtl *c, const int32_t *__restrict__ rp, double *pr, 
         c->beta = beta;
         c->last_diff = 0.0;
         c->diff_.v = 0;
-        c->blocks_done_.v = 0;
+            c->blocks_done_.v = 0;
     }
 }
 
-// One iteration's gather.  blockIdx.y == 0: each wave takes 64 consecutive
-// vertices (hubs excluded) and writes val, share and the block's |change|.
-// blockIdx.y == 1: a wave per hub chunk writes the chunk's partial sum.
-// Without hubs this kernel closes the iteration.  Bounded to eight waves per
-// SIMD (some registers spilled): more gathers in flight, rmat-22 1.23 -> 1.13
-// ms per iteration against six waves without spills.
-template <int BS>
-__global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, const int32_t *__restrict__ rp,
-                                                const int32_t *__restrict__ ci,
-                                                const int32_t *__restrict__ rpo, double *pr0,
-                                                double *pr1, double *sh0, double *sh1,
-                                                double *partial, const HubEntry *__restrict__ hs,
-                                                const int32_t *__restrict__ os, int32_t n,
-                                                int32_t nch, double teleport, double delta,
-                                                int32_t closes, int32_t parity,
-                                                unsigned long long *prof) {
+// Shares by id: the first HOT of them from LDS.  Both sides are read without
+// a branch: ids in LDS send their memory read to one common line.
+template <int HOT>
+struct Shares {
+    const double *sh, *hot;
+    __device__ __forceinline__ double get(int32_t u) const {
+        if (HOT == 0) return sh[u];
+        const double far = sh[max(u, HOT)], near = hot[min(u, HOT - 1)];
+        return u < HOT ? near : far;
+    }
+};
+
+// Sum of sh over the entries col[beg + lane], col[beg + lane + LPR], ... by LPR
+// lanes, all of which receive it.  Four entries per lane are in flight: a lane
+// past the row's end reads the last entry again and drops it, so that the
+// loads are issued together (under a condition each would be waited for).
+template <int LPR, int FLY, class S>
+__device__ __forceinline__ double lanes_sum(const int32_t *__restrict__ col, const S &sh,
+                                            int32_t beg, int32_t len, int32_t l) {
+    double s = 0.0;
+    for (int32_t t = l; __ballot(t < len); t += FLY * LPR) {
+        if (t < len) {
+            int32_t u[FLY];
+            double x[FLY];
+#pragma unroll
+            for (int q = 0; q < FLY; ++q) u[q] = __builtin_nontemporal_load(&col[beg + min(t + q * LPR, len - 1)]);
+#pragma unroll
+            for (int q = 0; q < FLY; ++q) x[q] = sh.get(u[q]);
+#pragma unroll
+            for (int q = 0; q < FLY; ++q)
+                if (t + q * LPR < len) s += x[q];
+        }
+    }
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+    return s;
+}
+
+// The same by 512 lanes whatever the block size (each thread of a smaller
+// block stands for 512 / BS of them, a block of 1024 sums two rows), their
+// waves added in order; the sum arrives on the first of the row's threads.
+template <int BS, int FLY, class S>
+__device__ __forceinline__ double block_row_sum(const int32_t *__restrict__ col, const S &sh,
+                                                int32_t beg, int32_t len, double *lds) {
+    constexpr int kLanes = 512, T = BS < kLanes ? BS : kLanes, V = kLanes / T;
+    constexpr int U = V >= FLY ? 1 : FLY / V;  // steps in flight
+    const int32_t tid = threadIdx.x % T;
+    double *mine = lds + threadIdx.x / T * (kLanes / kWave);
+    double acc[V];
+#pragma unroll
+    for (int a = 0; a < V; ++a) acc[a] = 0.0;
+    for (int32_t t = tid; t < len; t += kLanes * U) {
+        int32_t u[U * V];
+        double x[U * V];
+#pragma unroll
+        for (int q = 0; q < U * V; ++q) u[q] = __builtin_nontemporal_load(&col[beg + min(t + q * T, len - 1)]);
+#pragma unroll
+        for (int q = 0; q < U * V; ++q) x[q] = sh.get(u[q]);
+#pragma unroll
+        for (int q = 0; q < U * V; ++q)
+            if (t + q * T < len) acc[q % V] += x[q];
+    }
+#pragma unroll
+    for (int a = 0; a < V; ++a) {
+        const double s = wave_sum_f64(acc[a]);
+        if (lane_id() == 0) mine[a * (T / kWave) + tid / kWave] = s;
+    }
+    __syncthreads();
+    double s = 0.0;
+    if (tid == 0)
+        for (int k = 0; k < kLanes / kWave; ++k) s += mine[k];
+    __syncthreads();
+    return s;
+}
+
+// One iteration's gather: blocks walk the tiles of the row classes, heaviest
+// first (a tile: one piece or row of the block classes, BS / lanes rows of the
+// others), and the last block closes the iteration.
+template <int BS, int HOT>
+__global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *pr0, double *pr1, double *sh0,
+                                                   double *sh1, double *partial, int32_t *arrived, double teleport,
+                                                   double delta, int32_t parity, unsigned long long *prof) {
     const int32_t st = read_pr_state(c);
     if ((st & 1) || ((st >> 1) & 1) != parity) return;
-    __shared__ int32_t s_coff[BS], s_beg[BS], s_deg[BS];
-    __shared__ double s_acc[BS], s_w[BS / kWave];
+    __shared__ double s_w[BS > 512 ? BS / kWave : 8];
+    constexpr int kTeam = BS > 512 ? 512 : BS;  // threads per row of the block classes
     __shared__ unsigned long long s_red[1];
     const double *pr = parity ? pr1 : pr0;
-    const double *sh = parity ? sh1 : sh0;
+    constexpr int FLY = 4;  // entries in flight per lane (8: rmat-22 13.7 -> 14.7 ms, road-2500 1.8 -> 2.2)
+    __shared__ double s_hot[HOT ? HOT : 1];
+    const Shares<HOT> sh{parity ? sh1 : sh0, s_hot};
     double *pr_n = parity ? pr0 : pr1;
     double *sh_n = parity ? sh0 : sh1;
-    const int lane = lane_id();
-    const int wbase = threadIdx.x - lane;
+    if (HOT) {
+        for (int32_t k = threadIdx.x; k < HOT; k += BS) s_hot[k] = sh.sh[k];
+        __syncthreads();
+    }
     unsigned long long my_items = 0, my_edges = 0;
-    double my_diff = 0.0;
-    if (blockIdx.y == 0) {
-        const WaveScratch ws{s_coff + wbase, s_beg + wbase, s_deg + wbase, s_acc + wbase, nullptr};
-        for (int32_t b = blockIdx.x * BS + wbase; b < n; b += gridDim.x * BS) {
-            const int32_t v = b + lane;
-            int32_t beg = 0, deg = 0, dout = 0;
-            if (v < n) {
-                beg = rp[v];
-                deg = rp[v + 1] - beg;
-                dout = rpo == rp ? deg : rpo[v + 1] - rpo[v];
-            }
-            const bool hub = deg > kHubDeg, shortrow = deg <= kPrShortRow;
-            // short rows: the lane's own row, all loads issued before the
-            // in-order sum; longer rows: the wave's chunked sum
-            double sum = 0.0;
-            if (shortrow) {
-                int32_t u[kPrShortRow];
-                double x[kPrShortRow];
-#pragma unroll
-                for (int j = 0; j < kPrShortRow; ++j) u[j] = j < deg ? ci[beg + j] : 0;
-#pragma unroll
-                for (int j = 0; j < kPrShortRow; ++j) x[j] = j < deg ? sh[u[j]] : 0.0;
-#pragma unroll
-                for (int j = 0; j < kPrShortRow; ++j)
-                    if (j < deg) sum += x[j];
-            }
-            const double chunked = wave_chunk_sum(beg, hub || shortrow ? 0 : deg, ws,
-                                                  [&](int32_t e, int32_t) { return sh[ci[e]]; });
-            if (!shortrow) sum = chunked;
-            if (v < n && !hub) {
-                const double val = teleport + delta * sum;
-                my_diff += fabs(val - pr[v]);
-                pr_n[v] = val;
-                sh_n[v] = dout > 0 ? val / (double)dout : 0.0;
-                ++my_items;
-                my_edges += (unsigned long long)deg;
+    unsigned long long diff_sum = 0;  // on the waves' first lanes
+    double my_diff = 0.0;             // this tile's
+    auto settle = [&](int32_t i, int32_t len, double sum) {
+        const int32_t x = p.order ? p.order[i] : i;
+        const int32_t dout = p.out_deg ? p.out_deg[x] : len;
+        const double val = teleport + delta * sum;
+        my_diff += fabs(val - pr[x]);
+        pr_n[x] = val;
+        sh_n[x] = dout > 0 ? val / (double)dout : 0.0;
+        ++my_items;
+        my_edges += (unsigned long long)len;
+    };
+    auto rows_of = [&](auto lanes, int cls, int32_t tile) {
+        constexpr int LPR = decltype(lanes)::value;
+        const int32_t i = p.row0[cls] + (tile - p.tile0[cls]) * (BS / LPR) + (int32_t)threadIdx.x / LPR;
+        const int32_t l = threadIdx.x % LPR;
+        const bool mine = i < p.row0[cls + 1];
+        int2 row = make_int2(0, 0);
+        if (mine) {
+            if (p.rows) row = p.rows[i];
+            else row = make_int2(p.rp[i], p.rp[i + 1] - p.rp[i]);
+        }
+        const double sum = lanes_sum<LPR, FLY>(p.col, sh, row.x, row.y, l);
+        if (mine && l == 0) settle(i, row.y, sum);
+    };
+    const int32_t ntiles = p.tile0[kPrRowClasses];
+    for (int32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        if (tile >= p.tile0[5]) rows_of(std::integral_constant<int, 1>{}, 5, tile);
+        else if (tile >= p.tile0[4]) rows_of(std::integral_constant<int, 4>{}, 4, tile);
+        else if (tile >= p.tile0[3]) rows_of(std::integral_constant<int, 16>{}, 3, tile);
+        else if (tile >= p.tile0[2]) rows_of(std::integral_constant<int, 64>{}, 2, tile);
+        else {
+            const bool whole = tile >= p.tile0[1];  // a row, or a piece of one
+            const int32_t k = (tile - (whole ? p.tile0[1] : 0)) * (BS / kTeam) + (int32_t)threadIdx.x / kTeam;
+            const int32_t i = whole ? p.row0[1] + k : k;
+            const bool mine = whole ? i < p.row0[2] : i < p.n_pieces;
+            int2 row = make_int2(0, 0);
+            if (mine) row = whole ? p.rows[i] : p.pieces[i];
+            const double sum = block_row_sum<BS, FLY>(p.col, sh, row.x, row.y, s_w);
+            if (mine && threadIdx.x % kTeam == 0) {
+                if (whole) settle(i, row.y, sum);
+                }
+            if (!whole) {  // the last piece of a row to arrive settles it, on its team's first wave
+                int32_t r = -1;
+                if (mine && threadIdx.x % kTeam == 0) {
+                    const int32_t owner = p.piece_row[i];
+                    __hip_atomic_store(&partial[i], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __builtin_amdgcn_s_waitcnt(0);  // the sum is where every block reads it before it is counted
+                    if (atomicAdd(&arrived[owner], 1) == p.split[owner].y - 1) {
+                        arrived[owner] = 0;
+                        r = owner;
+                    }
+                }
+                r = __shfl(r, 0, kWave);
+                if (r >= 0 && threadIdx.x % kTeam < kWave) {
+                    const int2 h = p.split[r];
+                    double s = 0.0;
+                    for (int32_t k2 = lane_id(); k2 < h.y; k2 += kWave) s += ld_agent(&partial[h.x + k2]);
+                    s = wave_sum_f64(s);
+                    if (lane_id() == 0) settle(r, p.rows[r].y, s);
+                }
             }
         }
-        add_block_diff<BS>(c, my_diff, s_w);
-    } else {
-        // with a grid that is a multiple of 8, block (x, 1) runs on XCD x mod 8
-        for_xcd_chunks<BS>(nch, [&](int64_t k) {
-            const HubEntry h = hs[os[k]];
-            const int32_t rb = rp[h.v];
-            int32_t beg, end;
-            split_piece(rb, rp[h.v + 1] - rb, h.nchunks, (int32_t)k - h.chunk_base, beg, end);
-            hub_chunk((int32_t)k, beg, end, partial, [&](int32_t e) { return sh[ci[e]]; });
-            my_edges += lane == 0 ? (unsigned long long)(end - beg) : 0ull;
-        });
+        // a tile's |change| is summed in a fixed order and rounded once per wave: the same total however
+        // the tiles are dealt out
+        const double d = wave_sum_f64(my_diff);
+        if (lane_id() == 0) diff_sum += diff_fixed(d);
+        my_diff = 0.0;
     }
+    add_block_diff(c, diff_sum, s_red);
     flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
-    if (closes && last_block(c, working_blocks((int64_t)n, BS)) && threadIdx.x == 0) close_iteration(c);
+    if (last_block(c, working_blocks((int64_t)ntiles, 1)) && threadIdx.x == 0) close_iteration(c);
 }
 
-// Hubs of one iteration from their chunk sums, in row order (a thread per
-// hub); closes the iteration.
-__global__ void k_pr_hub_fin(PrCtl *c, const int32_t *__restrict__ rpo, double *pr0, double *pr1,
-                             double *sh0, double *sh1, const double *__restrict__ partial,
-                             const HubEntry *__restrict__ hs, int32_t nh, double teleport,
-                             double delta, int32_t parity) {
-    const int32_t st = read_pr_state(c);
-    if ((st & 1) || ((st >> 1) & 1) != parity) return;
-    __shared__ double s_w[256 / kWave];
-    const double *pr = parity ? pr1 : pr0;
-    double *pr_n = parity ? pr0 : pr1;
-    double *sh_n = parity ? sh0 : sh1;
-    double my_diff = 0.0;
+// Values of the ids to the caller's vertices.
+__global__ void k_pr_export(const double *__restrict__ pr, const int32_t *__restrict__ new_id, int32_t n,
+                            double *out) {
     const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < nh; j += stride) {
-        const HubEntry h = hs[j];
-        const double val = teleport + delta * sum_split_chunks(partial, h.chunk_base, h.nchunks);
-        my_diff += fabs(val - pr[h.v]);
-        pr_n[h.v] = val;
-        const int32_t dout = rpo[h.v + 1] - rpo[h.v];  // outgoing row (may be empty when directed)
-        sh_n[h.v] = dout > 0 ? val / (double)dout : 0.0;
+    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) out[v] = pr[new_id[v]];
+}
+
+// ---------------------------------------------------------------------------
+// The plan
+// ---------------------------------------------------------------------------
+__global__ void k_pr_out_deg(const int32_t *__restrict__ rp, const int32_t *__restrict__ old, int32_t n,
+                             int32_t *out_deg) {
+    const int32_t stride = gridDim.x * blockDim.x;
+    for (int32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
+        const int32_t v = old ? old[x] : x;
+        out_deg[x] = rp[v + 1] - rp[v];
     }
-    add_block_diff<256>(c, my_diff, s_w);
-    if (last_block(c, working_blocks((int64_t)nh, 256)) && threadIdx.x == 0) close_iteration(c);
+}
+
+// Length of the i-th row.
+__global__ void k_pr_row_len(const int32_t *__restrict__ rp, const int32_t *__restrict__ order,
+                             const int32_t *__restrict__ old, int32_t n, int32_t *len) {
+    const int32_t stride = gridDim.x * blockDim.x;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int32_t x = order ? order[i] : i, v = old ? old[x] : x;
+        len[i] = rp[v + 1] - rp[v];
+    }
+}
+
+// {first entry, entries} of the i-th row: at off[i] in a renumbered copy, else
+// where the graph has it.
+__global__ void k_pr_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ order,
+                          const int32_t *__restrict__ old, const int32_t *__restrict__ off, int32_t n,
+                          int2 *rows) {
+    const int32_t stride = gridDim.x * blockDim.x;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int32_t x = order ? order[i] : i, v = old ? old[x] : x;
+        const int32_t b = rp[v];
+        rows[i] = make_int2(off ? off[i] : b, rp[v + 1] - b);
+    }
+}
+
+// Renumbered entries of the rows [first, last), per lanes (16, or a block).
+template <int PER>
+__global__ __launch_bounds__(256) void k_pr_renumber(const int32_t *__restrict__ rp,
+                                                     const int32_t *__restrict__ ci,
+                                                     const int32_t *__restrict__ order,
+                                                     const int32_t *__restrict__ old,
+                                                     const int32_t *__restrict__ new_id,
+                                                     const int2 *__restrict__ rows, int32_t first,
+                                                     int32_t last, int32_t *col) {
+    const int64_t stride = (int64_t)gridDim.x * (256 / PER);
+    for (int64_t i = first + (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER; i < last; i += stride) {
+        const int32_t b = rp[old[order ? order[i] : i]];
+        const int2 row = rows[i];
+        for (int32_t k = threadIdx.x % PER; k < row.y; k += PER) col[row.x + k] = new_id[ci[b + k]];
+    }
+}
+
+namespace {
+constexpr int kPrHotPerThread = 9;  // shares in LDS per thread of a renumbered run: 144 KB of a CU's 160 at 32 waves
+constexpr int32_t kPrPiece = 8192;  // rows from here on are split into pieces (a power of two: whole rank classes)
+constexpr int32_t kPrRenumberFrom = 1 << 18;  // vertices: shares of 2 MB, half an XCD's L2
+}  // namespace
+
+// Whether gathers concentrate enough for renumbering to pay: the eighth of the
+// vertices of highest degree holds at least half of the entries (road grids
+// and uniform graphs keep their numbering, which may be a local one).
+static bool skewed(sp_graph g) {
+    int64_t seen = 0, entries = 0;
+    for (int32_t b = 0; b < kRankBuckets && seen < g->n / 8; ++b) {
+        const int32_t key = kRankBuckets - 1 - b;
+        const int64_t deg = key < kRankExact ? key : (int64_t)(32 + (key - kRankExact) % 32) << ((key - kRankExact) / 32 + 3);
+        const int64_t count = std::min<int64_t>(g->rank_first[b + 1] - g->rank_first[b], g->n / 8 - seen);
+        seen += count;
+        entries += count * deg;
+    }
+    return 2 * entries >= g->nnz;
+}
+
+void pr_plan_free(PrPlan *p) {
+    if (!p) return;
+    dev_free(p->rows);
+    dev_free(p->col);
+    dev_free(p->split);
+    delete p;
+}
+
+sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(g->mu);
+    if (g->pr_plan) return SP_OK;
+    const int32_t n = g->n;
+    const int32_t *rp = g->rp_in, *ci = g->ci_in;
+    struct Guard {
+        PrPlan *p = new PrPlan;
+        int32_t *tmp = nullptr;
+        ~Guard() {
+            pr_plan_free(p);
+            dev_free(tmp);
+        }
+    } gd;
+    PrPlan &pl = *gd.p;
+    constexpr int32_t longest = kPrPiece - 1;
+    // renumbered when it pays and its copy fits; the graph's own rows do otherwise
+    if (n > kPrRenumberFrom && g->max_degree > 8) {
+        sp_status st = ensure_rank_locked(g, s);
+        if (st == SP_OK && skewed(g)) st = dev_alloc((void **)&pl.col, sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1));
+        if (st != SP_OK && st != SP_ERR_OUT_OF_MEMORY) return st;
+        if (st != SP_OK) clear_error();
+        if (pl.col) {
+            pl.old_id = g->rank_old;
+            pl.new_id = g->rank_new;
+        }
+    }
+    const bool renum = pl.col != nullptr;
+    // undirected ranks list the rows by length already, and rows of one class need no list
+    const bool listed = g->max_degree > 8 && (!renum || g->directed);
+    const bool plain = !listed && !renum;  // the graph's own offsets serve
+    const size_t vn = (size_t)n;
+    const size_t row_bytes = (plain ? 0 : sizeof(int2) * vn) + sizeof(int32_t) * vn * (size_t)(listed + g->directed);
+    if (row_bytes) SP_TRY(dev_alloc(&pl.rows, row_bytes));
+    int2 *rows = plain ? nullptr : (int2 *)pl.rows;
+    int32_t *at = (int32_t *)pl.rows + (plain ? 0 : 2 * vn);
+    int32_t *order = listed ? at : nullptr;
+    int32_t *out_deg = g->directed ? at + (listed ? vn : 0) : nullptr;
+    int32_t *row0 = pl.view.row0;
+    if (listed) {
+        SP_TRY(sort_rows_by_class(rp, pl.old_id, n, longest, order, row0, s));
+    } else if (renum) {
+        const int32_t at_least[kRowClasses - 1] = {kPrPiece, 512, 129, 33, 9};
+        row0[0] = 0;
+        for (int c = 1; c < kRowClasses; ++c) row0[c] = rank_count(g, at_least[c - 1]);
+        row0[kRowClasses] = n;
+    } else {
+        row0[kRowClasses] = n;  // every row in the last class
+    }
+    const int maxb = device_cu_count() * 8;
+    const int vgrid = grid_for(n, 256, maxb);
+    if (out_deg)
+        hipLaunchKernelGGL(k_pr_out_deg, dim3(vgrid), dim3(256), 0, s, (const int32_t *)g->row_ptr, pl.old_id, n,
+                           out_deg);
+    int32_t *off = nullptr;
+    if (renum) {
+        SP_TRY(dev_alloc((void **)&gd.tmp, sizeof(int32_t) * (size_t)(n + 1 + scan_tiles(n))));
+        off = gd.tmp;
+        hipLaunchKernelGGL(k_pr_row_len, dim3(vgrid), dim3(256), 0, s, rp, (const int32_t *)order, pl.old_id, n, off);
+        launch_excl_scan(off, n, off, off + n + 1, s);
+    }
+    if (rows)
+        hipLaunchKernelGGL(k_pr_rows, dim3(vgrid), dim3(256), 0, s, rp, (const int32_t *)order, pl.old_id,
+                           (const int32_t *)off, n, rows);
+    if (renum) {
+        const int32_t block_rows = row0[2];
+        if (block_rows > 0)
+            hipLaunchKernelGGL(k_pr_renumber<256>, dim3(std::min(block_rows, maxb)), dim3(256), 0, s, rp, ci,
+                               (const int32_t *)order, pl.old_id, pl.new_id, (const int2 *)rows, 0, block_rows, pl.col);
+        hipLaunchKernelGGL(k_pr_renumber<16>, dim3(grid_for((int64_t)n - block_rows, 16, maxb)), dim3(256), 0, s, rp,
+                           ci, (const int32_t *)order, pl.old_id, pl.new_id, (const int2 *)rows, block_rows, n, pl.col);
+    }
+    SP_HIP(hipGetLastError());
+    size_t split_bytes = 0;
+    const int32_t ns = row0[1];  // a row per kPrPiece entries at most
+    if (ns > 0) {
+        std::vector<int2> srow((size_t)ns), split((size_t)ns), pieces;
+        std::vector<int32_t> owner;
+        SP_HIP(hipMemcpyAsync(srow.data(), rows, sizeof(int2) * (size_t)ns, hipMemcpyDeviceToHost, s));
+        SP_HIP(hipStreamSynchronize(s));
+        for (int32_t j = 0; j < ns; ++j) {
+            split[j].x = (int32_t)pieces.size();
+            for (int64_t k = 0; k < srow[j].y; k += kPrPiece) {
+                pieces.push_back(make_int2(srow[j].x + (int32_t)k, (int32_t)std::min<int64_t>(kPrPiece, srow[j].y - k)));
+                owner.push_back(j);
+            }
+            split[j].y = (int32_t)pieces.size() - split[j].x;
+        }
+        const size_t sb = sizeof(int2) * (size_t)ns, pb = sizeof(int2) * pieces.size(), ob = sizeof(int32_t) * owner.size();
+        split_bytes = sb + pb + ob;
+        SP_TRY(dev_alloc(&pl.split, split_bytes));
+        char *d = (char *)pl.split;
+        SP_HIP(hipMemcpyAsync(d, split.data(), sb, hipMemcpyHostToDevice, s));
+        SP_HIP(hipMemcpyAsync(d + sb, pieces.data(), pb, hipMemcpyHostToDevice, s));
+        SP_HIP(hipMemcpyAsync(d + sb + pb, owner.data(), ob, hipMemcpyHostToDevice, s));
+        SP_HIP(hipStreamSynchronize(s));
+        pl.view.split = (const int2 *)d;
+        pl.view.pieces = (const int2 *)(d + sb);
+        pl.view.piece_row = (const int32_t *)(d + sb + pb);
+        pl.view.n_pieces = (int32_t)pieces.size();
+        pl.n_split = ns;
+    }
+    SP_HIP(hipStreamSynchronize(s));
+    pl.view.col = renum ? pl.col : ci;
+    pl.view.rows = rows;
+    pl.view.rp = rp;
+    pl.view.order = order;
+    pl.view.out_deg = out_deg;
+    g->bytes += row_bytes + split_bytes + (renum ? sizeof(int32_t) * (size_t)g->nnz : 0);
+    g->pr_plan = gd.p;
+    gd.p = nullptr;
+    return SP_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -206,7 +482,8 @@ sp_status pr_ws_create(sp_graph g, PrWorkspace &ws) {
         st = dev_alloc((void **)&ws.pr[p], sizeof(double) * n);
         if (st == SP_OK) st = dev_alloc((void **)&ws.share[p], sizeof(double) * n);
     }
-    if (st == SP_OK) st = dev_alloc((void **)&ws.partial, sizeof(double) * ((size_t)g->pr_chunks + 1));
+    if (st == SP_OK) st = dev_alloc((void **)&ws.partial, sizeof(double) * ((size_t)g->pr_plan->view.n_pieces + 1));
+    if (st == SP_OK) st = dev_alloc((void **)&ws.arrived, sizeof(int32_t) * ((size_t)g->pr_plan->n_split + 1));
     if (st == SP_OK) st = dev_alloc((void **)&ws.ctl, sizeof(PrCtl));
     if (st != SP_OK) {
         pr_ws_destroy(ws);
@@ -234,6 +511,7 @@ void pr_ws_destroy(PrWorkspace &ws) {
         dev_free(ws.share[p]);
     }
     dev_free(ws.partial);
+    dev_free(ws.arrived);
     dev_free(ws.ctl);
     if (ws.ctl_host) (void)hipHostFree(ws.ctl_host);
     if (ws.ev0) (void)hipEventDestroy(ws.ev0);
@@ -243,28 +521,14 @@ void pr_ws_destroy(PrWorkspace &ws) {
 
 // `count` iterations starting at an even iteration (parity = k & 1).
 template <int BS>
-static void enqueue_iterations(sp_graph g, PrWorkspace &ws, int count, int grid, int fin_grid,
+static void enqueue_iterations(const PrPlan &pl, const PrView &view, PrWorkspace &ws, int count, int grid,
                                double teleport, double delta, hipStream_t s) {
-    const bool hubs = g->pr_n_hubs > 0;
+    auto pull = pl.col ? k_pr_pull<BS, kPrHotPerThread * BS> : k_pr_pull<BS, 0>;
     for (int k = 0; k < count; ++k) {
-        const int32_t parity = k & 1;
-        {
-            ProfScope ps(P_PR_PULL, s);
-            hipLaunchKernelGGL(k_pr_pull<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
-                               (const int32_t *)g->rp_in, (const int32_t *)g->ci_in,
-                               (const int32_t *)g->row_ptr, ws.pr[0],
-                               ws.pr[1], ws.share[0], ws.share[1], ws.partial,
-                               (const HubEntry *)g->pr_hubs, (const int32_t *)g->pr_owner, g->n,
-                               (int32_t)g->pr_chunks, teleport, delta, (int32_t)!hubs, parity,
-                               prof_counters(P_PR_PULL));
-        }
-        if (hubs) {
-            ProfScope ps(P_PR_HUB, s);
-            hipLaunchKernelGGL(k_pr_hub_fin, dim3(fin_grid), dim3(256), 0, s, ws.ctl,
-                               (const int32_t *)g->row_ptr, ws.pr[0], ws.pr[1], ws.share[0], ws.share[1],
-                               (const double *)ws.partial, (const HubEntry *)g->pr_hubs, g->pr_n_hubs,
-                               teleport, delta, parity);
-        }
+        ProfScope ps(P_PR_PULL, s);
+        hipLaunchKernelGGL(pull, dim3(grid), dim3(BS), 0, s, ws.ctl, view, ws.pr[0], ws.pr[1], ws.share[0],
+                           ws.share[1], ws.partial, ws.arrived, teleport, delta, (int32_t)(k & 1),
+                           prof_counters(P_PR_PULL));
     }
 }
 
@@ -278,12 +542,25 @@ template <int BS>
 static sp_status pr_run_bs(sp_graph g, PrWorkspace &ws, double beta, double delta, int32_t max_iter,
                            double *out_pr, const PrOpts &o, hipStream_t s, PrResult *res) {
     const int32_t n = g->n;
-    const int maxb = device_cu_count() * 8;
-    const int grid = grid_for((int64_t)n, BS, maxb);
-    const int fin_grid = grid_for((int64_t)g->pr_n_hubs, 256, maxb);
+    const PrPlan &pl = *g->pr_plan;
+    PrView view = pl.view;
+    constexpr int team = BS > 512 ? 512 : BS, team_rows = BS / team;
+    constexpr int lanes[kPrRowClasses] = {team, team, 64, 16, 4, 1};
+    view.tile0[0] = 0;
+    view.tile0[1] = (view.n_pieces + team_rows - 1) / team_rows;
+    for (int k = 1; k < kPrRowClasses; ++k) {
+        const int32_t rows = view.row0[k + 1] - view.row0[k], per = BS / lanes[k];
+        view.tile0[k + 1] = view.tile0[k] + (int32_t)(((int64_t)rows + per - 1) / per);
+    }
+    // Renumbered: twice the blocks that fit at once, which evens out their rows.  Else as many as fit, and half of
+    // that up to 2 M vertices: every block ends in two atomics to one line each, which take 5 ns a block
+    // (road-1000, 20 iterations: 587 -> 488 us).
+    const int threads_per_cu = pl.col ? 4096 : n > (1 << 21) ? 2048 : 1024;
+    const int grid = grid_for(view.tile0[kPrRowClasses], 1, device_cu_count() * threads_per_cu / BS);
     const double teleport = (1.0 - delta) / (double)n;
     hipLaunchKernelGGL(k_pr_init, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.ctl,
-                       (const int32_t *)g->row_ptr, ws.pr[0], ws.share[0], n, beta, max_iter);
+                       (const int32_t *)g->row_ptr, pl.old_id, ws.pr[0], ws.share[0], n, beta, max_iter, ws.arrived,
+                       pl.n_split);
     SP_HIP(hipGetLastError());
     const bool capture = o.chunk_iters > 0 && !prof_enabled();
     const int base = std::max(1, std::abs(o.chunk_iters));
@@ -292,17 +569,16 @@ static sp_status pr_run_bs(sp_graph g, PrWorkspace &ws, double beta, double delt
     for (;;) {
         if (capture) {
             const std::array<long long, 12> key = {
-                BS, grid, fin_grid, chunk, (long long)(intptr_t)ws.pr[0], (long long)(intptr_t)ws.ctl,
-                (long long)(intptr_t)g->pr_hubs, bits_of(teleport),
-                bits_of(delta), g->pr_n_hubs, 0, 0};
+                BS, grid, chunk, (long long)(intptr_t)ws.pr[0], (long long)(intptr_t)ws.ctl,
+                (long long)(intptr_t)g->pr_plan, bits_of(teleport), bits_of(delta), pl.n_split, 0, 0, 0};
             SP_TRY(replay_captured(&ws.cap_stream, ws.iters, key,
                                    [&](hipStream_t cs) {
-                                       enqueue_iterations<BS>(g, ws, chunk, grid, fin_grid, teleport, delta, cs);
+                                       enqueue_iterations<BS>(pl, view, ws, chunk, grid, teleport, delta, cs);
                                    },
                                    s));
             ++graph_launches;
         } else {
-            enqueue_iterations<BS>(g, ws, chunk, grid, fin_grid, teleport, delta, s);
+            enqueue_iterations<BS>(pl, view, ws, chunk, grid, teleport, delta, s);
             SP_HIP(hipGetLastError());
         }
         enqueued += chunk;
@@ -315,7 +591,13 @@ static sp_status pr_run_bs(sp_graph g, PrWorkspace &ws, double beta, double delt
         }
     }
     const int32_t iters = ws.ctl_host->state >> 1;
-    SP_HIP(hipMemcpyAsync(out_pr, ws.pr[iters & 1], sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, s));
+    if (pl.new_id) {
+        hipLaunchKernelGGL(k_pr_export, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s,
+                           (const double *)ws.pr[iters & 1], pl.new_id, n, out_pr);
+        SP_HIP(hipGetLastError());
+    } else {
+        SP_HIP(hipMemcpyAsync(out_pr, ws.pr[iters & 1], sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, s));
+    }
     if (res) {
         res->iterations = iters;
         res->diff = ws.ctl_host->last_diff;
@@ -326,8 +608,12 @@ static sp_status pr_run_bs(sp_graph g, PrWorkspace &ws, double beta, double delt
 
 sp_status pr_run(sp_graph g, PrWorkspace &ws, double beta, double delta, int32_t max_iter,
                  double *out_pr, const PrOpts &o, hipStream_t s, PrResult *res) {
-    switch (o.block) {
+    // blocks of 1024 hold the most shares per copy: rmat-22, 20 iterations: 15.2, 14.9 and 13.7 ms with 256,
+    // 512 and 1024 threads; the others measured best with 512 (rmat-15 337, 267, 254 us, uniform with 8 M edges
+    // 2.42, 2.47, 2.63 ms)
+    switch (o.block ? o.block : g->pr_plan->col ? 1024 : 512) {
         case 128: return pr_run_bs<128>(g, ws, beta, delta, max_iter, out_pr, o, s, res);
+        case 1024: return pr_run_bs<1024>(g, ws, beta, delta, max_iter, out_pr, o, s, res);
         case 512: return pr_run_bs<512>(g, ws, beta, delta, max_iter, out_pr, o, s, res);
         default: return pr_run_bs<256>(g, ws, beta, delta, max_iter, out_pr, o, s, res);
     }

@@ -6,11 +6,37 @@
 namespace sp {
 
 // Degrees below kRankExact are ranked exactly, higher ones by their leading
-// six bits; the vertices of degree >= kRankExact hold ranks [0, rank_heavy).
+// six bits, so the vertices of at least a given degree hold the first ranks
+// when that degree is at most kRankExact or a power of two.
 constexpr int32_t kRankExact = 256;
+constexpr int32_t kRankBuckets = 1024;
 
-// Builds g->rank_new / g->rank_old / g->rank_heavy once; the caller holds g->mu.
+// Class of a degree, 0 = heaviest: exact below 256, then 32 classes per octave.
+__host__ __device__ inline int32_t rank_bucket(int32_t deg) {
+    int32_t key = deg;
+    if (deg >= kRankExact) {
+        const int32_t e = 31 - __builtin_clz((unsigned)deg);  // 8..30
+        key = kRankExact + (e - 8) * 32 + ((deg >> (e - 5)) & 31);
+    }
+    return kRankBuckets - 1 - key;
+}
+
+// Builds g->rank_new / g->rank_old / g->rank_first once; the caller holds g->mu.
 sp_status ensure_rank_locked(sp_graph g, hipStream_t s);
+
+// Vertices of degree >= deg (at most kRankExact, or a power of two); after ensure_rank_locked.
+inline int32_t rank_count(sp_graph g, int32_t deg) { return g->rank_first[rank_bucket(deg) + 1]; }
+
+// Row classes by length, longest first, and a stable sort of n vertices into
+// them: order[i] = the i-th vertex, first[c] = where class c starts
+// (first[kRowClasses] = n).  Vertex x has the row of old[x] (x itself when old
+// is null) in rp.  Class 0 holds the rows longer than `longest`.
+constexpr int32_t kRowClasses = 6;
+__host__ __device__ inline int32_t row_class(int32_t len, int32_t longest) {
+    return len > longest ? 0 : len >= 512 ? 1 : len > 128 ? 2 : len > 32 ? 3 : len > 8 ? 4 : 5;
+}
+sp_status sort_rows_by_class(const int32_t *rp, const int32_t *old, int32_t n, int32_t longest, int32_t *order,
+                             int32_t *first, hipStream_t s);
 
 constexpr int32_t kScanTile = 1024;  // counts per scan tile (256 threads x 4)
 

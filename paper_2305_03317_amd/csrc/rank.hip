@@ -1,12 +1,12 @@
 // Vertices ranked by degree, highest first: rank_new[v] is v's rank, rank_old
 // its inverse.  Ties of equal degree go to the higher id first.  Degrees of
 // 256 and more are ranked by their leading six bits (the order only has to
-// put heavy vertices first; any fixed total order orients a graph).
+// put heavy vertices first; any fixed total order orients a graph).  The same
+// sort lists rows by length class (sort_rows_by_class).
 //
-// A stable counting sort over kRankBuckets degree classes: a wave per tile of
-// kRankTile ids counts its classes in LDS, the counts are scanned class by
-// class, and the same walk hands out the ranks.  About 0.2 ms for 4.2 M
-// vertices, once per graph.
+// A stable counting sort: a wave per tile of items counts its buckets in LDS,
+// the counts are scanned bucket by bucket, and the same walk hands out the
+// places.  About 0.2 ms for the degrees of 4.2 M vertices, once per graph.
 #include "common.h"
 #include "devutil.h"
 #include "rank.h"
@@ -14,54 +14,64 @@
 namespace sp {
 
 namespace {
-constexpr int32_t kRankBuckets = 1024;
-constexpr int32_t kRankTile = 256;  // ids per wave; longer where that would be over 2048 tiles
+constexpr int32_t kRankTile = 256;  // items per wave; longer where that would be over 2048 tiles
+
+// What is sorted: item i's bucket, and what to do with its place.
+struct ByDegree {  // item i is vertex n - 1 - i (ties rank the higher id first)
+    static constexpr int32_t kBuckets = kRankBuckets;
+    const int32_t *rp;
+    int32_t n;
+    int32_t *rank_new, *rank_old;
+    __device__ int32_t bucket(int64_t i) const {
+        const int32_t v = (int32_t)(n - 1 - i);
+        return rank_bucket(rp[v + 1] - rp[v]);
+    }
+    __device__ void place(int64_t i, int32_t r) const {
+        const int32_t v = (int32_t)(n - 1 - i);
+        rank_new[v] = r;
+        rank_old[r] = v;
+    }
+};
+struct ByRowClass {
+    static constexpr int32_t kBuckets = kRowClasses;
+    const int32_t *rp, *old;
+    int32_t n, longest;
+    int32_t *order;
+    __device__ int32_t bucket(int64_t i) const {
+        const int32_t v = old ? old[i] : (int32_t)i;
+        return row_class(rp[v + 1] - rp[v], longest);
+    }
+    __device__ void place(int64_t i, int32_t r) const { order[r] = (int32_t)i; }
+};
 }  // namespace
 
-// Class of a degree, 0 = heaviest: exact below 256, then 32 classes per octave.
-__device__ __forceinline__ int32_t rank_bucket(int32_t deg) {
-    int32_t key = deg;
-    if (deg >= kRankExact) {
-        const int32_t e = 31 - __clz(deg);  // 8..30
-        key = kRankExact + (e - 8) * 32 + ((deg >> (e - 5)) & 31);
-    }
-    return kRankBuckets - 1 - key;
-}
-
-// Tile t covers the ids n-1-i for i in [t, t+1) * tile (descending, so
-// that ties rank the higher id first).
-__global__ __launch_bounds__(kWave) void k_rank_count(const int32_t *__restrict__ rp, int32_t n,
-                                                      int32_t tile, int32_t ntiles, int32_t *hist) {
-    __shared__ int32_t s_cnt[kRankBuckets];
-    for (int32_t b = threadIdx.x; b < kRankBuckets; b += kWave) s_cnt[b] = 0;
+template <class Item>
+__global__ __launch_bounds__(kWave) void k_sort_count(Item it, int32_t tile, int32_t ntiles, int32_t *hist) {
+    __shared__ int32_t s_cnt[Item::kBuckets];
+    for (int32_t b = threadIdx.x; b < Item::kBuckets; b += kWave) s_cnt[b] = 0;
     __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * tile, i1 = min((int64_t)n, i0 + tile);
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kWave) {
-        const int32_t v = (int32_t)(n - 1 - i);
-        atomicAdd(&s_cnt[rank_bucket(rp[v + 1] - rp[v])], 1);
-    }
+    const int64_t i0 = (int64_t)blockIdx.x * tile, i1 = min((int64_t)it.n, i0 + tile);
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kWave) atomicAdd(&s_cnt[it.bucket(i)], 1);
     __syncthreads();
-    for (int32_t b = threadIdx.x; b < kRankBuckets; b += kWave)
+    for (int32_t b = threadIdx.x; b < Item::kBuckets; b += kWave)
         hist[(int64_t)b * ntiles + blockIdx.x] = s_cnt[b];
 }
 
-__global__ __launch_bounds__(kWave) void k_rank_place(const int32_t *__restrict__ rp, int32_t n,
-                                                      int32_t tile, int32_t ntiles,
-                                                      const int32_t *__restrict__ first,
-                                                      int32_t *rank_new, int32_t *rank_old) {
-    __shared__ int32_t s_at[kRankBuckets];
-    for (int32_t b = threadIdx.x; b < kRankBuckets; b += kWave)
+template <class Item>
+__global__ __launch_bounds__(kWave) void k_sort_place(Item it, int32_t tile, int32_t ntiles,
+                                                      const int32_t *__restrict__ first) {
+    __shared__ int32_t s_at[Item::kBuckets];
+    for (int32_t b = threadIdx.x; b < Item::kBuckets; b += kWave)
         s_at[b] = first[(int64_t)b * ntiles + blockIdx.x];
     __syncthreads();
     const int lane = lane_id();
-    const int64_t i0 = (int64_t)blockIdx.x * tile, i1 = min((int64_t)n, i0 + tile);
+    const int64_t i0 = (int64_t)blockIdx.x * tile, i1 = min((int64_t)it.n, i0 + tile);
     for (int64_t b = i0; b < i1; b += kWave) {
         const int64_t i = b + lane;
-        const int32_t v = (int32_t)(n - 1 - i);
-        const int32_t mine = i < i1 ? rank_bucket(rp[v + 1] - rp[v]) : -1;
+        const int32_t mine = i < i1 ? it.bucket(i) : -1;
         unsigned long long todo = __ballot(i < i1);
         int32_t r = 0;
-        while (todo) {  // one class of this step at a time, its lanes in order
+        while (todo) {  // one bucket of this step at a time, its lanes in order
             const int leader = __ffsll((long long)todo) - 1;
             const int32_t bk = __builtin_amdgcn_readlane(mine, leader);
             const unsigned long long same = __ballot(mine == bk);
@@ -72,10 +82,7 @@ __global__ __launch_bounds__(kWave) void k_rank_place(const int32_t *__restrict_
             __builtin_amdgcn_wave_barrier();
             todo &= ~same;
         }
-        if (i < i1) {
-            rank_new[v] = r;
-            rank_old[r] = v;
-        }
+        if (i < i1) it.place(i, r);
     }
 }
 
@@ -137,46 +144,65 @@ void launch_excl_scan(const int32_t *in, int64_t n, int32_t *out, int32_t *tiles
     hipLaunchKernelGGL(k_scan_add, dim3(nt), dim3(256), 0, s, out, n, (const int32_t *)tiles);
 }
 
-sp_status ensure_rank_locked(sp_graph g, hipStream_t s) {
-    if (g->rank_new) return SP_OK;
-    const int32_t n = g->n;
+// start[b] = first[b * stride] for b in [0, count).
+__global__ void k_sort_starts(const int32_t *__restrict__ first, int32_t stride, int32_t count, int32_t *start) {
+    for (int32_t b = threadIdx.x; b < count; b += blockDim.x) start[b] = first[(int64_t)b * stride];
+}
+
+// Stable counting sort of `it`; start[b] receives where bucket b begins
+// (start[kBuckets] = n).  Synchronises the stream.
+template <class Item>
+static sp_status counting_sort(const Item &it, int32_t *start, hipStream_t s) {
+    constexpr int32_t nb = Item::kBuckets;
+    const int32_t n = it.n;
     const int32_t tile = std::max(kRankTile, (n / 2048 / kWave + 1) * kWave);
     const int32_t ntiles = (int32_t)std::max<int64_t>(1, ((int64_t)n + tile - 1) / tile);
-    const int64_t cells = (int64_t)kRankBuckets * ntiles;
-    const size_t vn = (size_t)std::max(n, 1);
-    int32_t *rn = nullptr, *tmp = nullptr;
-    auto fail = [&](sp_status st) {
-        dev_free(rn);
-        dev_free(tmp);
-        return st;
-    };
-    sp_status st = dev_alloc((void **)&rn, 2 * sizeof(int32_t) * vn);
-    int32_t *ro = rn ? rn + vn : nullptr;
-    // counts, their scan (one more for the total), the scan's tiles
-    if (st == SP_OK) st = dev_alloc((void **)&tmp, sizeof(int32_t) * (size_t)(2 * cells + 1 + scan_tiles(cells)));
-    if (st != SP_OK) return fail(st);
-    int32_t *hist = tmp, *first = tmp + cells, *tiles = first + cells + 1;
+    const int64_t cells = (int64_t)nb * ntiles;
+    int32_t *tmp = nullptr;  // counts, their scan (one more for the total), the scan's tiles
+    SP_TRY(dev_alloc((void **)&tmp, sizeof(int32_t) * (size_t)(2 * cells + 2 + scan_tiles(cells))));
+    int32_t *hist = tmp, *first = tmp + cells + 1, *tiles = first + cells + 1;
+    for (int32_t b = 0; b <= nb; ++b) start[b] = 0;
+    hipError_t e = hipSuccess;
     if (n > 0) {
-        hipLaunchKernelGGL(k_rank_count, dim3(ntiles), dim3(kWave), 0, s, (const int32_t *)g->row_ptr, n, tile,
-                           ntiles, hist);
+        hipLaunchKernelGGL((k_sort_count<Item>), dim3(ntiles), dim3(kWave), 0, s, it, tile, ntiles, hist);
         launch_excl_scan(hist, cells, first, tiles, s);
-        hipLaunchKernelGGL(k_rank_place, dim3(ntiles), dim3(kWave), 0, s, (const int32_t *)g->row_ptr, n, tile,
-                           ntiles, (const int32_t *)first, rn, ro);
+        hipLaunchKernelGGL((k_sort_place<Item>), dim3(ntiles), dim3(kWave), 0, s, it, tile, ntiles,
+                           (const int32_t *)first);
+        hipLaunchKernelGGL(k_sort_starts, dim3(1), dim3(256), 0, s, (const int32_t *)first, ntiles, nb + 1, hist);
+        e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(start, hist, sizeof(int32_t) * (nb + 1), hipMemcpyDeviceToHost, s);
     }
-    hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-        set_error("ranking the vertices failed: %s", hipGetErrorString(e));
-        return fail(SP_ERR_DEVICE);
-    }
     dev_free(tmp);
-    g->rank_new = rn;
-    g->rank_old = ro;
-    g->bytes += 2 * sizeof(int32_t) * vn;
-    int32_t heavy = 0;
-    for (int32_t v = 0; v < n; ++v) heavy += g->host_deg[v] >= kRankExact;
-    g->rank_heavy = heavy;
+    if (e != hipSuccess) {
+        set_error("sorting the vertices failed: %s", hipGetErrorString(e));
+        return SP_ERR_DEVICE;
+    }
     return SP_OK;
+}
+
+sp_status ensure_rank_locked(sp_graph g, hipStream_t s) {
+    if (g->rank_new) return SP_OK;
+    const size_t vn = (size_t)std::max(g->n, 1);
+    int32_t *rn = nullptr;
+    SP_TRY(dev_alloc((void **)&rn, 2 * sizeof(int32_t) * vn));
+    std::vector<int32_t> start(kRankBuckets + 1);
+    const sp_status st = counting_sort(ByDegree{g->row_ptr, g->n, rn, rn + vn}, start.data(), s);
+    if (st < 0) {
+        dev_free(rn);
+        return st;
+    }
+    g->rank_first = std::move(start);
+    g->rank_new = rn;
+    g->rank_old = rn + vn;
+    g->bytes += 2 * sizeof(int32_t) * vn;
+    return SP_OK;
+}
+
+sp_status sort_rows_by_class(const int32_t *rp, const int32_t *old, int32_t n, int32_t longest, int32_t *order,
+                             int32_t *first, hipStream_t s) {
+    return counting_sort(ByRowClass{rp, old, n, longest, order}, first, s);
 }
 
 }  // namespace sp

@@ -552,7 +552,7 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     std::lock_guard<std::mutex> lk(g->mu);
     if (g->tc_orp) return SP_OK;
     SP_TRY(ensure_rank_locked(g, s));
-    const int32_t n = g->n, heavy = g->rank_heavy;
+    const int32_t n = g->n, heavy = rank_count(g, kRankExact);
     const int maxb = device_cu_count() * 8;
     const size_t vn = (size_t)std::max(n, 1);
     const int32_t *rp = g->row_ptr, *ci = g->col_idx, *rn = g->rank_new, *ro = g->rank_old;
