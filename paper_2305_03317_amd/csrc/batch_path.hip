@@ -66,6 +66,21 @@ __device__ __forceinline__ unsigned long long rl_u64(unsigned long long v, int j
     return (unsigned long long)lo | ((unsigned long long)hi << 32);
 }
 
+// Entries a wave takes of a level of cnt: 64 once the level fills kSpreadBlocks
+// blocks of waves, else the power of two from 4 up that spreads it over them.
+// A wave sums its dense entries one after another, so a small level in whole
+// waves runs on a few of them for as long as 64 rows take (uniform, 4,096
+// vertices, 16 sources: k_ms_sigma 53 us a level, k_ms_delta 83, eight blocks
+// working).  Under 4 the waves' own bookkeeping costs more than it spreads.
+constexpr int kSpreadBlocks = 512;
+template <int BS>
+__device__ __forceinline__ int32_t wave_share(int64_t cnt) {
+    const int64_t waves = (int64_t)min((int)gridDim.x, kSpreadBlocks) * (BS / kWave);
+    int32_t e = 4;
+    while (e < kWave && waves * e < cnt) e <<= 1;
+    return e;
+}
+
 __device__ __forceinline__ int rank_in(unsigned long long m, int s) {
     return __popcll(m & ((1ull << s) - 1ull));
 }
@@ -407,13 +422,19 @@ __global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int
                           int32_t *owner, int32_t *chunk_off, int32_t n,
                           long long nnz, unsigned long long active, double alpha, double beta) {
     __shared__ uint32_t s_vb[kSlots + 1];
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int32_t i = 0; i < n0; ++i) {
-            s_vb[i] = run;
-            run += (uint32_t)__popcll(qmask[i]);
+    // wave 0 holds entry i (n0 <= 64) in lane i
+    int32_t v0 = 0, d0 = 0, pc0 = 0;
+    unsigned long long m0 = 0;
+    if (threadIdx.x < kWave) {
+        if ((int32_t)threadIdx.x < n0) {
+            v0 = queue[threadIdx.x];
+            m0 = qmask[threadIdx.x];
+            d0 = rp[v0 + 1] - rp[v0];
+            pc0 = __popcll(m0);
         }
-        s_vb[n0] = run;
+        const int32_t incl = wave_incl_scan(pc0);
+        s_vb[threadIdx.x] = (uint32_t)(incl - pc0);
+        if (threadIdx.x == kWave - 1) s_vb[kSlots] = (uint32_t)incl;
     }
     __syncthreads();
     const int lane = lane_id();
@@ -429,23 +450,22 @@ __global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int
             qvb[i] = vb;
         }
     }
-    if (threadIdx.x == 0) {
-        unsigned long long fdeg = 0, settled = 0, pairs = 0;
-        int32_t nh = 0, nch = 0;
-        for (int32_t i = 0; i < n0; ++i) {
-            const int32_t v = queue[i];
-            const int32_t d = rp[v + 1] - rp[v];
-            fdeg += (unsigned long long)d;
-            pairs += (unsigned long long)__popcll(qmask[i]);
-            if (qmask[i] == active) settled += (unsigned long long)d;
-            if (d > kHubDeg) {  // at most kSlots hubs; split hubs start at a multiple of kXcds
-                const int32_t k = split_hub_nchunks(d);
-                const int32_t base = k >= kXcds ? (nch + kXcds - 1) & ~(kXcds - 1) : nch;
-                for (int32_t q = nch; q < base + k; ++q) owner[q] = nh;
-                hub_list[nh++] = HubEntry{v, i, base, k};
-                nch = base + k;
-            }
-        }
+    if (threadIdx.x >= kWave) return;
+    const unsigned long long fdeg = wave_sum_u64((unsigned long long)d0);
+    const unsigned long long pairs = wave_sum_u64((unsigned long long)pc0);
+    const unsigned long long settled = wave_sum_u64(m0 == active ? (unsigned long long)d0 : 0ull);
+    int32_t nh = 0, nch = 0;
+    for (unsigned long long hubs = __ballot(d0 > kHubDeg); hubs; hubs &= hubs - 1) {
+        // at most kSlots hubs; split hubs start at a multiple of kXcds
+        const int j = __ffsll((long long)hubs) - 1;
+        const int32_t k = split_hub_nchunks(rl_i32(d0, j));
+        const int32_t base = k >= kXcds ? (nch + kXcds - 1) & ~(kXcds - 1) : nch;
+        for (int32_t q = nch + lane; q < base + k; q += kWave) owner[q] = nh;
+        if (lane == 0) hub_list[nh] = HubEntry{rl_i32(v0, j), j, base, k};
+        ++nh;
+        nch = base + k;
+    }
+    if (lane == 0) {
         c->level = 0;
         c->lo = 0;
         c->hi = n0;
@@ -525,11 +545,12 @@ __global__ __launch_bounds__(BS) void k_ms_topdown(LevelCtl *c, const int32_t *_
         return false;
     };
     if (blockIdx.y == 0) {
-        for (int32_t b = lo + blockIdx.x * BS; b < hi; b += gridDim.x * BS) {
-            const int32_t i = b + threadIdx.x;
+        const int32_t per = BS / kWave * wave_share<BS>(hi - lo);  // entries per block and step
+        for (int64_t b = lo + (int64_t)blockIdx.x * per; b < hi; b += (int64_t)gridDim.x * per) {
+            const int64_t i = b + threadIdx.x;
             int32_t beg = 0, deg = 0;
             unsigned long long fm = 0;
-            if (i < hi) {
+            if (i < hi && (int32_t)threadIdx.x < per) {
                 const int32_t v = queue[i];
                 fm = qmask[i];
                 beg = rp[v];
@@ -615,11 +636,14 @@ __global__ __launch_bounds__(BS) void k_ms_bottomup(LevelCtl *c, const int32_t *
     const int32_t n = c->n_vertices;
     const int g = lane >> 3, j = lane & 7;
     unsigned long long my_items = 0, my_edges = 0, my_pull = 0;
-    for (int32_t b = blockIdx.x * BS; b < n; b += gridDim.x * BS) {
-        const int32_t v = b + threadIdx.x;
+    const int32_t share = wave_share<BS>(n);
+    const int32_t per = BS / kWave * share;
+    for (int64_t b = (int64_t)blockIdx.x * per; b < n; b += (int64_t)gridDim.x * per) {
+        const int64_t at = b + threadIdx.x / kWave * share + lane;
+        const int32_t v = (int32_t)min(at, (int64_t)n);
         int32_t beg = 0, deg = 0;
         unsigned long long u_s = 0;
-        if (v < n) {
+        if (at < n && lane < share) {
             u_s = c->live & ~seen[v];  // live only ever holds slots in use
             if (u_s) {
                 beg = rp[v];
@@ -807,9 +831,12 @@ __global__ __launch_bounds__(BS, 6) void k_ms_sigma(LevelCtl *c, const int32_t *
     unsigned long long my_deg = 0, my_settled = 0, my_flag = 0, my_pairs = 0, my_items = 0,
                        my_dag = 0, my_or = 0, my_scan = 0;
     double my_max = 0.0;
-    for (int32_t b = hi + (int32_t)(blockIdx.x * BS); b < tail; b += gridDim.x * BS) {
-        const int32_t i = b + (int32_t)threadIdx.x;
-        const bool valid = i < tail;
+    const int32_t share = wave_share<BS>((int64_t)tail - hi);
+    const int32_t per = BS / kWave * share;  // entries per block and step
+    for (int64_t b = hi + (int64_t)blockIdx.x * per; b < tail; b += (int64_t)gridDim.x * per) {
+        const int64_t at = b + threadIdx.x / kWave * share + lane;
+        const bool valid = at < tail && lane < share;
+        const int32_t i = (int32_t)min(at, (int64_t)tail);
         int32_t w = 0, beg = 0, end = 0, dout = 0;
         unsigned long long m = 0;
         if (valid) {
@@ -922,7 +949,7 @@ __global__ __launch_bounds__(BS, 6) void k_ms_sigma(LevelCtl *c, const int32_t *
         block_add_u64<BS>(my_pairs, s_red, prof + 3);
     }
     // the last block to finish closes the level
-    if (last_block(c, working_blocks((int64_t)tail - hi, BS)) && threadIdx.x == 0)
+    if (last_block(c, working_blocks((int64_t)tail - hi, per)) && threadIdx.x == 0)
         advance_level(c, level_off, hub_off, hub_lvl_chunks, qcap, hub_cap, chunk_off, owner_cap, push);
 }
 
@@ -1497,10 +1524,13 @@ __global__ __launch_bounds__(BS, 6) void k_ms_delta(LevelCtl *c, int32_t step,
     const uint32_t nl = (uint32_t)lvl + 1;
     const int lane = lane_id();
     unsigned long long my_items = 0, my_edges = 0, my_pairs = 0, my_slots = 0;
-    for (int32_t b = lo + (int32_t)(blockIdx.x * BS + threadIdx.x) - lane; b < hi;
-         b += gridDim.x * BS) {
-        const int32_t i = b + lane;
-        const bool valid = i < hi;
+    const int32_t share = wave_share<BS>((int64_t)hi - lo);
+    const int32_t per = BS / kWave * share;  // entries per block and step
+    for (int64_t b = lo + (int64_t)blockIdx.x * per + threadIdx.x / kWave * share; b < hi;
+         b += (int64_t)gridDim.x * per) {
+        const int64_t at = b + lane;
+        const bool valid = at < hi && lane < share;
+        const int32_t i = (int32_t)min(at, (int64_t)hi);
         int32_t v = 0, beg = 0, end = 0;
         unsigned long long m = 0;
         uint32_t vb = 0;
@@ -1563,7 +1593,7 @@ __global__ __launch_bounds__(BS, 6) void k_ms_delta(LevelCtl *c, int32_t step,
         block_add_u64<BS>(my_slots, s_red, prof + 3);
     }
     // when no hub kernel follows, the last block moves the sweep one level up
-    if (step && last_block(c, working_blocks((int64_t)hi - lo, BS)) && threadIdx.x == 0)
+    if (step && last_block(c, working_blocks((int64_t)hi - lo, per)) && threadIdx.x == 0)
         c->bwd_level = lvl - 1;
 }
 
@@ -1861,6 +1891,13 @@ static sp_status grow_queue(sp_graph g, BatchWorkspace &ws, int64_t qcap) {
 // The kernels of `count` forward levels starting at level `first`.  Every
 // kernel reads the level it works on from the control block, so the same
 // launches serve any chunk whose first level has the same parity.
+// Blocks for levels of up to cnt entries: one per BS of them, or what
+// wave_share spreads a small level over.
+template <int BS>
+static int level_grid(int64_t cnt, int maxb) {
+    return std::max(grid_for(cnt, BS, maxb), grid_for(cnt, BS / kWave * 4, std::min(maxb, kSpreadBlocks)));
+}
+
 template <int BS>
 static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int count, int grid,
                            int hub_grid, bool may_pull, hipStream_t s) {
@@ -1965,7 +2002,7 @@ static sp_status batch_forward(sp_graph g, BatchWorkspace &ws, int32_t n0, unsig
                                const BatchRunOpts &o, hipStream_t s, int32_t *graph_launches) {
     const int32_t n = g->n;
     const int maxb = device_cu_count() * 8;
-    const int grid = grid_for((int64_t)n, BS, maxb);
+    const int grid = level_grid<BS>(n, maxb);
     const bool may_pull = o.alpha > 0 && g->max_degree > 8;  // sparse meshes never pull
     const int hub_grid = xcd_grid(grid_for((partial_rows(g) - 1) * kWave, BS, maxb), maxb);
     hipLaunchKernelGGL(k_ms_clear, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.seen, ws.nxt,
@@ -2121,7 +2158,7 @@ static sp_status batch_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *src
         maxcnt = std::max<int64_t>(maxcnt, off[l + 1] - off[l]);
         if (l < levels - 1) maxh = std::max(maxh, hch[l]);
     }
-    const int grid_d = pow2_at_least(grid_for(maxcnt, BS, maxb), maxb);
+    const int grid_d = pow2_at_least(level_grid<BS>(maxcnt, maxb), maxb);
     const int grid_h =
         xcd_grid(pow2_at_least(grid_for((int64_t)std::max(maxh, 1) * kWave, BS, maxb), maxb), maxb);
     const bool hubs = maxh > 0;
