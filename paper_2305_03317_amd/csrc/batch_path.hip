@@ -67,16 +67,19 @@ __device__ __forceinline__ unsigned long long rl_u64(unsigned long long v, int j
 }
 
 // Entries a wave takes of a level of cnt: 64 once the level fills kSpreadBlocks
-// blocks of waves, else the power of two from 4 up that spreads it over them.
+// blocks of waves, else the power of two from 2 up that spreads it over them.
 // A wave sums its dense entries one after another, so a small level in whole
 // waves runs on a few of them for as long as 64 rows take (uniform, 4,096
 // vertices, 16 sources: k_ms_sigma 53 us a level, k_ms_delta 83, eight blocks
-// working).  Under 4 the waves' own bookkeeping costs more than it spreads.
-constexpr int kSpreadBlocks = 512;
+// working; now 13 and 20).  Measured with 512 to 2,048 blocks and from 1 to 4
+// entries: uniform-4096 468..507 us, directed rmat-18 2.13..2.34 ms, both best
+// with these.
+constexpr int32_t kLeastShare = 2;
+constexpr int kSpreadBlocks = 1024;
 template <int BS>
 __device__ __forceinline__ int32_t wave_share(int64_t cnt) {
     const int64_t waves = (int64_t)min((int)gridDim.x, kSpreadBlocks) * (BS / kWave);
-    int32_t e = 4;
+    int32_t e = kLeastShare;
     while (e < kWave && waves * e < cnt) e <<= 1;
     return e;
 }
@@ -497,6 +500,8 @@ __global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int
         c->in_hub_nchunks = 0;
         c->pull_cost_.v = 0;
         c->sigma_push = 0;
+        c->max_entries = 1;
+        c->max_hub_chunks = 0;
         c->hub_lo = 0;
         c->hub_hi = nh;
         c->hub_nchunks = nch;
@@ -511,21 +516,111 @@ __global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int
     }
 }
 
+// Hubs, lane = slot: each chunk of kHubChunk adjacency entries is reduced by
+// its own wave into a row of `partial` (64 doubles); a second kernel adds a
+// hub's rows in chunk order.  The kernel boundary between them makes the rows
+// visible without fences inside either kernel.  The chunk kernels are bounded
+// to eight waves per SIMD (their scalar registers otherwise allow seven):
+// rmat-22, per 1,024 sources, k_ms_delta_hub 108.1 -> 106.8 ms and
+// their pulls 48.1 -> 47.0 ms.
+__device__ __forceinline__ double sum_rows(const double *__restrict__ partial, int32_t base,
+                                           int32_t n) {
+    const int lane = lane_id();
+    double s = 0.0;
+    int32_t q = 0;
+    for (; q + 8 <= n; q += 8) {  // eight rows in flight, added in chunk order
+        double x[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] = partial[(int64_t)(base + q + t) * kSlots + lane];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) s += x[t];
+    }
+    for (; q < n; ++q) s += partial[(int64_t)(base + q) * kSlots + lane];
+    return s;
+}
+
+// A hub's chunk rows added in row order (split_id for a split hub).
+__device__ __forceinline__ double sum_hub_rows(const double *__restrict__ partial,
+                                               const HubEntry &h) {
+    if (h.nchunks < kXcds) return sum_rows(partial, h.chunk_base, h.nchunks);
+    const int lane = lane_id();
+    double s = 0.0;
+    for (int32_t r = 0; r < h.nchunks; r += 8) {  // nchunks is a multiple of 8
+        double x[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            x[t] = partial[(int64_t)(h.chunk_base + split_id(h.nchunks, r + t)) * kSlots + lane];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) s += x[t];
+    }
+    return s;
+}
+
+// Path counts of the level just built that k_ms_sigma_rest left to finish,
+// by the blocks of the next level's first kernel (y == 0): a pushed level's
+// largest count, one pass over its values [val_lo, reached_pairs), contiguous
+// in the value store (pushed sums are below 2^53, so no slot is flagged); else
+// its hubs' counts, each hub's chunk rows added in chunk order, a wave per hub.
+// Nothing reads either before that level's k_ms_sigma.
+__device__ __forceinline__ void settle_level(LevelCtl *c, const unsigned long long *__restrict__ qmask,
+                                             const uint32_t *__restrict__ qvb, double *val,
+                                             const HubEntry *__restrict__ hub_list,
+                                             const double *__restrict__ partial,
+                                             const HubEntry *__restrict__ in_hub_list) {
+    const int lane = lane_id();
+    unsigned long long my_flag = 0;
+    double my_max = 0.0;
+    if (c->sigma_push) {
+        const int64_t lo = (int64_t)c->val_lo, hi = (int64_t)c->reached_pairs;
+        for (int64_t k = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < hi;
+             k += (int64_t)gridDim.x * blockDim.x)
+            my_max = fmax(my_max, val[k]);
+    } else {
+        if (in_hub_list) hub_list = in_hub_list;  // directed: the level's incoming-row hubs
+        const int32_t hlo = in_hub_list ? 0 : c->hub_lo, hhi = in_hub_list ? c->in_hub_n : c->hub_hi;
+        if (c->level < 1 || hlo >= hhi) return;  // level 0 was given its counts
+        const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+        const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / kWave;
+        for (int64_t j = hlo + wave0; j < hhi; j += nwaves) {
+            const HubEntry h = hub_list[j];
+            const unsigned long long m = qmask[h.entry];
+            const double s = sum_hub_rows(partial, h);
+            const bool mine = (m >> lane) & 1ull;
+            if (mine) {
+                val[qvb[h.entry] + rank_in(m, lane)] = s;
+                my_max = fmax(my_max, s);
+            }
+            my_flag |= __ballot(mine && sigma_is_large(s));
+        }
+    }
+    my_max = wave_max_f64(my_max);
+    if (lane == 0) {
+        atomic_max_nonneg_f64(&c->sigma_max_bits_.v, my_max);
+        if (my_flag) atomicOr(&c->flagged_slots_.v, my_flag);
+    }
+}
+
 // Top-down discovery.  blockIdx.y == 0: block gather over the frontier's
 // entries (hubs excluded), one adjacency entry per lane.  blockIdx.y == 1:
-// the chunks of the frontier's hubs.
+// the chunks of the frontier's hubs.  It is the first kernel of a level in
+// either direction, and finishes the last one's path counts (settle_level).
 template <int BS>
 __global__ __launch_bounds__(BS) void k_ms_topdown(LevelCtl *c, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ ci,
                                                    const int32_t *__restrict__ rpi, int32_t *queue,
                                                    const unsigned long long *__restrict__ qmask,
+                                                   const uint32_t *__restrict__ qvb, double *val,
+                                                   const double *__restrict__ partial,
+                                                   const HubEntry *__restrict__ in_hub_list,
                                                    const unsigned long long *__restrict__ seen,
                                                    unsigned long long *nxt,
                                                    const HubEntry *__restrict__ hub_list,
                                                    const int32_t *__restrict__ owner,
                                                    const int32_t *__restrict__ chunk_off,
                                                    long long qcap, unsigned long long *prof) {
-    if (c->done || c->mode != MODE_TOPDOWN) return;
+    if (c->done) return;
+    if (blockIdx.y == 0) settle_level(c, qmask, qvb, val, hub_list, partial, in_hub_list);
+    if (c->mode != MODE_TOPDOWN) return;
     __shared__ int32_t s_beg[BS], s_off[BS], s_scan[BS / kWave + 1];
     __shared__ unsigned long long s_mask[BS];
     __shared__ int32_t s_qbuf[4 * BS], s_meta[2];
@@ -736,6 +831,9 @@ __device__ void advance_level(LevelCtl *c, int32_t *level_off, int32_t *hub_off,
     }
     const int32_t nl = c->level + 1;
     level_off[nl + 1] = tail;
+    // the reverse pass's grids: the largest level, the most hub chunks of one that has children
+    c->max_entries = max(c->max_entries, nf);
+    if (c->level >= 1) c->max_hub_chunks = max(c->max_hub_chunks, c->hub_nchunks);
     c->hub_lo = c->hub_next;
     c->hub_hi = c->hub_next + (int32_t)(hp >> 40);
     c->hub_nchunks = (int32_t)(hp & ((1ull << 40) - 1));
@@ -785,7 +883,7 @@ __device__ __forceinline__ bool push_sigma(const LevelCtl *c, int32_t max_deg) {
 // Path counts of the new entries [hi, tail).  Wave takes 64 entries, gives
 // each its value range, then: sparse entries are reduced by their own lane,
 // dense ones by the whole wave in turn, hubs are registered for
-// k_ms_sigma_hub.  Every entry's bookkeeping (qmask, value base, nxt reset,
+// k_ms_sigma_rest.  Every entry's bookkeeping (qmask, value base, nxt reset,
 // seen, front of the new level) is done here.  Six waves per SIMD, with some
 // registers spilled, beat fewer waves without spills (rmat-22, 64-source
 // batches, per 1,024 sources: 4 waves 55.4 ms in this kernel, 5: 56.1,
@@ -812,7 +910,7 @@ __global__ __launch_bounds__(BS, 6) void k_ms_sigma(LevelCtl *c, const int32_t *
     __shared__ int32_t s_scan[BS / kWave + 1], s_poff[BS], s_pbeg[BS];
     const uint32_t lvl = (uint32_t)c->level;
     // Path counts of the new level by pull (each new entry sums its parents
-    // over its incoming row) or by push (k_ms_sigma_push: each parent adds
+    // over its incoming row) or by push (k_ms_sigma_rest: each parent adds
     // its values into its children with float atomics), whichever reads
     // fewer adjacency entries: the new entries' incoming rows (counted by
     // discovery) against the parents' outgoing rows.  The push is taken only
@@ -901,7 +999,7 @@ __global__ __launch_bounds__(BS, 6) void k_ms_sigma(LevelCtl *c, const int32_t *
             hub_register(&c->hub_pack_.v, hub_list, hub_cap, c->hub_next, w, i, deg, owner,
                          c->chunk_next, owner_cap);
         }
-        if (sparse || dense) my_scan += (unsigned long long)deg;  // hubs: k_ms_sigma_hub
+        if (sparse || dense) my_scan += (unsigned long long)deg;  // hubs: k_ms_sigma_rest
         if (valid) {
             qmask[i] = m;
             qvb[i] = vb;
@@ -1127,63 +1225,20 @@ __global__ __launch_bounds__(BS) void k_ms_expand(
         advance_level(c, level_off, hub_off, hub_lvl_chunks, qcap, hub_cap, chunk_off, owner_cap, 0);
 }
 
-// Hubs, lane = slot: each chunk of kHubChunk adjacency entries is reduced by
-// its own wave into a row of `partial` (64 doubles); a second kernel adds a
-// hub's rows in chunk order.  The kernel boundary between them makes the rows
-// visible without fences inside either kernel.  The chunk kernels are bounded
-// to eight waves per SIMD (their scalar registers otherwise allow seven):
-// rmat-22, per 1,024 sources, k_ms_delta_hub 108.1 -> 106.8 ms and
-// k_ms_sigma_hub 48.1 -> 47.0 ms.
-__device__ __forceinline__ double sum_rows(const double *__restrict__ partial, int32_t base,
-                                           int32_t n) {
-    const int lane = lane_id();
-    double s = 0.0;
-    int32_t q = 0;
-    for (; q + 8 <= n; q += 8) {  // eight rows in flight, added in chunk order
-        double x[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] = partial[(int64_t)(base + q + t) * kSlots + lane];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) s += x[t];
-    }
-    for (; q < n; ++q) s += partial[(int64_t)(base + q) * kSlots + lane];
-    return s;
-}
-
-// A hub's chunk rows added in row order (split_id for a split hub).
-__device__ __forceinline__ double sum_hub_rows(const double *__restrict__ partial,
-                                               const HubEntry &h) {
-    if (h.nchunks < kXcds) return sum_rows(partial, h.chunk_base, h.nchunks);
-    const int lane = lane_id();
-    double s = 0.0;
-    for (int32_t r = 0; r < h.nchunks; r += 8) {  // nchunks is a multiple of 8
-        double x[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            x[t] = partial[(int64_t)(h.chunk_base + split_id(h.nchunks, r + t)) * kSlots + lane];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) s += x[t];
-    }
-    return s;
-}
-
 // Path counts of the current level's hubs (after advance), chunk by chunk.
 // Undirected: the level's segment of the pass's hub list, through the owner
 // map; directed (in_hub_list set): the level's incoming-row hubs, found by
 // binary search over their chunk bases.
 template <int BS>
-__global__ __launch_bounds__(BS, 8) void k_ms_sigma_hub(LevelCtl *c, const int32_t *__restrict__ rp,
-                                                     const int32_t *__restrict__ ci,
-                                                     const unsigned long long *__restrict__ qmask,
-                                                     const uint32_t *__restrict__ qvb,
-                                                     const uint4 *__restrict__ front_par,
-                                                     double *val, const HubEntry *hub_list,
-                                                     const int32_t *__restrict__ owner,
-                                                     const int32_t *__restrict__ chunk_off,
-                                                     const HubEntry *in_hub_list,
-                                                     double *partial, unsigned long long *prof) {
-    if (c->done || c->sigma_push) return;  // pushed: k_ms_sigma_push
-    __shared__ unsigned long long s_red[1];
+__device__ __forceinline__ void pull_hub_chunks(const LevelCtl *c, const int32_t *__restrict__ rp,
+                                                const int32_t *__restrict__ ci,
+                                                const unsigned long long *__restrict__ qmask,
+                                                const uint4 *__restrict__ front_par,
+                                                const double *val, const HubEntry *hub_list,
+                                                const int32_t *__restrict__ owner,
+                                                const int32_t *__restrict__ chunk_off,
+                                                const HubEntry *in_hub_list, double *partial,
+                                                unsigned long long *prof, unsigned long long *s_red) {
     const bool in = in_hub_list != nullptr;
     const int32_t nch = in ? c->in_hub_nchunks : c->hub_nchunks;
     const int32_t obase = in ? 0 : chunk_off[c->level], in_n = in ? c->in_hub_n : 0;
@@ -1205,39 +1260,6 @@ __global__ __launch_bounds__(BS, 8) void k_ms_sigma_hub(LevelCtl *c, const int32
         block_add_u64<BS>(my_edges, s_red, prof + 1);
         __syncthreads();
         block_add_u64<BS>(my_dag, s_red, prof + 2);
-    }
-}
-
-// Path counts of the current level's hubs: each hub's chunk rows added in
-// chunk order (one wave per hub entry).
-__global__ void k_ms_sigma_hub_fin(LevelCtl *c, const unsigned long long *__restrict__ qmask,
-                                   const uint32_t *__restrict__ qvb, double *val,
-                                   const HubEntry *__restrict__ hub_list,
-                                   const double *__restrict__ partial,
-                                   const HubEntry *__restrict__ in_hub_list) {
-    if (c->done || c->sigma_push) return;
-    if (in_hub_list) hub_list = in_hub_list;  // directed: the level's incoming-row hubs
-    const int32_t hlo = in_hub_list ? 0 : c->hub_lo, hhi = in_hub_list ? c->in_hub_n : c->hub_hi;
-    const int lane = lane_id();
-    const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / kWave;
-    unsigned long long my_flag = 0;
-    double my_max = 0.0;
-    for (int64_t j = hlo + wave0; j < hhi; j += nwaves) {
-        const HubEntry h = hub_list[j];
-        const unsigned long long m = qmask[h.entry];
-        const double s = sum_hub_rows(partial, h);
-        const bool mine = (m >> lane) & 1ull;
-        if (mine) {
-            val[qvb[h.entry] + rank_in(m, lane)] = s;
-            my_max = fmax(my_max, s);
-        }
-        my_flag |= __ballot(mine && sigma_is_large(s));
-    }
-    my_max = wave_max_f64(my_max);
-    if (lane == 0) {
-        atomic_max_nonneg_f64(&c->sigma_max_bits_.v, my_max);
-        if (my_flag) atomicOr(&c->flagged_slots_.v, my_flag);
     }
 }
 
@@ -1391,24 +1413,41 @@ __device__ __forceinline__ void push_parent(int32_t beg, int32_t end, unsigned l
     if (lane == 0) pairs += pr;
 }
 
-// blockIdx.y == 0: the parent level's entries without a hub row, like
-// k_ms_sigma's (a lane alone for few slots and a short row, else the wave in
-// turn); blockIdx.y == 1: the chunks of the parents' hub rows, one wave each.
+// What k_ms_sigma left of the level it closed.  A pushed level: the parents
+// add into their children.  blockIdx.y == 0: the parent level's entries
+// without a hub row, like k_ms_sigma's (a lane alone for few slots and a short
+// row, else the wave in turn); blockIdx.y == 1: the chunks of the parents' hub
+// rows, one wave each.  Else blockIdx.y == 0: the chunks of the level's hubs.
+// One launch serves both (an idle launch costs 4.5 us of a level); `which`
+// takes them apart for timing (1: pushes, 2: hubs, 3: both).
 template <int BS>
-__global__ __launch_bounds__(BS) void k_ms_sigma_push(LevelCtl *c,
-                                                      const int32_t *__restrict__ level_off,
-                                                      const int32_t *__restrict__ rp,
-                                                      const int32_t *__restrict__ ci,
-                                                      const int32_t *__restrict__ queue,
-                                                      const unsigned long long *__restrict__ qmask,
-                                                      const uint32_t *__restrict__ qvb,
-                                                      const uint4 *__restrict__ front_child,
-                                                      double *val, const HubEntry *hub_list,
-                                                      const int32_t *__restrict__ owner,
-                                                      const int32_t *__restrict__ chunk_off,
-                                                      const int32_t *__restrict__ hub_lvl_chunks,
-                                                      unsigned long long *prof) {
-    if (c->done || !c->sigma_push) return;
+__global__ __launch_bounds__(BS, 8) void k_ms_sigma_rest(LevelCtl *c,
+                                                         const int32_t *__restrict__ level_off,
+                                                         const int32_t *__restrict__ rp,
+                                                         const int32_t *__restrict__ ci,
+                                                         const int32_t *__restrict__ rpi,
+                                                         const int32_t *__restrict__ cii,
+                                                         const int32_t *__restrict__ queue,
+                                                         const unsigned long long *__restrict__ qmask,
+                                                         const uint32_t *__restrict__ qvb,
+                                                         const uint4 *__restrict__ front_par,
+                                                         const uint4 *__restrict__ front_child,
+                                                         double *val, const HubEntry *hub_list,
+                                                         const int32_t *__restrict__ owner,
+                                                         const int32_t *__restrict__ chunk_off,
+                                                         const int32_t *__restrict__ hub_lvl_chunks,
+                                                         const HubEntry *in_hub_list, double *partial,
+                                                         int32_t which, unsigned long long *prof_hub,
+                                                         unsigned long long *prof) {
+    if (c->done) return;
+    if (!c->sigma_push) {
+        __shared__ unsigned long long s_hub[1];
+        if ((which & 2) && blockIdx.y == 0)
+            pull_hub_chunks<BS>(c, rpi, cii, qmask, front_par, val, hub_list, owner, chunk_off, in_hub_list, partial,
+                                prof_hub, s_hub);
+        return;
+    }
+    if (!(which & 1)) return;
     __shared__ unsigned long long s_red[1];
     const int32_t pl = c->level - 1;  // parents
     const uint32_t tag = (uint32_t)c->level;
@@ -1416,9 +1455,11 @@ __global__ __launch_bounds__(BS) void k_ms_sigma_push(LevelCtl *c,
     unsigned long long my_items = 0, my_edges = 0, my_pairs = 0;
     if (blockIdx.y == 0) {
         const int32_t plo = level_off[pl], phi = level_off[pl + 1];
-        for (int32_t b = plo + (int32_t)(blockIdx.x * BS); b < phi; b += gridDim.x * BS) {
-            const int32_t i = b + (int32_t)threadIdx.x;
-            const bool valid = i < phi;
+        const int32_t share = wave_share<BS>((int64_t)phi - plo);
+        const int32_t per = BS / kWave * share;
+        for (int64_t b = plo + (int64_t)blockIdx.x * per; b < phi; b += (int64_t)gridDim.x * per) {
+            const int64_t i = b + threadIdx.x / kWave * share + lane;
+            const bool valid = i < phi && lane < share;
             int32_t beg = 0, end = 0;
             unsigned long long m = 0;
             uint32_t vb = 0;
@@ -1464,20 +1505,6 @@ __global__ __launch_bounds__(BS) void k_ms_sigma_push(LevelCtl *c,
         });
     }
     flush_counters<BS>(prof, my_items, my_edges, my_pairs, s_red);
-}
-
-// Largest path count of a pushed level: one pass over its values
-// [val_lo, reached_pairs), contiguous in the value store.  (Pushed sums are
-// below 2^53, so no slot is flagged here.)
-__global__ void k_ms_sigma_push_fin(LevelCtl *c, const double *__restrict__ val) {
-    if (c->done || !c->sigma_push) return;
-    const int64_t lo = (int64_t)c->val_lo, hi = (int64_t)c->reached_pairs;
-    double my_max = 0.0;
-    for (int64_t k = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < hi;
-         k += (int64_t)gridDim.x * blockDim.x)
-        my_max = fmax(my_max, val[k]);
-    my_max = wave_max_f64(my_max);
-    if (lane_id() == 0) atomic_max_nonneg_f64(&c->sigma_max_bits_.v, my_max);
 }
 
 // Finish slot `s` of an entry in the reverse pass: acc = sum of the
@@ -1895,7 +1922,7 @@ static sp_status grow_queue(sp_graph g, BatchWorkspace &ws, int64_t qcap) {
 // wave_share spreads a small level over.
 template <int BS>
 static int level_grid(int64_t cnt, int maxb) {
-    return std::max(grid_for(cnt, BS, maxb), grid_for(cnt, BS / kWave * 4, std::min(maxb, kSpreadBlocks)));
+    return std::max(grid_for(cnt, BS, maxb), grid_for(cnt, BS / kWave * kLeastShare, std::min(maxb, kSpreadBlocks)));
 }
 
 template <int BS>
@@ -1906,8 +1933,6 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
     const bool hubs = g->n_hubs > 0;
     const bool sigma_hubs = g->directed ? g->n_hubs_in > 0 : hubs;
     const HubEntry *in_list = g->directed ? (const HubEntry *)ws.in_hub_list : nullptr;
-    const int hub_fin_grid = grid_for((int64_t)std::max(g->n_hubs, g->n_hubs_in) * kWave, 256,
-                                      device_cu_count() * 8);
     for (int k = 0; k < count; ++k) {
         const int64_t l = first + k;  // level this group expands
         uint4 *fcur = ws.front[l & 1], *fnxt = ws.front[(l + 1) & 1];
@@ -1929,7 +1954,8 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
         {
             ProfScope ps(P_MS_TOPDOWN, s);
             hipLaunchKernelGGL(k_ms_topdown<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
-                               g->row_ptr, g->col_idx, (const int32_t *)g->rp_in, ws.queue, ws.qmask, ws.seen, ws.nxt,
+                               g->row_ptr, g->col_idx, (const int32_t *)g->rp_in, ws.queue, ws.qmask,
+                               (const uint32_t *)ws.qvb, ws.val, (const double *)ws.partial, in_list, ws.seen, ws.nxt,
                                (const HubEntry *)ws.hub_list, (const int32_t *)ws.owner,
                                (const int32_t *)ws.chunk_off, (long long)ws.qcap,
                                prof_counters(P_MS_TOPDOWN));
@@ -1951,32 +1977,24 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
                                ws.hub_off, ws.hub_lvl_chunks, ws.owner, (long long)ws.owner_cap,
                                ws.chunk_off, (int32_t)g->max_degree, prof_counters(P_MS_SIGMA));
         }
-        if (sigma_hubs) {
-            ProfScope ps(P_MS_SIGMA_HUB, s);
-            hipLaunchKernelGGL(k_ms_sigma_hub<BS>, dim3(hub_grid), dim3(BS), 0, s, ws.ctl,
-                               g->rp_in, g->ci_in, (const unsigned long long *)ws.qmask,
-                               (const uint32_t *)ws.qvb, (const uint4 *)fcur, ws.val,
-                               (const HubEntry *)ws.hub_list, (const int32_t *)ws.owner,
-                               (const int32_t *)ws.chunk_off, in_list, ws.partial,
-                               prof_counters(P_MS_SIGMA_HUB));
-            // (timed with the chunk kernel)
-            hipLaunchKernelGGL(k_ms_sigma_hub_fin, dim3(hub_fin_grid), dim3(256), 0, s, ws.ctl,
-                               (const unsigned long long *)ws.qmask, (const uint32_t *)ws.qvb,
-                               ws.val, (const HubEntry *)ws.hub_list, (const double *)ws.partial,
-                               in_list);
-        }
-        {
-            ProfScope ps(P_MS_SIGMA_PUSH, s);
-            hipLaunchKernelGGL(k_ms_sigma_push<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s,
-                               ws.ctl, (const int32_t *)ws.level_off, g->row_ptr, g->col_idx,
-                               (const int32_t *)ws.queue, (const unsigned long long *)ws.qmask,
-                               (const uint32_t *)ws.qvb, (const uint4 *)fnxt, ws.val,
-                               (const HubEntry *)ws.hub_list, (const int32_t *)ws.owner,
-                               (const int32_t *)ws.chunk_off, (const int32_t *)ws.hub_lvl_chunks,
-                               prof_counters(P_MS_SIGMA_PUSH));
-            // (timed with the push kernel)
-            hipLaunchKernelGGL(k_ms_sigma_push_fin, dim3(grid), dim3(256), 0, s, ws.ctl,
-                               (const double *)ws.val);
+        const int rest_grid = xcd_grid(std::max(grid, sigma_hubs ? hub_grid : 1), device_cu_count() * 8);
+        auto rest = [&](int kind, int which) {
+            ProfScope ps(kind, s);
+            hipLaunchKernelGGL(k_ms_sigma_rest<BS>, dim3(rest_grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
+                               (const int32_t *)ws.level_off, g->row_ptr, g->col_idx, (const int32_t *)g->rp_in,
+                               (const int32_t *)g->ci_in, (const int32_t *)ws.queue,
+                               (const unsigned long long *)ws.qmask, (const uint32_t *)ws.qvb, (const uint4 *)fcur,
+                               (const uint4 *)fnxt, ws.val, (const HubEntry *)ws.hub_list,
+                               (const int32_t *)ws.owner, (const int32_t *)ws.chunk_off,
+                               (const int32_t *)ws.hub_lvl_chunks, in_list, ws.partial, which,
+                               prof_counters(P_MS_SIGMA_HUB), prof_counters(P_MS_SIGMA_PUSH));
+        };
+        const int which = sigma_hubs ? 3 : 1;
+        if (prof_enabled() && sigma_hubs) {
+            rest(P_MS_SIGMA_HUB, 2);
+            rest(P_MS_SIGMA_PUSH, 1);
+        } else {
+            rest(P_MS_SIGMA_PUSH, which);
         }
     }
 }
@@ -2141,23 +2159,19 @@ static sp_status batch_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *src
     }
     const LevelCtl c = *ws.ctl_host;
     const int32_t levels = c.level + 1;
-    std::vector<int32_t> off(levels + 1), hch(levels);
-    SP_HIP(hipMemcpyAsync(off.data(), ws.level_off, sizeof(int32_t) * (levels + 1),
-                          hipMemcpyDeviceToHost, s));
-    SP_HIP(hipMemcpyAsync(hch.data(), ws.hub_lvl_chunks, sizeof(int32_t) * levels,
-                          hipMemcpyDeviceToHost, s));
-    SP_HIP(hipStreamSynchronize(s));
-    if (ex && (ex->dist || ex->sigma))
-        SP_TRY(launch_extract(g, ws, off, ex->dist, ex->sigma, nullptr, s));
+    std::vector<int32_t> off;  // level offsets, where per-source results are wanted
+    if (ex) {
+        off.resize(levels + 1);
+        SP_HIP(hipMemcpyAsync(off.data(), ws.level_off, sizeof(int32_t) * (levels + 1),
+                              hipMemcpyDeviceToHost, s));
+        SP_HIP(hipStreamSynchronize(s));
+        if (ex->dist || ex->sigma) SP_TRY(launch_extract(g, ws, off, ex->dist, ex->sigma, nullptr, s));
+    }
     // Reverse pass, device-driven: grids sized for the largest level (rounded
     // up to a power of two so that consecutive batches reuse one capture).
     const int maxb = device_cu_count() * 8;
-    int64_t maxcnt = 1;
-    int32_t maxh = 0;
-    for (int32_t l = 1; l < levels; ++l) {
-        maxcnt = std::max<int64_t>(maxcnt, off[l + 1] - off[l]);
-        if (l < levels - 1) maxh = std::max(maxh, hch[l]);
-    }
+    const int64_t maxcnt = c.max_entries;
+    const int32_t maxh = c.max_hub_chunks;
     const int grid_d = pow2_at_least(level_grid<BS>(maxcnt, maxb), maxb);
     const int grid_h =
         xcd_grid(pow2_at_least(grid_for((int64_t)std::max(maxh, 1) * kWave, BS, maxb), maxb), maxb);
@@ -2206,7 +2220,7 @@ static sp_status batch_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *src
         res->flagged_mask = c.flagged_slots_.v;
         res->td = c.topdown_levels;
         res->bu = c.bottomup_levels;
-        res->entries = off[levels];
+        res->entries = c.hi;
         res->graph_launches = graph_launches;
     }
     return SP_OK;

@@ -245,6 +245,8 @@ struct LevelCtl {
     HotU64 pull_cost_;
     int32_t sigma_push;
     unsigned long long val_lo;  // batched: first value of the current level
+    int32_t max_entries;     // batched: entries of the largest level past level 0 (at least 1)
+    int32_t max_hub_chunks;  // batched: most hub chunks of a level between level 0 and the deepest
 };
 
 
