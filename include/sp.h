@@ -358,7 +358,9 @@ sp_status sp_tune_cache_clear(void);
  * that depend on the direction chosen per round.  No sp_sssp call on the
  * graph may be running.  Adds 8 bytes per CSR entry of device memory (the
  * adjacency packed with its weights) plus 16 bytes per vertex of degree
- * above 256. */
+ * above 256; on graphs whose rows all hold at most 8 entries the rows at a
+ * fixed width of 4 or 8 entries (32 or 64 bytes per vertex); on large skewed
+ * graphs (over 2^18 vertices) 12 bytes per vertex for a numbering by degree. */
 sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flags, sp_stream s);
 
 /* Direction of the relaxation rounds. */
@@ -370,7 +372,7 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
 
 typedef struct sp_sssp_config {
     int32_t direction;    /* SP_SSSP_AUTO, SP_SSSP_PUSH or SP_SSSP_PULL */
-    int32_t block_size;   /* threads per workgroup: 128, 256 or 512 (0 = 256) */
+    int32_t block_size;   /* threads per workgroup: 128, 256 or 512 (0 = automatic) */
     double alpha;         /* automatic direction threshold, >= 0 (0 = 1.0: push only;
                              measured on RMAT graphs, a pull round costs about as
                              much as the push round it replaces, or more) */

@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "devutil.h"
+#include "rank.h"
 
 namespace sp {
 
@@ -435,6 +436,10 @@ static void release_pr_ws(sp_graph g, PrWorkspace *ws) {
 static void free_weights(sp_graph g) {
     dev_free(g->adjw);
     g->adjw = nullptr;
+    dev_free(g->sssp_ell);
+    g->sssp_ell = nullptr;
+    dev_free(g->sssp_rp);
+    g->sssp_rp = nullptr;
     g->max_weight = 0;
     g->bytes -= g->weight_bytes;
     g->weight_bytes = 0;
@@ -470,21 +475,40 @@ static sp_status upload_hub_layout(sp_graph g, const std::vector<HubEntry> &hubs
     return SP_OK;
 }
 
-// Every hub of the graph with its chunk range, in vertex order, and the hub
-// of every chunk: built once per graph on first use (SSSP pull rounds,
-// triangle counting), kept until the graph is released.
-sp_status ensure_static_hubs(sp_graph g, hipStream_t st) {
+// Every hub of the weighted rows (ranked or not, g->sssp_rp) with its chunk
+// range, in row order, and the hub of every chunk; kept while the numbering
+// stays.  No sp_sssp call is running on the graph (sp_graph_set_weights).
+sp_status build_static_hubs(sp_graph g, hipStream_t st) {
     std::lock_guard<std::mutex> lk(g->mu);
-    if (g->hub_static) return SP_OK;
+    const bool ranked = g->sssp_rp != nullptr;
+    if (g->hub_static && g->hub_static_ranked == ranked) return SP_OK;
     std::vector<HubEntry> hubs;
     std::vector<int32_t> owners;
-    for (int32_t v = 0; v < g->n; ++v)
-        if (g->host_deg[v] > kHubDeg) {
-            const int32_t nch = (g->host_deg[v] + kHubChunk - 1) / kHubChunk;
-            hubs.push_back(HubEntry{v, 0, (int32_t)owners.size(), nch});
-            owners.insert(owners.end(), (size_t)nch, (int32_t)hubs.size() - 1);
-        }
-    return upload_hub_layout(g, hubs, owners, st, &g->hub_static, &g->owner_static);
+    auto add = [&](int32_t v, int32_t deg) {
+        if (deg <= kHubDeg) return;
+        const int32_t nch = (deg + kHubChunk - 1) / kHubChunk;
+        hubs.push_back(HubEntry{v, 0, (int32_t)owners.size(), nch});
+        owners.insert(owners.end(), (size_t)nch, (int32_t)hubs.size() - 1);
+    };
+    if (ranked) {  // hubs are among the first ranks
+        std::vector<int32_t> off((size_t)rank_count(g, kRankExact) + 1);
+        SP_HIP(hipMemcpyAsync(off.data(), g->sssp_rp, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, st));
+        SP_HIP(hipStreamSynchronize(st));
+        for (size_t r = 0; r + 1 < off.size(); ++r) add((int32_t)r, off[r + 1] - off[r]);
+    } else {
+        for (int32_t v = 0; v < g->n; ++v) add(v, g->host_deg[v]);
+    }
+    HubEntry *hub_dev = nullptr;
+    int32_t *owner_dev = nullptr;
+    const size_t before = g->bytes;
+    SP_TRY(upload_hub_layout(g, hubs, owners, st, &hub_dev, &owner_dev));
+    if (g->hub_static) g->bytes = before;  // replaces one of the same size
+    dev_free(g->hub_static);
+    dev_free(g->owner_static);
+    g->hub_static = hub_dev;
+    g->owner_static = owner_dev;
+    g->hub_static_ranked = ranked;
+    return SP_OK;
 }
 
 // The per-source loop shared by sp_bc and sp_bc_noalloc: out_bc zeroed,
@@ -1092,13 +1116,13 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
         SP_HIP(hipStreamSynchronize(st));
         if (!weights_symmetric(g->n, hr.data(), hc.data(), w)) return SP_ERR_INVALID_ARGUMENT;
     }
-    SP_TRY(ensure_static_hubs(g, st));
     int2 *adjw = nullptr;
-    int32_t *wdev = nullptr;
+    int32_t *wdev = nullptr, *wrp = nullptr;
     unsigned int *bad = nullptr;  // bad[0]: count, bad[1]: largest weight (as int)
     auto cleanup = [&](sp_status code) {
         dev_free(adjw);
         dev_free(wdev);
+        dev_free(wrp);
         dev_free(bad);
         return code;
     };
@@ -1110,9 +1134,14 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
     unsigned int h_bad[2] = {0, 0};
     hipError_t e = hipMemsetAsync(bad, 0, 8, st);
     if (e == hipSuccess && wdev) e = hipMemcpyAsync(wdev, weights, (size_t)nnz * 4, hipMemcpyHostToDevice, st);
+    const int32_t *w_in = wdev ? wdev : weights;
     if (e == hipSuccess && nnz) {
+        rc = sssp_pack_ranked(g, w_in, adjw, bad, &wrp, st);
+        if (rc < 0) return cleanup(rc);
+    }
+    if (e == hipSuccess && nnz && !wrp) {
         hipLaunchKernelGGL(k_pack_weights, dim3(grid_for(nnz, 256, 4096)), dim3(256), 0, st,
-                           (const int32_t *)g->col_idx, (const int32_t *)(wdev ? wdev : weights), nnz,
+                           (const int32_t *)g->col_idx, w_in, nnz,
                            adjw, bad, (int *)(bad + 1));
         e = hipGetLastError();
     }
@@ -1130,15 +1159,30 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
     dev_free(bad);
     wdev = nullptr;
     bad = nullptr;
+    int32_t width = 0;
+    int2 *ell = sssp_mesh_rows(g, adjw, &width, st);
+    if (ell && (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess)) {
+        dev_free(ell);
+        set_error("fixed-width weighted rows could not be built");
+        return cleanup(SP_ERR_DEVICE);
+    }
     {
         std::lock_guard<std::mutex> lk(g->mu);
         free_weights(g);
         g->adjw = adjw;
+        g->sssp_ell = ell;
+        g->sssp_ell_w = width;
+        g->sssp_rp = wrp;
         g->max_weight = (int32_t)h_bad[1];
-        g->weight_bytes = adj_bytes;
+        g->weight_bytes = adj_bytes + (wrp ? sizeof(int32_t) * ((size_t)g->n + 1) : 0) + (ell ? sizeof(int2) * (size_t)g->n * (size_t)width : 0);
         g->bytes += g->weight_bytes;
     }
-    return SP_OK;
+    const sp_status hs = build_static_hubs(g, st);
+    if (hs < 0) {  // without them the weights cannot be used
+        std::lock_guard<std::mutex> lk(g->mu);
+        free_weights(g);
+    }
+    return hs;
     SP_GUARD_END
 }
 
@@ -1175,6 +1219,8 @@ sp_status sp_sssp(sp_graph g, int32_t source, int32_t *out_dist, const sp_sssp_c
         o.max_blocks = cfg->max_blocks;
         o.local_hops = cfg->local_hops;
     }
+    // waves of the mesh kernel work alone: smaller blocks spread a round's few over more CUs (road-3000 11.0 -> 10.4 ms)
+    if (o.block == 0) o.block = g->sssp_ell && sssp_local_hops(g, o.local_hops) > 0 ? 128 : 256;
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)s;
     SsspWorkspace *ws = nullptr;

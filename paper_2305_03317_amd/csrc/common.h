@@ -91,12 +91,18 @@ struct sp_graph_s {
     std::vector<sp::BatchWorkspace *> batch_pool;
     // Edge weights (sp_graph_set_weights), null until set: the adjacency
     // packed as {neighbour, weight} per CSR entry, so one 8-byte load gives
-    // both.
+    // both.  With sssp_rp set, rows and neighbours are numbered by rank
+    // (rank_new) and sssp_rp holds the rows' offsets; else row_ptr does.
+    int32_t *sssp_rp = nullptr;      // device, n + 1
     int2 *adjw = nullptr;            // device, nnz (>= 1 element allocated)
+    // The same rows at a fixed width, where all hold at most 8 entries (sssp_mesh_rows); else null.
+    int2 *sssp_ell = nullptr;        // device, n * sssp_ell_w
+    int32_t sssp_ell_w = 0;
     // Every hub with its chunk range, in vertex order, and the hub of each
     // chunk; built on first use by the whole-graph kernels (ensure_static_hubs).
     sp::HubEntry *hub_static = nullptr;  // device, n_hubs (>= 1)
     int32_t *owner_static = nullptr;     // device, hub_chunks (>= 1)
+    bool hub_static_ranked = false;      // hub_static names ranks
     // PageRank's rows in the order and numbering it gathers them (ensure_pr_plan).
     sp::PrPlan *pr_plan = nullptr;   // host
     // Vertices ranked by degree, highest first (ensure_rank_locked): rank of a
@@ -512,8 +518,8 @@ struct SsspCtl {
 struct SsspWorkspace {
     int device = -1;
     int32_t n = 0;
-    int2 *ds = nullptr;              // V: {distance, stamp}; stamp = last round whose
-                                     //   frontier holds the vertex (-1: never)
+    int32_t *dist = nullptr;         // V: distance
+    int32_t *stamp = nullptr;        // V: last round whose frontier holds the vertex (-1: never)
     int32_t *queue[2] = {nullptr, nullptr};  // V each: frontier by round parity
     HubEntry *hubs[2] = {nullptr, nullptr};  // n_hubs + 1 each: frontier hubs by parity
     int32_t *owner[2] = {nullptr, nullptr};  // hub_chunks + 1 each: hub index of each chunk
@@ -525,11 +531,14 @@ struct SsspWorkspace {
 };
 sp_status sssp_ws_create(sp_graph g, SsspWorkspace &ws);
 void sssp_ws_destroy(SsspWorkspace &ws);
+// Fixed-width rows (4 or 8) of a weighted graph whose rows all hold at most 8
+// entries, enqueued on s; null where they do not, or where memory is short.
+int2 *sssp_mesh_rows(sp_graph g, const int2 *adjw, int32_t *width, hipStream_t s);
 
 struct SsspOpts {
     int forced = -1;       // -1 auto, else SSSP_PUSH / SSSP_PULL
     double alpha = 1.0;    // a frontier never holds more than every entry: no pull rounds
-    int block = 256;
+    int block = 0;         // 0: automatic (sp_sssp resolves it)
     int chunk_rounds = 8;
     int max_blocks = 0;    // 0: automatic
     int local_hops = 0;    // 0: automatic, < 0: none, else hops per round (a power of two <= 128)
@@ -640,8 +649,14 @@ sp_status undirected_only(const char *what);
 // is within its documented range.
 sp_status check_batch_cfg(const sp_batch_config *cfg);
 
-// Builds g->hub_static / g->owner_static once (thread-safe).
-sp_status ensure_static_hubs(sp_graph g, hipStream_t s);
+// Every hub of the weighted rows, for pull rounds: built when weights are set.
+sp_status build_static_hubs(sp_graph g, hipStream_t s);
+// Packs the rows numbered by rank with their weights (each checked to lie in
+// [0, INT32_MAX - 1]: bad[0] counts the others, bad[1] is the largest).  On a
+// graph that renumbering does not suit, or without the memory for it, *out_rp
+// stays null and nothing is enqueued.
+sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, int32_t **out_rp,
+                           hipStream_t s);
 // Builds g->pr_plan once (thread-safe).
 sp_status ensure_pr_plan(sp_graph g, hipStream_t s);
 

@@ -289,16 +289,6 @@ __global__ void k_pr_out_deg(const int32_t *__restrict__ rp, const int32_t *__re
     }
 }
 
-// Length of the i-th row.
-__global__ void k_pr_row_len(const int32_t *__restrict__ rp, const int32_t *__restrict__ order,
-                             const int32_t *__restrict__ old, int32_t n, int32_t *len) {
-    const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int32_t x = order ? order[i] : i, v = old ? old[x] : x;
-        len[i] = rp[v + 1] - rp[v];
-    }
-}
-
 // {first entry, entries} of the i-th row: at off[i] in a renumbered copy, else
 // where the graph has it.
 __global__ void k_pr_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ order,
@@ -332,23 +322,7 @@ __global__ __launch_bounds__(256) void k_pr_renumber(const int32_t *__restrict__
 namespace {
 constexpr int kPrHotPerThread = 9;  // shares in LDS per thread of a renumbered run: 144 KB of a CU's 160 at 32 waves
 constexpr int32_t kPrPiece = 8192;  // rows from here on are split into pieces (a power of two: whole rank classes)
-constexpr int32_t kPrRenumberFrom = 1 << 18;  // vertices: shares of 2 MB, half an XCD's L2
 }  // namespace
-
-// Whether gathers concentrate enough for renumbering to pay: the eighth of the
-// vertices of highest degree holds at least half of the entries (road grids
-// and uniform graphs keep their numbering, which may be a local one).
-static bool skewed(sp_graph g) {
-    int64_t seen = 0, entries = 0;
-    for (int32_t b = 0; b < kRankBuckets && seen < g->n / 8; ++b) {
-        const int32_t key = kRankBuckets - 1 - b;
-        const int64_t deg = key < kRankExact ? key : (int64_t)(32 + (key - kRankExact) % 32) << ((key - kRankExact) / 32 + 3);
-        const int64_t count = std::min<int64_t>(g->rank_first[b + 1] - g->rank_first[b], g->n / 8 - seen);
-        seen += count;
-        entries += count * deg;
-    }
-    return 2 * entries >= g->nnz;
-}
 
 void pr_plan_free(PrPlan *p) {
     if (!p) return;
@@ -374,9 +348,9 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     PrPlan &pl = *gd.p;
     constexpr int32_t longest = kPrPiece - 1;
     // renumbered when it pays and its copy fits; the graph's own rows do otherwise
-    if (n > kPrRenumberFrom && g->max_degree > 8) {
+    if (n > kRenumberFrom && g->max_degree > 8) {
         sp_status st = ensure_rank_locked(g, s);
-        if (st == SP_OK && skewed(g)) st = dev_alloc((void **)&pl.col, sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1));
+        if (st == SP_OK && rank_skewed(g)) st = dev_alloc((void **)&pl.col, sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1));
         if (st != SP_OK && st != SP_ERR_OUT_OF_MEMORY) return st;
         if (st != SP_OK) clear_error();
         if (pl.col) {
@@ -415,8 +389,7 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     if (renum) {
         SP_TRY(dev_alloc((void **)&gd.tmp, sizeof(int32_t) * (size_t)(n + 1 + scan_tiles(n))));
         off = gd.tmp;
-        hipLaunchKernelGGL(k_pr_row_len, dim3(vgrid), dim3(256), 0, s, rp, (const int32_t *)order, pl.old_id, n, off);
-        launch_excl_scan(off, n, off, off + n + 1, s);
+        launch_row_offsets(rp, order, pl.old_id, n, off, off + n + 1, s);
     }
     if (rows)
         hipLaunchKernelGGL(k_pr_rows, dim3(vgrid), dim3(256), 0, s, rp, (const int32_t *)order, pl.old_id,

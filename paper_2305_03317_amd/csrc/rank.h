@@ -27,6 +27,16 @@ sp_status ensure_rank_locked(sp_graph g, hipStream_t s);
 // Vertices of degree >= deg (at most kRankExact, or a power of two); after ensure_rank_locked.
 inline int32_t rank_count(sp_graph g, int32_t deg) { return g->rank_first[rank_bucket(deg) + 1]; }
 
+// Vertices from which renumbering by rank is considered: 8-byte values of 2 MB,
+// half an XCD's L2.
+constexpr int32_t kRenumberFrom = 1 << 18;
+
+// Whether gathers concentrate enough for renumbering to pay: the eighth of the
+// vertices of highest degree holds at least half of the entries (road grids
+// and uniform graphs keep their numbering, which may be a local one).  After
+// ensure_rank_locked.
+bool rank_skewed(sp_graph g);
+
 // Row classes by length, longest first, and a stable sort of n vertices into
 // them: order[i] = the i-th vertex, first[c] = where class c starts
 // (first[kRowClasses] = n).  Vertex x has the row of old[x] (x itself when old
@@ -46,5 +56,10 @@ int64_t scan_tiles(int64_t n);
 // out[i] = sum of in[0..i) for i in [0, n]; out holds n + 1 values and may be
 // `in` itself when that has room.  `tiles`: scan_tiles(n) values of scratch.
 void launch_excl_scan(const int32_t *in, int64_t n, int32_t *out, int32_t *tiles, hipStream_t s);
+
+// off[i] = entries of the rows before the i-th, the row of vertex old[x] for
+// x = order[i] (either list null: the identity); n + 1 values.
+void launch_row_offsets(const int32_t *rp, const int32_t *order, const int32_t *old, int32_t n, int32_t *off,
+                        int32_t *tiles, hipStream_t s);
 
 }  // namespace sp

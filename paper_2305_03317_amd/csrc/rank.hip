@@ -200,6 +200,34 @@ sp_status ensure_rank_locked(sp_graph g, hipStream_t s) {
     return SP_OK;
 }
 
+bool rank_skewed(sp_graph g) {
+    int64_t seen = 0, entries = 0;
+    for (int32_t b = 0; b < kRankBuckets && seen < g->n / 8; ++b) {
+        const int32_t key = kRankBuckets - 1 - b, k = key - kRankExact;
+        const int64_t deg = k < 0 ? key : (int64_t)(32 + k % 32) << (k / 32 + 3);  // the class's least
+        const int64_t count = std::min<int64_t>(g->rank_first[b + 1] - g->rank_first[b], g->n / 8 - seen);
+        seen += count;
+        entries += count * deg;
+    }
+    return 2 * entries >= g->nnz;
+}
+
+__global__ void k_row_len(const int32_t *__restrict__ rp, const int32_t *__restrict__ order,
+                          const int32_t *__restrict__ old, int32_t n, int32_t *len) {
+    const int32_t stride = gridDim.x * blockDim.x;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int32_t x = order ? order[i] : i, v = old ? old[x] : x;
+        len[i] = rp[v + 1] - rp[v];
+    }
+}
+
+void launch_row_offsets(const int32_t *rp, const int32_t *order, const int32_t *old, int32_t n, int32_t *off,
+                        int32_t *tiles, hipStream_t s) {
+    hipLaunchKernelGGL(k_row_len, dim3(grid_for(n, 256, device_cu_count() * 8)), dim3(256), 0, s, rp, order, old, n,
+                       off);
+    launch_excl_scan(off, n, off, tiles, s);
+}
+
 sp_status sort_rows_by_class(const int32_t *rp, const int32_t *old, int32_t n, int32_t longest, int32_t *order,
                              int32_t *first, hipStream_t s) {
     return counting_sort(ByRowClass{rp, old, n, longest, order}, first, s);

@@ -7,9 +7,9 @@
 // neighbours (pull), until a round modifies nothing.  Here:
 //
 //   * the `modified` set of a round is a frontier queue (push reads it) and a
-//     stamp per vertex (pull reads it): ds[v] = {dist, stamp}, where stamp is
-//     the last round whose frontier holds v.  One 8-byte load gives a
-//     neighbour's distance and its membership;
+//     stamp per vertex (pull reads it): the last round whose frontier holds
+//     it.  Distances and stamps are arrays of their own, since a push reads
+//     distances only;
 //   * a push relaxation lowers dist[u] with atomicMin; the first thread in a
 //     round whose atomicMin lowered it raises u's stamp to the next round with
 //     atomicMax and appends u to the next frontier, so a vertex joins a
@@ -36,6 +36,7 @@
 #include "common.h"
 #include "devutil.h"
 #include "levels.h"
+#include "rank.h"
 
 namespace sp {
 
@@ -61,17 +62,20 @@ __device__ __forceinline__ int32_t candidate(int32_t d, int32_t w, bool &ovf) {
 // vertex and round: the first whose atomicMin lowered u's distance in this
 // round; it puts u into the next frontier.  A stale plain read can only be
 // too large, so skipping on it is safe.
-__device__ __forceinline__ bool relax_push(int2 *ds, int32_t u, int32_t nd, int32_t r, bool &lowered) {
+__device__ __forceinline__ bool relax_push(int32_t *dist, int32_t *stamp, int32_t u, int32_t nd, int32_t r, bool &lowered) {
     lowered = false;
-    if (nd >= ds[u].x) return false;
-    const int32_t old = atomicMin(&ds[u].x, nd);
+    if (nd >= dist[u]) return false;
+    const int32_t old = atomicMin(&dist[u], nd);
     if (nd >= old) return false;
     lowered = true;
-    return atomicMax(&ds[u].y, r + 1) < r + 1;
+    return atomicMax(&stamp[u], r + 1) < r + 1;
 }
 
-// Entries of a block's local frontier (see k_sssp_push).
+// Entries of a block's local frontier (see k_sssp_push_hops).
 constexpr int kLocalCap = 512;
+
+// Fewest frontier vertices a wave of k_sssp_mesh starts with.
+constexpr int kMeshLeast = 8;
 
 // The round state word (SsspCtl::state).
 struct RoundState {
@@ -176,16 +180,21 @@ __device__ void close_round(SsspCtl *c, int32_t mode, int32_t n, int32_t hub_cap
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_sssp_fill(int2 *ds, int32_t n) {
+__global__ void k_sssp_fill(int32_t *dist, int32_t *stamp, int32_t n) {
     const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) ds[v] = make_int2(kInf, -1);
+    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        dist[v] = kInf;
+        stamp[v] = -1;
+    }
 }
 
-__global__ void k_sssp_init(SsspCtl *c, const int32_t *__restrict__ rp, int2 *ds, int32_t *q0,
-                            HubEntry *h0, int32_t *o0, int32_t src, int32_t n, long long nnz,
+__global__ void k_sssp_init(SsspCtl *c, const int32_t *__restrict__ rp, int32_t *dist, int32_t *stamp, int32_t *q0,
+                            HubEntry *h0, int32_t *o0, int32_t src, const int32_t *__restrict__ new_id, int32_t n, long long nnz,
                             int32_t forced, double alpha, int32_t static_chunks) {
+    if (new_id) src = new_id[src];
     const int32_t deg = rp[src + 1] - rp[src];
-    ds[src] = make_int2(0, 0);
+    dist[src] = 0;
+    stamp[src] = 0;
     q0[0] = src;
     c->round = 0;
     c->done = 0;
@@ -212,13 +221,185 @@ __global__ void k_sssp_init(SsspCtl *c, const int32_t *__restrict__ rp, int2 *ds
     c->state = pack_state(1, nch, 0, mode, false);
 }
 
-// Push round.  blockIdx.y == 0: a block takes BS frontier vertices (hubs
-// excluded), scans their row lengths and walks the concatenated rows BS
+// Push round.  Waves work by themselves, without barriers.  blockIdx.y == 0:
+// a wave takes frontier vertices (hubs excluded; up to 64, fewer where that
+// leaves waves idle), lays their rows end to end, and walks them 256 entries
+// per step: a lane takes four consecutive entries, whose rows one search and
+// a short walk find, so four packed entries and then four distances are in
+// flight.  blockIdx.y == 1: a wave per chunk of the frontier's hubs.  The few
+// entries that may lower their vertex are gathered in LDS and settled 64 at a
+// time (relax_push), the vertices that join the next frontier written out in
+// batches: an atomic of the wave on the shared tail takes 5 ns of every
+// wave's time.  rmat-22: 5.1 -> 3.9 ms per
+// source against blocks of 256 that took an entry per thread between barriers;
+// rmat with 8,192 vertices 0.64 -> 0.30 ms.
+template <int BS>
+__global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__restrict__ rp,
+                                                  const int2 *__restrict__ adj, int32_t *dist,
+                                                  int32_t *stamp, int32_t *q0, int32_t *q1, HubEntry *h0,
+                                                  HubEntry *h1, int32_t *o0, int32_t *o1,
+                                                  int32_t hub_cap, int32_t chunk_cap, int32_t n,
+                                                  int32_t parity, unsigned long long *prof) {
+    const RoundState st = read_state(c);
+    if (st.done || st.pull || st.parity != parity) return;
+    constexpr int kWaves = BS / kWave, kFly = 4, kStep = kFly * kWave;
+    constexpr int kCand = kStep + kWave, kOut = 2 * kWave;
+    __shared__ int32_t s_off[kWaves][kWave + 1], s_beg[kWaves][kWave], s_d[kWaves][kWave];
+    __shared__ int2 s_cand[kWaves][kCand];
+    __shared__ int32_t s_out[kWaves][kOut];
+    __shared__ unsigned long long s_red[1];
+    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    const int32_t r = c->round, cnt = st.cnt, nch = st.chunks;
+    const int32_t *qc = parity ? q1 : q0;
+    int32_t *qn = parity ? q0 : q1;
+    const HubEntry *hc = parity ? h1 : h0;
+    HubEntry *hn = parity ? h0 : h1;
+    const int32_t *oc = parity ? o1 : o0;
+    int32_t *on = parity ? o0 : o1;
+    unsigned long long my_deg = 0, my_items = 0, my_edges = 0;
+    bool ovf = false;
+    int32_t ncand = 0, nout = 0;  // the same in every lane
+    auto flush = [&]() {
+        if (nout == 0) return;
+        int32_t base = 0;
+        if (lane == 0) base = atomicAdd(&c->tail_.v, nout);
+        base = __builtin_amdgcn_readfirstlane(base);
+        for (int32_t i = lane; i < nout; i += kWave) {
+            if (base + i < n) qn[base + i] = s_out[wv][i];
+            else atomicOr(&c->capacity_.v, 1);
+        }
+        nout = 0;
+        __builtin_amdgcn_wave_barrier();
+    };
+    // settles the last min(64, ncand) candidates
+    auto settle = [&]() {
+        const int32_t take_n = min(ncand, (int32_t)kWave);
+        ncand -= take_n;
+        bool take = false;
+        int32_t u = 0;
+        if (lane < take_n) {
+            const int2 x = s_cand[wv][ncand + lane];
+            u = x.x;
+            bool lowered;
+            take = relax_push(dist, stamp, u, x.y, r, lowered);
+            if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, u, my_deg);
+        }
+        const unsigned long long m = __ballot(take);
+        if (take) s_out[wv][nout + lanes_below(m)] = u;
+        nout += __popcll(m);
+        __builtin_amdgcn_wave_barrier();
+        if (nout > kOut - kWave) flush();
+    };
+    auto offer = [&](bool may, int32_t u, int32_t nd) {
+        const unsigned long long m = __ballot(may);
+        if (may) s_cand[wv][ncand + lanes_below(m)] = make_int2(u, nd);
+        ncand += __popcll(m);
+    };
+    // four entries per lane, loaded together; an entry that is none reads `adj[some]`
+    auto relax4 = [&](const int32_t (&e)[kFly], const int32_t (&d)[kFly], int32_t some) {
+        int2 x[kFly];
+        int32_t old[kFly];
+#pragma unroll
+        for (int q = 0; q < kFly; ++q) x[q] = adj[e[q] >= 0 ? e[q] : some];
+#pragma unroll
+        for (int q = 0; q < kFly; ++q) old[q] = dist[x[q].x];
+#pragma unroll
+        for (int q = 0; q < kFly; ++q) {
+            const int32_t nd = e[q] >= 0 ? candidate(d[q], x[q].y, ovf) : kInf;
+            offer(nd < old[q], x[q].x, nd);
+        }
+        __builtin_amdgcn_wave_barrier();
+        while (ncand >= kWave) settle();
+    };
+    bool working;
+    int nb0;
+    {
+        int32_t share = 2;
+        while (share < kWave && (int64_t)gridDim.x * kWaves * share < cnt) share <<= 1;
+        const int32_t per = kWaves * share;
+        nb0 = working_blocks(cnt, per);
+        working = blockIdx.y == 0 && (int)blockIdx.x < nb0;
+        if (blockIdx.y == 0) {
+            for (int64_t b = (int64_t)blockIdx.x * per + wv * share; b < cnt; b += (int64_t)gridDim.x * per) {
+                const int64_t i = b + lane;
+                int32_t beg = 0, deg = 0, d = 0;
+                if (i < cnt && lane < share) {
+                    const int32_t v = qc[i];
+                    beg = rp[v];
+                    deg = rp[v + 1] - beg;
+                    if (deg > kHubDeg) deg = 0;  // its chunks are taken by blockIdx.y == 1
+                    d = dist[v];
+                    ++my_items;
+                    my_edges += (unsigned long long)deg;
+                }
+                const int32_t incl = wave_incl_scan(deg);
+                const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+                s_off[wv][lane] = incl - deg;
+                if (lane == 0) s_off[wv][kWave] = total;
+                s_beg[wv][lane] = beg;
+                s_d[wv][lane] = d;
+                __builtin_amdgcn_wave_barrier();
+                const int32_t some = __builtin_amdgcn_readlane(beg, __ffsll((long long)(__ballot(deg > 0) | 1ull << 63)) - 1);
+                for (int32_t k0 = 0; k0 < total; k0 += kStep) {
+                    const int32_t k = k0 + lane * kFly;
+                    int32_t e[kFly], dk[kFly];
+                    int32_t a = 0, z = kWave - 1;
+                    while (a < z) {
+                        const int32_t mid = (a + z + 1) >> 1;
+                        if (s_off[wv][mid] <= k) a = mid; else z = mid - 1;
+                    }
+#pragma unroll
+                    for (int q = 0; q < kFly; ++q) {
+                        e[q] = -1;
+                        dk[q] = 0;
+                        if (k + q < total) {
+                            while (s_off[wv][a + 1] <= k + q) ++a;
+                            e[q] = s_beg[wv][a] + (k + q - s_off[wv][a]);
+                            dk[q] = s_d[wv][a];
+                        }
+                    }
+                    relax4(e, dk, some);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            for (int32_t k = blockIdx.x * kWaves + wv; k < nch; k += gridDim.x * kWaves) {
+                const HubEntry h = hc[oc[k]];
+                const int32_t beg = rp[h.v] + (k - h.chunk_base) * kHubChunk;
+                const int32_t end = min(rp[h.v + 1], beg + kHubChunk);
+                const int32_t d = dist[h.v];
+                my_edges += lane == 0 ? (unsigned long long)(end - beg) : 0ull;
+                for (int32_t e0 = beg; e0 < end; e0 += kStep) {
+                    int32_t e[kFly], dk[kFly];
+#pragma unroll
+                    for (int q = 0; q < kFly; ++q) {
+                        const int32_t at = e0 + q * kWave + lane;
+                        e[q] = at < end ? at : -1;
+                        dk[q] = d;
+                    }
+                    relax4(e, dk, beg);
+                }
+            }
+        }
+    }
+    while (ncand > 0) settle();
+    flush();
+    const int nb1 = working_blocks(nch, kWaves);
+    if (blockIdx.y == 1) working = (int)blockIdx.x < nb1;
+    if (__ballot(ovf) && lane == 0) atomicOr(&c->overflow_.v, 1);
+    block_add_u64<BS>(my_deg, s_red, &c->next_deg_.v);
+    flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
+    if (last_working_block(&c->blocks_done_.v, working, nb0 + nb1) && threadIdx.x == 0)
+        close_round(c, SSSP_PUSH, n, hub_cap, chunk_cap);
+}
+
+// Push round whose blocks also follow their own lowerings (long rows and an
+// explicit local_hops).  blockIdx.y == 0: a block takes BS frontier vertices
+// (hubs excluded), scans their row lengths and walks the concatenated rows BS
 // entries at a time, one entry per lane.  blockIdx.y == 1: blocks take the
 // chunks of the frontier's hubs.
 //
-// With HOPS > 0 (graphs of short rows, where rounds are many and small) a
-// block also follows its own lowerings for up to HOPS more hops inside the
+// A block follows its own lowerings for up to HOPS more hops inside the
 // round: every vertex it lowered goes, with the distance it wrote, into an
 // LDS list, and the list is expanded the same way.  Every lowering still
 // puts its vertex into the next frontier (first lowering in the round) or
@@ -227,15 +408,17 @@ __global__ void k_sssp_init(SsspCtl *c, const int32_t *__restrict__ rp, int2 *ds
 // from valid path lengths, and the improvements travel up to HOPS + 1 edges
 // per round instead of one.
 template <int BS, int HOPS>
-__global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__restrict__ rp,
-                                                  const int2 *__restrict__ adj, int2 *ds,
+__global__ __launch_bounds__(BS) void k_sssp_push_hops(SsspCtl *c, const int32_t *__restrict__ rp,
+                                                  const int2 *__restrict__ adj, int32_t *dist,
+                                                  int32_t *stamp,
                                                   int32_t *q0, int32_t *q1, HubEntry *h0,
                                                   HubEntry *h1, int32_t *o0, int32_t *o1,
                                                   int32_t hub_cap, int32_t chunk_cap, int32_t n,
                                                   int32_t parity, unsigned long long *prof) {
     const RoundState st = read_state(c);
     if (st.done || st.pull || st.parity != parity) return;
-    constexpr int kLists = HOPS > 0 ? 2 : 1, kCap = HOPS > 0 ? kLocalCap : 1;
+    static_assert(HOPS > 0, "k_sssp_push runs rounds without local hops");
+    constexpr int kLists = 2, kCap = kLocalCap;
     __shared__ int32_t s_beg[BS], s_off[BS], s_d[BS], s_scan[BS / kWave + 1];
     __shared__ int32_t s_qbuf[4 * BS], s_meta[2];
     __shared__ int32_t s_lv[kLists][kCap], s_ld[kLists][kCap], s_ln[2];
@@ -273,9 +456,9 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
                 u = e.x;
                 const int32_t nd = candidate(s_d[a], e.y, ovf);
                 bool lowered;
-                take = relax_push(ds, u, nd, r, lowered);
+                take = relax_push(dist, stamp, u, nd, r, lowered);
                 if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, u, my_deg);
-                if (HOPS > 0 && dst >= 0 && lowered) {
+                if (dst >= 0 && lowered) {
                     const int32_t at = atomicAdd(&s_ln[dst], 1);
                     if (at < kCap) {
                         s_lv[dst][at] = u;
@@ -298,12 +481,12 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
                 beg = rp[v];
                 deg = rp[v + 1] - beg;
                 if (deg > kHubDeg) deg = 0;  // its chunks are taken by blockIdx.y == 1
-                d = ds[v].x;
+                d = dist[v];
                 ++my_items;
                 my_edges += (unsigned long long)deg;
             }
-            if (HOPS > 0 && threadIdx.x == 0) s_ln[0] = 0;  // seen after the scan's barrier
-            walk(beg, deg, d, HOPS > 0 ? 0 : -1);
+            if (threadIdx.x == 0) s_ln[0] = 0;  // seen after the scan's barrier
+            walk(beg, deg, d, 0);
             int cur = 0;
             for (int hop = 0; hop < HOPS; ++hop) {
                 const int32_t ln = min(s_ln[cur], kCap);
@@ -333,7 +516,7 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
             const HubEntry h = hc[oc[k]];
             const int32_t beg = rp[h.v] + (k - h.chunk_base) * kHubChunk;
             const int32_t end = min(rp[h.v + 1], beg + kHubChunk);
-            const int32_t d = ds[h.v].x;
+            const int32_t d = dist[h.v];
             my_edges += threadIdx.x == 0 ? (unsigned long long)(end - beg) : 0ull;
             for (int32_t e0 = beg; e0 < end; e0 += BS) {
                 const int32_t e = e0 + threadIdx.x;
@@ -343,7 +526,7 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
                     const int2 x = adj[e];
                     u = x.x;
                     bool lowered;
-                    take = relax_push(ds, u, candidate(d, x.y, ovf), r, lowered);
+                    take = relax_push(dist, stamp, u, candidate(d, x.y, ovf), r, lowered);
                     if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, u, my_deg);
                 }
                 q.stage(take, u, &c->tail_.v, qn, n, &c->capacity_.v);
@@ -358,6 +541,155 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
         close_round(c, SSSP_PUSH, n, hub_cap, chunk_cap);
 }
 
+// Push round on graphs whose rows all hold at most 8 entries (sssp_mesh_rows),
+// where rounds are many and small, and what a round costs is the length of
+// its chain of dependent memory operations.  Each wave works by itself, without
+// barriers: it takes up to 64 frontier vertices, then follows its own lowerings
+// for `hops` more steps through a ring in LDS.  A step is one memory round
+// trip: a lane holds {vertex, distance, row}, lowers its neighbours with
+// atomicMin, and loads the neighbours' rows in the same breath, so that a
+// lowered neighbour enters the ring with its row (W = 4; rows of 8 are loaded
+// on the next step).  The fixed-width rows spare the offsets, the value that
+// atomicMin returns the read before it, and only what the ring cannot hold or
+// the last step lowered is put into the next frontier: every lowering is
+// expanded at its distance by the wave that made it or, from the frontier, at
+// the distance then current, so the rounds end at the same least fixed point.
+// road-1501: a hop took 4 us in the general kernel's chain of six operations
+// and two barriers, 13.7 ms in all; here a
+// step takes 1.6 us, 4.8 ms in all (starting waves on 32, 16, 8, 4 vertices: 5.4, 5.0, 4.8, 4.8 ms).
+constexpr int kMeshRing = 128;  // entries per wave
+template <int BS, int W>
+__global__ __launch_bounds__(BS) void k_sssp_mesh(SsspCtl *c, const int2 *__restrict__ ell, int32_t *dist,
+                                                  int32_t *stamp,
+                                                  int32_t *q0, int32_t *q1, int32_t n, int32_t hops,
+                                                  int32_t parity, unsigned long long *prof) {
+    const RoundState st = read_state(c);
+    if (st.done || st.pull || st.parity != parity) return;
+    constexpr int kWaves = BS / kWave;
+    constexpr bool kCarry = W <= 4;  // rows travel with the ring's entries
+    struct Row {
+        int4 part[W / 2];  // {id, weight, id, weight}; id -1 past the row's end
+    };
+    __shared__ int2 s_vd[kWaves][kMeshRing];
+    __shared__ Row s_row[kCarry ? kWaves : 1][kCarry ? kMeshRing : 1];
+    __shared__ unsigned long long s_red[1];
+    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    const int32_t r = c->round, cnt = st.cnt;
+    const int32_t *qc = parity ? q1 : q0;
+    int32_t *qn = parity ? q0 : q1;
+    unsigned long long my_items = 0, my_edges = 0;
+    bool ovf = false;
+    // frontier vertices per wave: few enough to use every wave, from kMeshLeast up
+    int32_t share = kMeshLeast;
+    while (share < kWave && (int64_t)gridDim.x * kWaves * share < cnt) share <<= 1;
+    const int32_t per = kWaves * share;
+    auto row_of = [&](int32_t v) {
+        Row x;
+        const int4 *p = reinterpret_cast<const int4 *>(ell + (int64_t)v * W);
+#pragma unroll
+        for (int k = 0; k < W / 2; ++k) x.part[k] = p[k];
+        return x;
+    };
+    // the lanes' vertices join the next frontier, each once per round
+    auto leave = [&](bool take, int32_t u) {
+        if (take) take = atomicMax(&stamp[u], r + 1) < r + 1;
+        const unsigned long long m = __ballot(take);
+        if (!m) return;
+        const int leader = __ffsll((long long)m) - 1;
+        int32_t at = 0;
+        if (lane == leader) at = atomicAdd(&c->tail_.v, __popcll(m));
+        at = shfl_i32(at, leader) + lanes_below(m);
+        if (take) {
+            if (at < n) qn[at] = u;
+            else atomicOr(&c->capacity_.v, 1);
+        }
+    };
+    for (int64_t b = (int64_t)blockIdx.x * per; b < cnt; b += (int64_t)gridDim.x * per) {
+        const int64_t i = b + wv * share + lane;
+        bool has = i < cnt && lane < share;
+        int32_t v = 0, d = 0;
+        Row row;
+        if (has) {
+            v = qc[i];
+            d = dist[v];
+            row = row_of(v);
+        }
+        uint32_t head = 0, tail = 0;  // ring positions, the same in every lane
+        for (int32_t step = 0; __ballot(has); ++step) {
+            int32_t to[W], nd[W], old[W];
+            Row nrow[kCarry ? W : 1];
+            if (has) {
+                ++my_items;
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    const int4 q = row.part[k / 2];
+                    const int32_t id = k & 1 ? q.z : q.x, w = k & 1 ? q.w : q.y;
+                    my_edges += id >= 0;
+                    // past the row's end: the vertex itself, which INT32_MAX does not lower
+                    to[k] = id >= 0 ? id : v;
+                    nd[k] = id >= 0 ? candidate(d, w, ovf) : kInf;
+                }
+#pragma unroll
+                for (int k = 0; k < W; ++k) old[k] = atomicMin(&dist[to[k]], nd[k]);
+                if (kCarry) {
+#pragma unroll
+                    for (int k = 0; k < W; ++k) nrow[k] = row_of(to[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                const bool low = has && nd[k] < old[k];
+                const unsigned long long m = __ballot(low);
+                if (!m) continue;
+                const uint32_t at = tail + (uint32_t)lanes_below(m);
+                const bool fits = at - head < (uint32_t)kMeshRing;
+                if (low && fits) {
+                    s_vd[wv][at % kMeshRing] = make_int2(to[k], nd[k]);
+                    if (kCarry) s_row[wv][at % kMeshRing] = nrow[k];
+                }
+                tail = min(tail + (uint32_t)__popcll(m), head + (uint32_t)kMeshRing);
+                if (__ballot(low && !fits)) leave(low && !fits, to[k]);
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (step >= hops) break;
+            const uint32_t left = min(tail - head, (uint32_t)kWave);
+            has = (uint32_t)lane < left;
+            if (has) {
+                const int2 x = s_vd[wv][(head + lane) % kMeshRing];
+                v = x.x;
+                d = x.y;
+                row = kCarry ? s_row[wv][(head + lane) % kMeshRing] : row_of(v);
+            }
+            head += left;
+            __builtin_amdgcn_wave_barrier();
+        }
+        while (head != tail) {
+            const uint32_t left = min(tail - head, (uint32_t)kWave);
+            const bool mine = (uint32_t)lane < left;
+            leave(mine, mine ? s_vd[wv][(head + lane) % kMeshRing].x : 0);
+            head += left;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (__ballot(ovf) && lane == 0) atomicOr(&c->overflow_.v, 1);
+    flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
+    const int nb = working_blocks(cnt, per);
+    if (last_working_block(&c->blocks_done_.v, (int)blockIdx.x < nb, nb) && threadIdx.x == 0)
+        close_round(c, SSSP_PUSH, n, 1, 1);
+}
+
+// Rows of at most W entries at a fixed width: {neighbour, weight}, {-1, 0} past the end.
+template <int W>
+__global__ void k_sssp_mesh_rows(const int32_t *__restrict__ rp, const int2 *__restrict__ adj, int32_t n,
+                                 int2 *ell) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)n * W; i += stride) {
+        const int32_t v = (int32_t)(i / W), k = (int32_t)(i % W);
+        const int32_t b = rp[v];
+        ell[i] = k < rp[v + 1] - b ? adj[b + k] : make_int2(-1, 0);
+    }
+}
+
 // Pull round.  blockIdx.y == 0: a block takes BS consecutive vertices (hubs
 // excluded), walks their concatenated rows one entry per lane, and folds each
 // entry's candidate into its vertex's LDS minimum; each vertex then stores
@@ -366,7 +698,8 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
 // chunk to its minimum and lower the hub with atomicMin.
 template <int BS>
 __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__restrict__ rp,
-                                                  const int2 *__restrict__ adj, int2 *ds,
+                                                  const int2 *__restrict__ adj, int32_t *dist,
+                                                  int32_t *stamp,
                                                   int32_t *q0, int32_t *q1, HubEntry *h0,
                                                   HubEntry *h1, int32_t *o0, int32_t *o1,
                                                   int32_t hub_cap, int32_t chunk_cap, int32_t n,
@@ -412,9 +745,8 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
                 if (k < total) {
                     const int32_t a = owner_of<BS>(s_off, k);
                     const int2 e = adj[s_beg[a] + (k - s_off[a])];
-                    const int2 su = ds[e.x];
-                    if (su.y >= r) {
-                        const int32_t nd = candidate(su.x, e.y, ovf);
+                    if (stamp[e.x] >= r) {
+                        const int32_t nd = candidate(dist[e.x], e.y, ovf);
                         if (nd < s_best[a]) atomicMin(&s_best[a], nd);
                     }
                 }
@@ -423,8 +755,9 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
             bool take = false;
             if (deg > 0) {
                 const int32_t best = s_best[threadIdx.x];
-                if (best < ds[v].x) {
-                    ds[v] = make_int2(best, r + 1);
+                if (best < dist[v]) {
+                    dist[v] = best;
+                    stamp[v] = r + 1;
                     take = true;
                     joined(c, rp, hn, on, hub_cap, chunk_cap, v, my_deg);
                 }
@@ -441,14 +774,13 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
             int32_t m = kInf;
             for (int32_t e = beg + threadIdx.x; e < end; e += BS) {
                 const int2 x = adj[e];
-                const int2 su = ds[x.x];
-                if (su.y >= r) m = min(m, candidate(su.x, x.y, ovf));
+                if (stamp[x.x] >= r) m = min(m, candidate(dist[x.x], x.y, ovf));
             }
             m = block_min_i32<BS>(m, s_min);
             bool take = false;
-            if (threadIdx.x == 0 && m < ds[h.v].x) {
-                const int32_t old = atomicMin(&ds[h.v].x, m);
-                take = m < old && atomicMax(&ds[h.v].y, r + 1) < r + 1;
+            if (threadIdx.x == 0 && m < dist[h.v]) {
+                const int32_t old = atomicMin(&dist[h.v], m);
+                take = m < old && atomicMax(&stamp[h.v], r + 1) < r + 1;
                 if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, h.v, my_deg);
             }
             q.stage(take, h.v, &c->tail_.v, qn, n, &c->capacity_.v);
@@ -466,12 +798,12 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
 // unreached neighbour means that neighbour's distance is INT32_MAX or more
 // (every relaxation into it saturated), which int32 cannot hold.
 __global__ void k_sssp_unfit(SsspCtl *c, const int32_t *__restrict__ rp,
-                             const int2 *__restrict__ adj, const int2 *__restrict__ ds, int32_t n) {
+                             const int2 *__restrict__ adj, const int32_t *__restrict__ dist, int32_t n) {
     const int32_t stride = gridDim.x * blockDim.x;
     for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
-        if (ds[u].x == kInf) continue;
+        if (dist[u] == kInf) continue;
         for (int32_t e = rp[u]; e < rp[u + 1]; ++e)
-            if (ds[adj[e].x].x == kInf) {
+            if (dist[adj[e].x] == kInf) {
                 atomicOr(&c->capacity_.v, 2);
                 return;
             }
@@ -479,12 +811,13 @@ __global__ void k_sssp_unfit(SsspCtl *c, const int32_t *__restrict__ rp,
 }
 
 // Distances to the caller's buffer, and the count of reached vertices.
-__global__ void k_sssp_export(SsspCtl *c, const int2 *__restrict__ ds, int32_t *out, int32_t n) {
+__global__ void k_sssp_export(SsspCtl *c, const int32_t *__restrict__ dist,
+                              const int32_t *__restrict__ new_id, int32_t *out, int32_t n) {
     __shared__ unsigned long long s_red[1];
     unsigned long long reached = 0;
     const int32_t stride = gridDim.x * blockDim.x;
     for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        const int32_t d = ds[v].x;
+        const int32_t d = dist[new_id ? new_id[v] : v];
         out[v] = d;
         reached += d != kInf;
     }
@@ -494,6 +827,101 @@ __global__ void k_sssp_export(SsspCtl *c, const int2 *__restrict__ ds, int32_t *
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
+// Rows [first, last) of the rank numbering, PER lanes each: {rank of the
+// neighbour, weight}; counts weights outside [0, INT32_MAX - 1] and tracks the largest.
+template <int PER>
+__global__ __launch_bounds__(256) void k_sssp_pack_ranked(const int32_t *__restrict__ rp,
+                                                          const int32_t *__restrict__ ci,
+                                                          const int32_t *__restrict__ w,
+                                                          const int32_t *__restrict__ rank_new,
+                                                          const int32_t *__restrict__ rank_old,
+                                                          const int32_t *__restrict__ wrp, int32_t first,
+                                                          int32_t last, int2 *adjw, unsigned int *bad) {
+    unsigned int b = 0;
+    int m = 0;
+    const int64_t stride = (int64_t)gridDim.x * (256 / PER);
+    for (int64_t r = first + (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER; r < last; r += stride) {
+        const int32_t at = rp[rank_old[r]], to = wrp[r], len = wrp[r + 1] - to;
+        for (int32_t k = threadIdx.x % PER; k < len; k += PER) {
+            const int32_t x = w[at + k];
+            if (x < 0 || x == kInf) ++b;
+            m = max(m, x);
+            adjw[to + k] = make_int2(rank_new[ci[at + k]], x);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+    if (b) atomicAdd(bad, b);
+    if (lane_id() == 0 && m > 0) atomicMax((int *)(bad + 1), m);
+}
+
+// Pushes on a large skewed graph are bound by their reads of the neighbours'
+// distances, mostly those of the heaviest vertices: numbered by rank these
+// fill consecutive lines, and the distances of the first million ranks (98% of
+// the entries on rmat-22) fit an XCD's 4 MB L2.  rmat-22:
+// 6.2 -> 5.1 ms per source.
+sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, int32_t **out_rp,
+                           hipStream_t s) {
+    *out_rp = nullptr;
+    const int32_t n = g->n;
+    if (n <= kRenumberFrom || g->max_degree <= 8) return SP_OK;
+    int32_t *wrp = nullptr, *tiles = nullptr;
+    sp_status st;
+    {
+        std::lock_guard<std::mutex> lk(g->mu);
+        st = ensure_rank_locked(g, s);
+        if (st == SP_OK && !rank_skewed(g)) return SP_OK;
+    }
+    if (st == SP_OK) st = dev_alloc((void **)&wrp, sizeof(int32_t) * ((size_t)n + 1));
+    if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(n));
+    if (st != SP_OK) {
+        dev_free(wrp);
+        if (st == SP_ERR_OUT_OF_MEMORY) {
+            clear_error();
+            return SP_OK;
+        }
+        return st;
+    }
+    launch_row_offsets(g->row_ptr, nullptr, g->rank_old, n, wrp, tiles, s);
+    const int32_t longer = rank_count(g, kRankExact);
+    const int maxb = device_cu_count() * 8;
+    if (longer > 0)
+        hipLaunchKernelGGL(k_sssp_pack_ranked<256>, dim3(std::min(longer, maxb)), dim3(256), 0, s,
+                           (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
+                           (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, (const int32_t *)wrp, 0, longer,
+                           adjw, bad);
+    hipLaunchKernelGGL(k_sssp_pack_ranked<16>, dim3(grid_for((int64_t)n - longer, 16, maxb)), dim3(256), 0, s,
+                       (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
+                       (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, (const int32_t *)wrp, longer, n,
+                       adjw, bad);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(s);  // the scan's scratch is done with
+    dev_free(tiles);
+    if (e != hipSuccess) {
+        dev_free(wrp);
+        set_error("numbering the weighted rows failed: %s", hipGetErrorString(e));
+        return SP_ERR_DEVICE;
+    }
+    *out_rp = wrp;
+    return SP_OK;
+}
+
+// Offsets of the rows of g->adjw.
+static const int32_t *weighted_rows(sp_graph g) { return g->sssp_rp ? g->sssp_rp : g->row_ptr; }
+
+int2 *sssp_mesh_rows(sp_graph g, const int2 *adjw, int32_t *width, hipStream_t s) {
+    *width = g->max_degree <= 4 ? 4 : 8;
+    int2 *ell = nullptr;
+    if (g->max_degree > 8 || g->n == 0) return nullptr;
+    if (dev_alloc((void **)&ell, sizeof(int2) * (size_t)g->n * (size_t)*width) != SP_OK) {
+        clear_error();  // the general kernel serves
+        return nullptr;
+    }
+    auto fill = *width == 4 ? k_sssp_mesh_rows<4> : k_sssp_mesh_rows<8>;
+    hipLaunchKernelGGL(fill, dim3(grid_for((int64_t)g->n * *width, 256, 8192)), dim3(256), 0, s,
+                       (const int32_t *)g->row_ptr, adjw, g->n, ell);
+    return ell;
+}
+
 sp_status sssp_ws_create(sp_graph g, SsspWorkspace &ws) {
     const int32_t n = std::max(g->n, 1);
     const size_t hubs = (size_t)g->n_hubs + 1, chunks = (size_t)g->hub_chunks + 1;
@@ -503,7 +931,8 @@ sp_status sssp_ws_create(sp_graph g, SsspWorkspace &ws) {
         sssp_ws_destroy(ws);
         return st;
     };
-    sp_status st = dev_alloc((void **)&ws.ds, sizeof(int2) * (size_t)n);
+    sp_status st = dev_alloc((void **)&ws.dist, sizeof(int32_t) * (size_t)n);
+    if (st == SP_OK) st = dev_alloc((void **)&ws.stamp, sizeof(int32_t) * (size_t)n);
     if (st == SP_OK) st = dev_alloc((void **)&ws.queue[0], sizeof(int32_t) * (size_t)n);
     if (st == SP_OK) st = dev_alloc((void **)&ws.queue[1], sizeof(int32_t) * (size_t)n);
     if (st == SP_OK) st = dev_alloc((void **)&ws.hubs[0], sizeof(HubEntry) * hubs);
@@ -528,7 +957,8 @@ void sssp_ws_destroy(SsspWorkspace &ws) {
     if (ws.rounds_short.exec) (void)hipGraphExecDestroy(ws.rounds_short.exec);
     if (ws.rounds_long.exec) (void)hipGraphExecDestroy(ws.rounds_long.exec);
     if (ws.cap_stream) (void)hipStreamDestroy(ws.cap_stream);
-    dev_free(ws.ds);
+    dev_free(ws.dist);
+    dev_free(ws.stamp);
     dev_free(ws.queue[0]);
     dev_free(ws.queue[1]);
     dev_free(ws.hubs[0]);
@@ -551,19 +981,27 @@ template <int BS, int HOPS>
 static void enqueue_rounds(sp_graph g, SsspWorkspace &ws, int rounds, int grid, bool hubs,
                            bool may_pull, bool may_push, hipStream_t s) {
     const int32_t hub_cap = g->n_hubs + 1, chunk_cap = (int32_t)g->hub_chunks + 1, n = g->n;
+    const int32_t *rp = weighted_rows(g);
     for (int k = 0; k < rounds; ++k) {
         const int32_t parity = k & 1;
-        if (may_push) {
+        if (HOPS > 0 && g->sssp_ell) {  // only pushes (rows of at most 8 entries, local hops)
             ProfScope ps(P_SSSP_PUSH, s);
-            hipLaunchKernelGGL((k_sssp_push<BS, HOPS>), dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
-                               (const int32_t *)g->row_ptr, (const int2 *)g->adjw, ws.ds, ws.queue[0],
+            auto mesh = g->sssp_ell_w == 4 ? k_sssp_mesh<BS, 4> : k_sssp_mesh<BS, 8>;
+            hipLaunchKernelGGL(mesh, dim3(grid), dim3(BS), 0, s, ws.ctl, (const int2 *)g->sssp_ell, ws.dist, ws.stamp, ws.queue[0],
+                               ws.queue[1], n, (int32_t)HOPS, parity, prof_counters(P_SSSP_PUSH));
+        } else if (may_push) {
+            ProfScope ps(P_SSSP_PUSH, s);
+            auto push = k_sssp_push<BS>;
+            if constexpr (HOPS > 0) push = k_sssp_push_hops<BS, HOPS>;
+            hipLaunchKernelGGL(push, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
+                               (const int32_t *)rp, (const int2 *)g->adjw, ws.dist, ws.stamp, ws.queue[0],
                                ws.queue[1], ws.hubs[0], ws.hubs[1], ws.owner[0], ws.owner[1],
                                hub_cap, chunk_cap, n, parity, prof_counters(P_SSSP_PUSH));
         }
         if (may_pull) {
             ProfScope ps(P_SSSP_PULL, s);
             hipLaunchKernelGGL(k_sssp_pull<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
-                               (const int32_t *)g->row_ptr, (const int2 *)g->adjw, ws.ds, ws.queue[0],
+                               (const int32_t *)rp, (const int2 *)g->adjw, ws.dist, ws.stamp, ws.queue[0],
                                ws.queue[1], ws.hubs[0], ws.hubs[1], ws.owner[0], ws.owner[1],
                                hub_cap, chunk_cap, n, (const HubEntry *)g->hub_static,
                                (const int32_t *)g->owner_static, parity, prof_counters(P_SSSP_PULL));
@@ -583,9 +1021,10 @@ static sp_status sssp_run_bs(sp_graph g, SsspWorkspace &ws, int32_t src, int32_t
     const bool may_pull = o.forced == SSSP_PULL || (o.forced < 0 && o.alpha > 1.0 && g->max_degree > 8);
     const bool may_push = o.forced != SSSP_PULL;
     const int forced = may_pull ? o.forced : SSSP_PUSH;
-    hipLaunchKernelGGL(k_sssp_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.ds, n);
-    hipLaunchKernelGGL(k_sssp_init, dim3(1), dim3(1), 0, s, ws.ctl, (const int32_t *)g->row_ptr,
-                       ws.ds, ws.queue[0], ws.hubs[0], ws.owner[0], src, n, (long long)g->nnz,
+    hipLaunchKernelGGL(k_sssp_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.dist, ws.stamp, n);
+    const int32_t *rp = weighted_rows(g), *new_id = g->sssp_rp ? (const int32_t *)g->rank_new : nullptr;
+    hipLaunchKernelGGL(k_sssp_init, dim3(1), dim3(1), 0, s, ws.ctl, rp, ws.dist, ws.stamp, ws.queue[0], ws.hubs[0],
+                       ws.owner[0], src, new_id, n, (long long)g->nnz,
                        forced, o.alpha, (int32_t)g->hub_chunks);
     SP_HIP(hipGetLastError());
     const bool capture = o.chunk_rounds > 0 && !prof_enabled();
@@ -596,9 +1035,9 @@ static sp_status sssp_run_bs(sp_graph g, SsspWorkspace &ws, int32_t src, int32_t
         const int chunk = (base + (base & 1)) * (deep ? 4 : 1);  // even: parity holds
         if (capture) {
             const std::array<long long, 12> key = {
-                BS * 16 + HOPS, grid, hubs, may_pull, may_push, chunk, (long long)(intptr_t)ws.ds,
+                BS * 16 + HOPS, grid, hubs, may_pull, may_push, chunk, (long long)(intptr_t)ws.dist,
                 (long long)(intptr_t)g->adjw, (long long)(intptr_t)g->hub_static,
-                (long long)(intptr_t)g->owner_static, (long long)(intptr_t)ws.ctl, g->n_hubs};
+                (long long)(intptr_t)g->sssp_ell, (long long)(intptr_t)ws.ctl, g->n_hubs};
             SP_TRY(replay_captured(&ws.cap_stream, deep ? ws.rounds_long : ws.rounds_short, key,
                                    [&](hipStream_t cs) {
                                        enqueue_rounds<BS, HOPS>(g, ws, chunk, grid, hubs, may_pull, may_push, cs);
@@ -634,7 +1073,7 @@ static sp_status sssp_run_bs(sp_graph g, SsspWorkspace &ws, int32_t src, int32_t
     }
     if (c.overflow_.v) {
         hipLaunchKernelGGL(k_sssp_unfit, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.ctl,
-                           (const int32_t *)g->row_ptr, (const int2 *)g->adjw, (const int2 *)ws.ds, n);
+                           rp, (const int2 *)g->adjw, (const int32_t *)ws.dist, n);
         SP_HIP(hipGetLastError());
         int32_t unfit = 0;
         SP_HIP(hipMemcpyAsync(&unfit, &ws.ctl->capacity_.v, sizeof(unfit), hipMemcpyDeviceToHost, s));
@@ -645,8 +1084,9 @@ static sp_status sssp_run_bs(sp_graph g, SsspWorkspace &ws, int32_t src, int32_t
             return SP_ERR_NOT_SUPPORTED;
         }
     }
-    hipLaunchKernelGGL(k_sssp_export, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.ctl,
-                       (const int2 *)ws.ds, out_dist, n);
+    // (512 blocks: each ends in an atomic on one counter, 4,096 of them took 55 us)
+    hipLaunchKernelGGL(k_sssp_export, dim3(grid_for(n, 256, 512)), dim3(256), 0, s, ws.ctl,
+                       (const int32_t *)ws.dist, new_id, out_dist, n);
     SP_HIP(hipGetLastError());
     if (res) {
         unsigned long long reached = 0;
