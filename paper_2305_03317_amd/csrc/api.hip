@@ -320,14 +320,16 @@ sp_status check_batch_cfg(const sp_batch_config *cfg) {
 }
 
 // Export helpers for sp_bfs_levels.
-__global__ void k_src_export(int32_t n, const int32_t *dist, const double *sigma, const double *delta,
-                             int32_t *out_dist, double *out_sigma, double *out_delta) {
+__global__ void k_src_export(int32_t n, const int32_t *__restrict__ dist, const double2 *__restrict__ sd,
+                             const int32_t *__restrict__ new_id, int32_t *out_dist, double *out_sigma,
+                             double *out_delta) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        const int32_t d = dist[v];
+        const int32_t x = new_id ? new_id[v] : (int32_t)v;
+        const int32_t d = dist[x];
         out_dist[v] = d;
-        if (out_sigma) out_sigma[v] = d >= 0 ? sigma[v] : 0.0;
-        if (out_delta) out_delta[v] = d > 0 ? delta[v] : 0.0;
+        if (out_sigma) out_sigma[v] = d >= 0 ? sd[x].x : 0.0;
+        if (out_delta) out_delta[v] = d > 0 ? sd[x].y : 0.0;
     }
 }
 
@@ -515,7 +517,7 @@ sp_status build_static_hubs(sp_graph g, hipStream_t st) {
 // then one pass per source in list order (block size from the graph's tuned
 // configuration).  Times the call with ws's events when it has them.
 sp_status bc_per_source(sp_graph g, SourceWorkspace &ws, const int32_t *sources, int32_t n_sources,
-                        double *out_bc, hipStream_t st, sp_stats *stats) {
+                        double *out_bc, hipStream_t st, sp_stats *stats, bool ranked) {
     sp_batch_config tcfg{};
     {
         std::lock_guard<std::mutex> lk(g->mu);
@@ -525,11 +527,13 @@ sp_status bc_per_source(sp_graph g, SourceWorkspace &ws, const int32_t *sources,
     if (tcfg.block_size && tcfg.block_size <= 512) o.block = tcfg.block_size;  // (1024: blocks engine only)
     const bool timed = ws.ev0 && ws.ev1;
     if (timed) SP_HIP(hipEventRecord(ws.ev0, st));
-    SP_TRY(launch_fill_f64(out_bc, g->n, 0.0, st));
+    o.ranked = ranked;
+    double *bc = ranked ? ws.bc : out_bc;
+    SP_TRY(launch_fill_f64(bc, g->n, 0.0, st));
     bool flagged = false;
     for (int32_t i = 0; i < n_sources; ++i) {
         SourceResult r;
-        SP_TRY(source_run(g, ws, sources[i], out_bc, true, o, st, &r));
+        SP_TRY(source_run(g, ws, sources[i], bc, true, o, st, &r));
         stats->n_passes++;
         stats->max_levels = std::max(stats->max_levels, r.levels);
         stats->levels_total += r.levels;
@@ -542,6 +546,7 @@ sp_status bc_per_source(sp_graph g, SourceWorkspace &ws, const int32_t *sources,
             flagged = true;
         }
     }
+    if (ranked) SP_TRY(launch_unrank(g, bc, out_bc, st));
     if (timed) {
         SP_HIP(hipEventRecord(ws.ev1, st));
         SP_HIP(hipEventSynchronize(ws.ev1));
@@ -818,6 +823,8 @@ sp_status sp_graph_release(sp_graph g) {
         dev_free(g->ci_in);
     }
     dev_free(g->rank_new);  // holds rank_old too
+    dev_free(g->rank_rp);
+    dev_free(g->rank_ci);
     dev_free(g->tc_orp);
     dev_free(g->tc_entries);
     dev_free(g->hub_static);
@@ -866,7 +873,12 @@ sp_status sp_bc(sp_graph g, const int32_t *sources, int32_t n_sources, double *o
         SourceWorkspace *ws;
         ~Rel() { release_source_ws(g, ws); }
     } rel{g, ws};
-    const sp_status rc = bc_per_source(g, *ws, sources, n_sources, out_bc, st, &stats);
+    bool ranked = n_sources > 0 && source_ranked(g, st);
+    if (ranked && !ws->bc && dev_alloc((void **)&ws->bc, sizeof(double) * (size_t)g->n) != SP_OK) {
+        clear_error();  // the graph's own numbering does as well
+        ranked = false;
+    }
+    const sp_status rc = bc_per_source(g, *ws, sources, n_sources, out_bc, st, &stats, ranked);
     if (rc >= 0) g_stats = stats;
     return rc;
     SP_GUARD_END
@@ -1036,11 +1048,12 @@ sp_status sp_bfs_levels(sp_graph g, int32_t source, int32_t *out_dist, double *o
         ~Rel() { release_source_ws(g, ws); }
     } rel{g, ws};
     SourceRunOpts o;
+    o.ranked = source_ranked(g, st);
     SourceResult r;
     SP_TRY(source_run(g, *ws, source, nullptr, out_delta != nullptr, o, st, &r));
     hipLaunchKernelGGL(k_src_export, dim3(grid_for(g->n, 256, 4096)), dim3(256), 0, st, g->n,
-                       (const int32_t *)ws->dist, (const double *)ws->sigma,
-                       (const double *)ws->delta, out_dist, out_sigma, out_delta);
+                       (const int32_t *)ws->dist, (const double2 *)ws->sd,
+                       o.ranked ? (const int32_t *)g->rank_new : nullptr, out_dist, out_sigma, out_delta);
     SP_HIP(hipGetLastError());
     SP_HIP(hipStreamSynchronize(st));
     return r.flagged ? SP_WARN_SIGMA_LARGE : SP_OK;

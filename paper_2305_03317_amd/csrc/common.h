@@ -110,6 +110,10 @@ struct sp_graph_s {
     int32_t *rank_new = nullptr;     // device, n; its allocation holds rank_old too
     int32_t *rank_old = nullptr;     // device, n
     std::vector<int32_t> rank_first; // host, kRankBuckets + 1
+    // Undirected rows numbered by rank (ensure_rank_csr_locked), each row's
+    // entries in their own order; null where it does not pay.
+    int32_t *rank_rp = nullptr;      // device, n + 1
+    int32_t *rank_ci = nullptr;      // device, nnz (>= 1)
     // Triangle counting (ensure_oriented, on first use), vertices by rank: row
     // v holds its neighbours of lower rank number (higher degree), ascending,
     // as 32-bit ids and (where they fit) as 16-bit ones; each entry's row; and
@@ -205,6 +209,8 @@ struct alignas(128) HotI32 {
     int32_t pad[31];
 };
 
+constexpr int32_t kSegLevels = 32;
+
 struct LevelCtl {
     // read-mostly part (written by init/advance)
     int32_t level;      // level of the current frontier
@@ -251,6 +257,8 @@ struct LevelCtl {
     HotU64 pull_cost_;
     int32_t sigma_push;
     unsigned long long val_lo;  // batched: first value of the current level
+    // Per-source path: offsets and hub chunk counts of the first kSegLevels levels.
+    int32_t seg_off[kSegLevels + 1], seg_chunks[kSegLevels];
     int32_t max_entries;     // batched: entries of the largest level past level 0 (at least 1)
     int32_t max_hub_chunks;  // batched: most hub chunks of a level between level 0 and the deepest
 };
@@ -296,17 +304,18 @@ struct SourceWorkspace {
     int device = -1;
     int32_t n = 0;
     int32_t *dist = nullptr;
-    double *sigma = nullptr;
-    double *delta = nullptr;
+    double2 *sd = nullptr;         // V: {sigma, delta}
     int32_t *queue = nullptr;
     int32_t *level_off = nullptr;  // device, levels + 2
     int32_t level_cap = 0;
     HubEntry *hub_list = nullptr;  // device, n_hubs + 1 (a hub occurs once per source)
-    HubEntry *in_hub_list = nullptr;  // device, n_hubs_in + 1 (directed graphs)
+    HubEntry *in_hub_list = nullptr;  // device, n_hubs_in + 1 (directed graphs only)
     int32_t *hub_off = nullptr;    // device, levels + 2: hub segment of each level
-    int32_t *hub_lvl_chunks = nullptr;  // device, levels + 1: chunk count of each level
-    unsigned int *hub_cnt = nullptr;    // device, n_hubs + 1: finished chunks per hub
+    int32_t *hub_end = nullptr;    // device, levels + 1: end of each level's chunk ids, over all levels
+    int32_t *owner = nullptr;      // device, owner_cap: hub of each chunk id (null: searched for)
+    long long owner_cap = 0;
     double *partial = nullptr;     // device, max(hub_chunks, hub_chunks_in) + 1
+    double *bc = nullptr;          // device, V: BC by rank (allocated when first needed)
     LevelCtl *ctl = nullptr;       // device
     LevelCtl *ctl_host = nullptr;  // pinned mirror
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -327,7 +336,13 @@ struct SourceRunOpts {
     double alpha = kDefaultAlpha, beta = kDefaultBeta;
     int block = kDefaultBlock;
     int chunk_levels = kDefaultChunkLevels;
+    bool ranked = false;  // on the rows numbered by rank (source_ranked): ws.dist, ws.sd and bc are by rank
 };
+// Whether the per-source path runs on g's rows numbered by rank, built here on
+// the first call (undirected, large and skewed, and the memory there).
+bool source_ranked(sp_graph g, hipStream_t s);
+// out[v] = bc[rank of v].
+sp_status launch_unrank(sp_graph g, const double *bc, double *out, hipStream_t s);
 struct SourceResult {
     int32_t levels = 0;   // levels including level 0
     int32_t reached = 0;
@@ -339,9 +354,10 @@ struct SourceResult {
 sp_status source_run(sp_graph g, SourceWorkspace &ws, int32_t src, double *bc, bool with_backward,
                      const SourceRunOpts &o, hipStream_t s, SourceResult *res);
 // sp_bc's work on a given workspace (api.hip): BC zeroed, then every source
-// in list order; counters added to *stats.  Synchronises the stream.
+// in list order; counters added to *stats.  ranked: on the rows numbered by
+// rank, with ws.bc allocated.  Synchronises the stream.
 sp_status bc_per_source(sp_graph g, SourceWorkspace &ws, const int32_t *sources, int32_t n_sources,
-                        double *out_bc, hipStream_t st, sp_stats *stats);
+                        double *out_bc, hipStream_t st, sp_stats *stats, bool ranked);
 // sp_bc's argument checks (null graph or output, sources in range).
 sp_status check_bc_args(sp_graph g, const int32_t *sources, int32_t n_sources, const double *out_bc,
                         const char *what);
@@ -597,7 +613,7 @@ struct PrView {
 struct PrPlan {
     PrView view{};           // tile0 is filled per launch (it depends on the block size)
     void *rows = nullptr;    // device allocation of view.rows, .order, .out_deg
-    int32_t *col = nullptr;  // device: the renumbered entries; null: the graph's own
+    int32_t *col = nullptr;  // device: the renumbered entries of a directed graph; null: rank_ci or the graph's own
     const int32_t *old_id = nullptr, *new_id = nullptr;  // device, null when not renumbered
     void *split = nullptr;   // device allocation of view.split, .pieces, .piece_row
     int32_t n_split = 0;     // rows of class 0

@@ -49,21 +49,25 @@ static size_t carve(sp_graph g, unsigned char *base, SourceWorkspace &ws) {
     ws.device = g->device;
     ws.n = g->n;
     ws.dist = (int32_t *)take(n * sizeof(int32_t));
-    ws.sigma = (double *)take(n * sizeof(double));
-    ws.delta = (double *)take(n * sizeof(double));
+    ws.sd = (double2 *)take(n * sizeof(double2));
     ws.queue = (int32_t *)take(n * sizeof(int32_t));
     ws.level_cap = (int32_t)lv;
     ws.level_off = (int32_t *)take(lv * sizeof(int32_t));
     ws.hub_off = (int32_t *)take(lv * sizeof(int32_t));
-    ws.hub_lvl_chunks = (int32_t *)take(lv * sizeof(int32_t));
+    ws.hub_end = (int32_t *)take(lv * sizeof(int32_t));
     ws.hub_list = (HubEntry *)take(((size_t)g->n_hubs + 1) * sizeof(HubEntry));
-    ws.in_hub_list = (HubEntry *)take(((size_t)g->n_hubs_in + 1) * sizeof(HubEntry));
-    ws.hub_cnt = (unsigned int *)take(((size_t)g->n_hubs + 1) * sizeof(unsigned int));
+    if (g->directed) ws.in_hub_list = (HubEntry *)take(((size_t)g->n_hubs_in + 1) * sizeof(HubEntry));
     ws.partial = (double *)take(
         ((size_t)std::max(g->split_hub_chunks, g->split_hub_chunks_in) + 1) * sizeof(double));
     ws.ctl = (LevelCtl *)take(sizeof(LevelCtl));
     ws.ctl_host = nullptr;
     ws.ev0 = ws.ev1 = nullptr;  // no events: the call synchronises its stream instead
+    // the owner map only where it still fits (a chunk's hub is searched for without it)
+    const size_t owner_bytes = align256(((size_t)g->split_hub_chunks + 1) * sizeof(int32_t));
+    if (off + owner_bytes <= kScratchBytes) {
+        ws.owner = (int32_t *)take(owner_bytes);
+        ws.owner_cap = g->split_hub_chunks + 1;
+    }
     return off;
 }
 
@@ -121,7 +125,7 @@ sp_status sp_bc_noalloc(sp_graph g, const int32_t *sources, int32_t n_sources, d
         SP_TRY(scratch_address(g->device, &base));
         carve(g, base, ws);
         ws.ctl_host = &g_ctl_host[g->device];
-        const sp_status rc = bc_per_source(g, ws, sources, n_sources, out_bc, (hipStream_t)s, &stats);
+        const sp_status rc = bc_per_source(g, ws, sources, n_sources, out_bc, (hipStream_t)s, &stats, false);
         if (rc >= 0) tls_stats() = stats;
         return rc;
     } catch (...) {

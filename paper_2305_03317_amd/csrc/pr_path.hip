@@ -198,6 +198,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
     unsigned long long my_items = 0, my_edges = 0;
     unsigned long long diff_sum = 0;  // on the waves' first lanes
     double my_diff = 0.0;             // this tile's
+    auto row_at = [&](int32_t i) { return p.rows ? p.rows[i] : make_int2(p.rp[i], p.rp[i + 1] - p.rp[i]); };
     auto settle = [&](int32_t i, int32_t len, double sum) {
         const int32_t x = p.order ? p.order[i] : i;
         const int32_t dout = p.out_deg ? p.out_deg[x] : len;
@@ -213,11 +214,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
         const int32_t i = p.row0[cls] + (tile - p.tile0[cls]) * (BS / LPR) + (int32_t)threadIdx.x / LPR;
         const int32_t l = threadIdx.x % LPR;
         const bool mine = i < p.row0[cls + 1];
-        int2 row = make_int2(0, 0);
-        if (mine) {
-            if (p.rows) row = p.rows[i];
-            else row = make_int2(p.rp[i], p.rp[i + 1] - p.rp[i]);
-        }
+        const int2 row = mine ? row_at(i) : make_int2(0, 0);
         const double sum = lanes_sum<LPR, FLY>(p.col, sh, row.x, row.y, l);
         if (mine && l == 0) settle(i, row.y, sum);
     };
@@ -233,7 +230,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
             const int32_t i = whole ? p.row0[1] + k : k;
             const bool mine = whole ? i < p.row0[2] : i < p.n_pieces;
             int2 row = make_int2(0, 0);
-            if (mine) row = whole ? p.rows[i] : p.pieces[i];
+            if (mine) row = whole ? row_at(i) : p.pieces[i];
             const double sum = block_row_sum<BS, FLY>(p.col, sh, row.x, row.y, s_w);
             if (mine && threadIdx.x % kTeam == 0) {
                 if (whole) settle(i, row.y, sum);
@@ -255,7 +252,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
                     double s = 0.0;
                     for (int32_t k2 = lane_id(); k2 < h.y; k2 += kWave) s += ld_agent(&partial[h.x + k2]);
                     s = wave_sum_f64(s);
-                    if (lane_id() == 0) settle(r, p.rows[r].y, s);
+                    if (lane_id() == 0) settle(r, row_at(r).y, s);
                 }
             }
         }
@@ -302,23 +299,6 @@ __global__ void k_pr_rows(const int32_t *__restrict__ rp, const int32_t *__restr
     }
 }
 
-// Renumbered entries of the rows [first, last), per lanes (16, or a block).
-template <int PER>
-__global__ __launch_bounds__(256) void k_pr_renumber(const int32_t *__restrict__ rp,
-                                                     const int32_t *__restrict__ ci,
-                                                     const int32_t *__restrict__ order,
-                                                     const int32_t *__restrict__ old,
-                                                     const int32_t *__restrict__ new_id,
-                                                     const int2 *__restrict__ rows, int32_t first,
-                                                     int32_t last, int32_t *col) {
-    const int64_t stride = (int64_t)gridDim.x * (256 / PER);
-    for (int64_t i = first + (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER; i < last; i += stride) {
-        const int32_t b = rp[old[order ? order[i] : i]];
-        const int2 row = rows[i];
-        for (int32_t k = threadIdx.x % PER; k < row.y; k += PER) col[row.x + k] = new_id[ci[b + k]];
-    }
-}
-
 namespace {
 constexpr int kPrHotPerThread = 9;  // shares in LDS per thread of a renumbered run: 144 KB of a CU's 160 at 32 waves
 constexpr int32_t kPrPiece = 8192;  // rows from here on are split into pieces (a power of two: whole rank classes)
@@ -348,20 +328,28 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     PrPlan &pl = *gd.p;
     constexpr int32_t longest = kPrPiece - 1;
     // renumbered when it pays and its copy fits; the graph's own rows do otherwise
-    if (n > kRenumberFrom && g->max_degree > 8) {
+    bool renum = false;
+    if (!g->directed) {  // the copy that the per-source path runs on too
+        SP_TRY(ensure_rank_csr_locked(g, s));
+        renum = g->rank_ci != nullptr;
+        if (renum) {
+            rp = g->rank_rp;
+            ci = g->rank_ci;
+        }
+    } else if (n > kRenumberFrom && g->max_degree > 8) {
         sp_status st = ensure_rank_locked(g, s);
         if (st == SP_OK && rank_skewed(g)) st = dev_alloc((void **)&pl.col, sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1));
         if (st != SP_OK && st != SP_ERR_OUT_OF_MEMORY) return st;
         if (st != SP_OK) clear_error();
-        if (pl.col) {
-            pl.old_id = g->rank_old;
-            pl.new_id = g->rank_new;
-        }
+        renum = pl.col != nullptr;
     }
-    const bool renum = pl.col != nullptr;
+    if (renum) {
+        pl.old_id = g->rank_old;
+        pl.new_id = g->rank_new;
+    }
     // undirected ranks list the rows by length already, and rows of one class need no list
     const bool listed = g->max_degree > 8 && (!renum || g->directed);
-    const bool plain = !listed && !renum;  // the graph's own offsets serve
+    const bool plain = !listed;  // the rows' own offsets serve
     const size_t vn = (size_t)n;
     const size_t row_bytes = (plain ? 0 : sizeof(int2) * vn) + sizeof(int32_t) * vn * (size_t)(listed + g->directed);
     if (row_bytes) SP_TRY(dev_alloc(&pl.rows, row_bytes));
@@ -386,30 +374,30 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
         hipLaunchKernelGGL(k_pr_out_deg, dim3(vgrid), dim3(256), 0, s, (const int32_t *)g->row_ptr, pl.old_id, n,
                            out_deg);
     int32_t *off = nullptr;
-    if (renum) {
+    if (pl.col) {
         SP_TRY(dev_alloc((void **)&gd.tmp, sizeof(int32_t) * (size_t)(n + 1 + scan_tiles(n))));
         off = gd.tmp;
         launch_row_offsets(rp, order, pl.old_id, n, off, off + n + 1, s);
+        launch_renumber(rp, ci, order, pl.old_id, pl.new_id, off, row0[2], n, pl.col, s);
     }
     if (rows)
         hipLaunchKernelGGL(k_pr_rows, dim3(vgrid), dim3(256), 0, s, rp, (const int32_t *)order, pl.old_id,
                            (const int32_t *)off, n, rows);
-    if (renum) {
-        const int32_t block_rows = row0[2];
-        if (block_rows > 0)
-            hipLaunchKernelGGL(k_pr_renumber<256>, dim3(std::min(block_rows, maxb)), dim3(256), 0, s, rp, ci,
-                               (const int32_t *)order, pl.old_id, pl.new_id, (const int2 *)rows, 0, block_rows, pl.col);
-        hipLaunchKernelGGL(k_pr_renumber<16>, dim3(grid_for((int64_t)n - block_rows, 16, maxb)), dim3(256), 0, s, rp,
-                           ci, (const int32_t *)order, pl.old_id, pl.new_id, (const int2 *)rows, block_rows, n, pl.col);
-    }
     SP_HIP(hipGetLastError());
     size_t split_bytes = 0;
     const int32_t ns = row0[1];  // a row per kPrPiece entries at most
     if (ns > 0) {
         std::vector<int2> srow((size_t)ns), split((size_t)ns), pieces;
         std::vector<int32_t> owner;
-        SP_HIP(hipMemcpyAsync(srow.data(), rows, sizeof(int2) * (size_t)ns, hipMemcpyDeviceToHost, s));
-        SP_HIP(hipStreamSynchronize(s));
+        if (rows) {
+            SP_HIP(hipMemcpyAsync(srow.data(), rows, sizeof(int2) * (size_t)ns, hipMemcpyDeviceToHost, s));
+            SP_HIP(hipStreamSynchronize(s));
+        } else {
+            std::vector<int32_t> first((size_t)ns + 1);
+            SP_HIP(hipMemcpyAsync(first.data(), rp, sizeof(int32_t) * first.size(), hipMemcpyDeviceToHost, s));
+            SP_HIP(hipStreamSynchronize(s));
+            for (int32_t j = 0; j < ns; ++j) srow[j] = make_int2(first[j], first[j + 1] - first[j]);
+        }
         for (int32_t j = 0; j < ns; ++j) {
             split[j].x = (int32_t)pieces.size();
             for (int64_t k = 0; k < srow[j].y; k += kPrPiece) {
@@ -433,12 +421,12 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
         pl.n_split = ns;
     }
     SP_HIP(hipStreamSynchronize(s));
-    pl.view.col = renum ? pl.col : ci;
+    pl.view.col = pl.col ? pl.col : ci;
     pl.view.rows = rows;
     pl.view.rp = rp;
     pl.view.order = order;
     pl.view.out_deg = out_deg;
-    g->bytes += row_bytes + split_bytes + (renum ? sizeof(int32_t) * (size_t)g->nnz : 0);
+    g->bytes += row_bytes + split_bytes + (pl.col ? sizeof(int32_t) * (size_t)g->nnz : 0);
     g->pr_plan = gd.p;
     gd.p = nullptr;
     return SP_OK;
@@ -496,7 +484,7 @@ void pr_ws_destroy(PrWorkspace &ws) {
 template <int BS>
 static void enqueue_iterations(const PrPlan &pl, const PrView &view, PrWorkspace &ws, int count, int grid,
                                double teleport, double delta, hipStream_t s) {
-    auto pull = pl.col ? k_pr_pull<BS, kPrHotPerThread * BS> : k_pr_pull<BS, 0>;
+    auto pull = pl.new_id ? k_pr_pull<BS, kPrHotPerThread * BS> : k_pr_pull<BS, 0>;
     for (int k = 0; k < count; ++k) {
         ProfScope ps(P_PR_PULL, s);
         hipLaunchKernelGGL(pull, dim3(grid), dim3(BS), 0, s, ws.ctl, view, ws.pr[0], ws.pr[1], ws.share[0],
@@ -528,7 +516,7 @@ static sp_status pr_run_bs(sp_graph g, PrWorkspace &ws, double beta, double delt
     // Renumbered: twice the blocks that fit at once, which evens out their rows.  Else as many as fit, and half of
     // that up to 2 M vertices: every block ends in two atomics to one line each, which take 5 ns a block
     // (road-1000, 20 iterations: 587 -> 488 us).
-    const int threads_per_cu = pl.col ? 4096 : n > (1 << 21) ? 2048 : 1024;
+    const int threads_per_cu = pl.new_id ? 4096 : n > (1 << 21) ? 2048 : 1024;
     const int grid = grid_for(view.tile0[kPrRowClasses], 1, device_cu_count() * threads_per_cu / BS);
     const double teleport = (1.0 - delta) / (double)n;
     hipLaunchKernelGGL(k_pr_init, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.ctl,
@@ -584,7 +572,7 @@ sp_status pr_run(sp_graph g, PrWorkspace &ws, double beta, double delta, int32_t
     // blocks of 1024 hold the most shares per copy: rmat-22, 20 iterations: 15.2, 14.9 and 13.7 ms with 256,
     // 512 and 1024 threads; the others measured best with 512 (rmat-15 337, 267, 254 us, uniform with 8 M edges
     // 2.42, 2.47, 2.63 ms)
-    switch (o.block ? o.block : g->pr_plan->col ? 1024 : 512) {
+    switch (o.block ? o.block : g->pr_plan->new_id ? 1024 : 512) {
         case 128: return pr_run_bs<128>(g, ws, beta, delta, max_iter, out_pr, o, s, res);
         case 1024: return pr_run_bs<1024>(g, ws, beta, delta, max_iter, out_pr, o, s, res);
         case 512: return pr_run_bs<512>(g, ws, beta, delta, max_iter, out_pr, o, s, res);

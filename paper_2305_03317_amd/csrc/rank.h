@@ -37,6 +37,18 @@ constexpr int32_t kRenumberFrom = 1 << 18;
 // ensure_rank_locked.
 bool rank_skewed(sp_graph g);
 
+// Builds g->rank_rp / g->rank_ci once, on an undirected graph over
+// kRenumberFrom vertices that is skewed; leaves them null on others and where
+// memory is short.  The caller holds g->mu.
+sp_status ensure_rank_csr_locked(sp_graph g, hipStream_t s);
+
+// Entries of the rows [0, rows) renumbered: row i goes to col[to[i]...], from
+// the row of vertex old[order[i]] (order null: the identity).  The first
+// `longer` rows take a block each, the others 16 lanes.
+void launch_renumber(const int32_t *rp, const int32_t *ci, const int32_t *order, const int32_t *old,
+                     const int32_t *new_id, const int32_t *to, int32_t longer, int32_t rows, int32_t *col,
+                     hipStream_t s);
+
 // Row classes by length, longest first, and a stable sort of n vertices into
 // them: order[i] = the i-th vertex, first[c] = where class c starts
 // (first[kRowClasses] = n).  Vertex x has the row of old[x] (x itself when old

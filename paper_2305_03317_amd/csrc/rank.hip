@@ -228,6 +228,70 @@ void launch_row_offsets(const int32_t *rp, const int32_t *order, const int32_t *
     launch_excl_scan(off, n, off, tiles, s);
 }
 
+template <int PER>
+__global__ __launch_bounds__(256) void k_renumber(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                                                  const int32_t *__restrict__ order,
+                                                  const int32_t *__restrict__ old,
+                                                  const int32_t *__restrict__ new_id,
+                                                  const int32_t *__restrict__ to, int32_t first, int32_t last,
+                                                  int32_t *col) {
+    const int64_t stride = (int64_t)gridDim.x * (256 / PER);
+    for (int64_t i = first + (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER; i < last; i += stride) {
+        const int32_t v = old[order ? order[i] : i];
+        const int32_t b = rp[v], len = rp[v + 1] - b, at = to[i];
+        for (int32_t k = threadIdx.x % PER; k < len; k += PER) col[at + k] = new_id[ci[b + k]];
+    }
+}
+
+void launch_renumber(const int32_t *rp, const int32_t *ci, const int32_t *order, const int32_t *old,
+                     const int32_t *new_id, const int32_t *to, int32_t longer, int32_t rows, int32_t *col,
+                     hipStream_t s) {
+    const int maxb = device_cu_count() * 8;
+    if (longer > 0)
+        hipLaunchKernelGGL(k_renumber<256>, dim3(std::min(longer, maxb)), dim3(256), 0, s, rp, ci, order, old, new_id,
+                           to, 0, longer, col);
+    if (rows > longer)
+        hipLaunchKernelGGL(k_renumber<16>, dim3(grid_for((int64_t)rows - longer, 16, maxb)), dim3(256), 0, s, rp, ci,
+                           order, old, new_id, to, longer, rows, col);
+}
+
+sp_status ensure_rank_csr_locked(sp_graph g, hipStream_t s) {
+    if (g->rank_ci || g->directed || g->n <= kRenumberFrom || g->max_degree <= 8) return SP_OK;
+    int32_t *rp = nullptr, *ci = nullptr, *tiles = nullptr;
+    sp_status st = ensure_rank_locked(g, s);
+    if (st == SP_OK && !rank_skewed(g)) return SP_OK;
+    const size_t nb = sizeof(int32_t) * ((size_t)g->n + 1), eb = sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1);
+    if (st == SP_OK) st = dev_alloc((void **)&rp, nb);
+    if (st == SP_OK) st = dev_alloc((void **)&ci, eb);
+    if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(g->n));
+    hipError_t e = hipSuccess;
+    if (st == SP_OK) {
+        launch_row_offsets(g->row_ptr, nullptr, g->rank_old, g->n, rp, tiles, s);
+        launch_renumber(g->row_ptr, g->col_idx, nullptr, g->rank_old, g->rank_new, rp, rank_count(g, kRankExact),
+                        g->n, ci, s);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
+    dev_free(tiles);
+    if (st == SP_OK && e == hipSuccess) {
+        g->rank_rp = rp;
+        g->rank_ci = ci;
+        g->bytes += nb + eb;
+        return SP_OK;
+    }
+    dev_free(rp);
+    dev_free(ci);
+    if (e != hipSuccess) {
+        set_error("numbering the rows by rank failed: %s", hipGetErrorString(e));
+        return SP_ERR_DEVICE;
+    }
+    if (st == SP_ERR_OUT_OF_MEMORY) {
+        clear_error();
+        return SP_OK;
+    }
+    return st;
+}
+
 sp_status sort_rows_by_class(const int32_t *rp, const int32_t *old, int32_t n, int32_t longest, int32_t *order,
                              int32_t *first, hipStream_t s) {
     return counting_sort(ByRowClass{rp, old, n, longest, order}, first, s);
