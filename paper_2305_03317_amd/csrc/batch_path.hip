@@ -602,25 +602,18 @@ __device__ __forceinline__ void settle_level(LevelCtl *c, const unsigned long lo
 
 // Top-down discovery.  blockIdx.y == 0: block gather over the frontier's
 // entries (hubs excluded), one adjacency entry per lane.  blockIdx.y == 1:
-// the chunks of the frontier's hubs.  It is the first kernel of a level in
-// either direction, and finishes the last one's path counts (settle_level).
+// the chunks of the frontier's hubs.
 template <int BS>
-__global__ __launch_bounds__(BS) void k_ms_topdown(LevelCtl *c, const int32_t *__restrict__ rp,
+__device__ __forceinline__ void ms_topdown(LevelCtl *c, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ ci,
                                                    const int32_t *__restrict__ rpi, int32_t *queue,
                                                    const unsigned long long *__restrict__ qmask,
-                                                   const uint32_t *__restrict__ qvb, double *val,
-                                                   const double *__restrict__ partial,
-                                                   const HubEntry *__restrict__ in_hub_list,
                                                    const unsigned long long *__restrict__ seen,
                                                    unsigned long long *nxt,
                                                    const HubEntry *__restrict__ hub_list,
                                                    const int32_t *__restrict__ owner,
                                                    const int32_t *__restrict__ chunk_off,
                                                    long long qcap, unsigned long long *prof) {
-    if (c->done) return;
-    if (blockIdx.y == 0) settle_level(c, qmask, qvb, val, hub_list, partial, in_hub_list);
-    if (c->mode != MODE_TOPDOWN) return;
     __shared__ int32_t s_beg[BS], s_off[BS], s_scan[BS / kWave + 1];
     __shared__ unsigned long long s_mask[BS];
     __shared__ int32_t s_qbuf[4 * BS], s_meta[2];
@@ -709,14 +702,13 @@ __global__ __launch_bounds__(BS) void k_ms_topdown(LevelCtl *c, const int32_t *_
 // all its unsettled slots are found.
 constexpr int kBuPerLane = 4;
 template <int BS>
-__global__ __launch_bounds__(BS) void k_ms_bottomup(LevelCtl *c, const int32_t *__restrict__ rp,
+__device__ __forceinline__ void ms_bottomup(LevelCtl *c, const int32_t *__restrict__ rp,
                                                     const int32_t *__restrict__ ci,
                                                     const unsigned long long *__restrict__ seen,
                                                     unsigned long long *nxt,
                                                     const uint4 *__restrict__ front_cur,
                                                     int32_t *queue, long long qcap,
                                                     unsigned long long *prof) {
-    if (c->done || c->mode != MODE_BOTTOMUP) return;
     __shared__ int32_t s_qbuf[4 * BS], s_meta[2];
     __shared__ int32_t s_coff[BS], s_beg[BS], s_deg[BS];
     __shared__ unsigned long long s_acc[BS], s_uns[BS];
@@ -802,6 +794,34 @@ __global__ __launch_bounds__(BS) void k_ms_bottomup(LevelCtl *c, const int32_t *
     q.finish(&c->tail_.v, queue, qcap, &c->overflow_.v);
     block_add_u64<BS>(my_pull, s_red, &c->pull_cost_.v);
     flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
+}
+
+// The first kernel of a level: finishes the last one's path counts
+// (settle_level) and discovers the next in the direction chosen.  `which` takes
+// the directions apart for timing (1: top-down, 2: bottom-up, 3: both).
+template <int BS>
+__global__ __launch_bounds__(BS) void k_ms_discover(LevelCtl *c, const int32_t *__restrict__ rp,
+                                                    const int32_t *__restrict__ ci,
+                                                    const int32_t *__restrict__ rpi,
+                                                    const int32_t *__restrict__ cii, int32_t *queue,
+                                                    const unsigned long long *__restrict__ qmask,
+                                                    const uint32_t *__restrict__ qvb, double *val,
+                                                    const double *__restrict__ partial,
+                                                    const HubEntry *__restrict__ in_hub_list,
+                                                    const unsigned long long *__restrict__ seen,
+                                                    unsigned long long *nxt, const uint4 *__restrict__ front_cur,
+                                                    const HubEntry *__restrict__ hub_list,
+                                                    const int32_t *__restrict__ owner,
+                                                    const int32_t *__restrict__ chunk_off, long long qcap,
+                                                    int32_t which, unsigned long long *prof_td,
+                                                    unsigned long long *prof_bu) {
+    if (c->done) return;
+    if (blockIdx.y == 0 && (which & 1)) settle_level(c, qmask, qvb, val, hub_list, partial, in_hub_list);
+    if (c->mode == MODE_TOPDOWN) {
+        if (which & 1) ms_topdown<BS>(c, rp, ci, rpi, queue, qmask, seen, nxt, hub_list, owner, chunk_off, qcap, prof_td);
+    } else if ((which & 2) && blockIdx.y == 0) {
+        ms_bottomup<BS>(c, rpi, cii, seen, nxt, front_cur, queue, qcap, prof_bu);
+    }
 }
 
 // End of a forward level (one thread): close the new frontier, turn the hub
@@ -1951,20 +1971,20 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
                                (int32_t)(l & 1), prof_counters(P_MS_EXPAND));
             continue;
         }
-        {
-            ProfScope ps(P_MS_TOPDOWN, s);
-            hipLaunchKernelGGL(k_ms_topdown<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
-                               g->row_ptr, g->col_idx, (const int32_t *)g->rp_in, ws.queue, ws.qmask,
+        auto discover = [&](int kind, int which) {
+            ProfScope ps(kind, s);
+            hipLaunchKernelGGL(k_ms_discover<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl, g->row_ptr,
+                               g->col_idx, (const int32_t *)g->rp_in, (const int32_t *)g->ci_in, ws.queue, ws.qmask,
                                (const uint32_t *)ws.qvb, ws.val, (const double *)ws.partial, in_list, ws.seen, ws.nxt,
-                               (const HubEntry *)ws.hub_list, (const int32_t *)ws.owner,
-                               (const int32_t *)ws.chunk_off, (long long)ws.qcap,
-                               prof_counters(P_MS_TOPDOWN));
-        }
-        if (may_pull) {
-            ProfScope ps(P_MS_BOTTOMUP, s);
-            hipLaunchKernelGGL(k_ms_bottomup<BS>, dim3(grid), dim3(BS), 0, s, ws.ctl, g->rp_in,
-                               g->ci_in, ws.seen, ws.nxt, fcur, ws.queue, (long long)ws.qcap,
-                               prof_counters(P_MS_BOTTOMUP));
+                               (const uint4 *)fcur, (const HubEntry *)ws.hub_list, (const int32_t *)ws.owner,
+                               (const int32_t *)ws.chunk_off, (long long)ws.qcap, which,
+                               prof_counters(P_MS_TOPDOWN), prof_counters(P_MS_BOTTOMUP));
+        };
+        if (prof_enabled() && may_pull) {
+            discover(P_MS_TOPDOWN, 1);
+            discover(P_MS_BOTTOMUP, 2);
+        } else {
+            discover(P_MS_TOPDOWN, 3);
         }
         {
             ProfScope ps(P_MS_SIGMA, s);

@@ -11,8 +11,9 @@
 //             block moves the frontier window and picks the direction of the
 //             next level from the frontier's and the unreached vertices'
 //             adjacency sizes;
-//   sigma_hub: path counts of the new level's hubs (see kHubDeg), chunk by
-//             chunk; the last chunk of a hub to arrive adds them up.
+//   hubs:     path counts of the new level's hubs (see kHubDeg), chunk by
+//             chunk, beside the next level's discovery; the last chunk of a
+//             hub to arrive adds them up.
 // The queue holds the vertices in level order; level_off[l] is where level l
 // starts, so the reverse pass replays the levels without a second BFS.
 //
@@ -275,8 +276,7 @@ __device__ __forceinline__ int32_t rows_per_wave(int64_t cnt) {
 // entries at a time, one entry per lane.  blockIdx.y == 1: blocks walk the
 // chunks of the frontier's hubs.
 template <int BS>
-__global__ __launch_bounds__(BS) void k_src_topdown(LevelCtl *c, SrcView p, unsigned long long *prof) {
-    if (c->done || c->mode != MODE_TOPDOWN) return;
+__device__ __forceinline__ void src_topdown(LevelCtl *c, const SrcView &p, unsigned long long *prof) {
     const int32_t *__restrict__ rp = p.rp, *__restrict__ ci = p.ci;
     int32_t *dist = p.dist, *queue = p.queue;
     __shared__ int32_t s_beg[BS], s_off[BS], s_scan[BS / kWave + 1];
@@ -346,8 +346,7 @@ __global__ __launch_bounds__(BS) void k_src_topdown(LevelCtl *c, SrcView p, unsi
 // Bottom-up discovery: every unreached vertex looks for a neighbour on the
 // current level, 8 entries per lane group, and stops once it finds one.
 template <int BS>
-__global__ __launch_bounds__(BS) void k_src_bottomup(LevelCtl *c, SrcView p, unsigned long long *prof) {
-    if (c->done || c->mode != MODE_BOTTOMUP) return;
+__device__ __forceinline__ void src_bottomup(LevelCtl *c, const SrcView &p, unsigned long long *prof) {
     const int32_t *__restrict__ rp = p.rpi, *__restrict__ ci = p.cii;
     int32_t *dist = p.dist, *queue = p.queue;
     __shared__ int32_t s_qbuf[4 * BS], s_meta[2];
@@ -377,6 +376,51 @@ __global__ __launch_bounds__(BS) void k_src_bottomup(LevelCtl *c, SrcView p, uns
     }
     q.finish(&c->tail_.v, queue, n, &c->overflow_.v);
     flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
+}
+
+// Path counts of the current level's hubs (parents one level up).
+// Undirected: the level's hub segment; directed: the incoming-row list.
+template <int BS>
+__device__ __forceinline__ void src_sigma_hub(LevelCtl *c, const SrcView &p, unsigned long long *prof) {
+    const bool in = p.in_hub_list != nullptr;
+    const int32_t hlo = c->hub_lo, hhi = c->hub_hi, start = in ? 0 : chunk_start(p, c->level);
+    const int32_t nch = in ? c->in_hub_nchunks : c->hub_nchunks;
+    HubEntry *hubs = in ? p.in_hub_list : p.hub_list;
+    const RowTerms<false> terms{p.cii, p.dist, p.sd, c->level - 1};
+    __shared__ unsigned long long s_red[1];
+    unsigned long long my_edges = 0, my_pairs = 0;
+    for_xcd_chunks<BS>(nch, [&](int64_t k) {
+        const int32_t j = in ? hub_find(hubs, 0, c->in_hub_n, (int32_t)k) : hub_of(p, start, hlo, hhi, (int32_t)k);
+        const HubEntry h = hubs[j];
+        double s;
+        if (hub_piece<false>(terms, p.rpi, hubs + j, h, (int32_t)k, 0.0, p.partial, &s, my_edges, my_pairs) &&
+            lane_id() == 0) {
+            p.sd[h.v].x = s;
+            atomic_max_nonneg_f64(&c->sigma_max_bits_.v, s);
+            if (sigma_is_large(s)) atomicOr(&c->flagged_slots_.v, 1ull);
+        }
+    });
+    flush_counters<BS>(prof, 0, my_edges, my_pairs, s_red);
+}
+
+// The first kernel of a level: what discovers the next one, in the direction
+// chosen, and beside it the path counts of this level's hubs, which nothing
+// reads before the next level's k_src_sigma (three launches cost 4.5 us each
+// where they had nothing to do).  blockIdx.y == 0: top-down without the hubs,
+// or bottom-up; 1: the frontier's hub chunks, top-down; 2: hub path counts.
+// `which` takes them apart for timing (1: top-down, 2: bottom-up, 4: hubs).
+template <int BS>
+__global__ __launch_bounds__(BS) void k_src_discover(LevelCtl *c, SrcView p, int32_t which,
+                                                     unsigned long long *prof_td, unsigned long long *prof_bu,
+                                                     unsigned long long *prof_hub) {
+    if (c->done) return;
+    if (blockIdx.y == 2) {
+        if ((which & 4) && c->level >= 1) src_sigma_hub<BS>(c, p, prof_hub);  // level 0 was given its count
+    } else if (c->mode == MODE_TOPDOWN) {
+        if (which & 1) src_topdown<BS>(c, p, prof_td);
+    } else if (blockIdx.y == 0) {
+        if (which & 2) src_bottomup<BS>(c, p, prof_bu);
+    }
 }
 
 // End of a forward level (one thread of k_src_sigma's last block).
@@ -423,7 +467,7 @@ __device__ void src_advance(LevelCtl *c, const SrcView &p) {
 }
 
 // Path counts of the new frontier: sigma[w] = sum of sigma[u] over neighbours
-// u on the current level.  Hubs are registered for k_src_sigma_hub: by
+// u on the current level.  Hubs are registered for k_src_discover: by
 // outgoing length (discovery, reverse pass) and, on a directed graph, by
 // incoming length in a list of this level's own.  The last block closes the level.
 template <int BS>
@@ -474,32 +518,6 @@ __global__ __launch_bounds__(BS, 8) void k_src_sigma(LevelCtl *c, SrcView p, uns
     block_add_u64<BS>(my_deg, s_red, &c->next_deg_.v);
     flush_counters<BS>(prof, my_items, my_scan, my_pairs, s_red);
     if (last_block(c, working_blocks((int64_t)tail - hi, per)) && threadIdx.x == 0) src_advance(c, p);
-}
-
-// Path counts of the current level's hubs (parents one level up).
-// Undirected: the level's hub segment; directed: the incoming-row list.
-template <int BS>
-__global__ __launch_bounds__(BS, 8) void k_src_sigma_hub(LevelCtl *c, SrcView p, unsigned long long *prof) {
-    if (c->done) return;
-    const bool in = p.in_hub_list != nullptr;
-    const int32_t hlo = c->hub_lo, hhi = c->hub_hi, start = in ? 0 : chunk_start(p, c->level);
-    const int32_t nch = in ? c->in_hub_nchunks : c->hub_nchunks;
-    HubEntry *hubs = in ? p.in_hub_list : p.hub_list;
-    const RowTerms<false> terms{p.cii, p.dist, p.sd, c->level - 1};
-    __shared__ unsigned long long s_red[1];
-    unsigned long long my_edges = 0, my_pairs = 0;
-    for_xcd_chunks<BS>(nch, [&](int64_t k) {
-        const int32_t j = in ? hub_find(hubs, 0, c->in_hub_n, (int32_t)k) : hub_of(p, start, hlo, hhi, (int32_t)k);
-        const HubEntry h = hubs[j];
-        double s;
-        if (hub_piece<false>(terms, p.rpi, hubs + j, h, (int32_t)k, 0.0, p.partial, &s, my_edges, my_pairs) &&
-            lane_id() == 0) {
-            p.sd[h.v].x = s;
-            atomic_max_nonneg_f64(&c->sigma_max_bits_.v, s);
-            if (sigma_is_large(s)) atomicOr(&c->flagged_slots_.v, 1ull);
-        }
-    });
-    flush_counters<BS>(prof, 0, my_edges, my_pairs, s_red);
 }
 
 // Reverse sweep over one level.  blockIdx.y == 0: its rows without the hubs;
@@ -661,30 +679,30 @@ static sp_status source_run_bs(sp_graph g, SourceWorkspace &ws, int32_t src, dou
                        o.ranked ? (const int32_t *)g->rank_new : nullptr, n, (long long)g->nnz,
                        may_pull ? o.alpha : 0.0, o.beta);  // alpha 0: never switch to bottom-up
     SP_HIP(hipGetLastError());
+    const int hub_grid = hubs_in ? grid_for(g->split_hub_chunks_in * kWave, BS, maxb) : 1;
+    const dim3 discover_grid(hubs || hubs_in ? xcd_grid(std::max(grid, hub_grid), maxb) : grid,
+                             hubs_in ? 3 : hubs ? 2 : 1);
+    auto discover = [&](int kind, int which) {
+        ProfScope ps(kind, s);
+        hipLaunchKernelGGL(k_src_discover<BS>, discover_grid, dim3(BS), 0, s, ws.ctl, p, which,
+                           prof_counters(P_SRC_TOPDOWN), prof_counters(P_SRC_BOTTOMUP),
+                           prof_counters(P_SRC_SIGMA_HUB));
+    };
     int32_t enqueued = 0;
     for (;;) {
         const int chunk = std::max(1, std::abs(o.chunk_levels));
         for (int k = 0; k < chunk; ++k) {
-            {
-                ProfScope ps(P_SRC_TOPDOWN, s);
-                hipLaunchKernelGGL(k_src_topdown<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl, p,
-                                   prof_counters(P_SRC_TOPDOWN));
-            }
-            if (may_pull) {
-                ProfScope ps(P_SRC_BOTTOMUP, s);
-                hipLaunchKernelGGL(k_src_bottomup<BS>, dim3(grid), dim3(BS), 0, s, ws.ctl, p,
-                                   prof_counters(P_SRC_BOTTOMUP));
+            if (prof_enabled()) {
+                discover(P_SRC_TOPDOWN, 1);
+                if (may_pull) discover(P_SRC_BOTTOMUP, 2);
+                if (hubs_in) discover(P_SRC_SIGMA_HUB, 4);
+            } else {
+                discover(P_SRC_TOPDOWN, 7);
             }
             {
                 ProfScope ps(P_SRC_SIGMA, s);
                 hipLaunchKernelGGL(k_src_sigma<BS>, dim3(level_grid(n)), dim3(BS), 0, s, ws.ctl, p,
                                    prof_counters(P_SRC_SIGMA));
-            }
-            if (hubs_in) {
-                ProfScope ps(P_SRC_SIGMA_HUB, s);
-                const int hub_grid = xcd_grid(grid_for(g->split_hub_chunks_in * kWave, BS, maxb), maxb);
-                hipLaunchKernelGGL(k_src_sigma_hub<BS>, dim3(hub_grid), dim3(BS), 0, s, ws.ctl, p,
-                                   prof_counters(P_SRC_SIGMA_HUB));
             }
         }
         SP_HIP(hipGetLastError());

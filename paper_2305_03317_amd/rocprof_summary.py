@@ -35,11 +35,11 @@ CSRC = os.path.join(HERE, "csrc")
 
 # kernel function name -> profile family reported by sp_profile_read
 FAMILY = {
-    "k_ms_topdown": "ms_topdown", "k_ms_bottomup": "ms_bottomup", "k_ms_sigma": "ms_sigma",
+    "k_ms_discover": "ms_discover", "k_ms_sigma": "ms_sigma",
     "k_ms_sigma_rest": "ms_sigma_hub", "k_ms_delta": "ms_delta", "k_ms_delta_hub": "ms_delta_hub",
-    "k_ms_expand": "ms_expand", "k_ms_bc": "ms_bc", "k_src_topdown": "src_topdown", "k_src_bottomup": "src_bottomup",
-    "k_src_sigma": "src_sigma", "k_src_sigma_hub": "src_sigma_hub", "k_src_delta": "src_delta",
-    "k_src_delta_hub": "src_delta_hub", "k_sssp_push": "sssp_push", "k_sssp_push_hops": "sssp_push", "k_sssp_mesh": "sssp_push", "k_sssp_pull": "sssp_pull",
+    "k_ms_expand": "ms_expand", "k_ms_bc": "ms_bc", "k_src_discover": "src_discover",
+    "k_src_sigma": "src_sigma", "k_src_delta": "src_delta",
+    "k_sssp_push": "sssp_push", "k_sssp_push_hops": "sssp_push", "k_sssp_mesh": "sssp_push", "k_sssp_pull": "sssp_pull",
     "k_pr_pull": "pr_pull", "k_tc_heavy": "tc_count", "k_tc_light": "tc_count",
     "k_wg_bc": "wg_bc", "k_wg_bc_ell": "wg_bc", "k_wg_bc_sum": "wg_bc_sum",
 }
