@@ -35,11 +35,10 @@
 // unreached vertices and the vertex's own source (level <= 0).
 //
 // Only the slot's own workgroup touches its arrays during the pass, so the
-// claim on a level is a workgroup-scope compare-and-swap, performed in the
-// XCD's L2.  The CSR-offset kernel reads levels another wave may have
-// claimed with workgroup-scope atomic loads; the fixed-width kernel reads
-// records with plain loads and invalidates the CU's L1 after each level
-// barrier instead.  Everything else is written with plain stores by waves of
+// claim on a level is a workgroup-scope compare-and-swap.  The CSR-offset
+// kernel reads levels another wave may have claimed with workgroup-scope
+// atomic loads; the fixed-width kernels read them with plain loads after the
+// level barrier.  Everything else is written with plain stores by waves of
 // the same workgroup and read after a barrier.
 //
 // Memory-level parallelism: a thread takes kEntries queue entries at once
@@ -56,13 +55,9 @@
 // -> claim, a path-count step queue entry -> row -> the neighbours' records,
 // and a reverse step queue entry -> row (and the vertex's own record) -> the
 // neighbours' records; the record of a neighbour that turns out not to be a
-// parent (child) is loaded and dropped.  Measured on a 2048 x 2048 grid
-// (64 sources, one per workgroup): a level costs about 46 us and scales with
-// the frontier, not with the chain of round trips -- the 64 workgroups'
-// record and row lines (128 bytes fetched per 16 used) keep the memory
-// system busy; spreading a source over 2 or 4 workgroups of one XCD, with a
-// barrier between the groups' phases, was slower (201 and 339 ms against
-// 181 ms for the whole pass).
+// parent (child) is loaded and dropped.  That is the directed kernel
+// (k_wg_bc_ell); an undirected graph takes k_wg_bc_mesh, whose levels stay in
+// LDS.
 #include "common.h"
 #include "devutil.h"
 
@@ -131,13 +126,12 @@ __device__ __forceinline__ int32_t at_or_none(const int32_t *queue, int32_t i, i
     return i < end ? x : -1;
 }
 
-// Level barrier of the fixed-width kernel, whose records are read with plain
-// loads: after the workgroup barrier the CU's L1 is invalidated, so the next
-// phase sees in L2 the levels other waves claimed there with
-// compare-and-swap and the values they stored.
+// Level barrier of the fixed-width kernels.  One workgroup's waves share their
+// CU's L1, which stores and atomics keep up to date: the barrier orders all.
+// (An agent-scope acquire here invalidated the L1 and the XCD's L2 at every
+// level of every workgroup: a third of the whole pass.)
 __device__ __forceinline__ void sync_records() {
     __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
 // A record in one 16-byte load (the empty asm marks the pad word used, so
@@ -334,6 +328,339 @@ __global__ __launch_bounds__(BS) void k_wg_bc_ell(const int32_t *__restrict__ el
     }
 }
 
+// The pass over fixed-width rows of an undirected graph.  Everything a level
+// needs of the one before stays in LDS: a frontier entry holds its vertex, its
+// path count and its row (the parent that claimed it marked there), a finished
+// entry of the reverse sweep its rho, by position in the level.  In memory
+// there are, per vertex, its position in BFS order (pos; -1 unreached) and, per
+// position, the vertex (queue), the value (sig) and a link to the children.
+//
+// Forward, a level is one round trip: the positions of the neighbours but the
+// parent, and their rows in the same breath.  An unreached one is claimed in an
+// LDS hash table (in levels past kMeshCap by compare-and-swap on pos, to -2):
+// an atomic on memory is performed behind the L2, and at four a vertex they
+// alone moved 70 GB of the pass.  A claimed vertex takes the claimer's path
+// count; a child that another entry claimed too is listed, and its count summed
+// again over its row, in row order, once the level's positions stand (4 vertices
+// in a hundred on a road grid).
+//
+// The children a vertex claimed have consecutive positions, in row order: link
+// holds the first (relative to its level), a bit per claimed neighbour, and
+// whether others claimed some.  The reverse sweep therefore reads queue, sig
+// and link in order, one level ahead of use, and its chain holds no round trip
+// but for the vertices with shared children, which look their row's positions up.
+//
+// Sums run in row order on every path, whoever claimed a vertex: the same bits.
+// Entries of a level past kMeshCap live in memory only.
+//
+// road-2048 (spanning tree and 2% more of a 2048 x 2048 grid), 64 sources,
+// blocks of 1,024: 168 ms with a record per vertex, claimed by atomics, an
+// invalidation after each level and two sweeps over the rows; 125 ms with the
+// levels in LDS, 95 without the invalidation, 61 with atomics on the neighbours
+// in question only, 54 with the claims in LDS.
+constexpr int kMeshMulti = 1024;  // shared children listed per level (more: every new vertex is summed again)
+constexpr int kMeshTable = 8192;  // kMeshCap * (W - 1), all that a level held in LDS can claim, and room
+constexpr uint32_t kLinkSlow = 1u << 24;
+template <int W>
+constexpr int kMeshCap = W == 4 ? 2048 : 1024;
+
+template <int BS, int W>
+__global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ ell,
+                                                   const int32_t *__restrict__ slot_src, int32_t n,
+                                                   int32_t *pos_all, uint32_t *link_all, double *sig_all,
+                                                   double *delta_all, double *sigma_out, int32_t *queue_all,
+                                                   int32_t *loff_all, WgSlotResult *res,
+                                                   unsigned long long *prof) {
+    constexpr int kCap = kMeshCap<W>;
+    struct Row {
+        int4 part[W / 4];
+        __device__ __forceinline__ int32_t at(int k) const {
+            const int4 x = part[k / 4];
+            return k % 4 == 0 ? x.x : k % 4 == 1 ? x.y : k % 4 == 2 ? x.z : x.w;
+        }
+        // this row with parent p's slots marked (-2 - p)
+        __device__ __forceinline__ Row marked(int32_t p) const {
+            Row x = *this;
+#pragma unroll
+            for (int q = 0; q < W / 4; ++q) {
+                int4 &y = x.part[q];
+                y = make_int4(y.x == p ? -2 - p : y.x, y.y == p ? -2 - p : y.y, y.z == p ? -2 - p : y.z,
+                              y.w == p ? -2 - p : y.w);
+            }
+            return x;
+        }
+    };
+    __shared__ int32_t s_v[2][kCap];
+    __shared__ int32_t s_claim[kMeshTable];  // vertices the level being built claimed, by hash; -1 empty
+    __shared__ double s_val[2][kCap];  // sigma forward, rho in reverse
+    __shared__ Row s_row[2][kCap];
+    __shared__ int32_t s_multi[kMeshMulti];
+    __shared__ int32_t s_tail, s_nmulti, s_flag;
+    __shared__ double s_max[BS / kWave];
+    __shared__ unsigned long long s_red[1];
+    const int32_t slot = blockIdx.x;
+    const int64_t base = (int64_t)slot * n;
+    int32_t *pos = pos_all + base;
+    uint32_t *link = link_all + base;
+    double *sig = sig_all + base;
+    double *delta = delta_all + base;
+    double *sig_out = sigma_out ? sigma_out + base : nullptr;  // sp_batch_levels' sigma
+    int32_t *queue = queue_all + base;
+    int32_t *loff = loff_all + (int64_t)slot * ((int64_t)n + 2);
+    const int32_t src = slot_src[slot];
+    const int lane = lane_id(), wave0 = threadIdx.x - lane;
+    auto row_of = [&](int32_t v) {
+        Row x;
+        const int4 *r = reinterpret_cast<const int4 *>(ell + (int64_t)v * W);
+#pragma unroll
+        for (int q = 0; q < W / 4; ++q) x.part[q] = r[q];
+        return x;
+    };
+    if (threadIdx.x == 0) {
+        pos[src] = 0;
+        queue[0] = src;
+        sig[0] = 1.0;
+        if (sig_out) sig_out[src] = 1.0;
+        loff[0] = 0;
+        loff[1] = 1;
+        s_v[0][0] = src;
+        s_val[0][0] = 1.0;
+        s_row[0][0] = row_of(src);
+        s_tail = 1;
+        s_nmulti = 0;
+        s_flag = 0;
+    }
+    auto clear_claims = [&](int32_t entries) {  // of level entries; returns the table's mask
+        int32_t size = 64;
+        while (size < min(entries, kCap) * 2 * (W - 1) && size < kMeshTable) size *= 2;
+        for (int32_t i = 4 * (int32_t)threadIdx.x; i < size; i += 4 * BS)
+            *reinterpret_cast<int4 *>(&s_claim[i]) = make_int4(-1, -1, -1, -1);
+        return size - 1;
+    };
+    int32_t mask = clear_claims(1);
+    sync_records();
+    int32_t lo = 0, hi = 1, level = 0, cur = 0;
+    double my_max = 1.0;
+    unsigned long long my_edges = 0, my_pairs = 0;
+    for (;;) {
+        const int32_t nxt = cur ^ 1;
+        const bool small = hi - lo <= kCap;  // the table holds all that such a level can claim
+        for (int32_t b = lo + wave0; b < hi; b += BS) {
+            const int32_t i = b + lane, k = i - lo;
+            const bool has = i < hi;
+            int32_t v = 0, id[W], old[W];
+            double sv = 0.0;
+            Row nrow[W == 4 ? W : 1];
+            uint32_t claimed = 0, shared = 0;
+            if (has) {
+                Row row;
+                if (k < kCap) {
+                    v = s_v[cur][k];
+                    sv = s_val[cur][k];
+                    row = s_row[cur][k];
+                } else {
+                    v = queue[i];
+                    sv = sig[i];
+                    row = row_of(v);
+                }
+#pragma unroll
+                for (int q = 0; q < W; ++q) {
+                    const int32_t u = row.at(q);
+                    my_edges += u != -1;
+                    id[q] = u;
+                    old[q] = 0;
+                    if (u >= 0) {
+                        old[q] = pos[u];
+                        if (W == 4) nrow[q % (W == 4 ? W : 1)] = row_of(u);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < W; ++q)
+                    if (old[q] == -1) {
+                        if (small) {  // LDS
+                            uint32_t h = (uint32_t)id[q] * 0x9E3779B1u >> 16 & mask;
+                            while ((old[q] = atomicCAS(&s_claim[h], -1, id[q])) != -1 && old[q] != id[q])
+                                h = (h + 1) & mask;
+                            old[q] = old[q] == -1 ? -1 : -2;
+                        } else {
+                            old[q] = claim_level(&pos[id[q]], -2);
+                        }
+                    }
+#pragma unroll
+                for (int q = 0; q < W; ++q) {
+                    claimed |= (uint32_t)(old[q] == -1) << q;
+                    shared |= (uint32_t)(old[q] == -2 || old[q] >= hi) << q;
+                }
+            }
+            const int32_t cnt = __popc(claimed);
+            const int32_t incl = wave_incl_scan(cnt);
+            const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+            int32_t at = 0;
+            if (lane == 0 && total) at = atomicAdd(&s_tail, total);  // LDS
+            at = __builtin_amdgcn_readfirstlane(at) + incl - cnt;
+            if (has) {
+                const int32_t first = at - hi;
+                link[i] = cnt && first > 0xffff ? kLinkSlow
+                                                : (uint32_t)(cnt ? first : 0) | claimed << 16 | (shared ? kLinkSlow : 0u);
+#pragma unroll
+                for (int q = 0; q < W; ++q) {
+                    if ((claimed >> q) & 1u) {
+                        pos[id[q]] = at;
+                        queue[at] = id[q];
+                        sig[at] = sv;
+                        if (sig_out) sig_out[id[q]] = sv;
+                        if (at - hi < kCap) {
+                            s_v[nxt][at - hi] = id[q];
+                            s_val[nxt][at - hi] = sv;
+                            s_row[nxt][at - hi] = (W == 4 ? nrow[q % (W == 4 ? W : 1)] : row_of(id[q])).marked(v);
+                        }
+                        ++at;
+                        ++my_pairs;
+                    }
+                    if ((shared >> q) & 1u) {
+                        const int32_t m = atomicAdd(&s_nmulti, 1);  // LDS
+                        if (m < kMeshMulti) s_multi[m] = id[q];
+                        ++my_pairs;
+                    }
+                }
+            }
+        }
+        sync_records();
+        const int32_t tail = s_tail, nmulti = s_nmulti;
+        mask = clear_claims(tail - hi);
+        if (tail == hi) break;  // block-uniform: every thread read the same tail
+        if (nmulti > 0) {
+            const bool listed = nmulti <= kMeshMulti;
+            for (int32_t m = threadIdx.x; m < (listed ? nmulti : tail - hi); m += BS) {
+                const int32_t w = listed ? s_multi[m] : queue[hi + m];
+                const int32_t j = listed ? pos[w] : hi + m, k = j - hi;
+                const Row row = k < kCap ? s_row[nxt][k] : row_of(w);
+                int32_t p[W];
+#pragma unroll
+                for (int q = 0; q < W; ++q) p[q] = pos[row.at(q) < -1 ? -2 - row.at(q) : max(row.at(q), 0)];
+                double acc = 0.0;
+#pragma unroll
+                for (int q = 0; q < W; ++q)
+                    if (row.at(q) != -1 && p[q] >= lo && p[q] < hi)
+                        acc += p[q] - lo < kCap ? s_val[cur][p[q] - lo] : sig[p[q]];
+                sig[j] = acc;
+                if (sig_out) sig_out[w] = acc;
+                if (k < kCap) s_val[nxt][k] = acc;
+                my_max = fmax(my_max, acc);
+                if (sigma_is_large(acc)) s_flag = 1;
+            }
+            sync_records();
+        }
+        if (threadIdx.x == 0) {
+            loff[level + 2] = tail;
+            s_nmulti = 0;
+        }
+        // a claimed vertex has its claimer's count, so only the sums above raise the largest
+        __syncthreads();
+        lo = hi;
+        hi = tail;
+        ++level;
+        cur = nxt;
+    }
+    // Reverse sweep from the deepest level up to level 1.  ahead: the entries
+    // this thread takes first on the next level up, loaded a level early (their
+    // range a level before that).
+    int32_t z2 = hi, z = hi, a = loff[level], up = level >= 1 ? loff[level - 1] : 0;
+    struct Entry {
+        int32_t v;
+        uint32_t lk;
+        double sv;
+    };
+    auto entry = [&](int32_t i) { return Entry{queue[i], link[i], sig[i]}; };
+    Entry ahead = entry(min(a + (int32_t)threadIdx.x, z - 1));
+    for (int32_t l = level; l >= 1; --l) {
+        const int32_t nxt = cur ^ 1, upper = l >= 2 ? loff[l - 2] : 0;
+        Entry e = ahead;
+        if (l >= 2) ahead = entry(min(up + (int32_t)threadIdx.x, a - 1));
+        for (int32_t i = a + (int32_t)threadIdx.x; i < z; i += BS) {
+            if (i != a + (int32_t)threadIdx.x) e = entry(i);
+            auto rho = [&](int32_t k) { return k < kCap ? s_val[cur][k] : sig[z + k]; };
+            double acc = 0.0;
+            if (e.lk & kLinkSlow) {
+                const Row row = row_of(e.v);
+                int32_t p[W];
+#pragma unroll
+                for (int q = 0; q < W; ++q) p[q] = pos[max(row.at(q), 0)];
+#pragma unroll
+                for (int q = 0; q < W; ++q)
+                    if (row.at(q) >= 0 && p[q] >= z && p[q] < z2) {
+                        acc += rho(p[q] - z);
+                        ++my_pairs;
+                    }
+            } else {
+                const int32_t first = (int32_t)(e.lk & 0xffffu), c = __popc((e.lk >> 16) & 0xffu);
+                for (int32_t q = 0; q < c; ++q) acc += rho(first + q);
+                my_pairs += c;
+            }
+            const double dv = e.sv * acc;
+            delta[e.v] = dv;
+            const double r = (1.0 + dv) / e.sv;
+            if (i - a < kCap) s_val[nxt][i - a] = r;
+            else sig[i] = r;
+        }
+        if (z - a > kCap) sync_records();
+        else __syncthreads();
+        z2 = z;
+        z = a;
+        a = up;
+        up = upper;
+        cur = nxt;
+    }
+    my_max = wave_max_f64(my_max);
+    if (lane == 0) s_max[threadIdx.x / kWave] = my_max;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double m = 0.0;
+        for (int w = 0; w < BS / kWave; ++w) m = fmax(m, s_max[w]);
+        res[slot] = WgSlotResult{level + 1, hi, m, s_flag};
+    }
+    if (prof) {
+        __syncthreads();
+        block_add_u64<BS>(threadIdx.x == 0 ? (unsigned long long)hi : 0ull, s_red, prof + 0);
+        __syncthreads();
+        block_add_u64<BS>(my_edges, s_red, prof + 1);
+        __syncthreads();
+        block_add_u64<BS>(my_pairs, s_red, prof + 2);
+    }
+}
+
+// Positions -1 (unreached).
+__global__ void k_wg_fill_pos(int2 *pos, int64_t pairs) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < pairs; i += stride)
+        pos[i] = make_int2(-1, -1);
+}
+
+// k_wg_extract by position: the level of position p is the last whose offset
+// is at most p.
+__global__ void k_wg_extract_mesh(int32_t n, int32_t nslots, const int32_t *__restrict__ pos,
+                                  const int32_t *__restrict__ loff, const WgSlotResult *__restrict__ res,
+                                  const double *__restrict__ delta, int32_t *out_dist, double *out_sigma,
+                                  double *out_delta) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)n * nslots; i += stride) {
+        const int32_t s = (int32_t)(i / n), p = pos[i];
+        int32_t d = -1;
+        if (p >= 0) {
+            const int32_t *off = loff + (int64_t)s * ((int64_t)n + 2);
+            int32_t lo = 0, hi = res[s].levels - 1;
+            while (lo < hi) {
+                const int32_t mid = (lo + hi + 1) >> 1;
+                if (off[mid] <= p) lo = mid; else hi = mid - 1;
+            }
+            d = lo;
+        }
+        if (out_dist) out_dist[i] = d;
+        if (out_sigma && d < 0) out_sigma[i] = 0.0;  // reached: written by the pass
+        if (out_delta) out_delta[i] = d > 0 ? delta[i] : 0.0;
+    }
+}
+
 // One source per workgroup: blockIdx.x = slot.
 template <int BS>
 __global__ __launch_bounds__(BS) void k_wg_bc(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
@@ -522,8 +849,11 @@ __global__ __launch_bounds__(BS) void k_wg_bc(const int32_t *__restrict__ rp, co
 // BC[v] += delta of v for every slot that reached v from another vertex, in
 // ascending slot order; consecutive slots with the same output array are
 // summed in a register.
-template <int BS>
+// MESH: whether a slot reached v comes from v's position (the source's is 0),
+// else from its record's level.
+template <int BS, bool MESH>
 __global__ __launch_bounds__(BS) void k_wg_bc_sum(int32_t n, int32_t nslots, const WgRec *__restrict__ rec,
+                                                  const int32_t *__restrict__ pos,
                                                   const double *__restrict__ delta, SlotTable tbl,
                                                   unsigned long long *prof) {
     __shared__ unsigned long long s_red[1];
@@ -540,7 +870,7 @@ __global__ __launch_bounds__(BS) void k_wg_bc_sum(int32_t n, int32_t nslots, con
                 acc = out[v];
             }
             const int64_t o = (int64_t)s * n + v;
-            if (rec[o].dist > 0) {
+            if ((MESH ? pos[o] : rec[o].dist) > 0) {
                 acc += delta[o];
                 ++my_items;
             }
@@ -623,8 +953,18 @@ static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, 
     int32_t *h_src = (int32_t *)ws.staging;
     for (int32_t i = 0; i < kSlots; ++i) h_src[i] = i < nslots ? srcs[i] : -1;
     SP_HIP(hipMemcpyAsync(ws.slot_src, h_src, kSlots * 4, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_wg_fill, dim3(grid_for(count, 256, 4096)), dim3(256), 0, s, ws.wg_rec, count);
     const int ew = ws.wg_ell_w;
+    // undirected fixed-width rows: k_wg_bc_mesh, whose positions, links and values share the records' memory
+    const bool mesh = ew != 0 && !g->directed;
+    const int64_t cells = (int64_t)ws.width * n;
+    double *sig = (double *)ws.wg_rec;
+    int32_t *pos = (int32_t *)(sig + cells);
+    uint32_t *link = (uint32_t *)(pos + cells);
+    if (mesh)  // (in pairs: of an odd count the entry behind, a link or an unused position, is cleared too)
+        hipLaunchKernelGGL(k_wg_fill_pos, dim3(grid_for((count + 1) / 2, 256, 4096)), dim3(256), 0, s, (int2 *)pos,
+                           (count + 1) / 2);
+    else
+        hipLaunchKernelGGL(k_wg_fill, dim3(grid_for(count, 256, 4096)), dim3(256), 0, s, ws.wg_rec, count);
     if (ew && !ws.wg_ell_built) {
         auto build = ew == 4 ? k_wg_ell<4> : k_wg_ell<8>;
         hipLaunchKernelGGL(build, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, (const int32_t *)g->row_ptr,
@@ -637,23 +977,28 @@ static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, 
     }
     {
         ProfScope ps(P_WG_BC, s);
-        const int32_t *ell_in = g->directed ? ws.wg_ell_in : ws.wg_ell;
-        if (ew == 4)
-            hipLaunchKernelGGL((k_wg_bc_ell<BS, 4>), dim3(nslots), dim3(BS), 0, s, (const int32_t *)ws.wg_ell,
-                               ell_in, (const int32_t *)ws.slot_src, n, ws.wg_rec, ws.wg_delta, ex ? ex->sigma : nullptr,
+        if (mesh) {
+            auto pass = ew == 4 ? k_wg_bc_mesh<BS, 4> : k_wg_bc_mesh<BS, 8>;
+            hipLaunchKernelGGL(pass, dim3(nslots), dim3(BS), 0, s, (const int32_t *)ws.wg_ell,
+                               (const int32_t *)ws.slot_src, n, pos, link, sig, ws.wg_delta, ex ? ex->sigma : nullptr,
                                ws.wg_queue, ws.wg_loff, ws.wg_res, prof_counters(P_WG_BC));
-        else if (ew == 8)
-            hipLaunchKernelGGL((k_wg_bc_ell<BS, 8>), dim3(nslots), dim3(BS), 0, s, (const int32_t *)ws.wg_ell,
-                               ell_in, (const int32_t *)ws.slot_src, n, ws.wg_rec, ws.wg_delta, ex ? ex->sigma : nullptr,
-                               ws.wg_queue, ws.wg_loff, ws.wg_res, prof_counters(P_WG_BC));
-        else
+        } else if (ew) {
+            auto pass = ew == 4 ? k_wg_bc_ell<BS, 4> : k_wg_bc_ell<BS, 8>;
+            hipLaunchKernelGGL(pass, dim3(nslots), dim3(BS), 0, s, (const int32_t *)ws.wg_ell,
+                               (const int32_t *)ws.wg_ell_in, (const int32_t *)ws.slot_src, n, ws.wg_rec, ws.wg_delta,
+                               ex ? ex->sigma : nullptr, ws.wg_queue, ws.wg_loff, ws.wg_res, prof_counters(P_WG_BC));
+        } else
             hipLaunchKernelGGL(k_wg_bc<BS>, dim3(nslots), dim3(BS), 0, s, (const int32_t *)g->row_ptr,
                                (const int32_t *)g->col_idx, (const int32_t *)g->rp_in, (const int32_t *)g->ci_in,
                                (const int32_t *)ws.slot_src, n, ws.wg_rec, ws.wg_delta, ex ? ex->sigma : nullptr,
                                ws.wg_queue, ws.wg_loff, ws.wg_res, prof_counters(P_WG_BC));
     }
     SP_HIP(hipGetLastError());
-    if (ex)
+    if (ex && mesh)
+        hipLaunchKernelGGL(k_wg_extract_mesh, dim3(grid_for(count, 256, 4096)), dim3(256), 0, s, n, nslots,
+                           (const int32_t *)pos, (const int32_t *)ws.wg_loff, (const WgSlotResult *)ws.wg_res,
+                           (const double *)ws.wg_delta, ex->dist, ex->sigma, ex->delta);
+    else if (ex)
         hipLaunchKernelGGL(k_wg_extract, dim3(grid_for(count, 256, 4096)), dim3(256), 0, s, count,
                            (const WgRec *)ws.wg_rec, (const double *)ws.wg_delta, ex->dist, ex->sigma,
                            ex->delta);
@@ -665,8 +1010,9 @@ static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, 
     }
     if (any_out) {
         ProfScope ps(P_MS_BC, s);
-        hipLaunchKernelGGL(k_wg_bc_sum<BS>, dim3(grid_for(n, BS, device_cu_count() * 8)), dim3(BS), 0, s, n,
-                           nslots, (const WgRec *)ws.wg_rec, (const double *)ws.wg_delta, tbl,
+        auto sum = mesh ? k_wg_bc_sum<BS, true> : k_wg_bc_sum<BS, false>;
+        hipLaunchKernelGGL(sum, dim3(grid_for(n, BS, device_cu_count() * 8)), dim3(BS), 0, s, n, nslots,
+                           (const WgRec *)ws.wg_rec, (const int32_t *)pos, (const double *)ws.wg_delta, tbl,
                            prof_counters(P_MS_BC));
     }
     SP_HIP(hipGetLastError());

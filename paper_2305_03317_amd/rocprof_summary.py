@@ -41,7 +41,7 @@ FAMILY = {
     "k_src_sigma": "src_sigma", "k_src_delta": "src_delta",
     "k_sssp_push": "sssp_push", "k_sssp_push_hops": "sssp_push", "k_sssp_mesh": "sssp_push", "k_sssp_pull": "sssp_pull",
     "k_pr_pull": "pr_pull", "k_tc_heavy": "tc_count", "k_tc_light": "tc_count",
-    "k_wg_bc": "wg_bc", "k_wg_bc_ell": "wg_bc", "k_wg_bc_sum": "wg_bc_sum",
+    "k_wg_bc": "wg_bc", "k_wg_bc_ell": "wg_bc", "k_wg_bc_mesh": "wg_bc", "k_wg_bc_sum": "wg_bc_sum",
 }
 
 
