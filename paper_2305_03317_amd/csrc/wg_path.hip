@@ -330,39 +330,69 @@ __global__ __launch_bounds__(BS) void k_wg_bc_ell(const int32_t *__restrict__ el
 
 // The pass over fixed-width rows of an undirected graph.  Everything a level
 // needs of the one before stays in LDS: a frontier entry holds its vertex, its
-// path count and its row (the parent that claimed it marked there), a finished
-// entry of the reverse sweep its rho, by position in the level.  In memory
-// there are, per vertex, its position in BFS order (pos; -1 unreached) and, per
-// position, the vertex (queue), the value (sig) and a link to the children.
+// path count and its row, with the parent that claimed it marked there; a
+// finished entry of the reverse sweep its rho, by position in the level.  In
+// memory there are, per vertex, its position in BFS order (pos; -1 unreached)
+// and, per position, the vertex (queue), the path count (sig) and a link to the
+// children.
 //
-// Forward, a level is one round trip: the positions of the neighbours but the
-// parent, and their rows in the same breath.  An unreached one is claimed in an
-// LDS hash table (in levels past kMeshCap by compare-and-swap on pos, to -2):
-// an atomic on memory is performed behind the L2, and at four a vertex they
-// alone moved 70 GB of the pass.  A claimed vertex takes the claimer's path
-// count; a child that another entry claimed too is listed, and its count summed
-// again over its row, in row order, once the level's positions stand (4 vertices
-// in a hundred on a road grid).
+// Forward, a level is one round trip: the rows of an entry's neighbours but the
+// parent and, in the same breath, the positions of those that may be reached
+// already.  A neighbour of a vertex lies at most a level away, so these are the
+// ones whose hash is in the filter of this level or the one before (s_seen), one
+// in ten on a road grid.  An unreached one is claimed in an LDS hash table (by
+// compare-and-swap on pos, to -2, if its place there is crowded or the level is
+// past kMeshCap): an atomic on memory is performed behind the L2, and at four a vertex they alone moved
+// 70 GB of the pass.  A claimed vertex takes the claimer's path count.  A child
+// that another entry claimed too is marked by its hash (s_shared), and adds its
+// parents' counts up in row order when its own turn comes, its row's positions
+// having been loaded with its neighbours' rows; a mark met by chance only adds
+// up a single parent.
 //
 // The children a vertex claimed have consecutive positions, in row order: link
 // holds the first (relative to its level), a bit per claimed neighbour, and
-// whether others claimed some.  The reverse sweep therefore reads queue, sig
-// and link in order, one level ahead of use, and its chain holds no round trip
-// but for the vertices with shared children, which look their row's positions up.
+// whether others claimed some.  The reverse sweep therefore reads queue, sig and
+// link in order, three levels ahead of use; the vertices with shared children
+// (8 in a hundred) have their rows, then their row's positions, loaded in the
+// two levels between.
 //
 // Sums run in row order on every path, whoever claimed a vertex: the same bits.
 // Entries of a level past kMeshCap live in memory only.
 //
-// road-2048 (spanning tree and 2% more of a 2048 x 2048 grid), 64 sources,
-// blocks of 1,024: 168 ms with a record per vertex, claimed by atomics, an
-// invalidation after each level and two sweeps over the rows; 125 ms with the
-// levels in LDS, 95 without the invalidation, 61 with atomics on the neighbours
-// in question only, 54 with the claims in LDS.
-constexpr int kMeshMulti = 1024;  // shared children listed per level (more: every new vertex is summed again)
-constexpr int kMeshTable = 8192;  // kMeshCap * (W - 1), all that a level held in LDS can claim, and room
+// What bounds it: on the largest grids the one CU a source has -- per level of
+// 1,400 entries some 5,000 lines in and out of its L1 -- and on small ones the
+// instructions of one wave's turn (2 us a level forward, 1.4 in reverse).
+// Spanning tree and 2% more of a grid, blocks of 1,024, 64 sources (300 x 300:
+// 16), whole call:
+//   grid                                           300    512   1000   2048
+//   a record per vertex, claimed by atomics, an
+//   invalidation after each level                                   168 ms
+//   levels in LDS, positions                                           125
+//   without the invalidation                                            95
+//   atomics on the neighbours in question only     3.7    7.7   19.5    61
+//   claims in LDS                                  3.8    7.7   17.9    54
+//   shared children in their own turn, the reverse
+//   sweep's loads three levels ahead               3.4    6.6   15.9  53.5
+//   the filter                                     3.6    6.9   15.6  51.3
+// (a table of each level's positions in LDS in place of pos, forward: 5.0, 9.5,
+// 21.3 and 73.7 ms -- more instructions than the round trip it saves; two
+// entries in flight per thread: 3.7, 7.1, 16.9 and 56.7.)
+constexpr int kMeshTable = 4096;   // entries of the claims' hash table
+constexpr int kMeshProbes = 64;    // a key lies this close behind its hash, or not in the table
+constexpr int kMeshSeen = 32768;   // bits of a level's filter
+constexpr int kMeshOffsets = 4096;  // level offsets held in LDS by the reverse sweep
 constexpr uint32_t kLinkSlow = 1u << 24;
 template <int W>
-constexpr int kMeshCap = W == 4 ? 2048 : 1024;
+constexpr int kMeshCap = W == 4 ? 2048 : 1024;  // entries of a level held in LDS
+
+// Workgroup barrier that orders LDS only: stores to memory stay in flight.
+__device__ __forceinline__ void sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ uint32_t mesh_hash(int32_t v) { return (uint32_t)v * 0x9E3779B1u >> 16; }
 
 template <int BS, int W>
 __global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ ell,
@@ -373,32 +403,18 @@ __global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ e
                                                    unsigned long long *prof) {
     constexpr int kCap = kMeshCap<W>;
     struct Row {
-        int4 part[W / 4];
-        __device__ __forceinline__ int32_t at(int k) const {
-            const int4 x = part[k / 4];
-            return k % 4 == 0 ? x.x : k % 4 == 1 ? x.y : k % 4 == 2 ? x.z : x.w;
-        }
-        // this row with parent p's slots marked (-2 - p)
-        __device__ __forceinline__ Row marked(int32_t p) const {
-            Row x = *this;
-#pragma unroll
-            for (int q = 0; q < W / 4; ++q) {
-                int4 &y = x.part[q];
-                y = make_int4(y.x == p ? -2 - p : y.x, y.y == p ? -2 - p : y.y, y.z == p ? -2 - p : y.z,
-                              y.w == p ? -2 - p : y.w);
-            }
-            return x;
-        }
+        int32_t x[W];
     };
+    __shared__ __attribute__((aligned(16))) int32_t s_key[kMeshTable];  // claimed for the next level; -1 empty
+    __shared__ uint32_t s_seen[3][kMeshSeen / 32];  // hashes of a level's vertices
+    __shared__ uint32_t s_shared[2][kMeshTable / 32];  // hashes of a level's vertices with several parents
+    __shared__ __attribute__((aligned(16))) Row s_row[2][kCap];  // the parent that claimed the entry: -2 - parent
     __shared__ int32_t s_v[2][kCap];
-    __shared__ int32_t s_claim[kMeshTable];  // vertices the level being built claimed, by hash; -1 empty
-    __shared__ double s_val[2][kCap];  // sigma forward, rho in reverse
-    __shared__ Row s_row[2][kCap];
-    __shared__ int32_t s_multi[kMeshMulti];
-    __shared__ int32_t s_tail, s_nmulti, s_flag;
+    __shared__ double s_val[3][kCap];  // sigma forward, rho in reverse
+    __shared__ int32_t s_tail, s_flag;
     __shared__ double s_max[BS / kWave];
     __shared__ unsigned long long s_red[1];
-    const int32_t slot = blockIdx.x;
+    const int32_t slot = blockIdx.x, tid = threadIdx.x;
     const int64_t base = (int64_t)slot * n;
     int32_t *pos = pos_all + base;
     uint32_t *link = link_all + base;
@@ -408,88 +424,122 @@ __global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ e
     int32_t *queue = queue_all + base;
     int32_t *loff = loff_all + (int64_t)slot * ((int64_t)n + 2);
     const int32_t src = slot_src[slot];
-    const int lane = lane_id(), wave0 = threadIdx.x - lane;
+    const int lane = lane_id(), wave0 = tid - lane;
+
     auto row_of = [&](int32_t v) {
-        Row x;
-        const int4 *r = reinterpret_cast<const int4 *>(ell + (int64_t)v * W);
+        Row r;
+        const int4 *p = reinterpret_cast<const int4 *>(ell + (int64_t)v * W);
 #pragma unroll
-        for (int q = 0; q < W / 4; ++q) x.part[q] = r[q];
-        return x;
+        for (int q = 0; q < W / 4; ++q) {
+            const int4 y = p[q];
+            r.x[4 * q] = y.x, r.x[4 * q + 1] = y.y, r.x[4 * q + 2] = y.z, r.x[4 * q + 3] = y.w;
+        }
+        return r;
     };
-    if (threadIdx.x == 0) {
+    for (int32_t i = 4 * tid; i < kMeshTable; i += 4 * BS)
+        *reinterpret_cast<int4 *>(&s_key[i]) = make_int4(-1, -1, -1, -1);
+    for (int32_t i = tid; i < kMeshTable / 32; i += BS) s_shared[0][i] = s_shared[1][i] = 0;
+    for (int32_t i = tid; i < kMeshSeen / 32; i += BS) s_seen[0][i] = s_seen[1][i] = s_seen[2][i] = 0;
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t h = mesh_hash(src) & (kMeshSeen - 1);
+        s_seen[0][h >> 5] = 1u << (h & 31);
         pos[src] = 0;
-        queue[0] = src;
-        sig[0] = 1.0;
-        if (sig_out) sig_out[src] = 1.0;
         loff[0] = 0;
         loff[1] = 1;
         s_v[0][0] = src;
         s_val[0][0] = 1.0;
         s_row[0][0] = row_of(src);
         s_tail = 1;
-        s_nmulti = 0;
         s_flag = 0;
     }
-    auto clear_claims = [&](int32_t entries) {  // of level entries; returns the table's mask
-        int32_t size = 64;
-        while (size < min(entries, kCap) * 2 * (W - 1) && size < kMeshTable) size *= 2;
-        for (int32_t i = 4 * (int32_t)threadIdx.x; i < size; i += 4 * BS)
-            *reinterpret_cast<int4 *>(&s_claim[i]) = make_int4(-1, -1, -1, -1);
-        return size - 1;
+    __syncthreads();
+
+    // Forward.
+    struct Entry {
+        int32_t v;
+        double sv;
+        Row row, at;         // neighbours and their positions
+        Row next[W == 4 ? W : 1];  // the neighbours' rows
+        bool shared;         // several parents
     };
-    int32_t mask = clear_claims(1);
-    sync_records();
-    int32_t lo = 0, hi = 1, level = 0, cur = 0;
+    int32_t plo = 0, lo = 0, hi = 1, level = 0, t = 0, mask = 63;  // t: level % 3
     double my_max = 1.0;
     unsigned long long my_edges = 0, my_pairs = 0;
+    auto fetch = [&](Entry &e, int32_t k) {  // entry k of the level
+        if (lo + k >= hi) return;
+        const int tp = t == 0 ? 2 : t - 1;
+        if (k < kCap) {
+            e.v = s_v[level & 1][k];
+            e.sv = s_val[t][k];
+            e.row = s_row[level & 1][k];
+        } else {
+            e.v = queue[lo + k];
+            e.sv = sig[lo + k];
+            e.row = row_of(e.v);
+        }
+        const uint32_t h = mesh_hash(e.v) & (kMeshTable - 1);
+        e.shared = (s_shared[level & 1][h >> 5] >> (h & 31)) & 1u;
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            int32_t u = e.row.x[q];
+            e.at.x[q] = -2;
+            my_edges += u != -1;
+            if (u < -1 && e.shared) u = -2 - u;
+            if (u >= 0) {
+                const uint32_t g = mesh_hash(u) & (kMeshSeen - 1);
+                if (((s_seen[tp][g >> 5] | s_seen[t][g >> 5]) >> (g & 31)) & 1u) e.at.x[q] = pos[u];
+                else e.at.x[q] = -1;
+                if (W == 4) e.next[q % (W == 4 ? W : 1)] = row_of(u);
+            }
+        }
+    };
+    Entry e;
+    fetch(e, tid);
     for (;;) {
-        const int32_t nxt = cur ^ 1;
-        const bool small = hi - lo <= kCap;  // the table holds all that such a level can claim
-        for (int32_t b = lo + wave0; b < hi; b += BS) {
-            const int32_t i = b + lane, k = i - lo;
+        const int tp = t == 0 ? 2 : t - 1, tn = t == 2 ? 0 : t + 1, nx = (level + 1) & 1;
+        const int probes = hi - lo <= kCap ? kMeshProbes : 0;
+        auto process = [&](Entry &x, int32_t k) {
+            const int32_t i = lo + k;
             const bool has = i < hi;
-            int32_t v = 0, id[W], old[W];
-            double sv = 0.0;
-            Row nrow[W == 4 ? W : 1];
             uint32_t claimed = 0, shared = 0;
             if (has) {
-                Row row;
-                if (k < kCap) {
-                    v = s_v[cur][k];
-                    sv = s_val[cur][k];
-                    row = s_row[cur][k];
-                } else {
-                    v = queue[i];
-                    sv = sig[i];
-                    row = row_of(v);
+                if (x.shared) {
+                    double acc = 0.0;
+#pragma unroll
+                    for (int q = 0; q < W; ++q) {
+                        const int32_t p = x.at.x[q];
+                        if (p >= plo && p < lo) acc += p - plo < kCap ? s_val[tp][p - plo] : sig[p];
+                    }
+                    x.sv = acc;
+                    if (k < kCap) s_val[t][k] = acc;
+                    my_max = fmax(my_max, acc);
+                    if (sigma_is_large(acc)) s_flag = 1;
                 }
+                queue[i] = x.v;
+                sig[i] = x.sv;
+                if (sig_out) sig_out[x.v] = x.sv;
 #pragma unroll
                 for (int q = 0; q < W; ++q) {
-                    const int32_t u = row.at(q);
-                    my_edges += u != -1;
-                    id[q] = u;
-                    old[q] = 0;
-                    if (u >= 0) {
-                        old[q] = pos[u];
-                        if (W == 4) nrow[q % (W == 4 ? W : 1)] = row_of(u);
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < W; ++q)
-                    if (old[q] == -1) {
-                        if (small) {  // LDS
-                            uint32_t h = (uint32_t)id[q] * 0x9E3779B1u >> 16 & mask;
-                            while ((old[q] = atomicCAS(&s_claim[h], -1, id[q])) != -1 && old[q] != id[q])
-                                h = (h + 1) & mask;
-                            old[q] = old[q] == -1 ? -1 : -2;
-                        } else {
-                            old[q] = claim_level(&pos[id[q]], -2);
+                    const int32_t u = x.row.x[q];
+                    int32_t found = x.at.x[q];
+                    if (found == -1) {
+                        uint32_t h = mesh_hash(u);
+                        for (int step = 0;; ++step, ++h) {
+                            if (step == probes) {  // no room
+                                found = claim_level(&pos[u], -2);
+                                break;
+                            }
+                            found = atomicCAS(&s_key[h & mask], -1, u);  // LDS
+                            if (found == -1) break;
+                            if (found == u) {
+                                found = hi;
+                                break;
+                            }
                         }
                     }
-#pragma unroll
-                for (int q = 0; q < W; ++q) {
-                    claimed |= (uint32_t)(old[q] == -1) << q;
-                    shared |= (uint32_t)(old[q] == -2 || old[q] >= hi) << q;
+                    claimed |= (uint32_t)(found == -1) << q;
+                    shared |= (uint32_t)(u >= 0 && (found == -2 || found >= hi)) << q;
                 }
             }
             const int32_t cnt = __popc(claimed);
@@ -502,126 +552,156 @@ __global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ e
                 const int32_t first = at - hi;
                 link[i] = cnt && first > 0xffff ? kLinkSlow
                                                 : (uint32_t)(cnt ? first : 0) | claimed << 16 | (shared ? kLinkSlow : 0u);
+                my_pairs += cnt + __popc(shared);
 #pragma unroll
                 for (int q = 0; q < W; ++q) {
+                    const int32_t u = x.row.x[q];
                     if ((claimed >> q) & 1u) {
-                        pos[id[q]] = at;
-                        queue[at] = id[q];
-                        sig[at] = sv;
-                        if (sig_out) sig_out[id[q]] = sv;
-                        if (at - hi < kCap) {
-                            s_v[nxt][at - hi] = id[q];
-                            s_val[nxt][at - hi] = sv;
-                            s_row[nxt][at - hi] = (W == 4 ? nrow[q % (W == 4 ? W : 1)] : row_of(id[q])).marked(v);
+                        pos[u] = at;
+                        const uint32_t g = mesh_hash(u) & (kMeshSeen - 1);
+                        atomicOr(&s_seen[tn][g >> 5], 1u << (g & 31));  // LDS
+                        const int32_t j = at - hi;
+                        if (j < kCap) {
+                            Row r = W == 4 ? x.next[q % (W == 4 ? W : 1)] : row_of(u);
+#pragma unroll
+                            for (int w = 0; w < W; ++w) r.x[w] = r.x[w] == x.v ? -2 - x.v : r.x[w];
+                            s_v[nx][j] = u;
+                            s_val[tn][j] = x.sv;
+                            s_row[nx][j] = r;
+                        } else {
+                            queue[at] = u;
+                            sig[at] = x.sv;
                         }
                         ++at;
-                        ++my_pairs;
                     }
                     if ((shared >> q) & 1u) {
-                        const int32_t m = atomicAdd(&s_nmulti, 1);  // LDS
-                        if (m < kMeshMulti) s_multi[m] = id[q];
-                        ++my_pairs;
+                        const uint32_t h = mesh_hash(u) & (kMeshTable - 1);
+                        atomicOr(&s_shared[nx][h >> 5], 1u << (h & 31));  // LDS
                     }
                 }
             }
+        };
+        for (int32_t b = wave0; b < hi - lo; b += BS) {
+            if (b != wave0) fetch(e, b + lane);
+            process(e, b + lane);
         }
-        sync_records();
-        const int32_t tail = s_tail, nmulti = s_nmulti;
-        mask = clear_claims(tail - hi);
-        if (tail == hi) break;  // block-uniform: every thread read the same tail
-        if (nmulti > 0) {
-            const bool listed = nmulti <= kMeshMulti;
-            for (int32_t m = threadIdx.x; m < (listed ? nmulti : tail - hi); m += BS) {
-                const int32_t w = listed ? s_multi[m] : queue[hi + m];
-                const int32_t j = listed ? pos[w] : hi + m, k = j - hi;
-                const Row row = k < kCap ? s_row[nxt][k] : row_of(w);
-                int32_t p[W];
-#pragma unroll
-                for (int q = 0; q < W; ++q) p[q] = pos[row.at(q) < -1 ? -2 - row.at(q) : max(row.at(q), 0)];
-                double acc = 0.0;
-#pragma unroll
-                for (int q = 0; q < W; ++q)
-                    if (row.at(q) != -1 && p[q] >= lo && p[q] < hi)
-                        acc += p[q] - lo < kCap ? s_val[cur][p[q] - lo] : sig[p[q]];
-                sig[j] = acc;
-                if (sig_out) sig_out[w] = acc;
-                if (k < kCap) s_val[nxt][k] = acc;
-                my_max = fmax(my_max, acc);
-                if (sigma_is_large(acc)) s_flag = 1;
-            }
-            sync_records();
-        }
-        if (threadIdx.x == 0) {
-            loff[level + 2] = tail;
-            s_nmulti = 0;
-        }
-        // a claimed vertex has its claimer's count, so only the sums above raise the largest
         __syncthreads();
+        const int32_t tail = s_tail;
+        if (tid == 0) loff[level + 2] = tail;
+        if (tail == hi) break;
+        plo = lo;
         lo = hi;
         hi = tail;
         ++level;
-        cur = nxt;
+        t = tn;
+        fetch(e, tid);
+        for (int32_t i = 4 * tid; i <= mask; i += 4 * BS)
+            *reinterpret_cast<int4 *>(&s_key[i]) = make_int4(-1, -1, -1, -1);
+        for (int32_t i = tid; i < kMeshTable / 32; i += BS) s_shared[(level + 1) & 1][i] = 0;
+        for (int32_t i = tid; i < kMeshSeen / 32; i += BS) s_seen[tp][i] = 0;
+        mask = 63;
+        while (mask < (hi - lo) * 8 && mask < kMeshTable - 1) mask = 2 * mask + 1;
+        sync_lds();
     }
-    // Reverse sweep from the deepest level up to level 1.  ahead: the entries
-    // this thread takes first on the next level up, loaded a level early (their
-    // range a level before that).
-    int32_t z2 = hi, z = hi, a = loff[level], up = level >= 1 ? loff[level - 1] : 0;
-    struct Entry {
+
+    // Reverse, from the deepest level up to level 1.  A level's entries go
+    // through three stages of loads, a level apart, before their turn: the
+    // entry itself, the row and the row's positions (of those with shared
+    // children).
+    struct Stage {
         int32_t v;
         uint32_t lk;
         double sv;
+        Row row;
     };
-    auto entry = [&](int32_t i) { return Entry{queue[i], link[i], sig[i]}; };
-    Entry ahead = entry(min(a + (int32_t)threadIdx.x, z - 1));
-    for (int32_t l = level; l >= 1; --l) {
-        const int32_t nxt = cur ^ 1, upper = l >= 2 ? loff[l - 2] : 0;
-        Entry e = ahead;
-        if (l >= 2) ahead = entry(min(up + (int32_t)threadIdx.x, a - 1));
-        for (int32_t i = a + (int32_t)threadIdx.x; i < z; i += BS) {
-            if (i != a + (int32_t)threadIdx.x) e = entry(i);
-            auto rho = [&](int32_t k) { return k < kCap ? s_val[cur][k] : sig[z + k]; };
-            double acc = 0.0;
-            if (e.lk & kLinkSlow) {
-                const Row row = row_of(e.v);
-                int32_t p[W];
+    int32_t *s_off = s_key, off0 = max(0, level + 3 - kMeshOffsets);
+    __syncthreads();
+    for (int32_t i = tid; i < kMeshOffsets; i += BS) s_off[i] = loff[min(off0 + i, level + 2)];
+    __syncthreads();
+    auto off = [&](int32_t l) { return s_off[l - off0]; };
+    auto stage1 = [&](Stage &x, int32_t l) {
+        if (l < 1) return;
+        const int32_t i = min(off(l) + tid, off(l + 1) - 1);
+        x.v = queue[i];
+        x.lk = link[i];
+        x.sv = sig[i];
+    };
+    auto stage2 = [&](Stage &x, int32_t l) {
+        if (l >= 1 && (x.lk & kLinkSlow)) x.row = row_of(x.v);
+    };
+    auto stage3 = [&](Stage &x, int32_t l) {
+        if (l >= 1 && (x.lk & kLinkSlow)) {
 #pragma unroll
-                for (int q = 0; q < W; ++q) p[q] = pos[max(row.at(q), 0)];
-#pragma unroll
-                for (int q = 0; q < W; ++q)
-                    if (row.at(q) >= 0 && p[q] >= z && p[q] < z2) {
-                        acc += rho(p[q] - z);
-                        ++my_pairs;
-                    }
-            } else {
-                const int32_t first = (int32_t)(e.lk & 0xffffu), c = __popc((e.lk >> 16) & 0xffu);
-                for (int32_t q = 0; q < c; ++q) acc += rho(first + q);
-                my_pairs += c;
-            }
-            const double dv = e.sv * acc;
-            delta[e.v] = dv;
-            const double r = (1.0 + dv) / e.sv;
-            if (i - a < kCap) s_val[nxt][i - a] = r;
-            else sig[i] = r;
+            for (int q = 0; q < W; ++q)
+                if (x.row.x[q] >= 0) x.row.x[q] = pos[x.row.x[q]];
         }
-        if (z - a > kCap) sync_records();
-        else __syncthreads();
-        z2 = z;
-        z = a;
-        a = up;
-        up = upper;
-        cur = nxt;
+    };
+    auto finish = [&](const Stage &x, int32_t i, int32_t l) {
+        const int32_t a = off(l), z = off(l + 1), z2 = off(l + 2);
+        auto rho = [&](int32_t k) { return k < kCap ? s_val[(l + 1) & 1][k] : sig[z + k]; };
+        double acc = 0.0;
+        if (x.lk & kLinkSlow) {
+#pragma unroll
+            for (int q = 0; q < W; ++q)
+                if (x.row.x[q] >= z && x.row.x[q] < z2) {
+                    acc += rho(x.row.x[q] - z);
+                    ++my_pairs;
+                }
+        } else {
+            const int32_t first = (int32_t)(x.lk & 0xffffu), c = __popc((x.lk >> 16) & 0xffu);
+            for (int32_t q = 0; q < c; ++q) acc += rho(first + q);
+            my_pairs += c;
+        }
+        const double dv = x.sv * acc;
+        delta[x.v] = dv;
+        const double r = (1.0 + dv) / x.sv;
+        if (i - a < kCap) s_val[l & 1][i - a] = r;
+        else sig[i] = r;
+    };
+    Stage st[4];
+    stage1(st[0], level);
+    stage1(st[1], level - 1);
+    stage1(st[2], level - 2);
+    stage2(st[0], level);
+    stage2(st[1], level - 1);
+    stage3(st[0], level);
+    for (int32_t l = level; l >= 1;) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (l < 1) break;
+            if (l - 3 < off0 && off0 > 0) {
+                __syncthreads();
+                off0 = max(0, l + 3 - kMeshOffsets);
+                for (int32_t i = tid; i < kMeshOffsets; i += BS) s_off[i] = loff[min(off0 + i, level + 2)];
+                __syncthreads();
+            }
+            stage3(st[(u + 1) & 3], l - 1);
+            stage2(st[(u + 2) & 3], l - 2);
+            stage1(st[(u + 3) & 3], l - 3);
+            const int32_t a = off(l), z = off(l + 1);
+            if (a + tid < z) finish(st[u], a + tid, l);
+            for (int32_t i = a + tid + BS; i < z; i += BS) {
+                Stage x{queue[i], link[i], sig[i], {}};
+                stage2(x, l);
+                stage3(x, l);
+                finish(x, i, l);
+            }
+            if (z - a > kCap) __syncthreads();
+            else sync_lds();
+            --l;
+        }
     }
     my_max = wave_max_f64(my_max);
-    if (lane == 0) s_max[threadIdx.x / kWave] = my_max;
+    if (lane == 0) s_max[tid / kWave] = my_max;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double m = 0.0;
         for (int w = 0; w < BS / kWave; ++w) m = fmax(m, s_max[w]);
         res[slot] = WgSlotResult{level + 1, hi, m, s_flag};
     }
     if (prof) {
         __syncthreads();
-        block_add_u64<BS>(threadIdx.x == 0 ? (unsigned long long)hi : 0ull, s_red, prof + 0);
+        block_add_u64<BS>(tid == 0 ? (unsigned long long)hi : 0ull, s_red, prof + 0);
         __syncthreads();
         block_add_u64<BS>(my_edges, s_red, prof + 1);
         __syncthreads();
