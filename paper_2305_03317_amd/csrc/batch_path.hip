@@ -1826,7 +1826,7 @@ size_t batch_ws_bytes(sp_graph g, int64_t qcap, int32_t width, int32_t engine) {
     if (engine == SP_ENGINE_BLOCKS) return wg_ws_bytes(g, width) + kSlots * 4 + sizeof(LevelCtl);
     return V * (8 + 8 + 16 + 16) + V * kSlots * 8 + (size_t)value_capacity(g, width) * 8 +
            (size_t)qcap * 16 + (V + 2) * 12 + kSlots * 4 +
-           (size_t)hub_capacity(g) * sizeof(HubEntry) + ((size_t)g->n_hubs + 1) * 4 +
+           (size_t)hub_capacity(g) * sizeof(HubEntry) +
            (size_t)in_hub_capacity(g) * sizeof(HubEntry) +
            (size_t)owner_capacity(g) * 4 + (V + 2) * 4 +
            (size_t)partial_rows(g) * kSlots * 8 + sizeof(LevelCtl);
@@ -1870,11 +1870,9 @@ sp_status batch_ws_create(sp_graph g, int64_t qcap, int32_t width, int32_t engin
     SP_TRY(dev_alloc((void **)&ws.hub_off, (size_t)ws.level_cap * 4));
     SP_TRY(dev_alloc((void **)&ws.hub_lvl_chunks, (size_t)ws.level_cap * 4));
     SP_TRY(dev_alloc((void **)&ws.hub_list, (size_t)ws.hub_cap * sizeof(HubEntry)));
-    SP_TRY(dev_alloc((void **)&ws.hub_cnt, ((size_t)g->n_hubs + 1) * 4));
     SP_TRY(dev_alloc((void **)&ws.partial, (size_t)partial_rows(g) * kSlots * 8));
     ws.in_hub_cap = in_hub_capacity(g);
     if (ws.in_hub_cap) SP_TRY(dev_alloc((void **)&ws.in_hub_list, (size_t)ws.in_hub_cap * sizeof(HubEntry)));
-    SP_HIP(hipMemset(ws.hub_cnt, 0, ((size_t)g->n_hubs + 1) * 4));
     SP_TRY(dev_alloc((void **)&ws.slot_src, kSlots * 4));
     SP_TRY(dev_alloc((void **)&ws.ctl, sizeof(LevelCtl)));
     SP_HIP(hipHostMalloc((void **)&ws.ctl_host, sizeof(LevelCtl), hipHostMallocDefault));
@@ -1908,7 +1906,6 @@ void batch_ws_destroy(BatchWorkspace &ws) {
     dev_free(ws.hub_list);
     dev_free(ws.owner);
     dev_free(ws.chunk_off);
-    dev_free(ws.hub_cnt);
     dev_free(ws.partial);
     dev_free(ws.in_hub_list);
     dev_free(ws.slot_src);

@@ -376,6 +376,8 @@ struct SlotTable {
 // Blocks engine, per (slot, vertex): the BFS level (-1 unreached) and a
 // value -- sigma after the forward pass; with fixed-width rows, rho =
 // (1 + delta) / sigma once the reverse pass has finished the vertex.
+// (Undirected graphs with fixed-width rows lay positions, links and path
+// counts out over the same bytes.)
 struct alignas(16) WgRec {
     int32_t dist;
     int32_t pad;
@@ -434,7 +436,6 @@ struct BatchWorkspace {
     int32_t *chunk_off = nullptr;        // device, level_cap: first owner slot of each level
     int32_t *hub_off = nullptr;          // device, level_cap: hub segment of each level
     int32_t *hub_lvl_chunks = nullptr;   // device, level_cap
-    unsigned int *hub_cnt = nullptr;     // device, n_hubs + 1
     double *partial = nullptr;           // device, partial_rows x 64
     HubEntry *in_hub_list = nullptr;     // device, directed graphs: one level's incoming-row hubs
     int64_t in_hub_cap = 0;

@@ -15,12 +15,6 @@ __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
 __device__ __forceinline__ int32_t shfl_i32(int32_t v, int src) { return __shfl(v, src, kWave); }
 
-__device__ __forceinline__ unsigned long long shfl_u64(unsigned long long v, int src) {
-    return __shfl(v, src, kWave);
-}
-
-__device__ __forceinline__ double shfl_f64(double v, int src) { return __shfl(v, src, kWave); }
-
 // Number of set lanes of `m` below the calling lane.
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
     const int l = lane_id();
@@ -165,77 +159,13 @@ __device__ __forceinline__ void block_add_u64(unsigned long long x, unsigned lon
 
 namespace sp {
 
-// Per-wave LDS scratch for the chunked reductions below (64 entries each).
+// Per-wave LDS scratch of wave_chunk_any (64 entries each).
 struct WaveScratch {
-    int32_t *coff;  // first chunk index of each lane's vertex
+    int32_t *coff;  // the lanes whose vertex has entries
     int32_t *beg;   // adjacency start
     int32_t *deg;   // adjacency length (0 = nothing to do)
-    double *acc;    // running sum of each lane's vertex
-    double *val;    // per-vertex operand the term may read (e.g. sigma[v])
+    double *acc;    // 1.0 once an entry of the lane's vertex is found
 };
-
-// Wave-level sum over the adjacency of up to 64 vertices, one per lane.
-// Every vertex's adjacency is cut into chunks of 8 entries aligned at its row
-// start.  A step gives 8 chunks to 8 groups of 8 lanes (one entry per lane),
-// folds each chunk with a fixed xor tree, and adds the chunk sums to the
-// vertex's running sum in chunk order.  The result therefore depends only on
-// the vertex's own adjacency, not on the lane or wave that handled it, and the
-// lanes stay busy whatever the degree mix.  term(e, owner) is the
-// contribution of adjacency entry e of the vertex held by lane `owner`.
-template <class Term>
-__device__ __forceinline__ double wave_chunk_sum(int32_t beg, int32_t deg, const WaveScratch &ws,
-                                                 Term term) {
-    const int lane = lane_id();
-    const int32_t nch = (deg + 7) >> 3;
-    const int32_t incl = wave_incl_scan(nch);
-    const int32_t total = __shfl(incl, kWave - 1, kWave);
-    ws.coff[lane] = incl - nch;
-    ws.beg[lane] = beg;
-    ws.deg[lane] = deg;
-    ws.acc[lane] = 0.0;
-    __builtin_amdgcn_wave_barrier();
-    const int g = lane >> 3, j = lane & 7;
-    for (int32_t t0 = 0; t0 < total; t0 += 8) {
-        const int32_t k = t0 + g;
-        int32_t a = -1;
-        double x = 0.0;
-        if (k < total) {
-            int32_t lo = 0, hi = kWave - 1;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi + 1) >> 1;
-                if (ws.coff[mid] <= k) lo = mid; else hi = mid - 1;
-            }
-            a = lo;
-            const int32_t off = (k - ws.coff[a]) * 8 + j;
-            if (off < ws.deg[a]) x = term(ws.beg[a] + off, a);
-        }
-        x += __shfl_xor(x, 1, kWave);
-        x += __shfl_xor(x, 2, kWave);
-        x += __shfl_xor(x, 4, kWave);
-        int32_t ag[8];
-        double xg[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            ag[q] = __shfl(a, q * 8, kWave);
-            xg[q] = __shfl(x, q * 8, kWave);
-        }
-        const int32_t a_prev = __shfl(a, ((g + 7) & 7) * 8, kWave);
-        if (j == 0 && a >= 0 && (g == 0 || a_prev != a)) {
-            double s = ws.acc[a];
-            bool run = true;
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q >= g) {
-                    if (run && ag[q] == a) s += xg[q];
-                    else run = false;
-                }
-            ws.acc[a] = s;
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-    __builtin_amdgcn_wave_barrier();
-    return ws.acc[lane];
-}
 
 // Wave-level "any": does some adjacency entry of each lane's vertex satisfy
 // pred?  The lanes with entries are compacted; group g of 8 lanes takes them
@@ -288,20 +218,6 @@ __device__ __forceinline__ bool wave_chunk_any(int32_t beg, int32_t deg, const W
     return ws.acc[lane] != 0.0;
 }
 
-// One chunk of a hub: lanes stride over its entries, each summing in order,
-// then a fixed xor tree; the chunk's sum goes to partial[k].  A finishing
-// kernel adds a hub's chunk sums in chunk order (the kernel boundary makes
-// them visible, so no fence is needed here).
-template <class Term>
-__device__ __forceinline__ void hub_chunk(int32_t k, int32_t beg, int32_t end, double *partial,
-                                          Term term) {
-    const int lane = lane_id();
-    double x = 0.0;
-    for (int32_t e = beg + lane; e < end; e += kWave) x += term(e);
-    x = wave_sum_f64(x);
-    if (lane == 0) partial[k] = x;
-}
-
 // Rows cut by row eighths (kXcds): a row of deg entries in nchunks = 8m
 // near-equal pieces; chunk id offset t = 8g + x is piece x*m + g, in the x-th
 // eighth of the row.  Workgroups are dispatched to the device's XCDs
@@ -338,42 +254,6 @@ __device__ __forceinline__ void for_xcd_chunks(int64_t nch, F f) {
         for (int64_t k = (int64_t)blockIdx.x * wpb + w; k < nch; k += (int64_t)gridDim.x * wpb)
             f(k);
     }
-}
-
-// Sum of a split row's chunk sums in row order, eight loads in flight.
-__device__ __forceinline__ double sum_split_chunks(const double *__restrict__ partial,
-                                                   int32_t base, int32_t n) {
-    double s = 0.0;
-    for (int32_t r = 0; r < n; r += 8) {  // n is a multiple of 8
-        double x[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] = partial[base + split_id(n, r + t)];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) s += x[t];
-    }
-    return s;
-}
-
-// Sum of partial[base .. base+n) in index order, eight loads in flight.
-__device__ __forceinline__ double sum_chunks(const double *__restrict__ partial, int32_t base,
-                                             int32_t n) {
-    double s = 0.0;
-    int32_t q = 0;
-    for (; q + 8 <= n; q += 8) {
-        double x[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] = partial[base + q + t];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) s += x[t];
-    }
-    for (; q < n; ++q) s += partial[base + q];
-    return s;
-}
-
-// A hub's chunk sums in row order under the split chunking (hub_chunk_range).
-__device__ __forceinline__ double sum_hub_chunks(const double *__restrict__ partial, int32_t base,
-                                                 int32_t n) {
-    return n < kXcds ? sum_chunks(partial, base, n) : sum_split_chunks(partial, base, n);
 }
 
 }  // namespace sp

@@ -356,7 +356,7 @@ __device__ __forceinline__ void src_bottomup(LevelCtl *c, const SrcView &p, unsi
     StagedQueue<BS, 4 * BS> q;
     q.init(s_qbuf, s_meta);
     const int wbase = threadIdx.x & ~(kWave - 1);
-    const WaveScratch ws{s_coff + wbase, s_beg + wbase, s_deg + wbase, s_acc + wbase, nullptr};
+    const WaveScratch ws{s_coff + wbase, s_beg + wbase, s_deg + wbase, s_acc + wbase};
     const int32_t lvl = c->level, n = c->n_vertices;
     unsigned long long my_items = 0, my_edges = 0;
     for (int32_t b = blockIdx.x * BS; b < n; b += gridDim.x * BS) {
