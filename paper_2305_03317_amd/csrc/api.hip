@@ -826,7 +826,6 @@ sp_status sp_graph_release(sp_graph g) {
     dev_free(g->rank_rp);
     dev_free(g->rank_ci);
     dev_free(g->tc_orp);
-    dev_free(g->tc_entries);
     dev_free(g->hub_static);
     dev_free(g->owner_static);
     pr_plan_free(g->pr_plan);

@@ -118,9 +118,8 @@ struct sp_graph_s {
     // v holds its neighbours of lower rank number (higher degree), ascending,
     // as 32-bit ids and (where they fit) as 16-bit ones; each entry's row; and
     // per vertex u the entries that name it, each as {row start, entry}.
-    int32_t *tc_orp = nullptr;       // device, n + 1; its allocation holds tc_iptr too
+    int32_t *tc_orp = nullptr;       // device, n + 1; its allocation holds the arrays below too
     int32_t *tc_iptr = nullptr;      // device, n + 1
-    void *tc_entries = nullptr;      // device allocation of the five arrays below
     int32_t *tc_oci = nullptr;       // tc_m (+ padding)
     uint16_t *tc_olo = nullptr;      // tc_m (+ padding): low 16 bits of tc_oci
     int32_t *tc_osrc = nullptr;      // tc_m (>= 1)

@@ -38,7 +38,7 @@ constexpr int32_t kTcUnit = 512;       // entries naming u per work unit
 constexpr int32_t kTcPosCap = 4096;    // per-vertex counts of N(u) kept in LDS up to this length
 constexpr int32_t kTcSortBits = 1 << 19;  // rows of lower ids are sorted through a bitmap of this size
 constexpr int32_t kTcHot = 4096;      // ids whose names are counted in LDS first
-constexpr int32_t kTcNamedTile = 1 << 15;
+constexpr int32_t kTcNamedTile = 1 << 15, kTcNamedLeast = 1 << 11;  // entries of a block's tile
 constexpr int32_t kTcSortCap = 8192;   // bitonic rows (a row of a higher id holds under 4,400 entries)
 }  // namespace
 
@@ -154,15 +154,18 @@ __global__ __launch_bounds__(256) void k_tc_fill(const int32_t *__restrict__ rp,
 }
 
 // Rows of 2..64 entries sorted by a wave each (an entry's place is the number
-// of smaller ones); longer rows listed for the block kernels.
-__global__ __launch_bounds__(256) void k_tc_sort_small(const int32_t *__restrict__ orp, int32_t n, int32_t *oci,
-                                                       int32_t *big, int32_t *nbig) {
+// of smaller ones); longer rows listed for the block kernels.  A wave takes
+// `share` rows (a power of two up to 64), one after another, the next one's
+// entries loaded meanwhile: 64 of them, each waiting for its load, made a graph
+// of any size wait 170 us and more (rmat-13 169 -> 15 us; rmat-22 392).
+__global__ __launch_bounds__(256) void k_tc_sort_small(const int32_t *__restrict__ orp, int32_t n, int32_t share,
+                                                       int32_t *oci, int32_t *big, int32_t *nbig) {
     const int lane = lane_id();
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t v0 = (int64_t)blockIdx.x * 256 + threadIdx.x - lane; v0 < n; v0 += stride) {
+    const int64_t stride = (int64_t)gridDim.x * (256 / kWave) * share;
+    for (int64_t v0 = ((int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * share; v0 < n; v0 += stride) {
         const int64_t v = v0 + lane;
         int32_t b = 0, len = 0;
-        if (v < n) {
+        if (v < n && lane < share) {
             b = orp[v];
             len = orp[v + 1] - b;
         }
@@ -175,11 +178,20 @@ __global__ __launch_bounds__(256) void k_tc_sort_small(const int32_t *__restrict
             if (len > kWave) big[at + lanes_below(more)] = (int32_t)v;
         }
         unsigned long long todo = __ballot(len >= 2 && len <= kWave);
-        while (todo) {
+        int32_t nb = 0, nl = 0, nx = 0;  // the next row and its entries
+        auto take = [&]() {
+            nl = 0;
+            if (!todo) return;
             const int src = __ffsll((long long)todo) - 1;
             todo &= todo - 1;
-            const int32_t rb = __builtin_amdgcn_readlane(b, src), rl = __builtin_amdgcn_readlane(len, src);
-            const int32_t x = lane < rl ? oci[rb + lane] : INT32_MAX;
+            nb = __builtin_amdgcn_readlane(b, src);
+            nl = __builtin_amdgcn_readlane(len, src);
+            nx = lane < nl ? oci[nb + lane] : INT32_MAX;
+        };
+        take();
+        while (nl) {
+            const int32_t rb = nb, rl = nl, x = nx;
+            take();
             int32_t place = 0;
             for (int32_t j = 0; j < rl; ++j) {
                 const int32_t y = __builtin_amdgcn_readlane(x, j);
@@ -270,11 +282,11 @@ __global__ __launch_bounds__(256) void k_tc_sort_net(const int32_t *__restrict__
 // heaviest vertices are named by most rows, so a block first counts the names
 // of the ids below kTcHot in its tile in LDS and reserves each id's places
 // with one atomic (rmat-22: 41% of the entries; 7.1 ms with an atomic each).
-__global__ __launch_bounds__(256) void k_tc_named(const int32_t *__restrict__ oci, int64_t m, uint16_t *olo,
-                                                  int32_t *named, int32_t *slot) {
+__global__ __launch_bounds__(256) void k_tc_named(const int32_t *__restrict__ oci, int64_t m, int32_t tile,
+                                                  uint16_t *olo, int32_t *named, int32_t *slot) {
     __shared__ int32_t s_at[kTcHot];
-    for (int64_t t0 = (int64_t)blockIdx.x * kTcNamedTile; t0 < m; t0 += (int64_t)gridDim.x * kTcNamedTile) {
-        const int64_t t1 = min(m, t0 + kTcNamedTile);
+    for (int64_t t0 = (int64_t)blockIdx.x * tile; t0 < m; t0 += (int64_t)gridDim.x * tile) {
+        const int64_t t1 = min(m, t0 + tile);
         for (int32_t i = threadIdx.x; i < kTcHot; i += 256) s_at[i] = 0;
         __syncthreads();
         for (int64_t e = t0 + threadIdx.x; e < t1; e += 256) {
@@ -556,19 +568,35 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     const int maxb = device_cu_count() * 8;
     const size_t vn = (size_t)std::max(n, 1);
     const int32_t *rp = g->row_ptr, *ci = g->col_idx, *rn = g->rank_new, *ro = g->rank_old;
-    TcBlock rows, entries, work, places;
+    const int32_t nu = std::min(n, kTcBits);
     int32_t *orp, *oci, *osrc, *iptr, *tiles, *big, *slot;
     uint16_t *olo;
     int2 *inl;
     int4 *units;
     unsigned long long *ctl;  // [0] entries that rise in (degree, id) order, [1] rows over 64
-    rows.add(&orp, vn + 1);
-    rows.add(&iptr, vn + 1);
-    SP_TRY(rows.alloc());
-    work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
-    work.add(&ctl, 2);
-    work.add(&big, vn + 1);
-    SP_TRY(work.alloc());
+    // Kept arrays and scratch, one block each, for me entries: half the graph's.
+    // (A graph that is not symmetric may turn out to have more.)
+    size_t me = (size_t)g->nnz / 2 + 1;
+    int64_t unit_cap = 0;
+    auto lay_out = [&](TcBlock &keep, TcBlock &work) {
+        const size_t padded = me + 8;  // 4-entry loads may run past the last row
+        unit_cap = (int64_t)me / kTcUnit + nu + 1;
+        keep.add(&orp, vn + 1);
+        keep.add(&ctl, 2);  // right behind orp: both come back in one copy
+        keep.add(&iptr, vn + 1);
+        keep.add(&oci, padded);
+        keep.add(&olo, padded);
+        keep.add(&osrc, me);
+        keep.add(&inl, me);
+        keep.add(&units, (size_t)unit_cap);
+        work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
+        work.add(&big, vn + 1);
+        work.add(&slot, me);
+        SP_TRY(keep.alloc());
+        return work.alloc();
+    };
+    TcBlock keep, work;
+    SP_TRY(lay_out(keep, work));
     hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)2);
     const int row_grid = grid_for((int64_t)n - heavy, 16, maxb);
     if (n > 0) {
@@ -580,28 +608,30 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     }
     launch_excl_scan(orp, n, orp, tiles, s);
     SP_HIP(hipGetLastError());
-    int32_t m = 0;
-    unsigned long long exact = 0;
-    SP_HIP(hipMemcpyAsync(&m, orp + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    SP_HIP(hipMemcpyAsync(&exact, ctl, sizeof(exact), hipMemcpyDeviceToHost, s));
+    char back[512];  // from orp[n], at most 256 bytes before ctl
+    const size_t to_ctl = (size_t)((char *)ctl - (char *)(orp + n));
+    SP_HIP(hipMemcpyAsync(back, orp + n, to_ctl + sizeof(*ctl), hipMemcpyDeviceToHost, s));
     SP_HIP(hipStreamSynchronize(s));
+    int32_t m;
+    unsigned long long exact;
+    std::memcpy(&m, back, sizeof(m));
+    std::memcpy(&exact, back + to_ctl, sizeof(exact));
     if ((int64_t)exact * 2 != g->nnz) {
         // a simple symmetric graph orients exactly one entry of each pair
         set_error("triangle counting needs a simple undirected CSR (%lld oriented entries of %lld)",
                   (long long)exact, (long long)g->nnz);
         return SP_ERR_INVALID_ARGUMENT;
     }
-    const size_t me = (size_t)std::max(m, 1), padded = me + 8;  // 4-entry loads may run past the last row
-    const int32_t nu = std::min(n, kTcBits);
-    const int64_t unit_cap = (int64_t)me / kTcUnit + nu + 1;
-    entries.add(&oci, padded);
-    entries.add(&olo, padded);
-    entries.add(&osrc, me);
-    entries.add(&inl, me);
-    entries.add(&units, (size_t)unit_cap);
-    SP_TRY(entries.alloc());
-    places.add(&slot, me);
-    SP_TRY(places.alloc());
+    TcBlock keep_more, work_more;
+    const bool more = (size_t)m > me;
+    if (more) {
+        const int32_t *offsets = orp;
+        me = (size_t)m;
+        SP_TRY(lay_out(keep_more, work_more));
+        SP_HIP(hipMemcpyAsync(orp, offsets, sizeof(int32_t) * (vn + 1), hipMemcpyDeviceToDevice, s));
+        hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)2);
+    }
+    TcBlock &kept = more ? keep_more : keep;
     const int ent_grid = grid_for(m, 256, 2 * maxb);
     int32_t un[2] = {0, 0};
     if (n > 0) {
@@ -611,8 +641,10 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
         hipLaunchKernelGGL(k_tc_fill<false>, dim3(row_grid), dim3(256), 0, s, rp, ci, rn, ro, heavy, n,
                            (const int32_t *)orp, oci, osrc);
         int32_t *nbig = (int32_t *)(ctl + 1);
-        hipLaunchKernelGGL(k_tc_sort_small, dim3(grid_for(n, 256, maxb)), dim3(256), 0, s, (const int32_t *)orp, n,
-                           oci, big, nbig);
+        int32_t share = 4;
+        while (share < kWave && (int64_t)share * (256 / kWave) * maxb < n) share *= 2;
+        hipLaunchKernelGGL(k_tc_sort_small, dim3(grid_for(n, 256 / kWave * share, maxb)), dim3(256), 0, s,
+                           (const int32_t *)orp, n, share, oci, big, nbig);
         hipLaunchKernelGGL(k_tc_sort_bits<kTcLow / 32>, dim3(maxb), dim3(256), 0, s, (const int32_t *)orp, oci,
                            (const int32_t *)big, (const int32_t *)nbig, 0, kTcLow);
         if (n > kTcLow)
@@ -622,8 +654,10 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
             hipLaunchKernelGGL(k_tc_sort_net, dim3(maxb), dim3(256), 0, s, (const int32_t *)orp, oci,
                                (const int32_t *)big, (const int32_t *)nbig, kTcSortBits);
         SP_TRY(launch_fill_i32(iptr, n, 0, s));
-        hipLaunchKernelGGL(k_tc_named, dim3(grid_for(m, kTcNamedTile, maxb)), dim3(256), 0, s, (const int32_t *)oci, (int64_t)m, olo, iptr,
-                           slot);
+        int32_t tile = kTcNamedLeast;
+        while (tile < kTcNamedTile && (int64_t)tile * device_cu_count() < m) tile *= 2;
+        hipLaunchKernelGGL(k_tc_named, dim3(grid_for(m, tile, maxb)), dim3(256), 0, s, (const int32_t *)oci,
+                           (int64_t)m, tile, olo, iptr, slot);
         launch_excl_scan(iptr, n, iptr, tiles, s);
         hipLaunchKernelGGL(k_tc_inlist, dim3(ent_grid), dim3(256), 0, s, (const int32_t *)oci, (const int32_t *)osrc,
                            (const int32_t *)orp, (const int32_t *)iptr, (const int32_t *)slot, (int64_t)m, inl);
@@ -634,12 +668,12 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
         hipLaunchKernelGGL(k_tc_unit_fill, dim3(grid_for(nu, 256, maxb)), dim3(256), 0, s, (const int32_t *)iptr, nu,
                            (const int32_t *)first, units, unit_cap);
         SP_HIP(hipGetLastError());
-        SP_HIP(hipMemcpyAsync(&un[0], first + std::min(nu, kTcLow), sizeof(int32_t), hipMemcpyDeviceToHost, s));
         SP_HIP(hipMemcpyAsync(&un[1], first + nu, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        if (nu > kTcLow) SP_HIP(hipMemcpyAsync(&un[0], first + kTcLow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     }
     SP_HIP(hipStreamSynchronize(s));
-    g->bytes += rows.bytes + entries.bytes;
-    g->tc_entries = std::exchange(entries.base, nullptr);
+    if (nu <= kTcLow) un[0] = un[1];
+    g->bytes += kept.bytes;
     g->tc_oci = oci;
     g->tc_olo = olo;
     g->tc_osrc = osrc;
@@ -649,7 +683,7 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     g->tc_units_lo = un[0];
     g->tc_units_n = (int32_t)std::min<int64_t>(un[1], unit_cap);
     g->tc_m = m;
-    g->tc_orp = (int32_t *)std::exchange(rows.base, nullptr);  // the rows' block begins with orp
+    g->tc_orp = (int32_t *)std::exchange(kept.base, nullptr);  // the block begins with orp
     return SP_OK;
 }
 
