@@ -207,7 +207,9 @@ typedef struct sp_stats {
 /* Per-source path: one BFS pass per source, sources in list order.
  *   sources    host array of n_sources vertex ids in [0, V).
  *   out_bc     device array of V doubles: zeroed, then receives BC.
- * Returns SP_OK or SP_WARN_SIGMA_LARGE (synchronises the stream). */
+ * Returns SP_OK or SP_WARN_SIGMA_LARGE (synchronises the stream).  On large
+ * skewed undirected graphs (2^20 vertices and more) the first call of 8 sources
+ * or more keeps the copy of the rows that sp_pagerank describes. */
 sp_status sp_bc(sp_graph g, const int32_t *sources, int32_t n_sources, double *out_bc,
                 sp_stream s);
 
@@ -461,7 +463,10 @@ typedef struct sp_pagerank_stats {
  *   max_iter  >= 1
  *   out_pr    device double[V]: receives the values of the last iteration.
  *   cfg       may be NULL.
- * Synchronises the stream. */
+ * Synchronises the stream.  The first call lays the rows out for the pull; on
+ * large skewed graphs (over 400,000 vertices) that is a copy of them numbered by
+ * degree, 4 bytes per CSR entry and 12 per vertex, kept with the graph (done
+ * without where memory is short). */
 sp_status sp_pagerank(sp_graph g, double beta, double delta, int32_t max_iter, double *out_pr,
                       const sp_pagerank_config *cfg, sp_stream s);
 

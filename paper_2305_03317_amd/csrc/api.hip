@@ -872,7 +872,7 @@ sp_status sp_bc(sp_graph g, const int32_t *sources, int32_t n_sources, double *o
         SourceWorkspace *ws;
         ~Rel() { release_source_ws(g, ws); }
     } rel{g, ws};
-    bool ranked = n_sources > 0 && source_ranked(g, st);
+    bool ranked = n_sources > 0 && source_ranked(g, n_sources, st);
     if (ranked && !ws->bc && dev_alloc((void **)&ws->bc, sizeof(double) * (size_t)g->n) != SP_OK) {
         clear_error();  // the graph's own numbering does as well
         ranked = false;
@@ -1047,7 +1047,7 @@ sp_status sp_bfs_levels(sp_graph g, int32_t source, int32_t *out_dist, double *o
         ~Rel() { release_source_ws(g, ws); }
     } rel{g, ws};
     SourceRunOpts o;
-    o.ranked = source_ranked(g, st);
+    o.ranked = source_ranked(g, 1, st);
     SourceResult r;
     SP_TRY(source_run(g, *ws, source, nullptr, out_delta != nullptr, o, st, &r));
     hipLaunchKernelGGL(k_src_export, dim3(grid_for(g->n, 256, 4096)), dim3(256), 0, st, g->n,

@@ -338,8 +338,9 @@ struct SourceRunOpts {
     bool ranked = false;  // on the rows numbered by rank (source_ranked): ws.dist, ws.sd and bc are by rank
 };
 // Whether the per-source path runs on g's rows numbered by rank, built here on
-// the first call (undirected, large and skewed, and the memory there).
-bool source_ranked(sp_graph g, hipStream_t s);
+// the first call of enough sources (undirected, large and skewed, and the memory
+// there).
+bool source_ranked(sp_graph g, int32_t n_sources, hipStream_t s);
 // out[v] = bc[rank of v].
 sp_status launch_unrank(sp_graph g, const double *bc, double *out, hipStream_t s);
 struct SourceResult {

@@ -329,14 +329,15 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     constexpr int32_t longest = kPrPiece - 1;
     // renumbered when it pays and its copy fits; the graph's own rows do otherwise
     bool renum = false;
-    if (!g->directed) {  // the copy that the per-source path runs on too
+    const bool large = n > kPrRenumberFrom && g->max_degree > 8;
+    if (large && !g->directed) {  // the copy that the per-source path runs on too
         SP_TRY(ensure_rank_csr_locked(g, s));
         renum = g->rank_ci != nullptr;
         if (renum) {
             rp = g->rank_rp;
             ci = g->rank_ci;
         }
-    } else if (n > kRenumberFrom && g->max_degree > 8) {
+    } else if (large) {
         sp_status st = ensure_rank_locked(g, s);
         if (st == SP_OK && rank_skewed(g)) st = dev_alloc((void **)&pl.col, sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1));
         if (st != SP_OK && st != SP_ERR_OUT_OF_MEMORY) return st;

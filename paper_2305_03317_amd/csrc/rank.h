@@ -27,9 +27,20 @@ sp_status ensure_rank_locked(sp_graph g, hipStream_t s);
 // Vertices of degree >= deg (at most kRankExact, or a power of two); after ensure_rank_locked.
 inline int32_t rank_count(sp_graph g, int32_t deg) { return g->rank_first[rank_bucket(deg) + 1]; }
 
-// Vertices from which renumbering by rank is considered: 8-byte values of 2 MB,
-// half an XCD's L2.
+// Vertices above which renumbering by rank is considered.  Weighted rows, which
+// are written out anew in any case: 8-byte values of 2 MB, half an XCD's L2.
 constexpr int32_t kRenumberFrom = 1 << 18;
+// PageRank (once a graph): from here on 20 iterations win back what the copy
+// takes (first call, rmat, edge factor 16, with and without: 420,000 vertices
+// 2.7 and 2.7 ms, 600,000 3.0 and 3.5, 4,000,000 12.5 and 21.1).
+constexpr int32_t kPrRenumberFrom = 400000;
+// Per-source passes: four sources, copy made, with and without: 600,000
+// vertices 2.2 and 1.9 ms, 1,000,000 3.29 and 3.33, 2,000,000 5.4 and 6.4,
+// 4,000,000 9.9 and 13.7.  The copy takes as long as four to ten of the sources
+// it serves gain, so fewer than kSourceRankCount use it only where it is there
+// (sp_bfs_levels, 1,000,000 vertices, first call: 2.3 and 1.1 ms).
+constexpr int32_t kSourceRankFrom = 1 << 20;
+constexpr int32_t kSourceRankCount = 8;
 
 // Whether gathers concentrate enough for renumbering to pay: the eighth of the
 // vertices of highest degree holds at least half of the entries (road grids
@@ -37,9 +48,9 @@ constexpr int32_t kRenumberFrom = 1 << 18;
 // ensure_rank_locked.
 bool rank_skewed(sp_graph g);
 
-// Builds g->rank_rp / g->rank_ci once, on an undirected graph over
-// kRenumberFrom vertices that is skewed; leaves them null on others and where
-// memory is short.  The caller holds g->mu.
+// Builds g->rank_rp / g->rank_ci once, on an undirected graph that is skewed;
+// leaves them null on others and where memory is short.  The caller holds g->mu
+// and has looked at the size.
 sp_status ensure_rank_csr_locked(sp_graph g, hipStream_t s);
 
 // Entries of the rows [0, rows) renumbered: row i goes to col[to[i]...], from

@@ -633,8 +633,10 @@ void source_ws_destroy(SourceWorkspace &ws) {
     ws = SourceWorkspace{};
 }
 
-bool source_ranked(sp_graph g, hipStream_t s) {
+bool source_ranked(sp_graph g, int32_t n_sources, hipStream_t s) {
+    if (g->n < kSourceRankFrom) return false;
     std::lock_guard<std::mutex> lk(g->mu);
+    if (!g->rank_ci && n_sources < kSourceRankCount) return false;
     return ensure_rank_csr_locked(g, s) == SP_OK && g->rank_ci != nullptr;
 }
 

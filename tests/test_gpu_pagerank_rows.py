@@ -28,10 +28,10 @@ def hubs_graph(copies: int, leaves: int, seed: int):
 
 
 @pytest.mark.parametrize("block", [0, 128, 256, 512])
-@pytest.mark.parametrize("copies,leaves", [(1, 20001), (3, 40000), (8, 300_000)])
+@pytest.mark.parametrize("copies,leaves", [(1, 20001), (3, 40000), (8, 420_000)])
 @pytest.mark.parametrize("directed", [False, True])
 def test_row_classes(copies, leaves, block, directed):
-    # 300,000 leaves, most of them without edges: past the size and the skew at which vertices are renumbered
+    # 420,000 leaves, most of them without edges: past the size and the skew at which vertices are renumbered
     from paper_2305_03317_amd import sp
     print(copies, leaves, block, directed, flush=True)
     rp, ci = hubs_graph(copies, leaves, 5)

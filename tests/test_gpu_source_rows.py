@@ -24,8 +24,8 @@ def make(name: str):
         return graphs.from_edges(9500 + len(LENGTHS), src, dst)
     if name == "deep":  # more levels than come back with the control block
         return graphs.from_edges(2000, np.arange(1999), np.arange(1, 2000))
-    rp, ci = graphs.rmat(14, 16, seed=4)  # "ranked": isolated vertices up to 300,000 in all
-    return np.concatenate([rp, np.full(300_000 - 16384, rp[-1], np.int32)]), ci
+    rp, ci = graphs.rmat(14, 16, seed=4)  # "ranked": isolated vertices up to 2^20 in all
+    return np.concatenate([rp, np.full((1 << 20) - 16384, rp[-1], np.int32)]), ci
 
 
 def close(got, ref):
@@ -42,7 +42,7 @@ def test_rows(name, directed):
     rp, ci = make(name)
     if directed:
         rp, ci = graphs.directed_from(rp, ci, 6)
-    src = graphs.sources(rp, 5, 7, min_degree=1)
+    src = graphs.sources(rp, 9, 7, min_degree=1)
     g = sp.sp_graph_upload(rp, ci, directed=directed)
     got = sp.sp_bc(g, src)[0].cpu().numpy()
     close(got, oracle.bc(rp, ci, src))
