@@ -417,9 +417,20 @@ __global__ void k_ms_clear(unsigned long long *seen, unsigned long long *nxt, ui
     }
 }
 
+// The distinct source vertices of a pass with their slots, and each slot's
+// source (-1: none).
+struct MsSources {
+    int32_t v[kSlots];
+    int32_t of_slot[kSlots];
+    unsigned long long m[kSlots];
+};
+
 // Level 0: entries [0, n0) hold the distinct source vertices and their slots.
-__global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int32_t *queue,
-                          const unsigned long long *qmask, uint32_t *qvb, int32_t n0,
+// They come as arguments: as three copies to the device they took 30 us of
+// every pass (uniform, 4,096 vertices, 16 sources, with the launch that started
+// the reverse pass gone too: 423 -> 381 us a call).
+__global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, MsSources src, int32_t *queue,
+                          unsigned long long *qmask, uint32_t *qvb, int32_t *slot_src, int32_t n0,
                           unsigned long long *seen, uint4 *front0, double *val, int32_t *level_off,
                           HubEntry *hub_list, int32_t *hub_off, int32_t *hub_lvl_chunks,
                           int32_t *owner, int32_t *chunk_off, int32_t n,
@@ -429,9 +440,12 @@ __global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int
     int32_t v0 = 0, d0 = 0, pc0 = 0;
     unsigned long long m0 = 0;
     if (threadIdx.x < kWave) {
+        slot_src[threadIdx.x] = src.of_slot[threadIdx.x];
         if ((int32_t)threadIdx.x < n0) {
-            v0 = queue[threadIdx.x];
-            m0 = qmask[threadIdx.x];
+            v0 = src.v[threadIdx.x];
+            m0 = src.m[threadIdx.x];
+            queue[threadIdx.x] = v0;
+            qmask[threadIdx.x] = m0;
             d0 = rp[v0 + 1] - rp[v0];
             pc0 = __popcll(m0);
         }
@@ -443,8 +457,8 @@ __global__ void k_ms_init(LevelCtl *c, const int32_t *__restrict__ rp, const int
     const int lane = lane_id();
     const int wv = threadIdx.x / kWave;
     for (int32_t i = wv; i < n0; i += blockDim.x / kWave) {
-        const int32_t v = queue[i];
-        const unsigned long long m = qmask[i];
+        const int32_t v = src.v[i];
+        const unsigned long long m = src.m[i];
         const uint32_t vb = s_vb[i];
         if ((m >> lane) & 1ull) val[vb + rank_in(m, lane)] = 1.0;
         if (lane == 0) {
@@ -847,6 +861,7 @@ __device__ void advance_level(LevelCtl *c, int32_t *level_off, int32_t *hub_off,
     const int32_t nf = tail - c->hi;
     if (nf <= 0) {
         c->done = 1;
+        c->bwd_level = c->bwd_last = c->level;  // the reverse pass starts at the deepest level
         return;
     }
     const int32_t nl = c->level + 1;
@@ -1768,14 +1783,6 @@ __global__ __launch_bounds__(BS) void k_ms_bc(int32_t n, const unsigned long lon
 // Per-slot results of one level into source-major arrays (for checks):
 // distance and sigma after the forward pass (values still hold sigma),
 // delta after the reverse pass.
-// Reverse-pass control: start at the deepest level; the last kernel of each
-// reverse level moves it one level up.
-__global__ void k_ms_bwd_init(LevelCtl *c) {
-    c->bwd_level = c->level;
-    c->bwd_last = c->level;
-    c->blocks_done_.v = 0;
-}
-
 __global__ void k_ms_extract(const int32_t *__restrict__ queue,
                              const unsigned long long *__restrict__ qmask,
                              const uint32_t *__restrict__ qvb, int32_t lo, int32_t hi, int32_t lvl,
@@ -1841,7 +1848,7 @@ sp_status batch_ws_create(sp_graph g, int64_t qcap, int32_t width, int32_t engin
         ws.qcap = 0;
         SP_TRY(wg_ws_alloc(g, width, ws));
         SP_TRY(dev_alloc((void **)&ws.slot_src, kSlots * 4));
-        SP_HIP(hipHostMalloc((void **)&ws.staging, kSlots * (4 + 8 + 4), hipHostMallocDefault));
+        SP_HIP(hipHostMalloc((void **)&ws.staging, kSlots * 4, hipHostMallocDefault));
         ws.bytes = batch_ws_bytes(g, 0, width, engine);
         return SP_OK;
     }
@@ -1876,7 +1883,6 @@ sp_status batch_ws_create(sp_graph g, int64_t qcap, int32_t width, int32_t engin
     SP_TRY(dev_alloc((void **)&ws.slot_src, kSlots * 4));
     SP_TRY(dev_alloc((void **)&ws.ctl, sizeof(LevelCtl)));
     SP_HIP(hipHostMalloc((void **)&ws.ctl_host, sizeof(LevelCtl), hipHostMallocDefault));
-    SP_HIP(hipHostMalloc((void **)&ws.staging, kSlots * (4 + 8 + 4), hipHostMallocDefault));
     SP_HIP(hipEventCreate(&ws.ev0));
     SP_HIP(hipEventCreate(&ws.ev1));
     ws.bytes = batch_ws_bytes(g, qcap, width, engine);
@@ -2033,8 +2039,8 @@ static sp_status replay_chunk(BatchWorkspace &ws, CapturedChunk &slot,
 // grow fourfold.  Chunk lengths are even and every chunk starts at an even
 // level, so the captured front-buffer parity holds for all of them.
 template <int BS>
-static sp_status batch_forward(sp_graph g, BatchWorkspace &ws, int32_t n0, unsigned long long active,
-                               const BatchRunOpts &o, hipStream_t s, int32_t *graph_launches) {
+static sp_status batch_forward(sp_graph g, BatchWorkspace &ws, const MsSources &src, int32_t n0,
+                               unsigned long long active, const BatchRunOpts &o, hipStream_t s, int32_t *graph_launches) {
     const int32_t n = g->n;
     const int maxb = device_cu_count() * 8;
     const int grid = level_grid<BS>(n, maxb);
@@ -2043,9 +2049,8 @@ static sp_status batch_forward(sp_graph g, BatchWorkspace &ws, int32_t n0, unsig
     hipLaunchKernelGGL(k_ms_clear, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.seen, ws.nxt,
                        ws.front[0], ws.front[1], n);
     hipLaunchKernelGGL(k_ms_init, dim3(1), dim3(256), 0, s, ws.ctl, (const int32_t *)g->row_ptr,
-                       (const int32_t *)ws.queue, (const unsigned long long *)ws.qmask, ws.qvb, n0,
-                       ws.seen, ws.front[0], ws.val, ws.level_off, ws.hub_list, ws.hub_off,
-                       ws.hub_lvl_chunks, ws.owner, ws.chunk_off, n, (long long)g->nnz, active,
+                       src, ws.queue, ws.qmask, ws.qvb, ws.slot_src, n0, ws.seen, ws.front[0], ws.val,
+                       ws.level_off, ws.hub_list, ws.hub_off, ws.hub_lvl_chunks, ws.owner, ws.chunk_off, n, (long long)g->nnz, active,
                        may_pull ? o.alpha : 0.0, o.beta);  // alpha 0: never switch to bottom-up
     SP_HIP(hipGetLastError());
     const bool capture = o.chunk_levels > 0 && !prof_enabled();  // events need direct launches
@@ -2145,27 +2150,18 @@ static sp_status batch_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *src
     const int32_t n = g->n;
     const unsigned long long active = nslots >= 64 ? ~0ull : ((1ull << nslots) - 1ull);
     // Level 0: distinct source vertices with the mask of their slots.
-    int32_t *h_q = (int32_t *)ws.staging;
-    unsigned long long *h_m = (unsigned long long *)(h_q + kSlots);
-    int32_t *h_src = (int32_t *)(h_m + kSlots);
+    MsSources src{};
     int32_t n0 = 0;
-    for (int32_t i = 0; i < kSlots; ++i) h_src[i] = i < nslots ? srcs[i] : -1;
+    for (int32_t i = 0; i < kSlots; ++i) src.of_slot[i] = i < nslots ? srcs[i] : -1;
     for (int32_t i = 0; i < nslots; ++i) {
         int32_t j = 0;
-        while (j < n0 && h_q[j] != srcs[i]) ++j;
-        if (j == n0) {
-            h_q[n0] = srcs[i];
-            h_m[n0] = 0;
-            ++n0;
-        }
-        h_m[j] |= 1ull << i;
+        while (j < n0 && src.v[j] != srcs[i]) ++j;
+        if (j == n0) src.v[n0++] = srcs[i];
+        src.m[j] |= 1ull << i;
     }
     int32_t graph_launches = 0;
     for (int attempt = 0; attempt < 2; ++attempt) {
-        SP_HIP(hipMemcpyAsync(ws.queue, h_q, n0 * 4, hipMemcpyHostToDevice, s));
-        SP_HIP(hipMemcpyAsync(ws.qmask, h_m, n0 * 8, hipMemcpyHostToDevice, s));
-        SP_HIP(hipMemcpyAsync(ws.slot_src, h_src, kSlots * 4, hipMemcpyHostToDevice, s));
-        SP_TRY(batch_forward<BS>(g, ws, n0, active, o, s, &graph_launches));
+        SP_TRY(batch_forward<BS>(g, ws, src, n0, active, o, s, &graph_launches));
         if (!ws.ctl_host->overflow_.v) break;
         if (attempt == 1) {
             set_error("multi-source queue overflow at capacity %lld", (long long)ws.qcap);
@@ -2193,7 +2189,6 @@ static sp_status batch_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *src
     const int grid_h =
         xcd_grid(pow2_at_least(grid_for((int64_t)std::max(maxh, 1) * kWave, BS, maxb), maxb), maxb);
     const bool hubs = maxh > 0;
-    hipLaunchKernelGGL(k_ms_bwd_init, dim3(1), dim3(1), 0, s, ws.ctl);
     const int32_t steps = levels - 1;  // levels L-1 .. 1
     const bool capture = o.chunk_levels > 0 && !prof_enabled();
     if (steps > 0 && capture) {

@@ -441,7 +441,7 @@ struct BatchWorkspace {
     int64_t in_hub_cap = 0;
     LevelCtl *ctl = nullptr;
     LevelCtl *ctl_host = nullptr;
-    void *staging = nullptr;             // pinned: level-0 entries and slot sources
+    void *staging = nullptr;             // pinned: slot sources (blocks engine)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     size_t bytes = 0;
     int32_t width = 0;                   // slots the value store is sized for
