@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -72,6 +73,7 @@ struct sp_graph_s {
     int32_t *rp_in = nullptr;
     int32_t *ci_in = nullptr;
     bool directed = false;
+    std::atomic<int32_t> wg_symmetric{-1};  // fixed-width rows are symmetric (rows_symmetric): 1, 0, -1 not looked at yet
     int32_t max_degree = 0;
     int32_t n_hubs = 0;          // vertices of degree > kHubDeg
     int64_t hub_chunks = 0;      // sum over hubs of ceil(degree / kHubChunk)
@@ -376,8 +378,8 @@ struct SlotTable {
 // Blocks engine, per (slot, vertex): the BFS level (-1 unreached) and a
 // value -- sigma after the forward pass; with fixed-width rows, rho =
 // (1 + delta) / sigma once the reverse pass has finished the vertex.
-// (Undirected graphs with fixed-width rows lay positions, links and path
-// counts out over the same bytes.)
+// (Symmetric fixed-width rows lay positions, links and path counts out over
+// the same bytes.)
 struct alignas(16) WgRec {
     int32_t dist;
     int32_t pad;

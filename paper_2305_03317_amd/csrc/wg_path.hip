@@ -55,9 +55,9 @@
 // -> claim, a path-count step queue entry -> row -> the neighbours' records,
 // and a reverse step queue entry -> row (and the vertex's own record) -> the
 // neighbours' records; the record of a neighbour that turns out not to be a
-// parent (child) is loaded and dropped.  That is the directed kernel
-// (k_wg_bc_ell); an undirected graph takes k_wg_bc_mesh, whose levels stay in
-// LDS.
+// parent (child) is loaded and dropped.  That is k_wg_bc_ell, for directed
+// graphs and for rows that are not symmetric; symmetric rows take k_wg_bc_mesh,
+// whose levels stay in LDS.
 #include "common.h"
 #include "devutil.h"
 
@@ -113,6 +113,32 @@ __global__ void k_wg_ell(const int32_t *__restrict__ rp, const int32_t *__restri
 #pragma unroll
         for (int k = 0; k < W; ++k) ell[v * W + k] = k < d ? ci[b + k] : -1;
     }
+}
+
+// Whether the rows are symmetric: every u occurs in v's row as often as v in
+// u's; *not_sym is set where they are not.  k_wg_bc_mesh needs it, and uploads do
+// not check it.
+template <int W>
+__global__ void k_wg_symmetric(const int32_t *__restrict__ ell, int32_t n, int32_t *not_sym) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    bool bad = false;
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        int32_t x[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) x[k] = ell[v * W + k];
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            if (x[k] < 0) continue;
+            int32_t here = 0, there = 0;
+#pragma unroll
+            for (int q = 0; q < W; ++q) {
+                here += x[q] == x[k];
+                there += ell[(int64_t)x[k] * W + q] == (int32_t)v;
+            }
+            bad |= here != there;
+        }
+    }
+    if (__ballot(bad) && lane_id() == 0) atomicOr(not_sym, 1);
 }
 
 // The loads below are issued unconditionally, from a valid address (row 0,
@@ -328,7 +354,7 @@ __global__ __launch_bounds__(BS) void k_wg_bc_ell(const int32_t *__restrict__ el
     }
 }
 
-// The pass over fixed-width rows of an undirected graph.  Everything a level
+// The pass over symmetric fixed-width rows (k_wg_symmetric).  Everything a level
 // needs of the one before stays in LDS: a frontier entry holds its vertex, its
 // path count and its row, with the parent that claimed it marked there; a
 // finished entry of the reverse sweep its rho, by position in the level.  In
@@ -338,7 +364,8 @@ __global__ __launch_bounds__(BS) void k_wg_bc_ell(const int32_t *__restrict__ el
 //
 // Forward, a level is one round trip: the rows of an entry's neighbours but the
 // parent and, in the same breath, the positions of those that may be reached
-// already.  A neighbour of a vertex lies at most a level away, so these are the
+// already.  A neighbour of a vertex lies at most a level away (the rows being
+// symmetric: a vertex claimed again would run the positions past n), so these are the
 // ones whose hash is in the filter of this level or the one before (s_seen), one
 // in ten on a road grid.  An unreached one is claimed in an LDS hash table (by
 // compare-and-swap on pos, to -2, if its place there is crowded or the level is
@@ -542,12 +569,15 @@ __global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ e
                     shared |= (uint32_t)(u >= 0 && (found == -2 || found >= hi)) << q;
                 }
             }
-            const int32_t cnt = __popc(claimed);
+            int32_t cnt = __popc(claimed);
             const int32_t incl = wave_incl_scan(cnt);
             const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
             int32_t at = 0;
             if (lane == 0 && total) at = atomicAdd(&s_tail, total);  // LDS
             at = __builtin_amdgcn_readfirstlane(at) + incl - cnt;
+            if (at + cnt > n) {  // no position is given out past the arrays (symmetric rows never ask for one)
+                while (cnt && at + cnt > n) claimed &= ~(0x80000000u >> __clz((int)claimed)), --cnt;
+            }
             if (has) {
                 const int32_t first = at - hi;
                 link[i] = cnt && first > 0xffff ? kLinkSlow
@@ -586,7 +616,7 @@ __global__ __launch_bounds__(BS) void k_wg_bc_mesh(const int32_t *__restrict__ e
             process(e, b + lane);
         }
         __syncthreads();
-        const int32_t tail = s_tail;
+        const int32_t tail = min(s_tail, n);
         if (tid == 0) loff[level + 2] = tail;
         if (tail == hi) break;
         plo = lo;
@@ -1024,6 +1054,27 @@ void wg_ws_free(BatchWorkspace &ws) {
     ws.wg_res = ws.wg_res_host = nullptr;
 }
 
+// Whether g's rows are symmetric, looked at on the graph's first pass (one
+// kernel over ws.wg_ell and a wait: 64 bytes read per entry at most).
+static sp_status rows_symmetric(sp_graph g, BatchWorkspace &ws, hipStream_t s, bool *out) {
+    int32_t known = g->wg_symmetric.load();
+    if (known < 0) {
+        int32_t *not_sym = ws.wg_loff;  // free until the pass
+        SP_TRY(launch_fill_i32(not_sym, 1, 0, s));
+        auto look = ws.wg_ell_w == 4 ? k_wg_symmetric<4> : k_wg_symmetric<8>;
+        hipLaunchKernelGGL(look, dim3(grid_for(g->n, 256, 4096)), dim3(256), 0, s, (const int32_t *)ws.wg_ell, g->n,
+                           not_sym);
+        SP_HIP(hipGetLastError());
+        int32_t bad = 0;
+        SP_HIP(hipMemcpyAsync(&bad, not_sym, sizeof(bad), hipMemcpyDeviceToHost, s));
+        SP_HIP(hipStreamSynchronize(s));
+        known = bad == 0;
+        g->wg_symmetric.store(known);
+    }
+    *out = known == 1;
+    return SP_OK;
+}
+
 template <int BS>
 static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, int32_t nslots,
                            double *const *bc_of_slot, hipStream_t s, BatchResult *res,
@@ -1034,17 +1085,6 @@ static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, 
     for (int32_t i = 0; i < kSlots; ++i) h_src[i] = i < nslots ? srcs[i] : -1;
     SP_HIP(hipMemcpyAsync(ws.slot_src, h_src, kSlots * 4, hipMemcpyHostToDevice, s));
     const int ew = ws.wg_ell_w;
-    // undirected fixed-width rows: k_wg_bc_mesh, whose positions, links and values share the records' memory
-    const bool mesh = ew != 0 && !g->directed;
-    const int64_t cells = (int64_t)ws.width * n;
-    double *sig = (double *)ws.wg_rec;
-    int32_t *pos = (int32_t *)(sig + cells);
-    uint32_t *link = (uint32_t *)(pos + cells);
-    if (mesh)  // (in pairs: of an odd count the entry behind, a link or an unused position, is cleared too)
-        hipLaunchKernelGGL(k_wg_fill_pos, dim3(grid_for((count + 1) / 2, 256, 4096)), dim3(256), 0, s, (int2 *)pos,
-                           (count + 1) / 2);
-    else
-        hipLaunchKernelGGL(k_wg_fill, dim3(grid_for(count, 256, 4096)), dim3(256), 0, s, ws.wg_rec, count);
     if (ew && !ws.wg_ell_built) {
         auto build = ew == 4 ? k_wg_ell<4> : k_wg_ell<8>;
         hipLaunchKernelGGL(build, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, (const int32_t *)g->row_ptr,
@@ -1055,6 +1095,18 @@ static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, 
         SP_HIP(hipGetLastError());
         ws.wg_ell_built = true;
     }
+    // symmetric fixed-width rows: k_wg_bc_mesh, whose positions, links and values share the records' memory
+    bool mesh = ew != 0 && !g->directed;
+    if (mesh) SP_TRY(rows_symmetric(g, ws, s, &mesh));
+    const int64_t cells = (int64_t)ws.width * n;
+    double *sig = (double *)ws.wg_rec;
+    int32_t *pos = (int32_t *)(sig + cells);
+    uint32_t *link = (uint32_t *)(pos + cells);
+    if (mesh)  // (in pairs: of an odd count the entry behind, a link or an unused position, is cleared too)
+        hipLaunchKernelGGL(k_wg_fill_pos, dim3(grid_for((count + 1) / 2, 256, 4096)), dim3(256), 0, s, (int2 *)pos,
+                           (count + 1) / 2);
+    else
+        hipLaunchKernelGGL(k_wg_fill, dim3(grid_for(count, 256, 4096)), dim3(256), 0, s, ws.wg_rec, count);
     {
         ProfScope ps(P_WG_BC, s);
         if (mesh) {
@@ -1064,8 +1116,9 @@ static sp_status wg_run_bs(sp_graph g, BatchWorkspace &ws, const int32_t *srcs, 
                                ws.wg_queue, ws.wg_loff, ws.wg_res, prof_counters(P_WG_BC));
         } else if (ew) {
             auto pass = ew == 4 ? k_wg_bc_ell<BS, 4> : k_wg_bc_ell<BS, 8>;
-            hipLaunchKernelGGL(pass, dim3(nslots), dim3(BS), 0, s, (const int32_t *)ws.wg_ell,
-                               (const int32_t *)ws.wg_ell_in, (const int32_t *)ws.slot_src, n, ws.wg_rec, ws.wg_delta,
+            const int32_t *ell_in = g->directed ? ws.wg_ell_in : ws.wg_ell;
+            hipLaunchKernelGGL(pass, dim3(nslots), dim3(BS), 0, s, (const int32_t *)ws.wg_ell, ell_in,
+                               (const int32_t *)ws.slot_src, n, ws.wg_rec, ws.wg_delta,
                                ex ? ex->sigma : nullptr, ws.wg_queue, ws.wg_loff, ws.wg_res, prof_counters(P_WG_BC));
         } else
             hipLaunchKernelGGL(k_wg_bc<BS>, dim3(nslots), dim3(BS), 0, s, (const int32_t *)g->row_ptr,
