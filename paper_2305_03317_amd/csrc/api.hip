@@ -443,6 +443,7 @@ static void free_weights(sp_graph g) {
     dev_free(g->sssp_rp);
     g->sssp_rp = nullptr;
     g->max_weight = 0;
+    ++g->weight_gen;
     g->bytes -= g->weight_bytes;
     g->weight_bytes = 0;
 }
@@ -510,6 +511,7 @@ sp_status build_static_hubs(sp_graph g, hipStream_t st) {
     g->hub_static = hub_dev;
     g->owner_static = owner_dev;
     g->hub_static_ranked = ranked;
+    ++g->weight_gen;
     return SP_OK;
 }
 

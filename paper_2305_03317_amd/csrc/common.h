@@ -132,6 +132,9 @@ struct sp_graph_s {
     int64_t tc_m = 0;
     int32_t max_weight = 0;
     size_t weight_bytes = 0;
+    // Counts what replaced any array above that the rounds read: captured rounds
+    // are keyed by it, since a later array may come to lie at an earlier one's address.
+    long long weight_gen = 0;
     std::vector<sp::SsspWorkspace *> sssp_pool;
     std::vector<sp::PrWorkspace *> pr_pool;
 };

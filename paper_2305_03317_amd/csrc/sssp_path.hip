@@ -1036,8 +1036,7 @@ static sp_status sssp_run_bs(sp_graph g, SsspWorkspace &ws, int32_t src, int32_t
         if (capture) {
             const std::array<long long, 12> key = {
                 BS * 16 + HOPS, grid, hubs, may_pull, may_push, chunk, (long long)(intptr_t)ws.dist,
-                (long long)(intptr_t)g->adjw, (long long)(intptr_t)g->hub_static,
-                (long long)(intptr_t)g->sssp_ell, (long long)(intptr_t)ws.ctl, g->n_hubs};
+                (long long)(intptr_t)ws.ctl, g->weight_gen, 0, 0, 0};
             SP_TRY(replay_captured(&ws.cap_stream, deep ? ws.rounds_long : ws.rounds_short, key,
                                    [&](hipStream_t cs) {
                                        enqueue_rounds<BS, HOPS>(g, ws, chunk, grid, hubs, may_pull, may_push, cs);
