@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <new>
+#include <utility>
 
 #include "common.h"
 #include "devutil.h"
@@ -338,22 +339,17 @@ __global__ void k_src_export(int32_t n, const int32_t *__restrict__ dist, const 
 // ---------------------------------------------------------------------------
 static thread_local sp_sssp_stats g_sssp_stats;
 
-// Pack each CSR entry with its weight; count weights outside [0, INT32_MAX - 1]
-// and track the largest.
+// Pack each CSR entry with its weight; count weights outside [0, INT32_MAX - 1].
 __global__ void k_pack_weights(const int32_t *__restrict__ ci, const int32_t *__restrict__ w,
-                               int64_t nnz, int2 *adjw, unsigned int *bad, int *maxw) {
+                               int64_t nnz, int2 *adjw, unsigned int *bad) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     unsigned int b = 0;
-    int m = 0;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += stride) {
         const int32_t x = w[e];
         if (x < 0 || x == INT32_MAX) ++b;
-        m = max(m, x);
         adjw[e] = make_int2(ci[e], x);
     }
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
     if (b) atomicAdd(bad, b);
-    if (lane_id() == 0 && m > 0) atomicMax(maxw, m);
 }
 
 // Host check (SP_VALIDATE): the entry of v in row u and of u in row v carry
@@ -437,54 +433,34 @@ static void release_pr_ws(sp_graph g, PrWorkspace *ws) {
 
 static void free_weights(sp_graph g) {
     dev_free(g->adjw);
-    g->adjw = nullptr;
     dev_free(g->sssp_ell);
-    g->sssp_ell = nullptr;
     dev_free(g->sssp_rp);
-    g->sssp_rp = nullptr;
-    g->max_weight = 0;
-    ++g->weight_gen;
-    g->bytes -= g->weight_bytes;
-    g->weight_bytes = 0;
+    dev_free(g->hub_static);
+    dev_free(g->owner_static);
+    g->adjw = g->sssp_ell = nullptr;
+    g->sssp_rp = g->owner_static = nullptr;
+    g->hub_static = nullptr;
 }
 
-// Upload a hub list and its chunk owner map; on success the device copies go
-// to *hub_out / *owner_out and their bytes are added to the graph's size.
-static sp_status upload_hub_layout(sp_graph g, const std::vector<HubEntry> &hubs,
-                                   const std::vector<int32_t> &owners, hipStream_t st,
-                                   HubEntry **hub_out, int32_t **owner_out) {
-    HubEntry *hub_dev = nullptr;
-    int32_t *owner_dev = nullptr;
-    const size_t hb = sizeof(HubEntry) * std::max<size_t>(hubs.size(), 1);
-    const size_t ob = sizeof(int32_t) * std::max<size_t>(owners.size(), 1);
-    sp_status rc = dev_alloc((void **)&hub_dev, hb);
-    if (rc == SP_OK) rc = dev_alloc((void **)&owner_dev, ob);
-    hipError_t e = hipSuccess;
-    if (rc == SP_OK && !hubs.empty())
-        e = hipMemcpyAsync(hub_dev, hubs.data(), hubs.size() * sizeof(HubEntry), hipMemcpyHostToDevice, st);
-    if (rc == SP_OK && e == hipSuccess && !owners.empty())
-        e = hipMemcpyAsync(owner_dev, owners.data(), owners.size() * sizeof(int32_t),
-                           hipMemcpyHostToDevice, st);
-    if (rc == SP_OK && e == hipSuccess) e = hipStreamSynchronize(st);
-    if (rc != SP_OK || e != hipSuccess) {
-        dev_free(hub_dev);
-        dev_free(owner_dev);
-        if (e != hipSuccess) set_error("hub list upload failed: %s", hipGetErrorString(e));
-        return rc != SP_OK ? rc : SP_ERR_DEVICE;
+// What sp_graph_set_weights builds before it replaces the graph's; freed unless taken.
+struct NewWeights {
+    int2 *adjw = nullptr, *ell = nullptr;
+    int32_t *rp = nullptr, *upload = nullptr, *owner = nullptr;
+    HubEntry *hubs = nullptr;
+    size_t hub_bytes = 0;
+    ~NewWeights() {
+        dev_free(adjw);
+        dev_free(ell);
+        dev_free(rp);
+        dev_free(upload);
+        dev_free(owner);
+        dev_free(hubs);
     }
-    *hub_out = hub_dev;
-    *owner_out = owner_dev;
-    g->bytes += hb + ob;
-    return SP_OK;
-}
+};
 
-// Every hub of the weighted rows (ranked or not, g->sssp_rp) with its chunk
-// range, in row order, and the hub of every chunk; kept while the numbering
-// stays.  No sp_sssp call is running on the graph (sp_graph_set_weights).
-sp_status build_static_hubs(sp_graph g, hipStream_t st) {
-    std::lock_guard<std::mutex> lk(g->mu);
-    const bool ranked = g->sssp_rp != nullptr;
-    if (g->hub_static && g->hub_static_ranked == ranked) return SP_OK;
+// Every hub of the weighted rows with its chunk range, in row order, and the
+// hub of every chunk.  rp: the rows' offsets by rank; null: the graph's rows.
+static sp_status build_static_hubs(sp_graph g, const int32_t *rp, NewWeights &nw, hipStream_t st) {
     std::vector<HubEntry> hubs;
     std::vector<int32_t> owners;
     auto add = [&](int32_t v, int32_t deg) {
@@ -493,25 +469,21 @@ sp_status build_static_hubs(sp_graph g, hipStream_t st) {
         hubs.push_back(HubEntry{v, 0, (int32_t)owners.size(), nch});
         owners.insert(owners.end(), (size_t)nch, (int32_t)hubs.size() - 1);
     };
-    if (ranked) {  // hubs are among the first ranks
+    if (rp) {  // hubs are among the first ranks
         std::vector<int32_t> off((size_t)rank_count(g, kRankExact) + 1);
-        SP_HIP(hipMemcpyAsync(off.data(), g->sssp_rp, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, st));
+        SP_HIP(hipMemcpyAsync(off.data(), rp, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, st));
         SP_HIP(hipStreamSynchronize(st));
         for (size_t r = 0; r + 1 < off.size(); ++r) add((int32_t)r, off[r + 1] - off[r]);
     } else {
         for (int32_t v = 0; v < g->n; ++v) add(v, g->host_deg[v]);
     }
-    HubEntry *hub_dev = nullptr;
-    int32_t *owner_dev = nullptr;
-    const size_t before = g->bytes;
-    SP_TRY(upload_hub_layout(g, hubs, owners, st, &hub_dev, &owner_dev));
-    if (g->hub_static) g->bytes = before;  // replaces one of the same size
-    dev_free(g->hub_static);
-    dev_free(g->owner_static);
-    g->hub_static = hub_dev;
-    g->owner_static = owner_dev;
-    g->hub_static_ranked = ranked;
-    ++g->weight_gen;
+    const size_t hb = sizeof(HubEntry) * hubs.size(), ob = sizeof(int32_t) * owners.size();
+    SP_TRY(dev_alloc((void **)&nw.hubs, hb));
+    SP_TRY(dev_alloc((void **)&nw.owner, ob));
+    SP_HIP(hipMemcpyAsync(nw.hubs, hubs.data(), hb, hipMemcpyHostToDevice, st));
+    SP_HIP(hipMemcpyAsync(nw.owner, owners.data(), ob, hipMemcpyHostToDevice, st));
+    SP_HIP(hipStreamSynchronize(st));
+    nw.hub_bytes = hb + ob;
     return SP_OK;
 }
 
@@ -1130,73 +1102,67 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
         SP_HIP(hipStreamSynchronize(st));
         if (!weights_symmetric(g->n, hr.data(), hc.data(), w)) return SP_ERR_INVALID_ARGUMENT;
     }
-    int2 *adjw = nullptr;
-    int32_t *wdev = nullptr, *wrp = nullptr;
-    unsigned int *bad = nullptr;  // bad[0]: count, bad[1]: largest weight (as int)
-    auto cleanup = [&](sp_status code) {
-        dev_free(adjw);
-        dev_free(wdev);
-        dev_free(wrp);
-        dev_free(bad);
-        return code;
-    };
+    std::lock_guard<std::mutex> one(g->weights_mu);
+    NewWeights nw;
     const size_t adj_bytes = sizeof(int2) * (size_t)std::max<int64_t>(nnz, 1);
-    sp_status rc = dev_alloc((void **)&adjw, adj_bytes);
-    if (rc == SP_OK) rc = dev_alloc((void **)&bad, 8);
-    if (rc == SP_OK && !on_dev && nnz) rc = dev_alloc((void **)&wdev, (size_t)nnz * 4);
-    if (rc != SP_OK) return cleanup(rc);
-    unsigned int h_bad[2] = {0, 0};
-    hipError_t e = hipMemsetAsync(bad, 0, 8, st);
-    if (e == hipSuccess && wdev) e = hipMemcpyAsync(wdev, weights, (size_t)nnz * 4, hipMemcpyHostToDevice, st);
-    const int32_t *w_in = wdev ? wdev : weights;
-    if (e == hipSuccess && nnz) {
-        rc = sssp_pack_ranked(g, w_in, adjw, bad, &wrp, st);
-        if (rc < 0) return cleanup(rc);
-    }
-    if (e == hipSuccess && nnz && !wrp) {
+    SP_TRY(dev_alloc((void **)&nw.adjw, adj_bytes + sizeof(unsigned int)));
+    unsigned int *bad = (unsigned int *)((char *)nw.adjw + adj_bytes);  // weights out of range
+    if (!on_dev && nnz) SP_TRY(dev_alloc((void **)&nw.upload, (size_t)nnz * 4));
+    unsigned int h_bad = 0;
+    SP_HIP(hipMemsetAsync(bad, 0, sizeof(h_bad), st));
+    if (nw.upload) SP_HIP(hipMemcpyAsync(nw.upload, weights, (size_t)nnz * 4, hipMemcpyHostToDevice, st));
+    const int32_t *w_in = nw.upload ? nw.upload : weights;
+    bool ranked = false;
+    if (nnz) SP_TRY(sssp_pack_ranked(g, w_in, nw.adjw, bad, &nw.rp, &ranked, st));
+    if (nnz && !ranked) {
         hipLaunchKernelGGL(k_pack_weights, dim3(grid_for(nnz, 256, 4096)), dim3(256), 0, st,
-                           (const int32_t *)g->col_idx, w_in, nnz,
-                           adjw, bad, (int *)(bad + 1));
-        e = hipGetLastError();
+                           (const int32_t *)g->col_idx, w_in, nnz, nw.adjw, bad);
+        SP_HIP(hipGetLastError());
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(h_bad, bad, 8, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        set_error("weight upload failed: %s", hipGetErrorString(e));
-        return cleanup(SP_ERR_DEVICE);
+    // Rows at a fixed width: into new memory now, into the earlier ones' once nothing can fail.
+    const int32_t width = sssp_mesh_width(g);
+    if (width && !g->sssp_ell &&
+        dev_alloc((void **)&nw.ell, sizeof(int2) * (size_t)g->n * (size_t)width) != SP_OK)
+        clear_error();  // the general kernel serves
+    if (nw.ell) launch_mesh_rows(g, nw.adjw, width, nw.ell, st);
+    SP_HIP(hipGetLastError());
+    SP_HIP(hipMemcpyAsync(&h_bad, bad, sizeof(h_bad), hipMemcpyDeviceToHost, st));
+    SP_HIP(hipStreamSynchronize(st));
+    if (h_bad) {
+        set_error("%u weights lie outside [0, 2^31 - 2]", h_bad);
+        return SP_ERR_INVALID_ARGUMENT;
     }
-    if (h_bad[0]) {
-        set_error("%u weights lie outside [0, 2^31 - 2]", h_bad[0]);
-        return cleanup(SP_ERR_INVALID_ARGUMENT);
+    const bool new_hubs = g->n_hubs > 0 && (!g->hub_static || g->hub_static_ranked != ranked);
+    if (new_hubs) SP_TRY(build_static_hubs(g, !ranked ? nullptr : nw.rp ? nw.rp : g->sssp_rp, nw, st));
+    if (g->sssp_ell) {
+        launch_mesh_rows(g, nw.adjw, width, g->sssp_ell, st);
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+            std::lock_guard<std::mutex> lk(g->mu);  // the earlier weights do without
+            dev_free(std::exchange(g->sssp_ell, nullptr));
+            ++g->weight_gen;
+            set_error("fixed-width weighted rows could not be built");
+            return SP_ERR_DEVICE;
+        }
     }
-    dev_free(wdev);
-    dev_free(bad);
-    wdev = nullptr;
-    bad = nullptr;
-    int32_t width = 0;
-    int2 *ell = sssp_mesh_rows(g, adjw, &width, st);
-    if (ell && (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess)) {
-        dev_free(ell);
-        set_error("fixed-width weighted rows could not be built");
-        return cleanup(SP_ERR_DEVICE);
+    // Everything is there: the earlier weights go only now.
+    std::lock_guard<std::mutex> lk(g->mu);
+    std::swap(g->adjw, nw.adjw);
+    if (nw.ell) std::swap(g->sssp_ell, nw.ell);
+    g->sssp_ell_w = width;
+    if (nw.rp || !ranked) std::swap(g->sssp_rp, nw.rp);  // (ranked and null: the offsets stay as they are)
+    if (new_hubs) {
+        std::swap(g->hub_static, nw.hubs);
+        std::swap(g->owner_static, nw.owner);
+        g->hub_static_ranked = ranked;
+        g->bytes += nw.hub_bytes - g->hub_bytes;
+        g->hub_bytes = nw.hub_bytes;
     }
-    {
-        std::lock_guard<std::mutex> lk(g->mu);
-        free_weights(g);
-        g->adjw = adjw;
-        g->sssp_ell = ell;
-        g->sssp_ell_w = width;
-        g->sssp_rp = wrp;
-        g->max_weight = (int32_t)h_bad[1];
-        g->weight_bytes = adj_bytes + (wrp ? sizeof(int32_t) * ((size_t)g->n + 1) : 0) + (ell ? sizeof(int2) * (size_t)g->n * (size_t)width : 0);
-        g->bytes += g->weight_bytes;
-    }
-    const sp_status hs = build_static_hubs(g, st);
-    if (hs < 0) {  // without them the weights cannot be used
-        std::lock_guard<std::mutex> lk(g->mu);
-        free_weights(g);
-    }
-    return hs;
+    const size_t bytes = adj_bytes + (ranked ? sizeof(int32_t) * ((size_t)g->n + 1) : 0) +
+                         (g->sssp_ell ? sizeof(int2) * (size_t)g->n * (size_t)width : 0);
+    g->bytes += bytes - g->weight_bytes;
+    g->weight_bytes = bytes;
+    ++g->weight_gen;
+    return SP_OK;
     SP_GUARD_END
 }
 

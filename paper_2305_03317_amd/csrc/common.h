@@ -97,13 +97,13 @@ struct sp_graph_s {
     // (rank_new) and sssp_rp holds the rows' offsets; else row_ptr does.
     int32_t *sssp_rp = nullptr;      // device, n + 1
     int2 *adjw = nullptr;            // device, nnz (>= 1 element allocated)
-    // The same rows at a fixed width, where all hold at most 8 entries (sssp_mesh_rows); else null.
+    // The same rows at a fixed width, where all hold at most 8 entries (sssp_mesh_width); else null.
     int2 *sssp_ell = nullptr;        // device, n * sssp_ell_w
     int32_t sssp_ell_w = 0;
-    // Every hub with its chunk range, in vertex order, and the hub of each
-    // chunk; built on first use by the whole-graph kernels (ensure_static_hubs).
-    sp::HubEntry *hub_static = nullptr;  // device, n_hubs (>= 1)
-    int32_t *owner_static = nullptr;     // device, hub_chunks (>= 1)
+    // Every hub of the weighted rows with its chunk range, in row order, and the
+    // hub of each chunk, for pull rounds; null without hubs.  Built with the weights.
+    sp::HubEntry *hub_static = nullptr;  // device, n_hubs
+    int32_t *owner_static = nullptr;     // device, hub_chunks
     bool hub_static_ranked = false;      // hub_static names ranks
     // PageRank's rows in the order and numbering it gathers them (ensure_pr_plan).
     sp::PrPlan *pr_plan = nullptr;   // host
@@ -130,8 +130,8 @@ struct sp_graph_s {
     int32_t tc_units_lo = 0;         // units of vertices below kTcLow, listed first
     int32_t tc_units_n = 0;
     int64_t tc_m = 0;
-    int32_t max_weight = 0;
-    size_t weight_bytes = 0;
+    size_t weight_bytes = 0, hub_bytes = 0;
+    std::mutex weights_mu;           // one replacement of the weights at a time
     // Counts what replaced any array above that the rounds read: captured rounds
     // are keyed by it, since a later array may come to lie at an earlier one's address.
     long long weight_gen = 0;
@@ -553,9 +553,10 @@ struct SsspWorkspace {
 };
 sp_status sssp_ws_create(sp_graph g, SsspWorkspace &ws);
 void sssp_ws_destroy(SsspWorkspace &ws);
-// Fixed-width rows (4 or 8) of a weighted graph whose rows all hold at most 8
-// entries, enqueued on s; null where they do not, or where memory is short.
-int2 *sssp_mesh_rows(sp_graph g, const int2 *adjw, int32_t *width, hipStream_t s);
+// Width of the fixed-width weighted rows (4 or 8) of a graph whose rows all
+// hold at most 8 entries, else 0; fills them from the packed rows.
+int32_t sssp_mesh_width(sp_graph g);
+void launch_mesh_rows(sp_graph g, const int2 *adjw, int32_t width, int2 *ell, hipStream_t s);
 
 struct SsspOpts {
     int forced = -1;       // -1 auto, else SSSP_PUSH / SSSP_PULL
@@ -671,14 +672,13 @@ sp_status undirected_only(const char *what);
 // is within its documented range.
 sp_status check_batch_cfg(const sp_batch_config *cfg);
 
-// Every hub of the weighted rows, for pull rounds: built when weights are set.
-sp_status build_static_hubs(sp_graph g, hipStream_t s);
 // Packs the rows numbered by rank with their weights (each checked to lie in
-// [0, INT32_MAX - 1]: bad[0] counts the others, bad[1] is the largest).  On a
-// graph that renumbering does not suit, or without the memory for it, *out_rp
-// stays null and nothing is enqueued.
+// [0, INT32_MAX - 1]: *bad counts the others).  *out_rp
+// receives the rows' offsets unless g->sssp_rp holds them already.  On a graph
+// that renumbering does not suit, or without the memory for it, *ranked stays
+// false and nothing is enqueued.
 sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, int32_t **out_rp,
-                           hipStream_t s);
+                           bool *ranked, hipStream_t s);
 // Builds g->pr_plan once (thread-safe).
 sp_status ensure_pr_plan(sp_graph g, hipStream_t s);
 

@@ -32,6 +32,8 @@
 // Every round only lowers distances toward the same least fixed point, so
 // the result does not depend on scheduling: it is the shortest-path distance
 // (INT32_MAX where unreached), bit for bit.
+#include <utility>
+
 #include "capture.h"
 #include "common.h"
 #include "devutil.h"
@@ -837,30 +839,28 @@ __global__ void k_sssp_export(SsspCtl *c, const int32_t *__restrict__ dist,
 // Host side
 // ---------------------------------------------------------------------------
 // Rows [first, last) of the rank numbering, PER lanes each: {rank of the
-// neighbour, weight}; counts weights outside [0, INT32_MAX - 1] and tracks the largest.
+// neighbour, weight}; counts weights outside [0, INT32_MAX - 1].  The ranks are
+// those of the earlier weights' rows, where there are some (`before`).
 template <int PER>
 __global__ __launch_bounds__(256) void k_sssp_pack_ranked(const int32_t *__restrict__ rp,
                                                           const int32_t *__restrict__ ci,
                                                           const int32_t *__restrict__ w,
                                                           const int32_t *__restrict__ rank_new,
                                                           const int32_t *__restrict__ rank_old,
-                                                          const int32_t *__restrict__ wrp, int32_t first,
+                                                          const int32_t *__restrict__ wrp,
+                                                          const int2 *__restrict__ before, int32_t first,
                                                           int32_t last, int2 *adjw, unsigned int *bad) {
     unsigned int b = 0;
-    int m = 0;
     const int64_t stride = (int64_t)gridDim.x * (256 / PER);
     for (int64_t r = first + (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER; r < last; r += stride) {
         const int32_t at = rp[rank_old[r]], to = wrp[r], len = wrp[r + 1] - to;
         for (int32_t k = threadIdx.x % PER; k < len; k += PER) {
             const int32_t x = w[at + k];
             if (x < 0 || x == kInf) ++b;
-            m = max(m, x);
-            adjw[to + k] = make_int2(rank_new[ci[at + k]], x);
+            adjw[to + k] = make_int2(before ? before[to + k].x : rank_new[ci[at + k]], x);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
     if (b) atomicAdd(bad, b);
-    if (lane_id() == 0 && m > 0) atomicMax((int *)(bad + 1), m);
 }
 
 // Pushes on a large skewed graph are bound by their reads of the neighbours'
@@ -869,66 +869,64 @@ __global__ __launch_bounds__(256) void k_sssp_pack_ranked(const int32_t *__restr
 // the entries on rmat-22) fit an XCD's 4 MB L2.  rmat-22:
 // 6.2 -> 5.1 ms per source.
 sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, int32_t **out_rp,
-                           hipStream_t s) {
-    *out_rp = nullptr;
+                           bool *ranked, hipStream_t s) {
     const int32_t n = g->n;
     if (n <= kRenumberFrom || g->max_degree <= 8) return SP_OK;
-    int32_t *wrp = nullptr, *tiles = nullptr;
-    sp_status st;
     {
         std::lock_guard<std::mutex> lk(g->mu);
-        st = ensure_rank_locked(g, s);
-        if (st == SP_OK && !rank_skewed(g)) return SP_OK;
-    }
-    if (st == SP_OK) st = dev_alloc((void **)&wrp, sizeof(int32_t) * ((size_t)n + 1));
-    if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(n));
-    if (st != SP_OK) {
-        dev_free(wrp);
+        const sp_status st = ensure_rank_locked(g, s);
         if (st == SP_ERR_OUT_OF_MEMORY) {
             clear_error();
             return SP_OK;
         }
-        return st;
+        if (st != SP_OK) return st;
+        if (!rank_skewed(g)) return SP_OK;
     }
-    launch_row_offsets(g->row_ptr, nullptr, g->rank_old, n, wrp, tiles, s);
+    const int32_t *wrp = g->sssp_rp;
+    if (!wrp) {  // the offsets depend on the rows alone: the first weights leave them for later ones
+        int32_t *tiles = nullptr;
+        sp_status st = dev_alloc((void **)out_rp, sizeof(int32_t) * ((size_t)n + 1));
+        if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(n));
+        if (st != SP_OK) {
+            dev_free(std::exchange(*out_rp, nullptr));
+            if (st != SP_ERR_OUT_OF_MEMORY) return st;
+            clear_error();
+            return SP_OK;
+        }
+        launch_row_offsets(g->row_ptr, nullptr, g->rank_old, n, *out_rp, tiles, s);
+        const hipError_t e = hipStreamSynchronize(s);  // the scan's scratch is done with
+        dev_free(tiles);
+        if (e != hipSuccess) {
+            set_error("numbering the weighted rows failed: %s", hipGetErrorString(e));
+            return SP_ERR_DEVICE;
+        }
+        wrp = *out_rp;
+    }
+    const int2 *before = g->sssp_rp ? g->adjw : nullptr;
     const int32_t longer = rank_count(g, kRankExact);
     const int maxb = device_cu_count() * 8;
     if (longer > 0)
         hipLaunchKernelGGL(k_sssp_pack_ranked<256>, dim3(std::min(longer, maxb)), dim3(256), 0, s,
                            (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
-                           (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, (const int32_t *)wrp, 0, longer,
-                           adjw, bad);
+                           (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, wrp, before, 0, longer, adjw,
+                           bad);
     hipLaunchKernelGGL(k_sssp_pack_ranked<16>, dim3(grid_for((int64_t)n - longer, 16, maxb)), dim3(256), 0, s,
                        (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
-                       (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, (const int32_t *)wrp, longer, n,
-                       adjw, bad);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(s);  // the scan's scratch is done with
-    dev_free(tiles);
-    if (e != hipSuccess) {
-        dev_free(wrp);
-        set_error("numbering the weighted rows failed: %s", hipGetErrorString(e));
-        return SP_ERR_DEVICE;
-    }
-    *out_rp = wrp;
+                       (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, wrp, before, longer, n, adjw, bad);
+    SP_HIP(hipGetLastError());
+    *ranked = true;
     return SP_OK;
 }
 
 // Offsets of the rows of g->adjw.
 static const int32_t *weighted_rows(sp_graph g) { return g->sssp_rp ? g->sssp_rp : g->row_ptr; }
 
-int2 *sssp_mesh_rows(sp_graph g, const int2 *adjw, int32_t *width, hipStream_t s) {
-    *width = g->max_degree <= 4 ? 4 : 8;
-    int2 *ell = nullptr;
-    if (g->max_degree > 8 || g->n == 0) return nullptr;
-    if (dev_alloc((void **)&ell, sizeof(int2) * (size_t)g->n * (size_t)*width) != SP_OK) {
-        clear_error();  // the general kernel serves
-        return nullptr;
-    }
-    auto fill = *width == 4 ? k_sssp_mesh_rows<4> : k_sssp_mesh_rows<8>;
-    hipLaunchKernelGGL(fill, dim3(grid_for((int64_t)g->n * *width, 256, 8192)), dim3(256), 0, s,
+int32_t sssp_mesh_width(sp_graph g) { return g->max_degree > 8 || g->n == 0 ? 0 : g->max_degree <= 4 ? 4 : 8; }
+
+void launch_mesh_rows(sp_graph g, const int2 *adjw, int32_t width, int2 *ell, hipStream_t s) {
+    auto fill = width == 4 ? k_sssp_mesh_rows<4> : k_sssp_mesh_rows<8>;
+    hipLaunchKernelGGL(fill, dim3(grid_for((int64_t)g->n * width, 256, 8192)), dim3(256), 0, s,
                        (const int32_t *)g->row_ptr, adjw, g->n, ell);
-    return ell;
 }
 
 sp_status sssp_ws_create(sp_graph g, SsspWorkspace &ws) {
