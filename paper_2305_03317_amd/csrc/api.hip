@@ -434,33 +434,31 @@ static void release_pr_ws(sp_graph g, PrWorkspace *ws) {
 static void free_weights(sp_graph g) {
     dev_free(g->adjw);
     dev_free(g->sssp_ell);
-    dev_free(g->sssp_rp);
     dev_free(g->hub_static);
     dev_free(g->owner_static);
     g->adjw = g->sssp_ell = nullptr;
-    g->sssp_rp = g->owner_static = nullptr;
+    g->owner_static = nullptr;
     g->hub_static = nullptr;
 }
 
 // What sp_graph_set_weights builds before it replaces the graph's; freed unless taken.
 struct NewWeights {
     int2 *adjw = nullptr, *ell = nullptr;
-    int32_t *rp = nullptr, *upload = nullptr, *owner = nullptr;
+    int32_t *upload = nullptr, *owner = nullptr;
     HubEntry *hubs = nullptr;
     size_t hub_bytes = 0;
     ~NewWeights() {
         dev_free(adjw);
         dev_free(ell);
-        dev_free(rp);
         dev_free(upload);
         dev_free(owner);
         dev_free(hubs);
     }
 };
 
-// Every hub of the weighted rows with its chunk range, in row order, and the
-// hub of every chunk.  rp: the rows' offsets by rank; null: the graph's rows.
-static sp_status build_static_hubs(sp_graph g, const int32_t *rp, NewWeights &nw, hipStream_t st) {
+// Every hub of the weighted rows (ranked or not) with its chunk range, in row
+// order, and the hub of every chunk.
+static sp_status build_static_hubs(sp_graph g, bool ranked, NewWeights &nw, hipStream_t st) {
     std::vector<HubEntry> hubs;
     std::vector<int32_t> owners;
     auto add = [&](int32_t v, int32_t deg) {
@@ -469,9 +467,9 @@ static sp_status build_static_hubs(sp_graph g, const int32_t *rp, NewWeights &nw
         hubs.push_back(HubEntry{v, 0, (int32_t)owners.size(), nch});
         owners.insert(owners.end(), (size_t)nch, (int32_t)hubs.size() - 1);
     };
-    if (rp) {  // hubs are among the first ranks
+    if (ranked) {  // hubs are among the first ranks
         std::vector<int32_t> off((size_t)rank_count(g, kRankExact) + 1);
-        SP_HIP(hipMemcpyAsync(off.data(), rp, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, st));
+        SP_HIP(hipMemcpyAsync(off.data(), g->rank_rp, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, st));
         SP_HIP(hipStreamSynchronize(st));
         for (size_t r = 0; r + 1 < off.size(); ++r) add((int32_t)r, off[r + 1] - off[r]);
     } else {
@@ -796,8 +794,7 @@ sp_status sp_graph_release(sp_graph g) {
         dev_free(g->rp_in);
         dev_free(g->ci_in);
     }
-    dev_free(g->rank_new);  // holds rank_old too
-    dev_free(g->rank_rp);
+    dev_free(g->rank_new);  // holds rank_old and rank_rp too
     dev_free(g->rank_ci);
     dev_free(g->tc_orp);
     dev_free(g->hub_static);
@@ -1113,17 +1110,18 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
     if (nw.upload) SP_HIP(hipMemcpyAsync(nw.upload, weights, (size_t)nnz * 4, hipMemcpyHostToDevice, st));
     const int32_t *w_in = nw.upload ? nw.upload : weights;
     bool ranked = false;
-    if (nnz) SP_TRY(sssp_pack_ranked(g, w_in, nw.adjw, bad, &nw.rp, &ranked, st));
+    if (nnz) SP_TRY(sssp_pack_ranked(g, w_in, nw.adjw, bad, &ranked, st));
     if (nnz && !ranked) {
         hipLaunchKernelGGL(k_pack_weights, dim3(grid_for(nnz, 256, 4096)), dim3(256), 0, st,
                            (const int32_t *)g->col_idx, w_in, nnz, nw.adjw, bad);
         SP_HIP(hipGetLastError());
     }
-    // Rows at a fixed width: into new memory now, into the earlier ones' once nothing can fail.
+    // Rows at a fixed width: into new memory now, or into the earlier ones' once nothing can fail (releasing
+    // them would take 250 us; small ones take 2).
     const int32_t width = sssp_mesh_width(g);
-    if (width && !g->sssp_ell &&
-        dev_alloc((void **)&nw.ell, sizeof(int2) * (size_t)g->n * (size_t)width) != SP_OK)
-        clear_error();  // the general kernel serves
+    const size_t ell_bytes = sizeof(int2) * (size_t)g->n * (size_t)width;
+    const bool in_place = g->sssp_ell && ell_bytes > (2u << 20);
+    if (width && !in_place && dev_alloc((void **)&nw.ell, ell_bytes) != SP_OK) clear_error();  // the general kernel serves
     if (nw.ell) launch_mesh_rows(g, nw.adjw, width, nw.ell, st);
     SP_HIP(hipGetLastError());
     SP_HIP(hipMemcpyAsync(&h_bad, bad, sizeof(h_bad), hipMemcpyDeviceToHost, st));
@@ -1133,8 +1131,8 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
         return SP_ERR_INVALID_ARGUMENT;
     }
     const bool new_hubs = g->n_hubs > 0 && (!g->hub_static || g->hub_static_ranked != ranked);
-    if (new_hubs) SP_TRY(build_static_hubs(g, !ranked ? nullptr : nw.rp ? nw.rp : g->sssp_rp, nw, st));
-    if (g->sssp_ell) {
+    if (new_hubs) SP_TRY(build_static_hubs(g, ranked, nw, st));
+    if (in_place) {
         launch_mesh_rows(g, nw.adjw, width, g->sssp_ell, st);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
             std::lock_guard<std::mutex> lk(g->mu);  // the earlier weights do without
@@ -1147,9 +1145,9 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
     // Everything is there: the earlier weights go only now.
     std::lock_guard<std::mutex> lk(g->mu);
     std::swap(g->adjw, nw.adjw);
-    if (nw.ell) std::swap(g->sssp_ell, nw.ell);
+    if (!in_place) std::swap(g->sssp_ell, nw.ell);
     g->sssp_ell_w = width;
-    if (nw.rp || !ranked) std::swap(g->sssp_rp, nw.rp);  // (ranked and null: the offsets stay as they are)
+    g->sssp_ranked = ranked;
     if (new_hubs) {
         std::swap(g->hub_static, nw.hubs);
         std::swap(g->owner_static, nw.owner);
@@ -1157,8 +1155,7 @@ sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flag
         g->bytes += nw.hub_bytes - g->hub_bytes;
         g->hub_bytes = nw.hub_bytes;
     }
-    const size_t bytes = adj_bytes + (ranked ? sizeof(int32_t) * ((size_t)g->n + 1) : 0) +
-                         (g->sssp_ell ? sizeof(int2) * (size_t)g->n * (size_t)width : 0);
+    const size_t bytes = adj_bytes + (g->sssp_ell ? ell_bytes : 0);
     g->bytes += bytes - g->weight_bytes;
     g->weight_bytes = bytes;
     ++g->weight_gen;

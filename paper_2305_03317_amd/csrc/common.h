@@ -93,9 +93,9 @@ struct sp_graph_s {
     std::vector<sp::BatchWorkspace *> batch_pool;
     // Edge weights (sp_graph_set_weights), null until set: the adjacency
     // packed as {neighbour, weight} per CSR entry, so one 8-byte load gives
-    // both.  With sssp_rp set, rows and neighbours are numbered by rank
-    // (rank_new) and sssp_rp holds the rows' offsets; else row_ptr does.
-    int32_t *sssp_rp = nullptr;      // device, n + 1
+    // both.  sssp_ranked: rows and neighbours are numbered by rank (rank_new,
+    // rows at rank_rp); else as in row_ptr.
+    bool sssp_ranked = false;
     int2 *adjw = nullptr;            // device, nnz (>= 1 element allocated)
     // The same rows at a fixed width, where all hold at most 8 entries (sssp_mesh_width); else null.
     int2 *sssp_ell = nullptr;        // device, n * sssp_ell_w
@@ -109,11 +109,11 @@ struct sp_graph_s {
     sp::PrPlan *pr_plan = nullptr;   // host
     // Vertices ranked by degree, highest first (ensure_rank_locked): rank of a
     // vertex, vertex of a rank, and where each degree class starts.
-    int32_t *rank_new = nullptr;     // device, n; its allocation holds rank_old too
+    int32_t *rank_new = nullptr;     // device, n; its allocation holds rank_old and rank_rp too
     int32_t *rank_old = nullptr;     // device, n
     std::vector<int32_t> rank_first; // host, kRankBuckets + 1
-    // Undirected rows numbered by rank (ensure_rank_csr_locked), each row's
-    // entries in their own order; null where it does not pay.
+    // Undirected rows numbered by rank: offsets (ensure_rank_rp_locked) and, where
+    // the copy pays (ensure_rank_csr_locked), each row's entries in their own order.
     int32_t *rank_rp = nullptr;      // device, n + 1
     int32_t *rank_ci = nullptr;      // device, nnz (>= 1)
     // Triangle counting (ensure_oriented, on first use), vertices by rank: row
@@ -673,12 +673,11 @@ sp_status undirected_only(const char *what);
 sp_status check_batch_cfg(const sp_batch_config *cfg);
 
 // Packs the rows numbered by rank with their weights (each checked to lie in
-// [0, INT32_MAX - 1]: *bad counts the others).  *out_rp
-// receives the rows' offsets unless g->sssp_rp holds them already.  On a graph
-// that renumbering does not suit, or without the memory for it, *ranked stays
-// false and nothing is enqueued.
-sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, int32_t **out_rp,
-                           bool *ranked, hipStream_t s);
+// [0, INT32_MAX - 1]: *bad counts the others).  On a graph that renumbering
+// does not suit, or without the memory for it, *ranked stays false and nothing
+// is enqueued.
+sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, bool *ranked,
+                           hipStream_t s);
 // Builds g->pr_plan once (thread-safe).
 sp_status ensure_pr_plan(sp_graph g, hipStream_t s);
 

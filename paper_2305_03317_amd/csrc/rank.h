@@ -24,6 +24,10 @@ __host__ __device__ inline int32_t rank_bucket(int32_t deg) {
 // Builds g->rank_new / g->rank_old / g->rank_first once; the caller holds g->mu.
 sp_status ensure_rank_locked(sp_graph g, hipStream_t s);
 
+// Builds g->rank_rp once, on an undirected graph; after ensure_rank_locked, the
+// caller holds g->mu.
+sp_status ensure_rank_rp_locked(sp_graph g, hipStream_t s);
+
 // Vertices of degree >= deg (at most kRankExact, or a power of two); after ensure_rank_locked.
 inline int32_t rank_count(sp_graph g, int32_t deg) { return g->rank_first[rank_bucket(deg) + 1]; }
 
@@ -48,8 +52,8 @@ constexpr int32_t kSourceRankCount = 8;
 // ensure_rank_locked.
 bool rank_skewed(sp_graph g);
 
-// Builds g->rank_rp / g->rank_ci once, on an undirected graph that is skewed;
-// leaves them null on others and where memory is short.  The caller holds g->mu
+// Builds g->rank_ci (and g->rank_rp) once, on an undirected graph that is
+// skewed; leaves it null on others and where memory is short.  The caller holds g->mu
 // and has looked at the size.
 sp_status ensure_rank_csr_locked(sp_graph g, hipStream_t s);
 

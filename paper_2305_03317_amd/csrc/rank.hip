@@ -22,9 +22,10 @@ struct ByDegree {  // item i is vertex n - 1 - i (ties rank the higher id first)
     const int32_t *rp;
     int32_t n;
     int32_t *rank_new, *rank_old;
+    int32_t skip;  // buckets of higher degrees than any
     __device__ int32_t bucket(int64_t i) const {
         const int32_t v = (int32_t)(n - 1 - i);
-        return rank_bucket(rp[v + 1] - rp[v]);
+        return rank_bucket(rp[v + 1] - rp[v]) - skip;
     }
     __device__ void place(int64_t i, int32_t r) const {
         const int32_t v = (int32_t)(n - 1 - i);
@@ -37,6 +38,7 @@ struct ByRowClass {
     const int32_t *rp, *old;
     int32_t n, longest;
     int32_t *order;
+    int32_t skip = 0;
     __device__ int32_t bucket(int64_t i) const {
         const int32_t v = old ? old[i] : (int32_t)i;
         return row_class(rp[v + 1] - rp[v], longest);
@@ -48,20 +50,20 @@ struct ByRowClass {
 template <class Item>
 __global__ __launch_bounds__(kWave) void k_sort_count(Item it, int32_t tile, int32_t ntiles, int32_t *hist) {
     __shared__ int32_t s_cnt[Item::kBuckets];
-    for (int32_t b = threadIdx.x; b < Item::kBuckets; b += kWave) s_cnt[b] = 0;
+    const int32_t nb = Item::kBuckets - it.skip;
+    for (int32_t b = threadIdx.x; b < nb; b += kWave) s_cnt[b] = 0;
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * tile, i1 = min((int64_t)it.n, i0 + tile);
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kWave) atomicAdd(&s_cnt[it.bucket(i)], 1);
     __syncthreads();
-    for (int32_t b = threadIdx.x; b < Item::kBuckets; b += kWave)
-        hist[(int64_t)b * ntiles + blockIdx.x] = s_cnt[b];
+    for (int32_t b = threadIdx.x; b < nb; b += kWave) hist[(int64_t)b * ntiles + blockIdx.x] = s_cnt[b];
 }
 
 template <class Item>
 __global__ __launch_bounds__(kWave) void k_sort_place(Item it, int32_t tile, int32_t ntiles,
                                                       const int32_t *__restrict__ first) {
     __shared__ int32_t s_at[Item::kBuckets];
-    for (int32_t b = threadIdx.x; b < Item::kBuckets; b += kWave)
+    for (int32_t b = threadIdx.x; b < Item::kBuckets - it.skip; b += kWave)
         s_at[b] = first[(int64_t)b * ntiles + blockIdx.x];
     __syncthreads();
     const int lane = lane_id();
@@ -153,28 +155,28 @@ __global__ void k_sort_starts(const int32_t *__restrict__ first, int32_t stride,
 // (start[kBuckets] = n).  Synchronises the stream.
 template <class Item>
 static sp_status counting_sort(const Item &it, int32_t *start, hipStream_t s) {
-    constexpr int32_t nb = Item::kBuckets;
+    const int32_t nb = Item::kBuckets - it.skip;
     const int32_t n = it.n;
     const int32_t tile = std::max(kRankTile, (n / 2048 / kWave + 1) * kWave);
     const int32_t ntiles = (int32_t)std::max<int64_t>(1, ((int64_t)n + tile - 1) / tile);
     const int64_t cells = (int64_t)nb * ntiles;
-    int32_t *tmp = nullptr;  // counts, their scan (one more for the total), the scan's tiles
-    SP_TRY(dev_alloc((void **)&tmp, sizeof(int32_t) * (size_t)(2 * cells + 2 + scan_tiles(cells))));
-    int32_t *hist = tmp, *first = tmp + cells + 1, *tiles = first + cells + 1;
-    for (int32_t b = 0; b <= nb; ++b) start[b] = 0;
+    int32_t *hist = nullptr;  // counts, scanned in place (one more for the total); the scan's tiles; the starts
+    SP_TRY(dev_alloc((void **)&hist, sizeof(int32_t) * (size_t)(cells + 1 + scan_tiles(cells) + nb + 1)));
+    int32_t *tiles = hist + cells + 1, *starts = tiles + scan_tiles(cells);
+    for (int32_t b = 0; b <= Item::kBuckets; ++b) start[b] = 0;
     hipError_t e = hipSuccess;
     if (n > 0) {
         hipLaunchKernelGGL((k_sort_count<Item>), dim3(ntiles), dim3(kWave), 0, s, it, tile, ntiles, hist);
-        launch_excl_scan(hist, cells, first, tiles, s);
+        launch_excl_scan(hist, cells, hist, tiles, s);
         hipLaunchKernelGGL((k_sort_place<Item>), dim3(ntiles), dim3(kWave), 0, s, it, tile, ntiles,
-                           (const int32_t *)first);
-        hipLaunchKernelGGL(k_sort_starts, dim3(1), dim3(256), 0, s, (const int32_t *)first, ntiles, nb + 1, hist);
+                           (const int32_t *)hist);
+        hipLaunchKernelGGL(k_sort_starts, dim3(1), dim3(256), 0, s, (const int32_t *)hist, ntiles, nb + 1, starts);
         e = hipGetLastError();
         if (e == hipSuccess)
-            e = hipMemcpyAsync(start, hist, sizeof(int32_t) * (nb + 1), hipMemcpyDeviceToHost, s);
+            e = hipMemcpyAsync(start + it.skip, starts, sizeof(int32_t) * (size_t)(nb + 1), hipMemcpyDeviceToHost, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    dev_free(tmp);
+    dev_free(hist);
     if (e != hipSuccess) {
         set_error("sorting the vertices failed: %s", hipGetErrorString(e));
         return SP_ERR_DEVICE;
@@ -185,10 +187,11 @@ static sp_status counting_sort(const Item &it, int32_t *start, hipStream_t s) {
 sp_status ensure_rank_locked(sp_graph g, hipStream_t s) {
     if (g->rank_new) return SP_OK;
     const size_t vn = (size_t)std::max(g->n, 1);
+    const size_t bytes = sizeof(int32_t) * (g->directed ? 2 * vn : 3 * vn + 1);  // undirected: room for rank_rp
     int32_t *rn = nullptr;
-    SP_TRY(dev_alloc((void **)&rn, 2 * sizeof(int32_t) * vn));
+    SP_TRY(dev_alloc((void **)&rn, bytes));
     std::vector<int32_t> start(kRankBuckets + 1);
-    const sp_status st = counting_sort(ByDegree{g->row_ptr, g->n, rn, rn + vn}, start.data(), s);
+    const sp_status st = counting_sort(ByDegree{g->row_ptr, g->n, rn, rn + vn, rank_bucket(g->max_degree)}, start.data(), s);
     if (st < 0) {
         dev_free(rn);
         return st;
@@ -196,7 +199,23 @@ sp_status ensure_rank_locked(sp_graph g, hipStream_t s) {
     g->rank_first = std::move(start);
     g->rank_new = rn;
     g->rank_old = rn + vn;
-    g->bytes += 2 * sizeof(int32_t) * vn;
+    g->bytes += bytes;
+    return SP_OK;
+}
+
+sp_status ensure_rank_rp_locked(sp_graph g, hipStream_t s) {
+    if (g->rank_rp) return SP_OK;
+    int32_t *rp = g->rank_old + std::max(g->n, 1), *tiles = nullptr;
+    SP_TRY(dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(g->n)));
+    launch_row_offsets(g->row_ptr, nullptr, g->rank_old, g->n, rp, tiles, s);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    dev_free(tiles);
+    if (e != hipSuccess) {
+        set_error("numbering the rows by rank failed: %s", hipGetErrorString(e));
+        return SP_ERR_DEVICE;
+    }
+    g->rank_rp = rp;
     return SP_OK;
 }
 
@@ -257,33 +276,24 @@ void launch_renumber(const int32_t *rp, const int32_t *ci, const int32_t *order,
 
 sp_status ensure_rank_csr_locked(sp_graph g, hipStream_t s) {
     if (g->rank_ci || g->directed || g->max_degree <= 8) return SP_OK;
-    int32_t *rp = nullptr, *ci = nullptr, *tiles = nullptr;
+    int32_t *ci = nullptr;
     sp_status st = ensure_rank_locked(g, s);
     if (st == SP_OK && !rank_skewed(g)) return SP_OK;
-    const size_t nb = sizeof(int32_t) * ((size_t)g->n + 1), eb = sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1);
-    if (st == SP_OK) st = dev_alloc((void **)&rp, nb);
+    const size_t eb = sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1);
+    if (st == SP_OK) st = ensure_rank_rp_locked(g, s);
     if (st == SP_OK) st = dev_alloc((void **)&ci, eb);
-    if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(g->n));
-    hipError_t e = hipSuccess;
     if (st == SP_OK) {
-        launch_row_offsets(g->row_ptr, nullptr, g->rank_old, g->n, rp, tiles, s);
-        launch_renumber(g->row_ptr, g->col_idx, nullptr, g->rank_old, g->rank_new, rp, rank_count(g, kRankExact),
-                        g->n, ci, s);
-        e = hipGetLastError();
+        launch_renumber(g->row_ptr, g->col_idx, nullptr, g->rank_old, g->rank_new, g->rank_rp,
+                        rank_count(g, kRankExact), g->n, ci, s);
+        hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-    }
-    dev_free(tiles);
-    if (st == SP_OK && e == hipSuccess) {
-        g->rank_rp = rp;
+        if (e != hipSuccess) {
+            dev_free(ci);
+            set_error("numbering the rows by rank failed: %s", hipGetErrorString(e));
+            return SP_ERR_DEVICE;
+        }
         g->rank_ci = ci;
-        g->bytes += nb + eb;
-        return SP_OK;
-    }
-    dev_free(rp);
-    dev_free(ci);
-    if (e != hipSuccess) {
-        set_error("numbering the rows by rank failed: %s", hipGetErrorString(e));
-        return SP_ERR_DEVICE;
+        g->bytes += eb;
     }
     if (st == SP_ERR_OUT_OF_MEMORY) {
         clear_error();

@@ -32,8 +32,6 @@
 // Every round only lowers distances toward the same least fixed point, so
 // the result does not depend on scheduling: it is the shortest-path distance
 // (INT32_MAX where unreached), bit for bit.
-#include <utility>
-
 #include "capture.h"
 #include "common.h"
 #include "devutil.h"
@@ -841,8 +839,8 @@ __global__ void k_sssp_export(SsspCtl *c, const int32_t *__restrict__ dist,
 // Rows [first, last) of the rank numbering, PER lanes each: {rank of the
 // neighbour, weight}; counts weights outside [0, INT32_MAX - 1].  The ranks are
 // those of the earlier weights' rows, where there are some (`before`).
-template <int PER>
-__global__ __launch_bounds__(256) void k_sssp_pack_ranked(const int32_t *__restrict__ rp,
+template <int BS, int PER>
+__global__ __launch_bounds__(BS) void k_sssp_pack_ranked(const int32_t *__restrict__ rp,
                                                           const int32_t *__restrict__ ci,
                                                           const int32_t *__restrict__ w,
                                                           const int32_t *__restrict__ rank_new,
@@ -851,13 +849,28 @@ __global__ __launch_bounds__(256) void k_sssp_pack_ranked(const int32_t *__restr
                                                           const int2 *__restrict__ before, int32_t first,
                                                           int32_t last, int2 *adjw, unsigned int *bad) {
     unsigned int b = 0;
-    const int64_t stride = (int64_t)gridDim.x * (256 / PER);
-    for (int64_t r = first + (int64_t)blockIdx.x * (256 / PER) + threadIdx.x / PER; r < last; r += stride) {
+    const int64_t stride = (int64_t)gridDim.x * (BS / PER);
+    for (int64_t r = first + (int64_t)blockIdx.x * (BS / PER) + threadIdx.x / PER; r < last; r += stride) {
         const int32_t at = rp[rank_old[r]], to = wrp[r], len = wrp[r + 1] - to;
-        for (int32_t k = threadIdx.x % PER; k < len; k += PER) {
-            const int32_t x = w[at + k];
-            if (x < 0 || x == kInf) ++b;
-            adjw[to + k] = make_int2(before ? before[to + k].x : rank_new[ci[at + k]], x);
+        constexpr int kFly = 4;  // a long row is one block's: with a load at a time rmat-20 took 330 us for them, not 190
+        for (int32_t k = threadIdx.x % PER; k < len; k += kFly * PER) {
+            int32_t x[kFly], u[kFly];
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) {
+                const int32_t j = min(k + q * PER, len - 1);
+                x[q] = w[at + j];
+                u[q] = before ? before[to + j].x : ci[at + j];
+            }
+            if (!before) {
+#pragma unroll
+                for (int q = 0; q < kFly; ++q) u[q] = rank_new[u[q]];
+            }
+#pragma unroll
+            for (int q = 0; q < kFly; ++q)
+                if (k + q * PER < len) {
+                    if (x[q] < 0 || x[q] == kInf) ++b;
+                    adjw[to + k + q * PER] = make_int2(u[q], x[q]);
+                }
         }
     }
     if (b) atomicAdd(bad, b);
@@ -868,58 +881,41 @@ __global__ __launch_bounds__(256) void k_sssp_pack_ranked(const int32_t *__restr
 // fill consecutive lines, and the distances of the first million ranks (98% of
 // the entries on rmat-22) fit an XCD's 4 MB L2.  rmat-22:
 // 6.2 -> 5.1 ms per source.
-sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, int32_t **out_rp,
-                           bool *ranked, hipStream_t s) {
+sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, bool *ranked,
+                           hipStream_t s) {
     const int32_t n = g->n;
     if (n <= kRenumberFrom || g->max_degree <= 8) return SP_OK;
     {
         std::lock_guard<std::mutex> lk(g->mu);
-        const sp_status st = ensure_rank_locked(g, s);
+        sp_status st = ensure_rank_locked(g, s);
+        if (st == SP_OK && !rank_skewed(g)) return SP_OK;
+        if (st == SP_OK) st = ensure_rank_rp_locked(g, s);
         if (st == SP_ERR_OUT_OF_MEMORY) {
             clear_error();
             return SP_OK;
         }
         if (st != SP_OK) return st;
-        if (!rank_skewed(g)) return SP_OK;
     }
-    const int32_t *wrp = g->sssp_rp;
-    if (!wrp) {  // the offsets depend on the rows alone: the first weights leave them for later ones
-        int32_t *tiles = nullptr;
-        sp_status st = dev_alloc((void **)out_rp, sizeof(int32_t) * ((size_t)n + 1));
-        if (st == SP_OK) st = dev_alloc((void **)&tiles, sizeof(int32_t) * (size_t)scan_tiles(n));
-        if (st != SP_OK) {
-            dev_free(std::exchange(*out_rp, nullptr));
-            if (st != SP_ERR_OUT_OF_MEMORY) return st;
-            clear_error();
-            return SP_OK;
-        }
-        launch_row_offsets(g->row_ptr, nullptr, g->rank_old, n, *out_rp, tiles, s);
-        const hipError_t e = hipStreamSynchronize(s);  // the scan's scratch is done with
-        dev_free(tiles);
-        if (e != hipSuccess) {
-            set_error("numbering the weighted rows failed: %s", hipGetErrorString(e));
-            return SP_ERR_DEVICE;
-        }
-        wrp = *out_rp;
-    }
-    const int2 *before = g->sssp_rp ? g->adjw : nullptr;
-    const int32_t longer = rank_count(g, kRankExact);
+    const int2 *before = g->sssp_ranked ? g->adjw : nullptr;
     const int maxb = device_cu_count() * 8;
-    if (longer > 0)
-        hipLaunchKernelGGL(k_sssp_pack_ranked<256>, dim3(std::min(longer, maxb)), dim3(256), 0, s,
-                           (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
-                           (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, wrp, before, 0, longer, adjw,
-                           bad);
-    hipLaunchKernelGGL(k_sssp_pack_ranked<16>, dim3(grid_for((int64_t)n - longer, 16, maxb)), dim3(256), 0, s,
-                       (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
-                       (const int32_t *)g->rank_new, (const int32_t *)g->rank_old, wrp, before, longer, n, adjw, bad);
+    auto pack = [&](auto kernel, int block, int rows_per_block, int32_t first, int32_t last) {
+        if (last > first)
+            hipLaunchKernelGGL(kernel, dim3(grid_for((int64_t)last - first, rows_per_block, maxb)), dim3(block), 0, s,
+                               (const int32_t *)g->row_ptr, (const int32_t *)g->col_idx, weights,
+                               (const int32_t *)g->rank_new, (const int32_t *)g->rank_old,
+                               (const int32_t *)g->rank_rp, before, first, last, adjw, bad);
+    };
+    const int32_t longest = rank_count(g, 8192), longer = rank_count(g, kRankExact);
+    pack(k_sssp_pack_ranked<1024, 1024>, 1024, 1, 0, longest);
+    pack(k_sssp_pack_ranked<256, 256>, 256, 1, longest, longer);
+    pack(k_sssp_pack_ranked<256, 16>, 256, 16, longer, n);
     SP_HIP(hipGetLastError());
     *ranked = true;
     return SP_OK;
 }
 
 // Offsets of the rows of g->adjw.
-static const int32_t *weighted_rows(sp_graph g) { return g->sssp_rp ? g->sssp_rp : g->row_ptr; }
+static const int32_t *weighted_rows(sp_graph g) { return g->sssp_ranked ? g->rank_rp : g->row_ptr; }
 
 int32_t sssp_mesh_width(sp_graph g) { return g->max_degree > 8 || g->n == 0 ? 0 : g->max_degree <= 4 ? 4 : 8; }
 
@@ -1029,7 +1025,7 @@ static sp_status sssp_run_bs(sp_graph g, SsspWorkspace &ws, int32_t src, int32_t
     const bool may_push = o.forced != SSSP_PULL;
     const int forced = may_pull ? o.forced : SSSP_PUSH;
     hipLaunchKernelGGL(k_sssp_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.dist, ws.stamp, n);
-    const int32_t *rp = weighted_rows(g), *new_id = g->sssp_rp ? (const int32_t *)g->rank_new : nullptr;
+    const int32_t *rp = weighted_rows(g), *new_id = g->sssp_ranked ? (const int32_t *)g->rank_new : nullptr;
     hipLaunchKernelGGL(k_sssp_init, dim3(1), dim3(1), 0, s, ws.ctl, rp, ws.dist, ws.stamp, ws.queue[0], ws.hubs[0],
                        ws.owner[0], src, new_id, n, (long long)g->nnz,
                        forced, o.alpha, (int32_t)g->hub_chunks);
