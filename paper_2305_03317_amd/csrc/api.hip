@@ -1197,7 +1197,8 @@ sp_status sp_sssp(sp_graph g, int32_t source, int32_t *out_dist, const sp_sssp_c
         o.local_hops = cfg->local_hops;
     }
     // waves of the mesh kernel work alone: smaller blocks spread a round's few over more CUs (road-3000 11.0 -> 10.4 ms)
-    if (o.block == 0) o.block = g->sssp_ell && sssp_local_hops(g, o.local_hops) > 0 ? 128 : 256;
+    if (o.block == 0)
+        o.block = g->sssp_ell && o.forced != SSSP_PULL && sssp_local_hops(g, o.local_hops) > 0 ? 128 : 256;
     DeviceGuard dg(g->device);
     hipStream_t st = (hipStream_t)s;
     SsspWorkspace *ws = nullptr;

@@ -987,7 +987,7 @@ static void enqueue_rounds(sp_graph g, SsspWorkspace &ws, int rounds, int grid, 
     const int32_t *rp = weighted_rows(g);
     for (int k = 0; k < rounds; ++k) {
         const int32_t parity = k & 1;
-        if (HOPS > 0 && g->sssp_ell) {  // only pushes (rows of at most 8 entries, local hops)
+        if (HOPS > 0 && g->sssp_ell && may_push) {  // rows of at most 8 entries, local hops
             ProfScope ps(P_SSSP_PUSH, s);
             auto mesh = g->sssp_ell_w == 4 ? k_sssp_mesh<BS, 4> : k_sssp_mesh<BS, 8>;
             hipLaunchKernelGGL(mesh, dim3(grid), dim3(BS), 0, s, ws.ctl, (const int2 *)g->sssp_ell, ws.dist, ws.stamp, ws.queue[0],
