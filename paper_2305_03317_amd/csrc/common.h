@@ -516,7 +516,7 @@ struct SsspCtl {
     // round, written by the closing block in one 64-bit store and read by
     // every block in one 64-bit load, so no block sees half of a round's
     // state: bits 0-30 frontier size, 31-54 its hubs' chunk count, 55 round
-    // parity, 56 pull round, 57 done.
+    // parity, 56 pull round, 57 done, 58-60 the logarithm of a push wave's share.
     unsigned long long state;
     int32_t round;       // round being run (read by the round's working blocks)
     int32_t done;        // host mirror of the done bit

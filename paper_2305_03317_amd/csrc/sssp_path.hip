@@ -32,6 +32,8 @@
 // Every round only lowers distances toward the same least fixed point, so
 // the result does not depend on scheduling: it is the shortest-path distance
 // (INT32_MAX where unreached), bit for bit.
+#include <type_traits>
+
 #include "capture.h"
 #include "common.h"
 #include "devutil.h"
@@ -77,24 +79,34 @@ constexpr int kLocalCap = 512;
 // Fewest frontier vertices a wave of k_sssp_mesh starts with.
 constexpr int kMeshLeast = 8;
 
+// Entries a wave of k_sssp_push takes at least of a frontier's rows, on average
+// (1, 64, 128, 256: 262,144 vertices of three entries 635, 569, 568, 593 us;
+// uniform, 65,536 vertices, 498, 501, 503, 518).
+constexpr int kPushStep = 128;
+
 // The round state word (SsspCtl::state).
 struct RoundState {
     int32_t cnt;      // frontier size
     int32_t chunks;   // chunks of the frontier's hubs
     int32_t parity;   // round & 1
     bool pull, done;
+    int32_t share;    // fewest frontier vertices a wave of k_sssp_push takes
 };
 
+// deg: the frontier's entries.
 __device__ __forceinline__ unsigned long long pack_state(int32_t cnt, int32_t chunks, int32_t round,
-                                                         int32_t mode, bool done) {
+                                                         int32_t mode, bool done, unsigned long long deg) {
+    const float rows = (float)kPushStep * (float)cnt / (float)max(deg, 1ull);  // of a step, on average
+    const int32_t lg = rows >= 64.0f ? 6 : max(1, 31 - __clz((int)rows | 1));
     return (unsigned long long)(uint32_t)cnt | ((unsigned long long)(uint32_t)chunks << 31) |
            ((unsigned long long)(round & 1) << 55) | ((unsigned long long)(mode == SSSP_PULL) << 56) |
-           ((unsigned long long)done << 57);
+           ((unsigned long long)done << 57) | ((unsigned long long)lg << 58);
 }
 
 __device__ __forceinline__ RoundState unpack_state(unsigned long long w) {
     return RoundState{(int32_t)(w & 0x7fffffffull), (int32_t)((w >> 31) & 0xffffffull),
-                      (int32_t)((w >> 55) & 1ull), ((w >> 56) & 1ull) != 0, ((w >> 57) & 1ull) != 0};
+                      (int32_t)((w >> 55) & 1ull), ((w >> 56) & 1ull) != 0, ((w >> 57) & 1ull) != 0,
+                      1 << (int32_t)((w >> 58) & 7ull)};
 }
 
 // Largest frontier hub chunk count the state word holds (24 bits).
@@ -114,10 +126,9 @@ __device__ __forceinline__ RoundState read_state(SsspCtl *c) {
 // entries count toward the next round's direction choice, and a hub is
 // registered for the next round's chunk blocks (list entry plus the owner of
 // each of its chunks).
-__device__ __forceinline__ void joined(SsspCtl *c, const int32_t *__restrict__ rp, HubEntry *hn,
+__device__ __forceinline__ void joined(SsspCtl *c, int32_t deg, HubEntry *hn,
                                        int32_t *on, int32_t hub_cap, int32_t chunk_cap, int32_t u,
                                        unsigned long long &my_deg) {
-    const int32_t deg = rp[u + 1] - rp[u];
     my_deg += (unsigned long long)deg;
     if (deg > kHubDeg) {
         const int32_t nch = (deg + kHubChunk - 1) / kHubChunk;
@@ -176,7 +187,7 @@ __device__ void close_round(SsspCtl *c, int32_t mode, int32_t n, int32_t hub_cap
     if (c->forced >= 0) next = c->forced;
     else if ((double)deg * c->alpha > (double)c->nnz) next = SSSP_PULL;
     c->done = done;
-    __hip_atomic_store(&c->state, pack_state(done ? 0 : tail, done ? 0 : (int32_t)nch, r, next, done),
+    __hip_atomic_store(&c->state, pack_state(done ? 0 : tail, done ? 0 : (int32_t)nch, r, next, done, deg),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -218,7 +229,7 @@ __global__ void k_sssp_init(SsspCtl *c, const int32_t *__restrict__ rp, int32_t 
     int32_t mode = SSSP_PUSH;
     if (forced >= 0) mode = forced;
     else if ((double)deg * alpha > (double)nnz) mode = SSSP_PULL;
-    c->state = pack_state(1, nch, 0, mode, false);
+    c->state = pack_state(1, nch, 0, mode, false, (unsigned long long)deg);
 }
 
 // Push round.  Waves work by themselves, without barriers.  blockIdx.y == 0:
@@ -243,13 +254,19 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
     const RoundState st = read_state(c);
     if (st.done || st.pull || st.parity != parity) return;
     constexpr int kWaves = BS / kWave, kFly = 4, kStep = kFly * kWave;
-    constexpr int kCand = kStep + kWave, kOut = 2 * kWave;
+    constexpr int kCand = kStep + kWave, kOut = kStep + kWave;
     __shared__ int32_t s_off[kWaves][kWave + 1], s_beg[kWaves][kWave], s_d[kWaves][kWave];
     __shared__ int2 s_cand[kWaves][kCand];
-    __shared__ int32_t s_out[kWaves][kOut];
-    __shared__ unsigned long long s_red[1];
+    __shared__ int32_t s_out[kWaves][kOut], s_left[kWaves], s_base;
+    __shared__ unsigned long long s_red[1], s_deg[kWaves];
     const int lane = lane_id(), wv = threadIdx.x / kWave;
-    const int32_t r = c->round, cnt = st.cnt, nch = st.chunks;
+    const int32_t cnt = st.cnt, nch = st.chunks;
+    int32_t share = st.share;
+    while (share < kWave && (int64_t)gridDim.x * kWaves * share < cnt) share <<= 1;
+    const int32_t per = kWaves * share;
+    const int nb0 = working_blocks(cnt, per), nb1 = working_blocks(nch, kWaves);
+    if ((int)blockIdx.x >= (blockIdx.y == 0 ? nb0 : nb1)) return;
+    const int32_t r = c->round;
     const int32_t *qc = parity ? q1 : q0;
     int32_t *qn = parity ? q0 : q1;
     const HubEntry *hc = parity ? h1 : h0;
@@ -259,36 +276,51 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
     unsigned long long my_deg = 0, my_items = 0, my_edges = 0;
     bool ovf = false;
     int32_t ncand = 0, nout = 0;  // the same in every lane
-    auto flush = [&]() {
-        if (nout == 0) return;
-        int32_t base = 0;
-        if (lane == 0) base = atomicAdd(&c->tail_.v, nout);
-        base = __builtin_amdgcn_readfirstlane(base);
+    auto write_out = [&](int32_t base) {
         for (int32_t i = lane; i < nout; i += kWave) {
             if (base + i < n) qn[base + i] = s_out[wv][i];
             else atomicOr(&c->capacity_.v, 1);
         }
         nout = 0;
+    };
+    auto flush = [&]() {
+        if (nout == 0) return;
+        int32_t base = 0;
+        if (lane == 0) base = atomicAdd(&c->tail_.v, nout);
+        write_out(__builtin_amdgcn_readfirstlane(base));
         __builtin_amdgcn_wave_barrier();
     };
-    // settles the last min(64, ncand) candidates
-    auto settle = [&]() {
-        const int32_t take_n = min(ncand, (int32_t)kWave);
+    // settles the last `groups` x 64 candidates together (of the last group, what is there)
+    auto settle = [&](auto groups) {
+        constexpr int G = decltype(groups)::value;
+        const int32_t take_n = min(ncand, (int32_t)(G * kWave));
         ncand -= take_n;
-        bool take = false;
-        int32_t u = 0;
-        if (lane < take_n) {
-            const int2 x = s_cand[wv][ncand + lane];
-            u = x.x;
-            bool lowered;
-            take = relax_push(dist, stamp, u, x.y, r, lowered);
-            if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, u, my_deg);
+        int2 x[G];
+        int32_t deg[G], old[G];
+        bool take[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            x[g] = s_cand[wv][ncand + min(g * kWave + lane, take_n - 1)];
+            if (G == 1 && lane >= take_n) x[g].y = kInf;  // lowers nothing
         }
-        const unsigned long long m = __ballot(take);
-        if (take) s_out[wv][nout + lanes_below(m)] = u;
-        nout += __popcll(m);
-        __builtin_amdgcn_wave_barrier();
-        if (nout > kOut - kWave) flush();
+#pragma unroll
+        for (int g = 0; g < G; ++g) deg[g] = rp[x[g].x + 1] - rp[x[g].x];
+#pragma unroll
+        for (int g = 0; g < G; ++g) old[g] = dist[x[g].x];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (x[g].y < old[g]) old[g] = atomicMin(&dist[x[g].x], x[g].y);
+#pragma unroll
+        for (int g = 0; g < G; ++g) take[g] = x[g].y < old[g] && atomicMax(&stamp[x[g].x], r + 1) < r + 1;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (take[g]) joined(c, deg[g], hn, on, hub_cap, chunk_cap, x[g].x, my_deg);
+            const unsigned long long m = __ballot(take[g]);
+            if (take[g]) s_out[wv][nout + lanes_below(m)] = x[g].x;
+            nout += __popcll(m);
+            __builtin_amdgcn_wave_barrier();
+            if (nout > kOut - kWave) flush();
+        }
     };
     auto offer = [&](bool may, int32_t u, int32_t nd) {
         const unsigned long long m = __ballot(may);
@@ -309,87 +341,97 @@ __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__r
             offer(nd < old[q], x[q].x, nd);
         }
         __builtin_amdgcn_wave_barrier();
-        while (ncand >= kWave) settle();
+        if (ncand >= 4 * kWave) settle(std::integral_constant<int, 4>{});
+        if (ncand >= 2 * kWave) settle(std::integral_constant<int, 2>{});
+        while (ncand >= kWave) settle(std::integral_constant<int, 1>{});
     };
-    bool working;
-    int nb0;
-    {
-        int32_t share = 2;
-        while (share < kWave && (int64_t)gridDim.x * kWaves * share < cnt) share <<= 1;
-        const int32_t per = kWaves * share;
-        nb0 = working_blocks(cnt, per);
-        working = blockIdx.y == 0 && (int)blockIdx.x < nb0;
-        if (blockIdx.y == 0) {
-            for (int64_t b = (int64_t)blockIdx.x * per + wv * share; b < cnt; b += (int64_t)gridDim.x * per) {
-                const int64_t i = b + lane;
-                int32_t beg = 0, deg = 0, d = 0;
-                if (i < cnt && lane < share) {
-                    const int32_t v = qc[i];
-                    beg = rp[v];
-                    deg = rp[v + 1] - beg;
-                    if (deg > kHubDeg) deg = 0;  // its chunks are taken by blockIdx.y == 1
-                    d = dist[v];
-                    ++my_items;
-                    my_edges += (unsigned long long)deg;
-                }
-                const int32_t incl = wave_incl_scan(deg);
-                const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
-                s_off[wv][lane] = incl - deg;
-                if (lane == 0) s_off[wv][kWave] = total;
-                s_beg[wv][lane] = beg;
-                s_d[wv][lane] = d;
-                __builtin_amdgcn_wave_barrier();
-                const int32_t some = __builtin_amdgcn_readlane(beg, __ffsll((long long)(__ballot(deg > 0) | 1ull << 63)) - 1);
-                for (int32_t k0 = 0; k0 < total; k0 += kStep) {
-                    const int32_t k = k0 + lane * kFly;
-                    int32_t e[kFly], dk[kFly];
-                    int32_t a = 0, z = kWave - 1;
-                    while (a < z) {
-                        const int32_t mid = (a + z + 1) >> 1;
-                        if (s_off[wv][mid] <= k) a = mid; else z = mid - 1;
-                    }
-#pragma unroll
-                    for (int q = 0; q < kFly; ++q) {
-                        e[q] = -1;
-                        dk[q] = 0;
-                        if (k + q < total) {
-                            while (s_off[wv][a + 1] <= k + q) ++a;
-                            e[q] = s_beg[wv][a] + (k + q - s_off[wv][a]);
-                            dk[q] = s_d[wv][a];
-                        }
-                    }
-                    relax4(e, dk, some);
-                }
-                __builtin_amdgcn_wave_barrier();
+    if (blockIdx.y == 0) {
+        for (int64_t b = (int64_t)blockIdx.x * per + wv * share; b < cnt; b += (int64_t)gridDim.x * per) {
+            const int64_t i = b + lane;
+            int32_t beg = 0, deg = 0, d = 0;
+            if (i < cnt && lane < share) {
+                const int32_t v = qc[i];
+                beg = rp[v];
+                deg = rp[v + 1] - beg;
+                if (deg > kHubDeg) deg = 0;  // its chunks are taken by blockIdx.y == 1
+                d = dist[v];
+                ++my_items;
+                my_edges += (unsigned long long)deg;
             }
-        } else {
-            for (int32_t k = blockIdx.x * kWaves + wv; k < nch; k += gridDim.x * kWaves) {
-                const HubEntry h = hc[oc[k]];
-                const int32_t beg = rp[h.v] + (k - h.chunk_base) * kHubChunk;
-                const int32_t end = min(rp[h.v + 1], beg + kHubChunk);
-                const int32_t d = dist[h.v];
-                my_edges += lane == 0 ? (unsigned long long)(end - beg) : 0ull;
-                for (int32_t e0 = beg; e0 < end; e0 += kStep) {
-                    int32_t e[kFly], dk[kFly];
-#pragma unroll
-                    for (int q = 0; q < kFly; ++q) {
-                        const int32_t at = e0 + q * kWave + lane;
-                        e[q] = at < end ? at : -1;
-                        dk[q] = d;
-                    }
-                    relax4(e, dk, beg);
+            const int32_t incl = wave_incl_scan(deg);
+            const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+            s_off[wv][lane] = incl - deg;
+            if (lane == 0) s_off[wv][kWave] = total;
+            s_beg[wv][lane] = beg;
+            s_d[wv][lane] = d;
+            __builtin_amdgcn_wave_barrier();
+            const int32_t some = __builtin_amdgcn_readlane(beg, __ffsll((long long)(__ballot(deg > 0) | 1ull << 63)) - 1);
+            for (int32_t k0 = 0; k0 < total; k0 += kStep) {
+                const int32_t k = k0 + lane * kFly;
+                int32_t e[kFly], dk[kFly];
+                int32_t a = 0, z = kWave - 1;
+                while (a < z) {
+                    const int32_t mid = (a + z + 1) >> 1;
+                    if (s_off[wv][mid] <= k) a = mid; else z = mid - 1;
                 }
+#pragma unroll
+                for (int q = 0; q < kFly; ++q) {
+                    e[q] = -1;
+                    dk[q] = 0;
+                    if (k + q < total) {
+                        while (s_off[wv][a + 1] <= k + q) ++a;
+                        e[q] = s_beg[wv][a] + (k + q - s_off[wv][a]);
+                        dk[q] = s_d[wv][a];
+                    }
+                }
+                relax4(e, dk, some);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    } else {
+        for (int32_t k = blockIdx.x * kWaves + wv; k < nch; k += gridDim.x * kWaves) {
+            const HubEntry h = hc[oc[k]];
+            const int32_t beg = rp[h.v] + (k - h.chunk_base) * kHubChunk;
+            const int32_t end = min(rp[h.v + 1], beg + kHubChunk);
+            const int32_t d = dist[h.v];
+            my_edges += lane == 0 ? (unsigned long long)(end - beg) : 0ull;
+            for (int32_t e0 = beg; e0 < end; e0 += kStep) {
+                int32_t e[kFly], dk[kFly];
+#pragma unroll
+                for (int q = 0; q < kFly; ++q) {
+                    const int32_t at = e0 + q * kWave + lane;
+                    e[q] = at < end ? at : -1;
+                    dk[q] = d;
+                }
+                relax4(e, dk, beg);
             }
         }
     }
-    while (ncand > 0) settle();
-    flush();
-    const int nb1 = working_blocks(nch, kWaves);
-    if (blockIdx.y == 1) working = (int)blockIdx.x < nb1;
+    while (ncand > 0) settle(std::integral_constant<int, 1>{});
+    // what the block's waves have left goes out with one atomic
+    const unsigned long long deg = wave_sum_u64(my_deg);
+    if (lane == 0) {
+        s_left[wv] = nout;
+        s_deg[wv] = deg;
+    }
+    __syncthreads();
+    int32_t before = 0;
+    for (int w = 0; w < wv; ++w) before += s_left[w];
+    if (threadIdx.x == 0) {
+        int32_t all = 0;
+        unsigned long long all_deg = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            all += s_left[w];
+            all_deg += s_deg[w];
+        }
+        if (all_deg) atomicAdd(&c->next_deg_.v, all_deg);
+        if (all) s_base = atomicAdd(&c->tail_.v, all);
+    }
+    __syncthreads();
+    write_out(s_base + before);
     if (__ballot(ovf) && lane == 0) atomicOr(&c->overflow_.v, 1);
-    block_add_u64<BS>(my_deg, s_red, &c->next_deg_.v);
     flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
-    if (last_working_block(&c->blocks_done_.v, working, nb0 + nb1) && threadIdx.x == 0)
+    if (last_working_block(&c->blocks_done_.v, true, nb0 + nb1) && threadIdx.x == 0)
         close_round(c, SSSP_PUSH, n, hub_cap, chunk_cap);
 }
 
@@ -457,7 +499,7 @@ __global__ __launch_bounds__(BS) void k_sssp_push_hops(SsspCtl *c, const int32_t
                 const int32_t nd = candidate(s_d[a], e.y, ovf);
                 bool lowered;
                 take = relax_push(dist, stamp, u, nd, r, lowered);
-                if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, u, my_deg);
+                if (take) joined(c, rp[u + 1] - rp[u], hn, on, hub_cap, chunk_cap, u, my_deg);
                 if (dst >= 0 && lowered) {
                     const int32_t at = atomicAdd(&s_ln[dst], 1);
                     if (at < kCap) {
@@ -527,7 +569,7 @@ __global__ __launch_bounds__(BS) void k_sssp_push_hops(SsspCtl *c, const int32_t
                     u = x.x;
                     bool lowered;
                     take = relax_push(dist, stamp, u, candidate(d, x.y, ovf), r, lowered);
-                    if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, u, my_deg);
+                    if (take) joined(c, rp[u + 1] - rp[u], hn, on, hub_cap, chunk_cap, u, my_deg);
                 }
                 q.stage(take, u, &c->tail_.v, qn, n, &c->capacity_.v);
             }
@@ -765,7 +807,7 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
                     dist[v] = best;
                     stamp[v] = r + 1;
                     take = true;
-                    joined(c, rp, hn, on, hub_cap, chunk_cap, v, my_deg);
+                    joined(c, deg, hn, on, hub_cap, chunk_cap, v, my_deg);
                 }
             }
             q.stage(take, v, &c->tail_.v, qn, n, &c->capacity_.v);
@@ -790,7 +832,7 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
             if (threadIdx.x == 0 && m < dist[h.v]) {
                 const int32_t old = atomicMin(&dist[h.v], m);
                 take = m < old && atomicMax(&stamp[h.v], r + 1) < r + 1;
-                if (take) joined(c, rp, hn, on, hub_cap, chunk_cap, h.v, my_deg);
+                if (take) joined(c, rp[h.v + 1] - rp[h.v], hn, on, hub_cap, chunk_cap, h.v, my_deg);
             }
             q.stage(take, h.v, &c->tail_.v, qn, n, &c->capacity_.v);
         }
