@@ -751,7 +751,7 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
                                                   HubEntry *h1, int32_t *o0, int32_t *o1,
                                                   int32_t hub_cap, int32_t chunk_cap, int32_t n,
                                                   const HubEntry *__restrict__ hs,
-                                                  const int32_t *__restrict__ os, int32_t parity,
+                                                  const int32_t *__restrict__ os, int32_t heavy, int32_t parity,
                                                   unsigned long long *prof) {
     const RoundState st = read_state(c);
     if (st.done || !st.pull || st.parity != parity) return;
@@ -766,15 +766,21 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
     q.init(s_qbuf, s_meta);
     unsigned long long my_deg = 0, my_items = 0, my_edges = 0;
     bool ovf = false;
-    const int nb0 = working_blocks(n, BS);
+    // rows numbered by rank: few of the `heavy` first ones a tile, which hold the long ones side by side
+    // (from 16 entries on, all together with others: rmat-20 3.51 ms, so 2.74)
+    constexpr int kFew = BS / 8;
+    const int32_t heavy_tiles = (heavy + kFew - 1) / kFew;
+    const int32_t tiles = heavy_tiles + (n - heavy + BS - 1) / BS;
+    const int nb0 = working_blocks(tiles, 1);
     const int nb1 = (int)min((int64_t)gridDim.x, (int64_t)nch);
     bool working;
     if (blockIdx.y == 0) {
         working = (int)blockIdx.x < nb0;
-        for (int32_t b = blockIdx.x * BS; b < n; b += gridDim.x * BS) {
-            const int32_t v = b + threadIdx.x;
+        for (int32_t b = blockIdx.x; b < tiles; b += gridDim.x) {
+            const bool few = b < heavy_tiles;
+            const int32_t v = few ? b * kFew + (int32_t)threadIdx.x : heavy + (b - heavy_tiles) * BS + (int32_t)threadIdx.x;
             int32_t beg = 0, deg = 0;
-            if (v < n) {
+            if (few ? (int)threadIdx.x < kFew && v < heavy : v < n) {
                 beg = rp[v];
                 deg = rp[v + 1] - beg;
                 if (deg > kHubDeg) deg = 0;  // its chunks are taken by blockIdx.y == 1
@@ -1049,7 +1055,8 @@ static void enqueue_rounds(sp_graph g, SsspWorkspace &ws, int rounds, int grid, 
                                (const int32_t *)rp, (const int2 *)g->adjw, ws.dist, ws.stamp, ws.queue[0],
                                ws.queue[1], ws.hubs[0], ws.hubs[1], ws.owner[0], ws.owner[1],
                                hub_cap, chunk_cap, n, (const HubEntry *)g->hub_static,
-                               (const int32_t *)g->owner_static, parity, prof_counters(P_SSSP_PULL));
+                               (const int32_t *)g->owner_static, g->sssp_ranked ? rank_count(g, 16) : 0, parity,
+                               prof_counters(P_SSSP_PULL));
         }
     }
 }
