@@ -574,29 +574,23 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     int2 *inl;
     int4 *units;
     unsigned long long *ctl;  // [0] entries that rise in (degree, id) order, [1] rows over 64
-    // Kept arrays and scratch, one block each, for me entries: half the graph's.
-    // (A graph that is not symmetric may turn out to have more.)
-    size_t me = (size_t)g->nnz / 2 + 1;
-    int64_t unit_cap = 0;
-    auto lay_out = [&](TcBlock &keep, TcBlock &work) {
-        const size_t padded = me + 8;  // 4-entry loads may run past the last row
-        unit_cap = (int64_t)me / kTcUnit + nu + 1;
-        keep.add(&orp, vn + 1);
-        keep.add(&ctl, 2);  // right behind orp: both come back in one copy
-        keep.add(&iptr, vn + 1);
-        keep.add(&oci, padded);
-        keep.add(&olo, padded);
-        keep.add(&osrc, me);
-        keep.add(&inl, me);
-        keep.add(&units, (size_t)unit_cap);
-        work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
-        work.add(&big, vn + 1);
-        work.add(&slot, me);
-        SP_TRY(keep.alloc());
-        return work.alloc();
-    };
+    // Kept arrays and scratch, one block each, for half the graph's entries.
+    const size_t me = (size_t)g->nnz / 2 + 1, padded = me + 8;  // 4-entry loads may run past the last row
+    const int64_t unit_cap = (int64_t)me / kTcUnit + nu + 1;
     TcBlock keep, work;
-    SP_TRY(lay_out(keep, work));
+    keep.add(&orp, vn + 1);
+    keep.add(&ctl, 2);  // right behind orp: both come back in one copy
+    keep.add(&iptr, vn + 1);
+    keep.add(&oci, padded);
+    keep.add(&olo, padded);
+    keep.add(&osrc, me);
+    keep.add(&inl, me);
+    keep.add(&units, (size_t)unit_cap);
+    work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
+    work.add(&big, vn + 1);
+    work.add(&slot, me);
+    SP_TRY(keep.alloc());
+    SP_TRY(work.alloc());
     hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)2);
     const int row_grid = grid_for((int64_t)n - heavy, 16, maxb);
     if (n > 0) {
@@ -616,22 +610,12 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     unsigned long long exact;
     std::memcpy(&m, back, sizeof(m));
     std::memcpy(&exact, back + to_ctl, sizeof(exact));
-    if ((int64_t)exact * 2 != g->nnz) {
-        // a simple symmetric graph orients exactly one entry of each pair
+    if ((int64_t)exact * 2 != g->nnz || (int64_t)m * 2 != g->nnz) {
+        // a simple symmetric graph orients exactly one entry of each pair, in either order
         set_error("triangle counting needs a simple undirected CSR (%lld oriented entries of %lld)",
                   (long long)exact, (long long)g->nnz);
         return SP_ERR_INVALID_ARGUMENT;
     }
-    TcBlock keep_more, work_more;
-    const bool more = (size_t)m > me;
-    if (more) {
-        const int32_t *offsets = orp;
-        me = (size_t)m;
-        SP_TRY(lay_out(keep_more, work_more));
-        SP_HIP(hipMemcpyAsync(orp, offsets, sizeof(int32_t) * (vn + 1), hipMemcpyDeviceToDevice, s));
-        hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)2);
-    }
-    TcBlock &kept = more ? keep_more : keep;
     const int ent_grid = grid_for(m, 256, 2 * maxb);
     int32_t un[2] = {0, 0};
     if (n > 0) {
@@ -673,7 +657,7 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     }
     SP_HIP(hipStreamSynchronize(s));
     if (nu <= kTcLow) un[0] = un[1];
-    g->bytes += kept.bytes;
+    g->bytes += keep.bytes;
     g->tc_oci = oci;
     g->tc_olo = olo;
     g->tc_osrc = osrc;
@@ -683,7 +667,7 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     g->tc_units_lo = un[0];
     g->tc_units_n = (int32_t)std::min<int64_t>(un[1], unit_cap);
     g->tc_m = m;
-    g->tc_orp = (int32_t *)std::exchange(kept.base, nullptr);  // the block begins with orp
+    g->tc_orp = (int32_t *)std::exchange(keep.base, nullptr);  // the block begins with orp
     return SP_OK;
 }
 
