@@ -482,9 +482,10 @@ sp_status sp_pagerank_get_last_stats(sp_pagerank_stats *out);
  * once at its lowest-degree vertex, which bounds the work by O(m^1.5); the
  * number is the same.  The graph must be simple and undirected (each edge
  * stored in both rows once, no self-loops), else SP_ERR_INVALID_ARGUMENT.
- * The oriented rows and their index (18 bytes per undirected edge + 16 per
- * vertex, up to 4 MB of work units) are built on the first call and kept
- * with the graph.
+ * Built on the first call and kept with the graph: the oriented rows of flat
+ * and small graphs (8 bytes per undirected edge + 4 per vertex), the oriented
+ * rows and their index of others (18 bytes per undirected edge + 20 per vertex,
+ * up to 4 MB of work units); where the index does not fit, the rows alone.
  * ------------------------------------------------------------------------ */
 
 typedef struct sp_tc_stats {

@@ -33,19 +33,16 @@ void clear_error() { g_err[0] = 0; }
 sp_stats &tls_stats() { return g_stats; }
 
 static std::atomic<long long> g_alloc_count{0};
-static long long alloc_fail_after() {
-    static long long v = [] {
-        const char *e = std::getenv("SP_TEST_FAIL_ALLOC_AFTER");
-        return e ? std::atoll(e) : -1ll;
-    }();
-    return v;
+static long long test_limit(const char *name) {
+    const char *e = std::getenv(name);
+    return e ? std::atoll(e) : -1ll;
 }
 
 sp_status dev_alloc(void **p, size_t bytes) {
     *p = nullptr;
-    const long long lim = alloc_fail_after();
-    if (lim >= 0 && g_alloc_count.fetch_add(1) >= lim) {
-        set_error("device allocation of %zu bytes refused by SP_TEST_FAIL_ALLOC_AFTER", bytes);
+    static const long long after = test_limit("SP_TEST_FAIL_ALLOC_AFTER"), over = test_limit("SP_TEST_FAIL_ALLOC_OVER");
+    if ((after >= 0 && g_alloc_count.fetch_add(1) >= after) || (over >= 0 && bytes > (size_t)over)) {
+        set_error("device allocation of %zu bytes refused by a test hook", bytes);
         return SP_ERR_OUT_OF_MEMORY;
     }
     hipError_t e = hipMalloc(p, std::max<size_t>(bytes, 256));
@@ -797,6 +794,7 @@ sp_status sp_graph_release(sp_graph g) {
     dev_free(g->rank_new);  // holds rank_old and rank_rp too
     dev_free(g->rank_ci);
     dev_free(g->tc_orp);
+    dev_free(g->tc_pair_orp);
     dev_free(g->hub_static);
     dev_free(g->owner_static);
     pr_plan_free(g->pr_plan);
@@ -1318,9 +1316,9 @@ sp_status sp_triangle_count(sp_graph g, int64_t *out_count, uint64_t *out_per_ve
     SP_HIP(hipEventCreate(&e1));
     SP_HIP(hipEventCreate(&e2));
     SP_TRY(dev_alloc((void **)&d_total, sizeof(unsigned long long)));
-    const bool built = g->tc_orp != nullptr;
+    const bool built = tc_built(g, out_per_vertex != nullptr);
     SP_HIP(hipEventRecord(e0, st));
-    SP_TRY(ensure_oriented(g, st));
+    SP_TRY(ensure_oriented(g, out_per_vertex != nullptr, st));
     SP_HIP(hipEventRecord(e1, st));
     SP_TRY(tc_run(g, d_total, (unsigned long long *)out_per_vertex, st));
     SP_HIP(hipEventRecord(e2, st));

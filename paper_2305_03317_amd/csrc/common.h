@@ -39,9 +39,10 @@ void clear_error();
         if (st_ < 0) return st_;            \
     } while (0)
 
-// Device allocation with an optional global test hook that makes the n-th
-// allocation fail (environment SP_TEST_FAIL_ALLOC_AFTER=n), so the
-// out-of-memory paths can be exercised without a full device.
+// Device allocation with optional global test hooks that make the n-th and
+// later allocations fail (environment SP_TEST_FAIL_ALLOC_AFTER=n), or those of
+// more than n bytes (SP_TEST_FAIL_ALLOC_OVER=n), so the out-of-memory paths can
+// be exercised without a full device.
 sp_status dev_alloc(void **p, size_t bytes);
 void dev_free(void *p);
 
@@ -126,10 +127,16 @@ struct sp_graph_s {
     uint16_t *tc_olo = nullptr;      // tc_m (+ padding): low 16 bits of tc_oci
     int32_t *tc_osrc = nullptr;      // tc_m (>= 1)
     int2 *tc_inl = nullptr;          // tc_m (>= 1)
-    int4 *tc_units = nullptr;        // tc_units_n (>= 1): {u, first, end, 0} of tc_inl
-    int32_t tc_units_lo = 0;         // units of vertices below kTcLow, listed first
-    int32_t tc_units_n = 0;
-    int64_t tc_m = 0;
+    int4 *tc_units = nullptr, *tc_units_hi = nullptr;  // {u, first, end, 0} of tc_inl: of vertices
+                                     // below kTcLow, and of the others
+    int32_t tc_units_n[2] = {0, 0};  // units of either
+    int64_t tc_m = 0;                // oriented entries, on either route
+    // Triangle counting of flat and small graphs: row v holds its neighbours above
+    // v by (degree, id), in row order, and each entry's row.
+    int32_t *tc_pair_orp = nullptr;  // device, n + 1; its allocation holds the arrays below too
+    int32_t *tc_pair_oci = nullptr, *tc_pair_osrc = nullptr;  // tc_m
+    bool tc_mixed = false;           // some row is not ascending: never by pairs
+    bool tc_no_index = false;        // the index did not fit: always by pairs
     size_t weight_bytes = 0, hub_bytes = 0;
     std::mutex weights_mu;           // one replacement of the weights at a time
     // Counts what replaced any array above that the rounds read: captured rounds
@@ -659,7 +666,9 @@ sp_status pr_run(sp_graph g, PrWorkspace &ws, double beta, double delta, int32_t
 // Triangle counting (tc_path.hip)
 // ---------------------------------------------------------------------------
 // Builds the oriented rows once per graph (thread-safe).
-sp_status ensure_oriented(sp_graph g, hipStream_t s);
+sp_status ensure_oriented(sp_graph g, bool per, hipStream_t s);
+// Whether that is done already for such a count.
+bool tc_built(sp_graph g, bool per);
 // Adds the graph's triangle count to *d_total (device, zeroed here) and, when
 // per is not null, each vertex's triangle count to per[v] (zeroed here).
 sp_status tc_run(sp_graph g, unsigned long long *d_total, unsigned long long *per, hipStream_t s);

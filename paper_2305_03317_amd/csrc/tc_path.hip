@@ -21,6 +21,9 @@
 // The oriented rows are built once per graph: row lengths, a scan, a
 // compacting copy, each row sorted (in registers, through an LDS bitmap, or by
 // a bitonic network), the entries that name each vertex, and the work units.
+//
+// On flat and small graphs the rows are short and that index costs more than
+// it saves: they are counted by binary searches, entry by entry (tc_by_pairs).
 #include <utility>
 
 #include "common.h"
@@ -40,11 +43,166 @@ constexpr int32_t kTcSortBits = 1 << 19;  // rows of lower ids are sorted throug
 constexpr int32_t kTcHot = 4096;      // ids whose names are counted in LDS first
 constexpr int32_t kTcNamedTile = 1 << 15, kTcNamedLeast = 1 << 11;  // entries of a block's tile
 constexpr int32_t kTcSortCap = 8192;   // bitonic rows (a row of a higher id holds under 4,400 entries)
+constexpr int32_t kTcFlat = 48;        // see tc_by_pairs
+constexpr int64_t kTcSmall = 1 << 17, kTcLight = 1 << 27;
 }  // namespace
 
 // rank(a) < rank(b): lower degree, ties broken by id.
 __device__ __forceinline__ bool rank_below(int32_t da, int32_t a, int32_t db, int32_t b) {
     return da < db || (da == db && a < b);
+}
+
+// ---------------------------------------------------------------------------
+// Pairs: flat and small graphs (tc_by_pairs), where an index costs more than it
+// saves.  Row v keeps the neighbours above v by (degree, id), in row order, and
+// every entry (v, u) searches the elements of the shorter of the two rows in
+// the longer one.
+// ---------------------------------------------------------------------------
+// Row lengths, LPR lanes to a row.  found[0]: entries that rise by rank (as
+// ensure_rank_locked orders them), found[1]: rows that are not ascending.
+template <int LPR>
+__global__ __launch_bounds__(256) void k_tc_pair_len(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                                                     int32_t n, int32_t *odeg, unsigned long long *found) {
+    __shared__ unsigned long long s_red[1];
+    const int l = threadIdx.x % LPR;
+    unsigned long long by_rank = 0;
+    bool mixed = false;
+    for (int64_t v = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; v < n;
+         v += (int64_t)gridDim.x * (256 / LPR)) {
+        const int32_t b = rp[v], e = rp[v + 1], dv = e - b, bv = rank_bucket(dv);
+        int32_t d = 0;
+        for (int32_t k = b + l; k < e; k += LPR) {
+            const int32_t u = ci[k], du = rp[u + 1] - rp[u], bu = rank_bucket(du);
+            d += rank_below(dv, (int32_t)v, du, u);
+            by_rank += bu < bv || (bu == bv && u > v);
+            mixed |= k > b && u < ci[k - 1];
+        }
+        for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, kWave);
+        if (l == 0) odeg[v] = d;
+    }
+    if (__ballot(mixed) && lane_id() == 0) atomicOr(&found[1], 1ull);
+    block_add_u64<256>(by_rank, s_red, &found[0]);
+}
+
+template <int LPR>
+__global__ __launch_bounds__(256) void k_tc_pair_fill(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                                                      int32_t n, const int32_t *__restrict__ orp, int32_t *oci,
+                                                      int32_t *osrc) {
+    const int l = threadIdx.x % LPR;
+    for (int64_t v = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; v < n;
+         v += (int64_t)gridDim.x * (256 / LPR)) {
+        const int32_t b = rp[v], e = rp[v + 1], dv = e - b;
+        int32_t at = orp[v];
+        for (int32_t k0 = b; k0 < e; k0 += LPR) {
+            const int32_t k = k0 + l;
+            int32_t u = 0;
+            bool keep = false;
+            if (k < e) {
+                u = ci[k];
+                keep = rank_below(dv, (int32_t)v, rp[u + 1] - rp[u], u);
+            }
+            const unsigned long long m = LPR == 1 ? (unsigned long long)keep : __ballot(keep);
+            if (keep) {
+                const int32_t p = at + (LPR == 1 ? 0 : lanes_below(m));
+                oci[p] = u;
+                osrc[p] = (int32_t)v;
+            }
+            at += __popcll(m);
+        }
+    }
+}
+
+// First position in a[lo, hi) holding a value >= x.
+__device__ __forceinline__ int32_t lower_bound(const int32_t *__restrict__ a, int32_t lo, int32_t hi,
+                                               int32_t x) {
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (a[mid] < x) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// The entries of a wave, one per lane.  Where the shorter row has at most
+// kTcLaneWork elements the lane walks it, the search window shrinking as the
+// walk moves up; longer ones are taken by the whole wave in turn.  per: each
+// triangle counts at its three vertices (those of the entry once for all of
+// its triangles).
+constexpr int32_t kTcLaneWork = 32;
+
+__global__ __launch_bounds__(256) void k_tc_pairs(const int32_t *__restrict__ orp, const int32_t *__restrict__ oci,
+                                                  const int32_t *__restrict__ osrc, int64_t m,
+                                                  unsigned long long *total, unsigned long long *per,
+                                                  unsigned long long *prof) {
+    __shared__ unsigned long long s_red[1];
+    const int lane = lane_id();
+    unsigned long long mine = 0, probes = 0;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x - lane; e0 < m; e0 += stride) {
+        const int64_t e = e0 + lane;
+        int32_t v = 0, u = 0, sb = 0, se = 0, lb = 0, le = 0;
+        if (e < m) {
+            v = osrc[e];
+            u = oci[e];
+            sb = orp[v];
+            se = orp[v + 1];
+            lb = orp[u];
+            le = orp[u + 1];
+            if (se - sb > le - lb) {  // walk the shorter row
+                int32_t t = sb; sb = lb; lb = t;
+                t = se; se = le; le = t;
+            }
+        }
+        const bool alone = se - sb <= kTcLaneWork;
+        if (alone) {
+            int32_t pos = lb;
+            unsigned int hits = 0;
+            for (int32_t i = sb; i < se && pos < le; ++i) {
+                const int32_t w = oci[i];
+                pos = lower_bound(oci, pos, le, w);
+                ++probes;
+                if (pos < le && oci[pos] == w) {
+                    ++hits;
+                    ++pos;
+                    if (per) atomicAdd(&per[w], 1ull);
+                }
+            }
+            mine += hits;
+            if (per && hits) {
+                atomicAdd(&per[v], (unsigned long long)hits);
+                atomicAdd(&per[u], (unsigned long long)hits);
+            }
+        }
+        unsigned long long big = __ballot(!alone);
+        while (big) {
+            const int src = __ffsll((long long)big) - 1;
+            big &= big - 1;
+            const int32_t bsb = __shfl(sb, src, kWave), bse = __shfl(se, src, kWave);
+            const int32_t blb = __shfl(lb, src, kWave), ble = __shfl(le, src, kWave);
+            unsigned long long hits = 0;
+            for (int32_t i = bsb + lane; i < bse; i += kWave) {
+                const int32_t w = oci[i];
+                const int32_t pos = lower_bound(oci, blb, ble, w);
+                ++probes;
+                if (pos < ble && oci[pos] == w) {
+                    ++hits;
+                    if (per) atomicAdd(&per[w], 1ull);
+                }
+            }
+            mine += hits;
+            if (per) {
+                hits = wave_sum_u64(hits);
+                if (lane == src && hits) {
+                    atomicAdd(&per[v], hits);
+                    atomicAdd(&per[u], hits);
+                }
+            }
+        }
+    }
+    block_add_u64<256>(mine, s_red, total);
+    if (prof) {
+        __syncthreads();
+        block_add_u64<256>(probes, s_red, prof + 1);
+    }
 }
 
 // Whether a vertex is counted with an LDS bitmap.  Marking and clearing one
@@ -70,7 +228,8 @@ __device__ __forceinline__ void tc_rows(const int32_t *__restrict__ rp, const in
     }
 }
 
-// Row lengths: odeg[v] = neighbours of v of lower rank number.  exact: how
+// Row lengths: odeg[v] = neighbours of v of lower rank number (and named[v]
+// cleared for k_tc_named).  exact: how
 // many entries rise in the (degree, id) order, which is half of them exactly
 // when a graph is simple and undirected (the two orders differ only between
 // vertices of degree >= kRankExact).
@@ -79,7 +238,7 @@ __global__ __launch_bounds__(256) void k_tc_outdeg(const int32_t *__restrict__ r
                                                    const int32_t *__restrict__ ci,
                                                    const int32_t *__restrict__ rank_new,
                                                    const int32_t *__restrict__ rank_old, int32_t first,
-                                                   int32_t n, int32_t heavy, int32_t *odeg,
+                                                   int32_t n, int32_t heavy, int32_t *odeg, int32_t *named,
                                                    unsigned long long *exact) {
     __shared__ unsigned long long s_red[1];
     __shared__ int32_t s_sum;
@@ -99,11 +258,17 @@ __global__ __launch_bounds__(256) void k_tc_outdeg(const int32_t *__restrict__ r
             __syncthreads();
             if (d) atomicAdd(&s_sum, d);
             __syncthreads();
-            if (threadIdx.x == 0) odeg[v] = s_sum;
+            if (threadIdx.x == 0) {
+                odeg[v] = s_sum;
+                named[v] = 0;
+            }
             __syncthreads();
         } else {
             for (int o = 8; o > 0; o >>= 1) d += __shfl_xor(d, o, kWave);
-            if (l == 0) odeg[v] = d;
+            if (l == 0) {
+                odeg[v] = d;
+                named[v] = 0;
+            }
         }
     });
     block_add_u64<256>(ex, s_red, exact);
@@ -315,23 +480,41 @@ __global__ void k_tc_inlist(const int32_t *__restrict__ oci, const int32_t *__re
         inl[iptr[oci[e]] + slot[e]] = make_int2(orp[osrc[e]], (int32_t)e);
 }
 
-// Work units of the vertices counted with a bitmap.
-__global__ void k_tc_unit_count(const int32_t *__restrict__ iptr, int32_t nu, int32_t *cnt) {
-    const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nu; u += stride) {
-        const int32_t named = iptr[u + 1] - iptr[u];
-        cnt[u] = tc_heavy(u, named) ? (named + kTcUnit - 1) / kTcUnit : 0;
-    }
+// Work units of the vertices counted with a bitmap: those of ids below kTcLow
+// and the others, in lists of their own, by id (in the order that an atomic per
+// wave gives them the count of rmat-18, edge factor 32, took 324 us, not 277).
+// A block's 256 ids lie on one side of kTcLow; first its sum, then its places.
+__device__ __forceinline__ int32_t tc_unit_count(const int32_t *__restrict__ iptr, int32_t u, int32_t nu) {
+    if (u >= nu) return 0;
+    const int32_t named = iptr[u + 1] - iptr[u];
+    return tc_heavy(u, named) ? (named + kTcUnit - 1) / kTcUnit : 0;
 }
 
-__global__ void k_tc_unit_fill(const int32_t *__restrict__ iptr, int32_t nu, const int32_t *__restrict__ first,
-                               int4 *units, int64_t cap) {
-    const int32_t stride = gridDim.x * blockDim.x;
-    for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < nu; u += stride) {
-        const int32_t b = iptr[u], e = iptr[u + 1];
-        for (int32_t k = first[u], j = b; k < first[u + 1] && k < cap; ++k, j += kTcUnit)
-            units[k] = make_int4(u, j, min(e, j + kTcUnit), 0);
-    }
+__global__ __launch_bounds__(256) void k_tc_unit_sums(const int32_t *__restrict__ iptr, int32_t nu, int32_t *sums) {
+    __shared__ int32_t s_scan[256 / kWave + 1];
+    int32_t all;
+    (void)block_excl_scan<256>(tc_unit_count(iptr, blockIdx.x * 256 + threadIdx.x, nu), s_scan, &all);
+    if (threadIdx.x == 0) sums[blockIdx.x] = all;
+}
+
+__global__ __launch_bounds__(256) void k_tc_units(const int32_t *__restrict__ iptr, int32_t nu,
+                                                  const int32_t *__restrict__ sums, int32_t *count, int4 *lo, int4 *hi,
+                                                  int32_t lo_cap, int32_t hi_cap) {
+    __shared__ int32_t s_scan[256 / kWave + 1];
+    const int32_t u = blockIdx.x * 256 + threadIdx.x;
+    const bool low = u < kTcLow;
+    int32_t before = 0, mine = tc_unit_count(iptr, u, nu), base, all;
+    for (int32_t b = (low ? 0 : kTcLow / 256) + (int32_t)threadIdx.x; b < (int32_t)blockIdx.x; b += 256)
+        before += sums[b];
+    (void)block_excl_scan<256>(before, s_scan, &base);
+    int32_t at = base + block_excl_scan<256>(mine, s_scan, &all);
+    int4 *units = low ? lo : hi;
+    const int32_t cap = low ? lo_cap : hi_cap;
+    if (threadIdx.x == 0 && (u + 256 >= nu || u + 256 == kTcLow)) count[low ? 0 : 1] = base + all;
+    if (mine == 0) return;
+    const int32_t b = iptr[u], e = iptr[u + 1];
+    for (int32_t k = 0; k < mine && at + k < cap; ++k)
+        units[at + k] = make_int4(u, b + k * kTcUnit, min(e, b + (k + 1) * kTcUnit), 0);
 }
 
 // Triangles by their middle vertex.  A block takes a unit {u, entries naming
@@ -447,16 +630,6 @@ __global__ __launch_bounds__(256) void k_tc_heavy(const int32_t *__restrict__ or
     }
 }
 
-// First position in a[lo, hi) holding a value >= x.
-__device__ __forceinline__ int32_t lower_bound(const int32_t *__restrict__ a, int32_t lo, int32_t hi,
-                                               int32_t x) {
-    while (lo < hi) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        if (a[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // Triangles whose middle vertex u has no bitmap: a wave takes kTcLightIds
 // consecutive vertices, and 16 lanes per entry (v, u) that names one of them
 // search the elements of the shorter of N(u) and N(v)'s entries before u in
@@ -560,8 +733,90 @@ struct TcBlock {
 };
 }  // namespace
 
-sp_status ensure_oriented(sp_graph g, hipStream_t s) {
+// Which graphs are counted by pairs rather than by bitmaps: flat ones (rows of
+// at most kTcFlat entries); others without an index yet, that are small
+// (kTcSmall entries; an eighth of it where the vertices' shares are counted too,
+// an atomic for every triangle) or light (entries x longest row).  First and
+// later counts, us, by pairs and by bitmaps:
+//   uniform, 2^20 vertices, 16.8 M entries, rows to 41     1426  643    2506  804
+//   uniform, 2^20 vertices, 33.5 M entries, rows to 63     4742 2360    4205 1493
+//   road grid, 2.25 M vertices                              205   59    1290  112
+//   rmat-12, 97,000 entries                                 175  111     318   95
+//   rmat-13, 204,000 entries, rows to 2,228                 325  143     314   99
+//   uniform, 8,192 vertices, 0.5 M entries, rows to 96      250  110     426  135
+//   uniform, 65,536 vertices, 4.2 M entries, rows to 108    660  458     658  221
+static bool tc_by_pairs(sp_graph g, bool per) {
+    if (g->tc_mixed) return false;
+    if (g->max_degree <= kTcFlat || g->tc_no_index) return true;
+    if (g->tc_orp) return false;
+    return per ? g->nnz <= kTcSmall / 8 : g->nnz <= kTcSmall || g->nnz * g->max_degree <= kTcLight;
+}
+
+bool tc_built(sp_graph g, bool per) {
     std::lock_guard<std::mutex> lk(g->mu);
+    return (tc_by_pairs(g, per) ? g->tc_pair_orp : g->tc_orp) != nullptr;
+}
+
+static sp_status refuse_csr(sp_graph g, long long kept) {
+    set_error("triangle counting needs a simple undirected CSR (%lld oriented entries of %lld)", kept,
+              (long long)g->nnz);
+    return SP_ERR_INVALID_ARGUMENT;
+}
+
+// The oriented rows of the pair route; *mixed (rows that are not ascending)
+// leaves the graph to the bitmaps, whose rows are sorted.
+static sp_status ensure_pairs(sp_graph g, bool *mixed, hipStream_t s) {
+    *mixed = false;
+    if (g->tc_pair_orp) return SP_OK;
+    const int32_t n = g->n;
+    const size_t vn = (size_t)std::max(n, 1), me = (size_t)g->nnz / 2;
+    const int maxb = device_cu_count() * 8;
+    int32_t *orp, *oci, *osrc, *tiles;
+    unsigned long long *found;
+    TcBlock keep, work;
+    keep.add(&orp, vn + 1);
+    keep.add(&found, 2);  // right behind orp: both come back in one copy
+    keep.add(&oci, me + 1);
+    keep.add(&osrc, me + 1);
+    work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
+    SP_TRY(keep.alloc());
+    SP_TRY(work.alloc());
+    const int32_t *rp = g->row_ptr, *ci = g->col_idx;
+    hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, found, (int64_t)2);
+    const bool wide = g->max_degree > kTcFlat;  // a wave per row, else a lane
+    const dim3 grid(grid_for(n, wide ? 4 : 256, maxb));
+    if (n > 0)
+        hipLaunchKernelGGL(wide ? k_tc_pair_len<kWave> : k_tc_pair_len<1>, grid, dim3(256), 0, s, rp, ci, n, orp, found);
+    launch_excl_scan(orp, n, orp, tiles, s);
+    SP_HIP(hipGetLastError());
+    char back[512];  // from orp[n], at most 256 bytes before found
+    const size_t to_found = (size_t)((char *)found - (char *)(orp + n));
+    SP_HIP(hipMemcpyAsync(back, orp + n, to_found + 2 * sizeof(*found), hipMemcpyDeviceToHost, s));
+    SP_HIP(hipStreamSynchronize(s));
+    int32_t m;
+    unsigned long long got[2];
+    std::memcpy(&m, back, sizeof(m));
+    std::memcpy(got, back + to_found, sizeof(got));
+    if ((int64_t)m * 2 != g->nnz || (int64_t)got[0] * 2 != g->nnz) return refuse_csr(g, m);
+    if (got[1]) {
+        *mixed = true;
+        return SP_OK;
+    }
+    if (m > 0)
+        hipLaunchKernelGGL(wide ? k_tc_pair_fill<kWave> : k_tc_pair_fill<1>, grid, dim3(256), 0, s, rp, ci, n,
+                           (const int32_t *)orp, oci, osrc);
+    SP_HIP(hipGetLastError());
+    SP_HIP(hipStreamSynchronize(s));
+    g->bytes += keep.bytes;
+    g->tc_pair_oci = oci;
+    g->tc_pair_osrc = osrc;
+    g->tc_m = m;
+    g->tc_pair_orp = (int32_t *)std::exchange(keep.base, nullptr);  // the block begins with orp
+    return SP_OK;
+}
+
+// The oriented rows and the index of the bitmap route.
+static sp_status ensure_index(sp_graph g, hipStream_t s) {
     if (g->tc_orp) return SP_OK;
     SP_TRY(ensure_rank_locked(g, s));
     const int32_t n = g->n, heavy = rank_count(g, kRankExact);
@@ -573,32 +828,35 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     uint16_t *olo;
     int2 *inl;
     int4 *units;
-    unsigned long long *ctl;  // [0] entries that rise in (degree, id) order, [1] rows over 64
+    unsigned long long *ctl;  // [0] entries that rise in (degree, id) order, [1] rows over 64, [2] units by list
     // Kept arrays and scratch, one block each, for half the graph's entries.
     const size_t me = (size_t)g->nnz / 2 + 1, padded = me + 8;  // 4-entry loads may run past the last row
-    const int64_t unit_cap = (int64_t)me / kTcUnit + nu + 1;
+    // units: one per kTcUnit entries, and a last one for each vertex that 8 entries or more name
+    const int32_t lows = std::min(nu, kTcLow), rest = (int32_t)std::min<int64_t>(nu, (int64_t)me / 8);
+    const int32_t lo_cap = (int32_t)(me / kTcUnit) + std::min(lows, rest) + 1;
+    const int32_t hi_cap = nu > lows ? (int32_t)(me / kTcUnit) + std::min(nu - lows, rest) + 1 : 0;
     TcBlock keep, work;
     keep.add(&orp, vn + 1);
-    keep.add(&ctl, 2);  // right behind orp: both come back in one copy
+    keep.add(&ctl, 3);  // right behind orp: both come back in one copy
     keep.add(&iptr, vn + 1);
     keep.add(&oci, padded);
     keep.add(&olo, padded);
     keep.add(&osrc, me);
     keep.add(&inl, me);
-    keep.add(&units, (size_t)unit_cap);
+    keep.add(&units, (size_t)lo_cap + (size_t)hi_cap);
     work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
-    work.add(&big, vn + 1);
+    work.add(&big, vn);
     work.add(&slot, me);
     SP_TRY(keep.alloc());
     SP_TRY(work.alloc());
-    hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)2);
+    hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, ctl, (int64_t)3);
     const int row_grid = grid_for((int64_t)n - heavy, 16, maxb);
     if (n > 0) {
         if (heavy)
             hipLaunchKernelGGL(k_tc_outdeg<true>, dim3(std::min(heavy, maxb)), dim3(256), 0, s, rp, ci, rn, ro, 0,
-                               heavy, heavy, orp, ctl);
+                               heavy, heavy, orp, iptr, ctl);
         hipLaunchKernelGGL(k_tc_outdeg<false>, dim3(row_grid), dim3(256), 0, s, rp, ci, rn, ro, heavy, n, heavy,
-                           orp, ctl);
+                           orp, iptr, ctl);
     }
     launch_excl_scan(orp, n, orp, tiles, s);
     SP_HIP(hipGetLastError());
@@ -612,9 +870,7 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     std::memcpy(&exact, back + to_ctl, sizeof(exact));
     if ((int64_t)exact * 2 != g->nnz || (int64_t)m * 2 != g->nnz) {
         // a simple symmetric graph orients exactly one entry of each pair, in either order
-        set_error("triangle counting needs a simple undirected CSR (%lld oriented entries of %lld)",
-                  (long long)exact, (long long)g->nnz);
-        return SP_ERR_INVALID_ARGUMENT;
+        return refuse_csr(g, (long long)exact);
     }
     const int ent_grid = grid_for(m, 256, 2 * maxb);
     int32_t un[2] = {0, 0};
@@ -637,7 +893,6 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
         if (n > kTcSortBits)
             hipLaunchKernelGGL(k_tc_sort_net, dim3(maxb), dim3(256), 0, s, (const int32_t *)orp, oci,
                                (const int32_t *)big, (const int32_t *)nbig, kTcSortBits);
-        SP_TRY(launch_fill_i32(iptr, n, 0, s));
         int32_t tile = kTcNamedLeast;
         while (tile < kTcNamedTile && (int64_t)tile * device_cu_count() < m) tile *= 2;
         hipLaunchKernelGGL(k_tc_named, dim3(grid_for(m, tile, maxb)), dim3(256), 0, s, (const int32_t *)oci,
@@ -645,18 +900,15 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
         launch_excl_scan(iptr, n, iptr, tiles, s);
         hipLaunchKernelGGL(k_tc_inlist, dim3(ent_grid), dim3(256), 0, s, (const int32_t *)oci, (const int32_t *)osrc,
                            (const int32_t *)orp, (const int32_t *)iptr, (const int32_t *)slot, (int64_t)m, inl);
-        int32_t *first = big;  // nu + 1 <= vn + 1 values; the row list is done with
-        hipLaunchKernelGGL(k_tc_unit_count, dim3(grid_for(nu, 256, maxb)), dim3(256), 0, s, (const int32_t *)iptr, nu,
-                           first);
-        launch_excl_scan(first, nu, first, tiles, s);
-        hipLaunchKernelGGL(k_tc_unit_fill, dim3(grid_for(nu, 256, maxb)), dim3(256), 0, s, (const int32_t *)iptr, nu,
-                           (const int32_t *)first, units, unit_cap);
+        int32_t *count = (int32_t *)(ctl + 2);
+        const int32_t blocks = (nu + 255) / 256;  // at most `big`'s length; the row list is done with
+        hipLaunchKernelGGL(k_tc_unit_sums, dim3(blocks), dim3(256), 0, s, (const int32_t *)iptr, nu, big);
+        hipLaunchKernelGGL(k_tc_units, dim3(blocks), dim3(256), 0, s, (const int32_t *)iptr, nu, (const int32_t *)big,
+                           count, units, units + lo_cap, lo_cap, hi_cap);
         SP_HIP(hipGetLastError());
-        SP_HIP(hipMemcpyAsync(&un[1], first + nu, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        if (nu > kTcLow) SP_HIP(hipMemcpyAsync(&un[0], first + kTcLow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        SP_HIP(hipMemcpyAsync(un, count, sizeof(un), hipMemcpyDeviceToHost, s));
     }
     SP_HIP(hipStreamSynchronize(s));
-    if (nu <= kTcLow) un[0] = un[1];
     g->bytes += keep.bytes;
     g->tc_oci = oci;
     g->tc_olo = olo;
@@ -664,25 +916,43 @@ sp_status ensure_oriented(sp_graph g, hipStream_t s) {
     g->tc_iptr = iptr;
     g->tc_inl = inl;
     g->tc_units = units;
-    g->tc_units_lo = un[0];
-    g->tc_units_n = (int32_t)std::min<int64_t>(un[1], unit_cap);
+    g->tc_units_hi = units + lo_cap;
+    g->tc_units_n[0] = std::min(un[0], lo_cap);
+    g->tc_units_n[1] = std::min(un[1], hi_cap);
     g->tc_m = m;
     g->tc_orp = (int32_t *)std::exchange(keep.base, nullptr);  // the block begins with orp
     return SP_OK;
+}
+
+sp_status ensure_oriented(sp_graph g, bool per, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(g->mu);
+    if (tc_by_pairs(g, per)) {
+        SP_TRY(ensure_pairs(g, &g->tc_mixed, s));
+        if (!g->tc_mixed) return SP_OK;
+    }
+    sp_status st = ensure_index(g, s);
+    if (st == SP_ERR_OUT_OF_MEMORY && !g->tc_mixed) {  // pairs take less than half of the memory
+        clear_error();
+        SP_TRY(ensure_pairs(g, &g->tc_mixed, s));
+        if (g->tc_mixed) return ensure_index(g, s);
+        g->tc_no_index = true;
+        return SP_OK;
+    }
+    return st;
 }
 
 template <bool PER>
 static void launch_tc_count(sp_graph g, unsigned long long *d_total, unsigned long long *per, hipStream_t s) {
     const int maxb = device_cu_count() * 8;
     unsigned long long *prof = prof_counters(P_TC_COUNT);
-    const int32_t lo = g->tc_units_lo, hi = g->tc_units_n - lo;
+    const int32_t lo = g->tc_units_n[0], hi = g->tc_units_n[1];
     auto heavy = [&](auto kernel, const int4 *units, int32_t count) {
         hipLaunchKernelGGL(kernel, dim3(std::min(count, maxb)), dim3(256), 0, s, (const int32_t *)g->tc_orp,
                            (const int32_t *)g->tc_oci, (const uint16_t *)g->tc_olo, (const int32_t *)g->tc_osrc,
                            (const int2 *)g->tc_inl, units, count, (const int32_t *)g->rank_old, d_total, per, prof);
     };
     if (lo > 0) heavy(k_tc_heavy<kTcLow, true, PER>, g->tc_units, lo);
-    if (hi > 0) heavy(k_tc_heavy<kTcBits, false, PER>, g->tc_units + lo, hi);
+    if (hi > 0) heavy(k_tc_heavy<kTcBits, false, PER>, g->tc_units_hi, hi);
     hipLaunchKernelGGL(k_tc_light, dim3(grid_for(g->n, kTcLightIds * (256 / kWave), 2 * maxb)), dim3(256), 0, s, (const int32_t *)g->tc_orp,
                        (const int32_t *)g->tc_oci, (const int32_t *)g->tc_osrc, (const int32_t *)g->tc_iptr,
                        (const int2 *)g->tc_inl, g->n, (const int32_t *)g->rank_old, d_total, per, prof);
@@ -691,9 +961,19 @@ static void launch_tc_count(sp_graph g, unsigned long long *d_total, unsigned lo
 sp_status tc_run(sp_graph g, unsigned long long *d_total, unsigned long long *per, hipStream_t s) {
     hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, s, d_total, (int64_t)1);
     if (per) hipLaunchKernelGGL(k_tc_zero, dim3(grid_for(g->n, 256, 4096)), dim3(256), 0, s, per, (int64_t)g->n);
+    bool pairs;
+    {
+        std::lock_guard<std::mutex> lk(g->mu);
+        pairs = tc_by_pairs(g, per != nullptr) && g->tc_pair_orp;
+    }
     if (g->tc_m > 0) {
         ProfScope ps(P_TC_COUNT, s);
-        if (per) launch_tc_count<true>(g, d_total, per, s);
+        if (pairs)
+            hipLaunchKernelGGL(k_tc_pairs, dim3(grid_for(g->tc_m, 256, device_cu_count() * 8)), dim3(256), 0, s,
+                               (const int32_t *)g->tc_pair_orp, (const int32_t *)g->tc_pair_oci,
+                               (const int32_t *)g->tc_pair_osrc, (int64_t)g->tc_m, d_total, per,
+                               prof_counters(P_TC_COUNT));
+        else if (per) launch_tc_count<true>(g, d_total, per, s);
         else launch_tc_count<false>(g, d_total, nullptr, s);
     }
     SP_HIP(hipGetLastError());

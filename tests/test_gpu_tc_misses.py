@@ -8,6 +8,9 @@ other takes."""
 from __future__ import annotations
 
 import math
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -15,6 +18,22 @@ import pytest
 from paper_2305_03317_amd import graphs
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+CHILD = r"""
+import sys, numpy as np
+sys.path.insert(0, %r)
+import oracle
+from paper_2305_03317_amd import graphs, sp
+rp, ci = graphs.rmat(14, 16, seed=5)
+g = sp.sp_graph_upload(rp, ci)
+for per in (True, False, True):
+    total, each = sp.sp_triangle_count(g, per_vertex=per)
+    assert total == oracle.triangles(rp, ci)
+    assert not per or np.array_equal(each.cpu().numpy().astype(np.int64), oracle.triangles_each(rp, ci))
+print("ok", sp.sp_graph_info(g))
+""" % ROOT
 
 
 def multipartite(parts: int, size: int, copies: int):
@@ -69,3 +88,34 @@ def test_one_way_entries_are_refused_whatever_order_they_rise_in(copies):
         sp.sp_triangle_count(g)
     assert e.value.status == sp.SP_ERR_INVALID_ARGUMENT
     g.release()
+
+
+@pytest.mark.parametrize("first", [False, True])
+@pytest.mark.parametrize("name", ["flat", "light", "small", "shuffled flat", "shuffled small", "skewed"])
+def test_routes_against_the_oracle(name, first):
+    """Both kinds of count on one graph, in either order; rows in any order within a row."""
+    import oracle
+    from paper_2305_03317_amd import sp
+    print(name, first, flush=True)
+    kind = name.split()[-1]
+    rp, ci = {"flat": lambda: graphs.uniform(6000, 60000, 3), "light": lambda: graphs.uniform(3000, 110000, 3),
+              "small": lambda: graphs.rmat(11, 8, seed=5), "skewed": lambda: graphs.rmat(14, 16, seed=5)}[kind]()
+    total, each = oracle.triangles(rp, ci), oracle.triangles_each(rp, ci)
+    if name.startswith("shuffled"):
+        rng = np.random.default_rng(4)
+        ci = np.concatenate([rng.permutation(ci[rp[v]:rp[v + 1]]) for v in range(len(rp) - 1)]).astype(np.int32)
+    g = sp.sp_graph_upload(rp, ci)
+    for per in (first, not first, first):
+        got, seen = sp.sp_triangle_count(g, per_vertex=per)
+        assert got == total
+        if per:
+            assert np.array_equal(seen.cpu().numpy().astype(np.int64), each)
+    assert sp.sp_tc_get_last_stats()["oriented_edges"] * 2 == len(ci)
+    g.release()
+
+
+def test_index_that_does_not_fit():
+    """No allocation over 2.5 MB: the rows alone (1.8 MB) serve where the index (4 MB) does not fit."""
+    env = dict(os.environ, SP_TEST_FAIL_ALLOC_OVER="2500000")
+    r = subprocess.run([sys.executable, "-c", CHILD], env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), (r.stdout, r.stderr)
