@@ -597,16 +597,17 @@ struct PrCtl {
     int32_t max_iter;
     double beta;         // continue while diff > beta
     double last_diff;    // diff of the last iteration run
-    HotU64 diff_;        // this iteration's sum of |change|, fixed point (2^-kPrDiffBits units)
+    HotU64 diff_;        // this iteration's sum of |change|, fixed point (1 / kPrDiffUnit)
     HotI32 blocks_done_; // working blocks of the closing kernel that finished
 };
-// Each wave rounds its sum of |change| over a tile's rows to a multiple of
-// 2^-60, and the rounded sums are added as integers: the total is the same
-// whatever the order, so the stopping decision is reproducible.  Its error is
-// at most 2^-61 a wave and tile (3e-14 for 4.2 M vertices, 2e-16 expected); the sum itself is at most 2 (the values
-// start at 1/N and each iteration's total is at most 1), below the 16 that
-// 64 bits hold at this scale.
-constexpr int kPrDiffBits = 60;
+// Each block rounds its sum of |change| to a multiple of 2^-62, and so does the
+// block that settles a row cut into pieces (8,192 entries or more); these are added
+// with integer atomics: the total is the same whatever the order, so the
+// stopping decision is reproducible.  Its error is at most 2^-63 for each of
+// them (under 1e-15 for 8,192 blocks and rows); the sum itself is at most 2 (the
+// values start at 1/N and each iteration's total is at most 1), below the 4
+// that 64 bits hold at this scale.
+constexpr double kPrDiffUnit = 0x1p62;
 
 // The rows PageRank gathers, sorted by length class.  Vertices may be
 // renumbered by degree rank ("ids" below; the vertex of id x is old[x]).

@@ -8,15 +8,14 @@
 // the reversed graph on a directed one; outdeg is always the outgoing row's
 // length, and a vertex without outgoing arcs passes nothing on.
 //
-// Design: each iteration is one pass over the entries.  The producer of a
-// value also stores share = val / outdeg, so the gather reads one double per
-// entry.  A plan made once per graph (ensure_pr_plan) lists the rows by length
-// class, and each class gives a row the lanes its length fills: 1 for up to 8
-// entries (summed in row order), 4 up to 32, 16 up to 128, 64 below 512, a
-// block from there on; rows longer than a 256th of all entries (at least
-// 16,384) are cut into pieces, whose sums a finishing kernel adds.  A lane
-// adds entries j, j + lanes, ... in order, four loads in flight, and a fixed
-// tree adds the lanes, so a vertex's sum depends only on its row.
+// Design: each iteration is one pass over the entries and one launch.  The
+// producer of a value also stores share = val / outdeg, so the gather reads one
+// double per entry.  A plan made once per graph (ensure_pr_plan) lists the rows by
+// length class, and each class gives a row the lanes its length fills: 1 for up to
+// 8 entries (summed in row order), 4 up to 32, 16 up to 128, 64 below 512, a
+// block from there on; rows of 8,192 entries and more are cut into pieces of that
+// many, and the last piece of a row to arrive adds their sums.  A lane adds entries j, j + lanes, ... in order, four loads in flight,
+// and a fixed tree adds the lanes, so a vertex's sum depends only on its row.
 //
 // On large skewed graphs the plan renumbers the vertices by degree rank: the
 // shares that most entries gather then fill consecutive lines that stay in
@@ -27,9 +26,10 @@
 // in LDS.  rmat-22: 1.09 -> 0.68 ms per iteration; rmat-15, where latency and
 // the number of launches count: 43 -> 13 us.
 //
-// The stopping test sums |val - pr| per block in a fixed order and adds the block
-// sums as fixed-point integers, so the total and the decision do not depend on
-// scheduling.  The last working block of an iteration's last kernel closes it;
+// The stopping test sums |val - pr| per block in a fixed order (the rows cut into
+// pieces each by themselves) and adds these sums as fixed-point integers, so the
+// total and the decision do not depend on scheduling.  The last working block
+// closes the iteration;
 // chunks of iterations are captured as HIP graphs and replayed until the
 // device reports done.
 #include <type_traits>
@@ -44,9 +44,7 @@ namespace sp {
 
 static_assert(kPrRowClasses == kRowClasses, "one tile range per row class");
 
-__device__ __forceinline__ unsigned long long diff_fixed(double x) {
-    return (unsigned long long)__double2ll_rn(x * 0x1p60);
-}
+__device__ __forceinline__ unsigned long long diff_fixed(double x) { return __double2ull_rn(x * kPrDiffUnit); }
 
 // Block-uniform read of the iteration state (iteration * 2 + done).
 __device__ __forceinline__ int32_t read_pr_state(PrCtl *c) {
@@ -56,19 +54,24 @@ __device__ __forceinline__ int32_t read_pr_state(PrCtl *c) {
     return s_state;
 }
 
-// Adds the block's |change| (fixed-point sums of its waves) to the iteration's total.
-__device__ __forceinline__ void add_block_diff(PrCtl *c, unsigned long long x, unsigned long long *lds) {
-    if (threadIdx.x == 0) lds[0] = 0;
+// Sum of the block's per-thread |change| in a fixed order, added to the
+// iteration's total as a fixed-point integer.
+template <int BS>
+__device__ __forceinline__ void add_block_diff(PrCtl *c, double x, double *lds) {
+    x = wave_sum_f64(x);
+    if (lane_id() == 0) lds[threadIdx.x / kWave] = x;
     __syncthreads();
-    if (lane_id() == 0 && x) atomicAdd(&lds[0], x);
-    __syncthreads();
-    if (threadIdx.x == 0 && lds[0]) atomicAdd(&c->diff_.v, lds[0]);
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < BS / kWave; ++w) s += lds[w];
+        if (s > 0.0) atomicAdd(&c->diff_.v, diff_fixed(s));
+    }
 }
 
 // End of an iteration (one thread of the last working block).
 __device__ void close_iteration(PrCtl *c) {
     const int32_t it = (c->state >> 1) + 1;
-    const double diff = (double)ld_agent(&c->diff_.v) * 0x1p-60;
+    const double diff = (double)ld_agent(&c->diff_.v) * (1.0 / kPrDiffUnit);
     c->diff_.v = 0;
     c->last_diff = diff;
     const bool done = !(diff > c->beta && it < c->max_iter);
@@ -94,7 +97,7 @@ __global__ void k_pr_init(PrCtl *c, const int32_t *__restrict__ rp, const int32_
         c->beta = beta;
         c->last_diff = 0.0;
         c->diff_.v = 0;
-            c->blocks_done_.v = 0;
+        c->blocks_done_.v = 0;
     }
 }
 
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
                                                    double delta, int32_t parity, unsigned long long *prof) {
     const int32_t st = read_pr_state(c);
     if ((st & 1) || ((st >> 1) & 1) != parity) return;
-    __shared__ double s_w[BS > 512 ? BS / kWave : 8];
+    __shared__ double s_w[BS > 512 ? BS / kWave : 8];  // (of 512 lanes, of the block's waves at the end)
     constexpr int kTeam = BS > 512 ? 512 : BS;  // threads per row of the block classes
     __shared__ unsigned long long s_red[1];
     const double *pr = parity ? pr1 : pr0;
@@ -196,18 +199,18 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
         __syncthreads();
     }
     unsigned long long my_items = 0, my_edges = 0;
-    unsigned long long diff_sum = 0;  // on the waves' first lanes
-    double my_diff = 0.0;             // this tile's
+    double my_diff = 0.0;  // over the block's tiles, which are the same in every run
     auto row_at = [&](int32_t i) { return p.rows ? p.rows[i] : make_int2(p.rp[i], p.rp[i + 1] - p.rp[i]); };
     auto settle = [&](int32_t i, int32_t len, double sum) {
         const int32_t x = p.order ? p.order[i] : i;
         const int32_t dout = p.out_deg ? p.out_deg[x] : len;
         const double val = teleport + delta * sum;
-        my_diff += fabs(val - pr[x]);
+        const double change = fabs(val - pr[x]);
         pr_n[x] = val;
         sh_n[x] = dout > 0 ? val / (double)dout : 0.0;
         ++my_items;
         my_edges += (unsigned long long)len;
+        return change;
     };
     auto rows_of = [&](auto lanes, int cls, int32_t tile) {
         constexpr int LPR = decltype(lanes)::value;
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
         const bool mine = i < p.row0[cls + 1];
         const int2 row = mine ? row_at(i) : make_int2(0, 0);
         const double sum = lanes_sum<LPR, FLY>(p.col, sh, row.x, row.y, l);
-        if (mine && l == 0) settle(i, row.y, sum);
+        if (mine && l == 0) my_diff += settle(i, row.y, sum);
     };
     const int32_t ntiles = p.tile0[kPrRowClasses];
     for (int32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -232,9 +235,7 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
             int2 row = make_int2(0, 0);
             if (mine) row = whole ? row_at(i) : p.pieces[i];
             const double sum = block_row_sum<BS, FLY>(p.col, sh, row.x, row.y, s_w);
-            if (mine && threadIdx.x % kTeam == 0) {
-                if (whole) settle(i, row.y, sum);
-                }
+            if (whole && mine && threadIdx.x % kTeam == 0) my_diff += settle(i, row.y, sum);
             if (!whole) {  // the last piece of a row to arrive settles it, on its team's first wave
                 int32_t r = -1;
                 if (mine && threadIdx.x % kTeam == 0) {
@@ -252,17 +253,16 @@ __global__ __launch_bounds__(BS, 8) void k_pr_pull(PrCtl *c, PrView p, double *p
                     double s = 0.0;
                     for (int32_t k2 = lane_id(); k2 < h.y; k2 += kWave) s += ld_agent(&partial[h.x + k2]);
                     s = wave_sum_f64(s);
-                    if (lane_id() == 0) settle(r, row_at(r).y, s);
+                    // whichever block that is: its |change| is rounded by itself
+                    if (lane_id() == 0) {
+                        const unsigned long long d = diff_fixed(settle(r, row_at(r).y, s));
+                        if (d) atomicAdd(&c->diff_.v, d);
+                    }
                 }
             }
         }
-        // a tile's |change| is summed in a fixed order and rounded once per wave: the same total however
-        // the tiles are dealt out
-        const double d = wave_sum_f64(my_diff);
-        if (lane_id() == 0) diff_sum += diff_fixed(d);
-        my_diff = 0.0;
     }
-    add_block_diff(c, diff_sum, s_red);
+    add_block_diff<BS>(c, my_diff, s_w);
     flush_counters<BS>(prof, my_items, my_edges, 0, s_red);
     if (last_block(c, working_blocks((int64_t)ntiles, 1)) && threadIdx.x == 0) close_iteration(c);
 }
