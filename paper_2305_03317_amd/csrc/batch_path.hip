@@ -1938,9 +1938,6 @@ static sp_status grow_queue(sp_graph g, BatchWorkspace &ws, int64_t qcap) {
     return SP_OK;
 }
 
-// The kernels of `count` forward levels starting at level `first`.  Every
-// kernel reads the level it works on from the control block, so the same
-// launches serve any chunk whose first level has the same parity.
 // Blocks for levels of up to cnt entries: one per BS of them, or what
 // wave_share spreads a small level over.
 template <int BS>
@@ -1948,6 +1945,9 @@ static int level_grid(int64_t cnt, int maxb) {
     return std::max(grid_for(cnt, BS, maxb), grid_for(cnt, BS / kWave * kLeastShare, std::min(maxb, kSpreadBlocks)));
 }
 
+// The kernels of `count` forward levels starting at level `first`.  Every
+// kernel reads the level it works on from the control block, so the same
+// launches serve any chunk whose first level has the same parity.
 template <int BS>
 static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int count, int grid,
                            int hub_grid, bool may_pull, hipStream_t s) {
@@ -1965,7 +1965,7 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
             // without dispatching the thousands of idle blocks a grid sized
             // for V would start (and retire) every level.
             ProfScope ps(P_MS_EXPAND, s);
-            hipLaunchKernelGGL(k_ms_expand<BS>, dim3(std::min(grid, device_cu_count())), dim3(BS), 0, s,
+            hipLaunchKernelGGL(k_ms_expand<BS>, dim3(grid_for((int64_t)g->n, BS, device_cu_count())), dim3(BS), 0, s,
                                ws.ctl, g->row_ptr,
                                g->col_idx, ws.queue, ws.qmask, ws.qvb, ws.seen, (int32_t *)ws.nxt,
                                (const uint4 *)fcur, fnxt, ws.val, (long long)ws.vcap,

@@ -14,7 +14,9 @@
 // length class, and each class gives a row the lanes its length fills: 1 for up to
 // 8 entries (summed in row order), 4 up to 32, 16 up to 128, 64 below 512, a
 // block from there on; rows of 8,192 entries and more are cut into pieces of that
-// many, and the last piece of a row to arrive adds their sums.  A lane adds entries j, j + lanes, ... in order, four loads in flight,
+// many, and the last piece of a row to arrive adds their sums.  Flat graphs (no
+// row over 64 entries) are not listed: 4 lanes a row, 1 where no row holds more
+// than 8.  A lane adds entries j, j + lanes, ... in order, four loads in flight,
 // and a fixed tree adds the lanes, so a vertex's sum depends only on its row.
 //
 // On large skewed graphs the plan renumbers the vertices by degree rank: the
@@ -301,6 +303,7 @@ __global__ void k_pr_rows(const int32_t *__restrict__ rp, const int32_t *__restr
 
 namespace {
 constexpr int kPrHotPerThread = 9;  // shares in LDS per thread of a renumbered run: 144 KB of a CU's 160 at 32 waves
+constexpr int32_t kPrFlat = 64;     // rows of at most this many entries are not told apart
 constexpr int32_t kPrPiece = 8192;  // rows from here on are split into pieces (a power of two: whole rank classes)
 }  // namespace
 
@@ -329,7 +332,7 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     constexpr int32_t longest = kPrPiece - 1;
     // renumbered when it pays and its copy fits; the graph's own rows do otherwise
     bool renum = false;
-    const bool large = n > kPrRenumberFrom && g->max_degree > 8;
+    const bool large = n > kPrRenumberFrom && g->max_degree > 8 && may_be_skewed(g);
     if (large && !g->directed) {  // the copy that the per-source path runs on too
         SP_TRY(ensure_rank_csr_locked(g, s));
         renum = g->rank_ci != nullptr;
@@ -348,8 +351,9 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
         pl.old_id = g->rank_old;
         pl.new_id = g->rank_new;
     }
-    // undirected ranks list the rows by length already, and rows of one class need no list
-    const bool listed = g->max_degree > 8 && (!renum || g->directed);
+    // undirected ranks list the rows by length already, and rows of one class need no list: rows of up to 8
+    // entries, and those of flat graphs, four lanes each (a list costs their first call 0.3 ms and more)
+    const bool listed = renum ? g->directed : g->max_degree > kPrFlat;
     const bool plain = !listed;  // the rows' own offsets serve
     const size_t vn = (size_t)n;
     const size_t row_bytes = (plain ? 0 : sizeof(int2) * vn) + sizeof(int32_t) * vn * (size_t)(listed + g->directed);
@@ -367,7 +371,8 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
         for (int c = 1; c < kRowClasses; ++c) row0[c] = rank_count(g, at_least[c - 1]);
         row0[kRowClasses] = n;
     } else {
-        row0[kRowClasses] = n;  // every row in the last class
+        row0[kRowClasses] = n;  // every row in the last class, or in the one before
+        if (g->max_degree > 8) row0[kRowClasses - 1] = n;
     }
     const int maxb = device_cu_count() * 8;
     const int vgrid = grid_for(n, 256, maxb);
@@ -514,10 +519,11 @@ static sp_status pr_run_bs(sp_graph g, PrWorkspace &ws, double beta, double delt
         const int32_t rows = view.row0[k + 1] - view.row0[k], per = BS / lanes[k];
         view.tile0[k + 1] = view.tile0[k] + (int32_t)(((int64_t)rows + per - 1) / per);
     }
-    // Renumbered: twice the blocks that fit at once, which evens out their rows.  Else as many as fit, and half of
-    // that up to 2 M vertices: every block ends in two atomics to one line each, which take 5 ns a block
-    // (road-1000, 20 iterations: 587 -> 488 us).
-    const int threads_per_cu = pl.new_id ? 4096 : n > (1 << 21) ? 2048 : 1024;
+    // Renumbered: twice the blocks that fit at once, which evens out their rows (small blocks up to 2 M vertices: as
+    // many as fit).  Else as many as fit, and half of that up to 2 M vertices: every block ends in two atomics to one
+    // line each, which take 5 ns a block (road-1000, 20 iterations: 587 -> 488 us; directed rmat-20, blocks of 256:
+    // 2.52 -> 2.28 ms).
+    const int threads_per_cu = pl.new_id ? (BS >= 512 || n > (1 << 21) ? 4096 : 2048) : n > (1 << 21) ? 2048 : 1024;
     const int grid = grid_for(view.tile0[kPrRowClasses], 1, device_cu_count() * threads_per_cu / BS);
     const double teleport = (1.0 - delta) / (double)n;
     hipLaunchKernelGGL(k_pr_init, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, ws.ctl,

@@ -51,6 +51,8 @@ constexpr int32_t kSourceRankCount = 8;
 // and uniform graphs keep their numbering, which may be a local one).  After
 // ensure_rank_locked.
 bool rank_skewed(sp_graph g);
+// Whether that can be, by the highest degree alone (flat graphs need no ranks to tell).
+inline bool may_be_skewed(sp_graph g) { return 2 * ((int64_t)g->n / 8) * g->max_degree >= g->nnz; }
 
 // Builds g->rank_ci (and g->rank_rp) once, on an undirected graph that is
 // skewed; leaves it null on others and where memory is short.  The caller holds g->mu

@@ -275,7 +275,7 @@ void launch_renumber(const int32_t *rp, const int32_t *ci, const int32_t *order,
 }
 
 sp_status ensure_rank_csr_locked(sp_graph g, hipStream_t s) {
-    if (g->rank_ci || g->directed || g->max_degree <= 8) return SP_OK;
+    if (g->rank_ci || g->directed || g->max_degree <= 8 || !may_be_skewed(g)) return SP_OK;
     int32_t *ci = nullptr;
     sp_status st = ensure_rank_locked(g, s);
     if (st == SP_OK && !rank_skewed(g)) return SP_OK;

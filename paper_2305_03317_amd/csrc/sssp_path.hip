@@ -932,7 +932,7 @@ __global__ __launch_bounds__(BS) void k_sssp_pack_ranked(const int32_t *__restri
 sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, bool *ranked,
                            hipStream_t s) {
     const int32_t n = g->n;
-    if (n <= kRenumberFrom || g->max_degree <= 8) return SP_OK;
+    if (n <= kRenumberFrom || g->max_degree <= 8 || !may_be_skewed(g)) return SP_OK;
     {
         std::lock_guard<std::mutex> lk(g->mu);
         sp_status st = ensure_rank_locked(g, s);
