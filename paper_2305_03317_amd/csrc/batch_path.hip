@@ -811,9 +811,9 @@ __device__ __forceinline__ void ms_bottomup(LevelCtl *c, const int32_t *__restri
 }
 
 // The first kernel of a level: finishes the last one's path counts
-// (settle_level) and discovers the next in the direction chosen.  `which` takes
+// (settle_level) and discovers the next in the direction chosen.  WHICH takes
 // the directions apart for timing (1: top-down, 2: bottom-up, 3: both).
-template <int BS>
+template <int BS, int WHICH>
 __global__ __launch_bounds__(BS) void k_ms_discover(LevelCtl *c, const int32_t *__restrict__ rp,
                                                     const int32_t *__restrict__ ci,
                                                     const int32_t *__restrict__ rpi,
@@ -827,13 +827,13 @@ __global__ __launch_bounds__(BS) void k_ms_discover(LevelCtl *c, const int32_t *
                                                     const HubEntry *__restrict__ hub_list,
                                                     const int32_t *__restrict__ owner,
                                                     const int32_t *__restrict__ chunk_off, long long qcap,
-                                                    int32_t which, unsigned long long *prof_td,
+                                                    unsigned long long *prof_td,
                                                     unsigned long long *prof_bu) {
     if (c->done) return;
-    if (blockIdx.y == 0 && (which & 1)) settle_level(c, qmask, qvb, val, hub_list, partial, in_hub_list);
+    if (blockIdx.y == 0 && (WHICH & 1)) settle_level(c, qmask, qvb, val, hub_list, partial, in_hub_list);
     if (c->mode == MODE_TOPDOWN) {
-        if (which & 1) ms_topdown<BS>(c, rp, ci, rpi, queue, qmask, seen, nxt, hub_list, owner, chunk_off, qcap, prof_td);
-    } else if ((which & 2) && blockIdx.y == 0) {
+        if (WHICH & 1) ms_topdown<BS>(c, rp, ci, rpi, queue, qmask, seen, nxt, hub_list, owner, chunk_off, qcap, prof_td);
+    } else if ((WHICH & 2) && blockIdx.y == 0) {
         ms_bottomup<BS>(c, rpi, cii, seen, nxt, front_cur, queue, qcap, prof_bu);
     }
 }
@@ -1453,9 +1453,9 @@ __device__ __forceinline__ void push_parent(int32_t beg, int32_t end, unsigned l
 // without a hub row, like k_ms_sigma's (a lane alone for few slots and a short
 // row, else the wave in turn); blockIdx.y == 1: the chunks of the parents' hub
 // rows, one wave each.  Else blockIdx.y == 0: the chunks of the level's hubs.
-// One launch serves both (an idle launch costs 4.5 us of a level); `which`
+// One launch serves both (an idle launch costs 4.5 us of a level); WHICH
 // takes them apart for timing (1: pushes, 2: hubs, 3: both).
-template <int BS>
+template <int BS, int WHICH>
 __global__ __launch_bounds__(BS, 8) void k_ms_sigma_rest(LevelCtl *c,
                                                          const int32_t *__restrict__ level_off,
                                                          const int32_t *__restrict__ rp,
@@ -1472,17 +1472,17 @@ __global__ __launch_bounds__(BS, 8) void k_ms_sigma_rest(LevelCtl *c,
                                                          const int32_t *__restrict__ chunk_off,
                                                          const int32_t *__restrict__ hub_lvl_chunks,
                                                          const HubEntry *in_hub_list, double *partial,
-                                                         int32_t which, unsigned long long *prof_hub,
+                                                         unsigned long long *prof_hub,
                                                          unsigned long long *prof) {
     if (c->done) return;
     if (!c->sigma_push) {
         __shared__ unsigned long long s_hub[1];
-        if ((which & 2) && blockIdx.y == 0)
+        if ((WHICH & 2) && blockIdx.y == 0)
             pull_hub_chunks<BS>(c, rpi, cii, qmask, front_par, val, hub_list, owner, chunk_off, in_hub_list, partial,
                                 prof_hub, s_hub);
         return;
     }
-    if (!(which & 1)) return;
+    if (!(WHICH & 1)) return;
     __shared__ unsigned long long s_red[1];
     const int32_t pl = c->level - 1;  // parents
     const uint32_t tag = (uint32_t)c->level;
@@ -1974,20 +1974,20 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
                                (int32_t)(l & 1), prof_counters(P_MS_EXPAND));
             continue;
         }
-        auto discover = [&](int kind, int which) {
+        auto discover = [&](int kind, auto kernel) {
             ProfScope ps(kind, s);
-            hipLaunchKernelGGL(k_ms_discover<BS>, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl, g->row_ptr,
+            hipLaunchKernelGGL(kernel, dim3(grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl, g->row_ptr,
                                g->col_idx, (const int32_t *)g->rp_in, (const int32_t *)g->ci_in, ws.queue, ws.qmask,
                                (const uint32_t *)ws.qvb, ws.val, (const double *)ws.partial, in_list, ws.seen, ws.nxt,
                                (const uint4 *)fcur, (const HubEntry *)ws.hub_list, (const int32_t *)ws.owner,
-                               (const int32_t *)ws.chunk_off, (long long)ws.qcap, which,
+                               (const int32_t *)ws.chunk_off, (long long)ws.qcap,
                                prof_counters(P_MS_TOPDOWN), prof_counters(P_MS_BOTTOMUP));
         };
         if (prof_enabled() && may_pull) {
-            discover(P_MS_TOPDOWN, 1);
-            discover(P_MS_BOTTOMUP, 2);
+            discover(P_MS_TOPDOWN, k_ms_discover<BS, 1>);
+            discover(P_MS_BOTTOMUP, k_ms_discover<BS, 2>);
         } else {
-            discover(P_MS_TOPDOWN, 3);
+            discover(P_MS_TOPDOWN, k_ms_discover<BS, 3>);
         }
         {
             ProfScope ps(P_MS_SIGMA, s);
@@ -2001,23 +2001,24 @@ static void enqueue_levels(sp_graph g, BatchWorkspace &ws, int64_t first, int co
                                ws.chunk_off, (int32_t)g->max_degree, prof_counters(P_MS_SIGMA));
         }
         const int rest_grid = xcd_grid(std::max(grid, sigma_hubs ? hub_grid : 1), device_cu_count() * 8);
-        auto rest = [&](int kind, int which) {
+        auto rest = [&](int kind, auto kernel) {
             ProfScope ps(kind, s);
-            hipLaunchKernelGGL(k_ms_sigma_rest<BS>, dim3(rest_grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
+            hipLaunchKernelGGL(kernel, dim3(rest_grid, hubs ? 2 : 1), dim3(BS), 0, s, ws.ctl,
                                (const int32_t *)ws.level_off, g->row_ptr, g->col_idx, (const int32_t *)g->rp_in,
                                (const int32_t *)g->ci_in, (const int32_t *)ws.queue,
                                (const unsigned long long *)ws.qmask, (const uint32_t *)ws.qvb, (const uint4 *)fcur,
                                (const uint4 *)fnxt, ws.val, (const HubEntry *)ws.hub_list,
                                (const int32_t *)ws.owner, (const int32_t *)ws.chunk_off,
-                               (const int32_t *)ws.hub_lvl_chunks, in_list, ws.partial, which,
+                               (const int32_t *)ws.hub_lvl_chunks, in_list, ws.partial,
                                prof_counters(P_MS_SIGMA_HUB), prof_counters(P_MS_SIGMA_PUSH));
         };
-        const int which = sigma_hubs ? 3 : 1;
-        if (prof_enabled() && sigma_hubs) {
-            rest(P_MS_SIGMA_HUB, 2);
-            rest(P_MS_SIGMA_PUSH, 1);
+        if (!sigma_hubs) {
+            rest(P_MS_SIGMA_PUSH, k_ms_sigma_rest<BS, 1>);
+        } else if (prof_enabled()) {
+            rest(P_MS_SIGMA_HUB, k_ms_sigma_rest<BS, 2>);
+            rest(P_MS_SIGMA_PUSH, k_ms_sigma_rest<BS, 1>);
         } else {
-            rest(P_MS_SIGMA_PUSH, which);
+            rest(P_MS_SIGMA_PUSH, k_ms_sigma_rest<BS, 3>);
         }
     }
 }

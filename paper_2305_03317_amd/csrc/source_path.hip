@@ -412,18 +412,17 @@ __device__ __forceinline__ void src_sigma_hub(LevelCtl *c, const SrcView &p, uns
 // reads before the next level's k_src_sigma (three launches cost 4.5 us each
 // where they had nothing to do).  blockIdx.y == 0: top-down without the hubs,
 // or bottom-up; 1: the frontier's hub chunks, top-down; 2: hub path counts.
-// `which` takes them apart for timing (1: top-down, 2: bottom-up, 4: hubs).
-template <int BS>
-__global__ __launch_bounds__(BS) void k_src_discover(LevelCtl *c, SrcView p, int32_t which,
-                                                     unsigned long long *prof_td, unsigned long long *prof_bu,
-                                                     unsigned long long *prof_hub) {
+// WHICH takes them apart for timing (1: top-down, 2: bottom-up, 4: hubs, 7: all).
+template <int BS, int WHICH>
+__global__ __launch_bounds__(BS) void k_src_discover(LevelCtl *c, SrcView p, unsigned long long *prof_td,
+                                                     unsigned long long *prof_bu, unsigned long long *prof_hub) {
     if (c->done) return;
     if (blockIdx.y == 2) {
-        if ((which & 4) && c->level >= 1) src_sigma_hub<BS>(c, p, prof_hub);  // level 0 was given its count
+        if ((WHICH & 4) && c->level >= 1) src_sigma_hub<BS>(c, p, prof_hub);  // level 0 was given its count
     } else if (c->mode == MODE_TOPDOWN) {
-        if (which & 1) src_topdown<BS>(c, p, prof_td);
+        if (WHICH & 1) src_topdown<BS>(c, p, prof_td);
     } else if (blockIdx.y == 0) {
-        if (which & 2) src_bottomup<BS>(c, p, prof_bu);
+        if (WHICH & 2) src_bottomup<BS>(c, p, prof_bu);
     }
 }
 
@@ -525,8 +524,9 @@ __global__ __launch_bounds__(BS, 8) void k_src_sigma(LevelCtl *c, SrcView p, uns
 }
 
 // Reverse sweep over one level.  blockIdx.y == 0: its rows without the hubs;
-// blockIdx.y == 1: the chunks of its hubs.
-template <int BS>
+// blockIdx.y == 1: the chunks of its hubs.  WHICH takes them apart for timing
+// (1: rows, 2: hubs, 3: both).
+template <int BS, int WHICH>
 __global__ __launch_bounds__(BS, 8) void k_src_delta(SrcView p, int32_t lvl, double *bc, unsigned long long *prof,
                                                      unsigned long long *prof_hub) {
     __shared__ int32_t s_list[BS];
@@ -535,7 +535,8 @@ __global__ __launch_bounds__(BS, 8) void k_src_delta(SrcView p, int32_t lvl, dou
     const int lane = lane_id();
     const RowTerms<true> terms{p.ci, p.dist, p.sd, lvl + 1};
     unsigned long long my_items = 0, my_edges = 0, my_pairs = 0;
-    if (blockIdx.y == 0) {
+    const bool rows = WHICH == 1 || (WHICH == 3 && blockIdx.y == 0);
+    if (rows) {
         int32_t *list = s_list + (threadIdx.x - lane);
         double *sum = s_sum + (threadIdx.x - lane);
         const int32_t lo = p.level_off[lvl], hi = p.level_off[lvl + 1];
@@ -574,7 +575,7 @@ __global__ __launch_bounds__(BS, 8) void k_src_delta(SrcView p, int32_t lvl, dou
             }
         });
     }
-    flush_counters<BS>(blockIdx.y == 0 ? prof : prof_hub, my_items, my_edges, my_pairs, s_red);
+    flush_counters<BS>(rows ? prof : prof_hub, my_items, my_edges, my_pairs, s_red);
 }
 
 // BC of the ranks to the caller's vertices.
@@ -688,9 +689,9 @@ static sp_status source_run_bs(sp_graph g, SourceWorkspace &ws, int32_t src, dou
     const int hub_grid = hubs_in ? grid_for(g->split_hub_chunks_in * kWave, BS, maxb) : 1;
     const dim3 discover_grid(hubs || hubs_in ? xcd_grid(std::max(grid, hub_grid), maxb) : grid,
                              hubs_in ? 3 : hubs ? 2 : 1);
-    auto discover = [&](int kind, int which) {
+    auto discover = [&](int kind, auto kernel) {
         ProfScope ps(kind, s);
-        hipLaunchKernelGGL(k_src_discover<BS>, discover_grid, dim3(BS), 0, s, ws.ctl, p, which,
+        hipLaunchKernelGGL(kernel, discover_grid, dim3(BS), 0, s, ws.ctl, p,
                            prof_counters(P_SRC_TOPDOWN), prof_counters(P_SRC_BOTTOMUP),
                            prof_counters(P_SRC_SIGMA_HUB));
     };
@@ -699,11 +700,11 @@ static sp_status source_run_bs(sp_graph g, SourceWorkspace &ws, int32_t src, dou
         const int chunk = std::max(1, std::abs(o.chunk_levels));
         for (int k = 0; k < chunk; ++k) {
             if (prof_enabled()) {
-                discover(P_SRC_TOPDOWN, 1);
-                if (may_pull) discover(P_SRC_BOTTOMUP, 2);
-                if (hubs_in) discover(P_SRC_SIGMA_HUB, 4);
+                discover(P_SRC_TOPDOWN, k_src_discover<BS, 1>);
+                if (may_pull) discover(P_SRC_BOTTOMUP, k_src_discover<BS, 2>);
+                if (hubs_in) discover(P_SRC_SIGMA_HUB, k_src_discover<BS, 4>);
             } else {
-                discover(P_SRC_TOPDOWN, 7);
+                discover(P_SRC_TOPDOWN, k_src_discover<BS, 7>);
             }
             {
                 ProfScope ps(P_SRC_SIGMA, s);
@@ -742,11 +743,17 @@ static sp_status source_run_bs(sp_graph g, SourceWorkspace &ws, int32_t src, dou
         for (int32_t l = top; l >= lo; --l) {
             const int32_t cnt = at_hand ? c.seg_off[l + 1] - c.seg_off[l] : off_w[l + 1 - lo] - off_w[l - lo];
             const int32_t chunks = at_hand ? c.seg_chunks[l] : end_w[l + 1 - lo] - end_w[l - lo];
-            ProfScope ps(P_SRC_DELTA, s);  // rows and hub chunks together
+            const bool both = hubs && chunks > 0;
             int gx = level_grid((int64_t)cnt);
-            if (hubs && chunks > 0) gx = xcd_grid(std::max(gx, grid_for((int64_t)chunks * kWave, BS, maxb)), maxb);
-            hipLaunchKernelGGL(k_src_delta<BS>, dim3(gx, hubs && chunks > 0 ? 2 : 1), dim3(BS), 0, s, p, l, bc,
-                               prof_counters(P_SRC_DELTA), prof_counters(P_SRC_DELTA_HUB));
+            if (both) gx = xcd_grid(std::max(gx, grid_for((int64_t)chunks * kWave, BS, maxb)), maxb);
+            auto delta = [&](int kind, int gy, auto kernel) {
+                ProfScope ps(kind, s);
+                hipLaunchKernelGGL(kernel, dim3(gx, gy), dim3(BS), 0, s, p, l, bc, prof_counters(P_SRC_DELTA),
+                                   prof_counters(P_SRC_DELTA_HUB));
+            };
+            if (!both || prof_enabled()) delta(P_SRC_DELTA, 1, k_src_delta<BS, 1>);
+            if (both && prof_enabled()) delta(P_SRC_DELTA_HUB, 1, k_src_delta<BS, 2>);
+            if (both && !prof_enabled()) delta(P_SRC_DELTA, 2, k_src_delta<BS, 3>);
         }
         SP_HIP(hipGetLastError());
     }

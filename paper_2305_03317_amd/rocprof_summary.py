@@ -35,13 +35,21 @@ CSRC = os.path.join(HERE, "csrc")
 
 # kernel function name -> profile family reported by sp_profile_read
 FAMILY = {
-    "k_ms_discover": "ms_discover", "k_ms_sigma": "ms_sigma",
-    "k_ms_sigma_rest": "ms_sigma_hub", "k_ms_delta": "ms_delta", "k_ms_delta_hub": "ms_delta_hub",
-    "k_ms_expand": "ms_expand", "k_ms_bc": "ms_bc", "k_src_discover": "src_discover",
-    "k_src_sigma": "src_sigma", "k_src_delta": "src_delta",
+    "k_ms_sigma": "ms_sigma", "k_ms_delta": "ms_delta", "k_ms_delta_hub": "ms_delta_hub",
+    "k_ms_expand": "ms_expand", "k_ms_bc": "ms_bc", "k_src_sigma": "src_sigma",
     "k_sssp_push": "sssp_push", "k_sssp_push_hops": "sssp_push", "k_sssp_mesh": "sssp_push", "k_sssp_pull": "sssp_pull",
     "k_pr_pull": "pr_pull", "k_tc_heavy": "tc_count", "k_tc_light": "tc_count",
     "k_wg_bc": "wg_bc", "k_wg_bc_ell": "wg_bc", "k_wg_bc_mesh": "wg_bc", "k_wg_bc_sum": "wg_bc_sum",
+}
+
+# Kernels that serve several families in one launch, and are launched once for
+# each while sp_profile_enable is on: family by the last template argument
+# (None: all at once, as outside of profiling; listed, but no family's).
+PARTS = {
+    "k_ms_discover": {"1": "ms_topdown", "2": "ms_bottomup", "3": None},
+    "k_ms_sigma_rest": {"1": "ms_sigma_push", "2": "ms_sigma_hub", "3": None},
+    "k_src_discover": {"1": "src_topdown", "2": "src_bottomup", "4": "src_sigma_hub", "7": None},
+    "k_src_delta": {"1": "src_delta", "2": "src_delta_hub", "3": None},
 }
 
 
@@ -64,6 +72,14 @@ def short_name(full: str) -> str:
 
 def base_name(short: str) -> str:
     return short.split("<")[0]
+
+
+def family_of(short: str):
+    """Family of a kernel by its name with template arguments; None: of none."""
+    base = base_name(short)
+    if base in PARTS:
+        return PARTS[base].get(short[len(base):].strip("<>").split(",")[-1].strip())
+    return FAMILY.get(base)
 
 
 def _one(d, pattern):
@@ -146,7 +162,7 @@ def main():
     names = sorted(set(fetch) | set(write), key=lambda k: -sum(fetch.get(k, [])))
     for k in names:
         fv, wv = fetch.get(k, []), write.get(k, [])
-        if not fv or base_name(k) not in FAMILY:
+        if not fv or (base_name(k) not in FAMILY and base_name(k) not in PARTS):
             continue
         nd = len(fv)
         f_avg = sum(fv) / nd
@@ -156,8 +172,8 @@ def main():
         lines.append("| %s | %d | %.2f | %.2f | %.2f | %.2f |" % (k, nd, f_avg / 2**20, w_avg / 2**20, per / 1e6, tot / 1e9))
         # several instances of a family (block sizes tried by the autotuner):
         # keep the one launched most, the configuration the timed steps use
-        f = FAMILY[base_name(k)]
-        if f not in fam or nd > fam[f]["dispatches"]:
+        f = family_of(k)
+        if f and (f not in fam or nd > fam[f]["dispatches"]):
             fam[f] = dict(kernel=k, dispatches=nd, fetch_bytes_per_launch=f_avg * cf,
                           write_bytes_per_launch=w_avg * cw, traffic_bytes_per_launch=per)
     os.makedirs(os.path.dirname(os.path.abspath(a.md)), exist_ok=True)
