@@ -31,7 +31,8 @@ PageRank on the same graphs (time per iteration, kernel roofline, numpy
 oracle), the triangle count of the RMAT graph, and BC on a directed version
 of it (both paths).
 
-Prints one JSON line.
+Prints one JSON line: the headline, its roofline, baselines and parity, and the
+main figures of each leg (headline()).  --detail FILE writes every figure.
 """
 from __future__ import annotations
 
@@ -86,16 +87,17 @@ BYTE_MODEL = {
     "src_delta": dict(items=44, edges=8, pairs=16),
     # SSSP rounds: items = frontier vertices (push: queue entry, row offsets,
     # own distance) or all vertices (pull: row offsets), edges = adjacency
-    # entries (packed {neighbour, weight} plus the neighbour's {dist, stamp})
-    "sssp_push": dict(items=20, edges=16),
-    "sssp_pull": dict(items=8, edges=16),
-    # PageRank iteration: items = non-hub vertices (row offsets, own value
-    # read, value and share written), edges = adjacency entries (column id,
-    # neighbour's share); hub chunks count their entries the same way
+    # entries (packed {neighbour, weight} plus the neighbour's distance, or its
+    # stamp)
+    "sssp_push": dict(items=20, edges=12),
+    "sssp_pull": dict(items=8, edges=12),
+    # PageRank iteration: items = vertices (row offsets, own value read, value
+    # and share written), edges = adjacency entries (column id, neighbour's
+    # share)
     "pr_pull": dict(items=28, edges=12),
-    # triangle count: edges = list elements walked (one 4-byte id each); the
-    # per-entry reads (row id, neighbour id, four offsets) are added
-    # separately from the oriented-entry count
+    # triangle count: edges = 4-byte words of the rows walked (an id, or two of
+    # 16 bits); the per-entry reads (row start and place) are added separately
+    # from the oriented-entry count
     "tc_count": dict(edges=4),
 }
 FORWARD = ("ms_topdown", "ms_bottomup", "ms_sigma", "ms_sigma_hub", "ms_sigma_push", "ms_expand")
@@ -308,12 +310,12 @@ def tc_benchmark(sp, torch, workload, small_scale=16):
     p, c = prof.get("tc_count"), counted.get("tc_count", {})
     roofline = None
     if p:
-        alg = algorithmic_bytes("tc_count", c) + 24 * m
+        alg = algorithmic_bytes("tc_count", c) + 8 * m
         achieved = alg / (p["total_ms"] * 1e-3) / 1e9
         roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "tc_count",
                     "avg_launch_ms": round(p["total_ms"] / max(p["launches"], 1), 4),
-                    "list_elements_walked": int(c.get("edges", 0))}
+                    "row_words_walked": int(c.get("edges", 0))}
         attach_traffic(roofline, "tc_" + workload)
     g.release()
     out = {"workload": spec["name"], "triangles": count, "count_ms": round(count_s * 1e3, 3),
@@ -670,6 +672,46 @@ def serving_benchmark(sp, torch, n_requests, seed=2005, budget_gb=230):
     return res
 
 
+# What the printed line keeps of each leg; a line of every figure is 14 KB, longer than
+# what a log's tail holds.
+LEG_KEYS = {
+    "per_source_path": ("sources", "ms_per_source", "teps", "block_size"),
+    "per_source_legs": ("sources", "ms_per_source"),
+    "road_batched": ("sources", "ms_per_pass", "engine"),
+    "sssp": ("sources", "ms_per_source", "rounds_mean", "entries_scanned_over_nnz"),
+    "pagerank": ("ms_per_iteration",),
+    "triangles": ("triangles", "count_ms", "build_ms"),
+    "directed_bc": ("batched_over_per_source", "per_source", "batched_all_sources"),
+}
+SERVING_KEYS = ("achieved_qps", "p50_ms", "p99_ms", "failed")
+
+
+def headline(line):
+    """The printed line: the headline with its workload, roofline, baselines
+    and parity, and the main figures of each leg."""
+    def pick(d, keys):
+        out = {k: d[k] for k in keys if k in d}
+        par = d.get("parity")
+        if par:
+            out["parity"] = par.get("pass", par.get("bit_exact", par.get("all_pass")))
+        return out
+
+    out = {k: v for k, v in line.items() if k not in LEG_KEYS and k not in ("kernels", "serving", "config")}
+    out["config"] = dict(line["config"])
+    tuned = out["config"].get("autotuned")
+    if tuned:
+        out["config"]["autotuned"] = {k: v for k, v in tuned.items() if k != "candidates"}
+    for leg, keys in LEG_KEYS.items():
+        d = line.get(leg)
+        if d:
+            out[leg] = pick(d, keys) if leg == "per_source_path" else {wl: pick(x, keys) for wl, x in d.items()}
+    serving = line.get("serving")
+    if serving:
+        out["serving"] = {ph: {k: serving[ph][k] for k in SERVING_KEYS}
+                          for ph in ("burst", "load50", "load80", "load95") if ph in serving}
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
     ap.add_argument("--gpus", type=int, default=1)
@@ -719,6 +761,9 @@ def main():
                     help="run only the road-like batched BC legs and print their JSON object")
     ap.add_argument("--only-serving", action="store_true",
                     help="run only the serving workload and print its JSON object")
+    ap.add_argument("--detail", default=None,
+                    help="file that receives every figure of every leg as JSON (the printed line holds the "
+                         "headline and a few of each leg)")
     ap.add_argument("--copy-gib", type=float, default=0.0,
                     help="first run one elementwise kernel that reads and writes this many GiB "
                          "(a known-size kernel that calibrates hardware byte counters in a "
@@ -1037,7 +1082,10 @@ def main():
         "triangles": triangles or None,
         "directed_bc": directed or None,
     }
-    print(json.dumps(line))
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(line, f, indent=1)
+    print(json.dumps(headline(line)))
 
 
 if __name__ == "__main__":

@@ -459,7 +459,6 @@ static sp_status build_static_hubs(sp_graph g, bool ranked, NewWeights &nw, hipS
     std::vector<HubEntry> hubs;
     std::vector<int32_t> owners;
     auto add = [&](int32_t v, int32_t deg) {
-        if (deg <= kHubDeg) return;
         const int32_t nch = (deg + kHubChunk - 1) / kHubChunk;
         hubs.push_back(HubEntry{v, 0, (int32_t)owners.size(), nch});
         owners.insert(owners.end(), (size_t)nch, (int32_t)hubs.size() - 1);
@@ -468,9 +467,11 @@ static sp_status build_static_hubs(sp_graph g, bool ranked, NewWeights &nw, hipS
         std::vector<int32_t> off((size_t)rank_count(g, kRankExact) + 1);
         SP_HIP(hipMemcpyAsync(off.data(), g->rank_rp, sizeof(int32_t) * off.size(), hipMemcpyDeviceToHost, st));
         SP_HIP(hipStreamSynchronize(st));
-        for (size_t r = 0; r + 1 < off.size(); ++r) add((int32_t)r, off[r + 1] - off[r]);
+        for (size_t r = 0; r + 1 < off.size(); ++r)
+            if (off[r + 1] - off[r] > kHubDeg) add((int32_t)r, off[r + 1] - off[r]);
     } else {
-        for (int32_t v = 0; v < g->n; ++v) add(v, g->host_deg[v]);
+        for (int32_t v = 0; v < g->n; ++v)
+            if (g->host_deg[v] > kHubDeg) add(v, g->host_deg[v]);
     }
     const size_t hb = sizeof(HubEntry) * hubs.size(), ob = sizeof(int32_t) * owners.size();
     SP_TRY(dev_alloc((void **)&nw.hubs, hb));

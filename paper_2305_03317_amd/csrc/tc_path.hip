@@ -601,7 +601,7 @@ __global__ __launch_bounds__(256) void k_tc_heavy(const int32_t *__restrict__ or
                     test4(x, at);
                     if (at2 != at) test4(y, at2);
                 }
-                if (prof && l == 0) tests += (unsigned long long)(e - b);
+                if (prof && l == 0) tests += (unsigned long long)(LO ? (e - b + 1) / 2 : e - b);  // 4-byte words
                 if (PER) {
                     uint32_t f = found;
                     for (int o = kTcLanes / 2; o > 0; o >>= 1) f += __shfl_xor(f, o, kWave);
