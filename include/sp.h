@@ -362,7 +362,8 @@ sp_status sp_tune_cache_clear(void);
  * adjacency packed with its weights) plus 16 bytes per vertex of degree
  * above 256; on graphs whose rows all hold at most 8 entries the rows at a
  * fixed width of 4 or 8 entries (32 or 64 bytes per vertex); on large skewed
- * graphs (over 2^18 vertices) 12 bytes per vertex for a numbering by degree. */
+ * graphs (over 2^20 vertices) 12 bytes per vertex for a numbering by degree.
+ * A call that fails leaves the earlier weights in place. */
 sp_status sp_graph_set_weights(sp_graph g, const int32_t *weights, uint32_t flags, sp_stream s);
 
 /* Direction of the relaxation rounds. */

@@ -31,9 +31,12 @@ sp_status ensure_rank_rp_locked(sp_graph g, hipStream_t s);
 // Vertices of degree >= deg (at most kRankExact, or a power of two); after ensure_rank_locked.
 inline int32_t rank_count(sp_graph g, int32_t deg) { return g->rank_first[rank_bucket(deg) + 1]; }
 
-// Vertices above which renumbering by rank is considered.  Weighted rows, which
-// are written out anew in any case: 8-byte values of 2 MB, half an XCD's L2.
-constexpr int32_t kRenumberFrom = 1 << 18;
+// Vertices above which renumbering by rank is considered.  Weighted rows (rmat,
+// edge factor 16): a query with and without 2^18 vertices 563 and 568 us, 2^19
+// 736 and 746, 2^20 1,287 and 1,328, 2^21 1,634 and 1,846, 2^22 3,112 and 4,152;
+// to replace the weights 97 and 71, 414 and 347, 501 and 402, 714 and 494, 1,117
+// and 726.
+constexpr int32_t kRenumberFrom = 1 << 20;
 // PageRank (once a graph): from here on 20 iterations win back what the copy
 // takes (first call, rmat, edge factor 16, with and without: 420,000 vertices
 // 2.7 and 2.7 ms, 600,000 3.0 and 3.5, 4,000,000 12.5 and 21.1).

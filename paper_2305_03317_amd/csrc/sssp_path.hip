@@ -232,18 +232,20 @@ __global__ void k_sssp_init(SsspCtl *c, const int32_t *__restrict__ rp, int32_t 
     c->state = pack_state(1, nch, 0, mode, false, (unsigned long long)deg);
 }
 
-// Push round.  Waves work by themselves, without barriers.  blockIdx.y == 0:
-// a wave takes frontier vertices (hubs excluded; up to 64, fewer where that
-// leaves waves idle), lays their rows end to end, and walks them 256 entries
-// per step: a lane takes four consecutive entries, whose rows one search and
-// a short walk find, so four packed entries and then four distances are in
-// flight.  blockIdx.y == 1: a wave per chunk of the frontier's hubs.  The few
-// entries that may lower their vertex are gathered in LDS and settled 64 at a
-// time (relax_push), the vertices that join the next frontier written out in
-// batches: an atomic of the wave on the shared tail takes 5 ns of every
-// wave's time.  rmat-22: 5.1 -> 3.9 ms per
-// source against blocks of 256 that took an entry per thread between barriers;
-// rmat with 8,192 vertices 0.64 -> 0.30 ms.
+// Push round.  Waves work by themselves, without barriers but the last.
+// blockIdx.y == 0: a wave takes frontier vertices (hubs excluded; up to 64, fewer
+// where that leaves waves idle, but of about kPushStep entries together), lays
+// their rows end to end, and walks them 256 entries per step: a lane takes four
+// consecutive entries, whose rows one search and a short walk find, so four
+// packed entries and then four distances are in flight.  blockIdx.y == 1: a wave
+// per chunk of the frontier's hubs.  Entries that may lower their vertex are
+// gathered in LDS and settled up to 256 together, the vertices that join the next
+// frontier written out in batches, the last one of all the block's waves with
+// one atomic: one on the shared tail takes 5 ns of every wave's time (an atomic
+// per wave, 262,144 vertices of three entries: 0.93 ms, so 0.53; uniform, 2^20
+// vertices, 2.73 and 2.19; rmat-20 1.54 and 1.29).  Against blocks of 256 that
+// took an entry per thread between barriers: rmat-22, rows not numbered by rank,
+// 4.9 -> 4.15 ms per source, rmat with 8,192 vertices 0.69 -> 0.31.
 template <int BS>
 __global__ __launch_bounds__(BS) void k_sssp_push(SsspCtl *c, const int32_t *__restrict__ rp,
                                                   const int2 *__restrict__ adj, int32_t *dist,
@@ -927,8 +929,8 @@ __global__ __launch_bounds__(BS) void k_sssp_pack_ranked(const int32_t *__restri
 // Pushes on a large skewed graph are bound by their reads of the neighbours'
 // distances, mostly those of the heaviest vertices: numbered by rank these
 // fill consecutive lines, and the distances of the first million ranks (98% of
-// the entries on rmat-22) fit an XCD's 4 MB L2.  rmat-22:
-// 6.2 -> 5.1 ms per source.
+// the entries on rmat-22) fit an XCD's 4 MB L2.  rmat-22: 4.15 -> 3.11 ms per
+// source (kRenumberFrom).
 sp_status sssp_pack_ranked(sp_graph g, const int32_t *weights, int2 *adjw, unsigned int *bad, bool *ranked,
                            hipStream_t s) {
     const int32_t n = g->n;

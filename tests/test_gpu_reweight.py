@@ -1,6 +1,6 @@
 """Weights replaced again and again on one graph, queries between some of the
 replacements only: captured rounds must never run on the arrays of earlier
-weights.  On a graph that is numbered by rank (over 2^18 vertices, skewed), on
+weights.  On a graph that is numbered by rank (over 2^20 vertices, skewed), on
 one whose rows are kept at a fixed width, and on one that is neither.  Distances
 bit for bit against the Dijkstra oracle; allocations of the same and other sizes
 in between move the addresses that the allocator gives out."""
@@ -28,7 +28,7 @@ sys.path.insert(0, %r)
 import oracle
 from paper_2305_03317_amd import graphs, sp
 rp, ci = graphs.rmat(12, 16, seed=4)
-rp = np.concatenate([rp, np.full(300_000 - 4096, rp[-1], np.int32)])   # numbered by rank
+rp = np.concatenate([rp, np.full(1_100_000 - 4096, rp[-1], np.int32)])   # numbered by rank
 a, b = graphs.weights(rp, ci, 1), graphs.weights(rp, ci, 2)
 s = int(graphs.sources(rp, 1, 7, min_degree=1)[0])
 g = sp.sp_graph_upload(rp, ci)
@@ -52,7 +52,7 @@ def make(name: str):
     rp, ci = graphs.rmat(14, 16, seed=4)
     if name == "rmat":
         return rp, ci
-    return np.concatenate([rp, np.full(300_000 - 16384, rp[-1], np.int32)]), ci  # "ranked"
+    return np.concatenate([rp, np.full(1_100_000 - 16384, rp[-1], np.int32)]), ci  # "ranked"
 
 
 @pytest.mark.parametrize("name", ["ranked", "road", "rmat"])
