@@ -87,8 +87,7 @@ BYTE_MODEL = {
     "src_delta": dict(items=44, edges=8, pairs=16),
     # SSSP rounds: items = frontier vertices (push: queue entry, row offsets,
     # own distance) or all vertices (pull: row offsets), edges = adjacency
-    # entries (packed {neighbour, weight} plus the neighbour's distance, or its
-    # stamp)
+    # entries (packed {neighbour, weight} plus the neighbour's distance)
     "sssp_push": dict(items=20, edges=12),
     "sssp_pull": dict(items=8, edges=12),
     # PageRank iteration: items = vertices (row offsets, own value read, value

@@ -6,17 +6,18 @@
 // with an atomic Min (push), or every vertex takes the Min over its modified
 // neighbours (pull), until a round modifies nothing.  Here:
 //
-//   * the `modified` set of a round is a frontier queue (push reads it) and a
-//     stamp per vertex (pull reads it): the last round whose frontier holds
-//     it.  Distances and stamps are arrays of their own, since a push reads
-//     distances only;
+//   * the `modified` set of a round is a frontier queue, which push rounds
+//     read; a stamp per vertex, the last round whose frontier holds it, keeps
+//     it free of repeats.  Distances and stamps are arrays of their own, since
+//     relaxations read distances only;
 //   * a push relaxation lowers dist[u] with atomicMin; the first thread in a
 //     round whose atomicMin lowered it raises u's stamp to the next round with
 //     atomicMax and appends u to the next frontier, so a vertex joins a
 //     frontier at most once per round;
 //   * a pull round walks every vertex's row, takes the least candidate over
-//     neighbours whose stamp is at least the current round (in the current
-//     frontier, or lowered earlier in this round), and stores it when lower;
+//     the neighbours that have a distance (more than the modified ones: what
+//     the others offer was taken before and lowers nothing), and stores it
+//     when lower;
 //   * rows longer than kHubDeg entries ("hubs") are cut into chunks of
 //     kHubChunk entries that blocks take one at a time: in push rounds the
 //     frontier's hubs (registered when they join it), in pull rounds every
@@ -741,10 +742,12 @@ __global__ void k_sssp_mesh_rows(const int32_t *__restrict__ rp, const int2 *__r
 // blockIdx.y == 1: blocks take the chunks of every hub of the graph, reduce a
 // chunk to its minimum and lower the hub with atomicMin.
 //
-// A vertex first reached in this round may show its stamp before its distance:
-// it offers nothing then (it is in the next frontier).  Taken as a saturated
-// candidate it had the check after the rounds run for nothing, a thread per
-// row: rmat-18 from 0.8 to 5.5 ms, rmat-20 from 3.0 to 24 ms.
+// An entry takes one gather, the neighbour's distance.  Passing over neighbours
+// that were not lowered takes their stamps too, two gathers for most entries of
+// the rounds that are worth a pull, and a compare with the vertex's minimum drops
+// their offers as well.  All rounds pulled, and alpha 50, us: rmat-20 3,053 and
+// 2,217, so 2,772 and 1,786; rmat, 10^6 vertices, 2,471 and 2,084, so 2,179 and
+// 1,657; 750,000 vertices, 1,833 and 1,241, so 1,671 and 1,091.
 template <int BS>
 __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__restrict__ rp,
                                                   const int2 *__restrict__ adj, int32_t *dist,
@@ -769,7 +772,8 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
     unsigned long long my_deg = 0, my_items = 0, my_edges = 0;
     bool ovf = false;
     // rows numbered by rank: few of the `heavy` first ones a tile, which hold the long ones side by side
-    // (from 16 entries on, all together with others: rmat-20 3.51 ms, so 2.74)
+    // (from 16 entries on; all pulled, like the others and so: rmat-21 5.3 and 4.6 ms, rmat-22 11.5 and 11.1,
+    // 2^21 vertices and edge factor 4 3.8 and 1.9)
     constexpr int kFew = BS / 8;
     const int32_t heavy_tiles = (heavy + kFew - 1) / kFew;
     const int32_t tiles = heavy_tiles + (n - heavy + BS - 1) / BS;
@@ -791,27 +795,26 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
             }
             int32_t total;
             const int32_t off = block_excl_scan<BS>(deg, s_scan, &total);
+            const int32_t own = deg > 0 ? dist[v] : kInf;
             s_beg[threadIdx.x] = beg;
             s_off[threadIdx.x] = off;
-            s_best[threadIdx.x] = kInf;
+            s_best[threadIdx.x] = own;
             __syncthreads();
             for (int32_t k0 = 0; k0 < total; k0 += BS) {
                 const int32_t k = k0 + threadIdx.x;
                 if (k < total) {
                     const int32_t a = owner_of<BS>(s_off, k);
                     const int2 e = adj[s_beg[a] + (k - s_off[a])];
-                    if (stamp[e.x] >= r) {
-                        const int32_t d = dist[e.x];
-                        const int32_t nd = d != kInf ? candidate(d, e.y, ovf) : kInf;
-                        if (nd < s_best[a]) atomicMin(&s_best[a], nd);
-                    }
+                    const int32_t d = dist[e.x];
+                    const int32_t nd = d != kInf ? candidate(d, e.y, ovf) : kInf;
+                    if (nd < s_best[a]) atomicMin(&s_best[a], nd);
                 }
             }
             __syncthreads();
             bool take = false;
             if (deg > 0) {
                 const int32_t best = s_best[threadIdx.x];
-                if (best < dist[v]) {
+                if (best < own) {
                     dist[v] = best;
                     stamp[v] = r + 1;
                     take = true;
@@ -830,10 +833,8 @@ __global__ __launch_bounds__(BS) void k_sssp_pull(SsspCtl *c, const int32_t *__r
             int32_t m = kInf;
             for (int32_t e = beg + threadIdx.x; e < end; e += BS) {
                 const int2 x = adj[e];
-                if (stamp[x.x] >= r) {
-                    const int32_t du = dist[x.x];
-                    if (du != kInf) m = min(m, candidate(du, x.y, ovf));
-                }
+                const int32_t du = dist[x.x];
+                if (du != kInf) m = min(m, candidate(du, x.y, ovf));
             }
             m = block_min_i32<BS>(m, s_min);
             bool take = false;
