@@ -794,8 +794,7 @@ sp_status sp_graph_release(sp_graph g) {
     }
     dev_free(g->rank_new);  // holds rank_old and rank_rp too
     dev_free(g->rank_ci);
-    dev_free(g->tc_orp);
-    dev_free(g->tc_pair_orp);
+    for (void *b : g->tc_blocks) dev_free(b);
     dev_free(g->hub_static);
     dev_free(g->owner_static);
     pr_plan_free(g->pr_plan);

@@ -121,7 +121,7 @@ struct sp_graph_s {
     // v holds its neighbours of lower rank number (higher degree), ascending,
     // as 32-bit ids and (where they fit) as 16-bit ones; each entry's row; and
     // per vertex u the entries that name it, each as {row start, entry}.
-    int32_t *tc_orp = nullptr;       // device, n + 1; its allocation holds the arrays below too
+    int32_t *tc_orp = nullptr;       // device, n + 1
     int32_t *tc_iptr = nullptr;      // device, n + 1
     int32_t *tc_oci = nullptr;       // tc_m (+ padding)
     uint16_t *tc_olo = nullptr;      // tc_m (+ padding): low 16 bits of tc_oci
@@ -131,9 +131,10 @@ struct sp_graph_s {
                                      // below kTcLow, and of the others
     int32_t tc_units_n[2] = {0, 0};  // units of either
     int64_t tc_m = 0;                // oriented entries, on either route
+    std::vector<void *> tc_blocks;   // what either route's arrays lie in
     // Triangle counting of flat and small graphs: row v holds its neighbours above
     // v by (degree, id), in row order, and each entry's row.
-    int32_t *tc_pair_orp = nullptr;  // device, n + 1; its allocation holds the arrays below too
+    int32_t *tc_pair_orp = nullptr;  // device, n + 1
     int32_t *tc_pair_oci = nullptr, *tc_pair_osrc = nullptr;  // tc_m
     bool tc_mixed = false;           // some row is not ascending: never by pairs
     bool tc_no_index = false;        // the index did not fit: always by pairs

@@ -44,7 +44,7 @@ constexpr int32_t kTcHot = 4096;      // ids whose names are counted in LDS firs
 constexpr int32_t kTcNamedTile = 1 << 15, kTcNamedLeast = 1 << 11;  // entries of a block's tile
 constexpr int32_t kTcSortCap = 8192;   // bitonic rows (a row of a higher id holds under 4,400 entries)
 constexpr int32_t kTcFlat = 48;        // see tc_by_pairs
-constexpr int64_t kTcSmall = 1 << 17, kTcLight = 1 << 27;
+constexpr int64_t kTcSmall = 1 << 22, kTcLight = 1 << 27;
 }  // namespace
 
 // rank(a) < rank(b): lower degree, ties broken by id.
@@ -64,6 +64,7 @@ template <int LPR>
 __global__ __launch_bounds__(256) void k_tc_pair_len(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                                                      int32_t n, int32_t *odeg, unsigned long long *found) {
     __shared__ unsigned long long s_red[1];
+    constexpr int kFly = LPR == 1 ? 1 : 4;  // entries of a lane in flight
     const int l = threadIdx.x % LPR;
     unsigned long long by_rank = 0;
     bool mixed = false;
@@ -71,11 +72,24 @@ __global__ __launch_bounds__(256) void k_tc_pair_len(const int32_t *__restrict__
          v += (int64_t)gridDim.x * (256 / LPR)) {
         const int32_t b = rp[v], e = rp[v + 1], dv = e - b, bv = rank_bucket(dv);
         int32_t d = 0;
-        for (int32_t k = b + l; k < e; k += LPR) {
-            const int32_t u = ci[k], du = rp[u + 1] - rp[u], bu = rank_bucket(du);
-            d += rank_below(dv, (int32_t)v, du, u);
-            by_rank += bu < bv || (bu == bv && u > v);
-            mixed |= k > b && u < ci[k - 1];
+        for (int32_t k0 = b + l; k0 < e; k0 += kFly * LPR) {
+            int32_t u[kFly], before[kFly], du[kFly];
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) {
+                const int32_t k = min(k0 + q * LPR, e - 1);
+                u[q] = ci[k];
+                before[q] = ci[max(k - 1, b)];
+            }
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) du[q] = rp[u[q] + 1] - rp[u[q]];
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) {
+                if (k0 + q * LPR >= e) continue;
+                const int32_t bu = rank_bucket(du[q]);
+                d += rank_below(dv, (int32_t)v, du[q], u[q]);
+                by_rank += bu < bv || (bu == bv && u[q] > v);
+                mixed |= u[q] < before[q];
+            }
         }
         for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, kWave);
         if (l == 0) odeg[v] = d;
@@ -88,26 +102,29 @@ template <int LPR>
 __global__ __launch_bounds__(256) void k_tc_pair_fill(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                                                       int32_t n, const int32_t *__restrict__ orp, int32_t *oci,
                                                       int32_t *osrc) {
+    constexpr int kFly = LPR == 1 ? 1 : 4;
     const int l = threadIdx.x % LPR;
     for (int64_t v = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR; v < n;
          v += (int64_t)gridDim.x * (256 / LPR)) {
         const int32_t b = rp[v], e = rp[v + 1], dv = e - b;
         int32_t at = orp[v];
-        for (int32_t k0 = b; k0 < e; k0 += LPR) {
-            const int32_t k = k0 + l;
-            int32_t u = 0;
-            bool keep = false;
-            if (k < e) {
-                u = ci[k];
-                keep = rank_below(dv, (int32_t)v, rp[u + 1] - rp[u], u);
+        for (int32_t k0 = b; k0 < e; k0 += kFly * LPR) {
+            int32_t u[kFly], du[kFly];
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) u[q] = ci[min(k0 + q * LPR + l, e - 1)];
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) du[q] = rp[u[q] + 1] - rp[u[q]];
+#pragma unroll
+            for (int q = 0; q < kFly; ++q) {
+                const bool keep = k0 + q * LPR + l < e && rank_below(dv, (int32_t)v, du[q], u[q]);
+                const unsigned long long m = LPR == 1 ? (unsigned long long)keep : __ballot(keep);
+                if (keep) {
+                    const int32_t p = at + (LPR == 1 ? 0 : lanes_below(m));
+                    oci[p] = u[q];
+                    osrc[p] = (int32_t)v;
+                }
+                at += __popcll(m);
             }
-            const unsigned long long m = LPR == 1 ? (unsigned long long)keep : __ballot(keep);
-            if (keep) {
-                const int32_t p = at + (LPR == 1 ? 0 : lanes_below(m));
-                oci[p] = u;
-                osrc[p] = (int32_t)v;
-            }
-            at += __popcll(m);
         }
     }
 }
@@ -712,44 +729,88 @@ __global__ void k_tc_zero(unsigned long long *p, int64_t n) {
 // Host side
 // ---------------------------------------------------------------------------
 namespace {
-// Arrays carved from one device allocation each (an allocation or release
-// costs tens of microseconds, as much as building a small graph's rows);
-// freed unless kept.
+// Arrays carved from few device allocations; freed unless kept.  One of under 2
+// MB takes 1 us, a larger one 250 to 490 (3 MB in one 284, in three 4): arrays
+// below that share blocks that stay below it, the others one block of their own.
+constexpr size_t kTcBlockLess = 2000 << 10;
+
 struct TcBlock {
-    void *base = nullptr;
+    struct Part {
+        void **at;
+        size_t bytes;
+        bool beside;  // in the block of the array before it, right behind
+    };
+    std::vector<Part> parts;
+    std::vector<void *> blocks;
     size_t bytes = 0;
-    std::vector<std::pair<void **, size_t>> parts;
     template <class T>
-    void add(T **p, size_t count) {
-        parts.emplace_back((void **)p, bytes);
-        bytes += (sizeof(T) * count + 255) & ~(size_t)255;
+    void add(T **p, size_t count, bool beside = false) {
+        parts.push_back({(void **)p, (sizeof(T) * count + 255) & ~(size_t)255, beside});
     }
     sp_status alloc() {
-        SP_TRY(dev_alloc(&base, bytes));
-        for (auto &x : parts) *x.first = (char *)base + x.second;
+        struct Block {
+            size_t used;
+            bool small;
+        };
+        std::vector<Block> plan;
+        std::vector<std::pair<size_t, size_t>> place;  // block, offset
+        for (size_t i = 0; i < parts.size(); ++i) {
+            size_t b = parts[i].beside ? place.back().first : plan.size();
+            if (!parts[i].beside) {
+                size_t need = parts[i].bytes;
+                for (size_t j = i + 1; j < parts.size() && parts[j].beside; ++j) need += parts[j].bytes;
+                const bool small = need <= kTcBlockLess;
+                for (size_t j = 0; j < plan.size(); ++j)
+                    if (plan[j].small == small && (!small || plan[j].used + need <= kTcBlockLess)) b = j;
+                if (b == plan.size()) plan.push_back({0, small});
+            }
+            place.emplace_back(b, plan[b].used);
+            plan[b].used += parts[i].bytes;
+        }
+        blocks.assign(plan.size(), nullptr);
+        for (size_t b = 0; b < plan.size(); ++b) {
+            SP_TRY(dev_alloc(&blocks[b], plan[b].used));
+            bytes += plan[b].used;
+        }
+        for (size_t i = 0; i < parts.size(); ++i) *parts[i].at = (char *)blocks[place[i].first] + place[i].second;
         return SP_OK;
     }
-    ~TcBlock() { dev_free(base); }
+    void keep_with(sp_graph g) {
+        g->tc_blocks.insert(g->tc_blocks.end(), blocks.begin(), blocks.end());
+        blocks.clear();
+        g->bytes += bytes;
+    }
+    ~TcBlock() {
+        for (void *b : blocks) dev_free(b);
+    }
 };
 }  // namespace
 
 // Which graphs are counted by pairs rather than by bitmaps: flat ones (rows of
-// at most kTcFlat entries); others without an index yet, that are small
-// (kTcSmall entries; an eighth of it where the vertices' shares are counted too,
-// an atomic for every triangle) or light (entries x longest row).  First and
-// later counts, us, by pairs and by bitmaps:
+// at most kTcFlat entries); others without an index yet, that are small (entries
+// x average row at most kTcSmall; a 32nd of it where the vertices' shares are
+// counted too, an atomic for every triangle) or light (entries x longest row).
+// First and later counts, us, by pairs and by bitmaps, and entries x average row:
 //   uniform, 2^20 vertices, 16.8 M entries, rows to 41     1426  643    2506  804
 //   uniform, 2^20 vertices, 33.5 M entries, rows to 63     4742 2360    4205 1493
 //   road grid, 2.25 M vertices                              205   59    1290  112
-//   rmat-12, 97,000 entries                                 175  111     318   95
-//   rmat-13, 204,000 entries, rows to 2,228                 325  143     314   99
 //   uniform, 8,192 vertices, 0.5 M entries, rows to 96      250  110     426  135
 //   uniform, 65,536 vertices, 4.2 M entries, rows to 108    660  458     658  221
+//   rmat, 65,536 vertices, 0.25 M entries                   190   84     352   98   1.0 M
+//   rmat, 32,768 vertices, 0.24 M entries                   198  103     329   98   1.8 M
+//   rmat, 16,384 vertices, 0.23 M entries                   213  124     334   96   3.2 M
+//   rmat, 262,144 vertices, 1.0 M entries                   396  194     548  105   4.0 M
+//   rmat, 8,192 vertices, 0.20 M entries                    231  142     308   98   5.1 M
+//   rmat, 131,072 vertices, 1.0 M entries                   414  233     470  110   7.6 M
+//   rmat, 65,536 vertices, 1.8 M entries                    715  499     494  128    51 M
+// and by vertex, later counts: 8,192 vertices, 31,000 entries 113 and 123 (0.11 M),
+// 2,048 vertices, 26,000 entries 183 and 136 (0.32 M).
 static bool tc_by_pairs(sp_graph g, bool per) {
     if (g->tc_mixed) return false;
     if (g->max_degree <= kTcFlat || g->tc_no_index) return true;
     if (g->tc_orp) return false;
-    return per ? g->nnz <= kTcSmall / 8 : g->nnz <= kTcSmall || g->nnz * g->max_degree <= kTcLight;
+    const int64_t spread = g->nnz * g->nnz / g->n;
+    return per ? spread <= kTcSmall / 32 : spread <= kTcSmall || g->nnz * g->max_degree <= kTcLight;
 }
 
 bool tc_built(sp_graph g, bool per) {
@@ -775,7 +836,7 @@ static sp_status ensure_pairs(sp_graph g, bool *mixed, hipStream_t s) {
     unsigned long long *found;
     TcBlock keep, work;
     keep.add(&orp, vn + 1);
-    keep.add(&found, 2);  // right behind orp: both come back in one copy
+    keep.add(&found, 2, true);  // right behind orp: both come back in one copy
     keep.add(&oci, me + 1);
     keep.add(&osrc, me + 1);
     work.add(&tiles, (size_t)scan_tiles((int64_t)vn));
@@ -807,11 +868,11 @@ static sp_status ensure_pairs(sp_graph g, bool *mixed, hipStream_t s) {
                            (const int32_t *)orp, oci, osrc);
     SP_HIP(hipGetLastError());
     SP_HIP(hipStreamSynchronize(s));
-    g->bytes += keep.bytes;
+    keep.keep_with(g);
     g->tc_pair_oci = oci;
     g->tc_pair_osrc = osrc;
     g->tc_m = m;
-    g->tc_pair_orp = (int32_t *)std::exchange(keep.base, nullptr);  // the block begins with orp
+    g->tc_pair_orp = orp;
     return SP_OK;
 }
 
@@ -837,7 +898,7 @@ static sp_status ensure_index(sp_graph g, hipStream_t s) {
     const int32_t hi_cap = nu > lows ? (int32_t)(me / kTcUnit) + std::min(nu - lows, rest) + 1 : 0;
     TcBlock keep, work;
     keep.add(&orp, vn + 1);
-    keep.add(&ctl, 3);  // right behind orp: both come back in one copy
+    keep.add(&ctl, 3, true);  // right behind orp: both come back in one copy
     keep.add(&iptr, vn + 1);
     keep.add(&oci, padded);
     keep.add(&olo, padded);
@@ -909,7 +970,7 @@ static sp_status ensure_index(sp_graph g, hipStream_t s) {
         SP_HIP(hipMemcpyAsync(un, count, sizeof(un), hipMemcpyDeviceToHost, s));
     }
     SP_HIP(hipStreamSynchronize(s));
-    g->bytes += keep.bytes;
+    keep.keep_with(g);
     g->tc_oci = oci;
     g->tc_olo = olo;
     g->tc_osrc = osrc;
@@ -920,7 +981,7 @@ static sp_status ensure_index(sp_graph g, hipStream_t s) {
     g->tc_units_n[0] = std::min(un[0], lo_cap);
     g->tc_units_n[1] = std::min(un[1], hi_cap);
     g->tc_m = m;
-    g->tc_orp = (int32_t *)std::exchange(keep.base, nullptr);  // the block begins with orp
+    g->tc_orp = orp;
     return SP_OK;
 }
 

@@ -26,7 +26,7 @@ import sys, numpy as np
 sys.path.insert(0, %r)
 import oracle
 from paper_2305_03317_amd import graphs, sp
-rp, ci = graphs.rmat(14, 16, seed=5)
+rp, ci = graphs.uniform(8192, 800000, 5)
 g = sp.sp_graph_upload(rp, ci)
 for per in (True, False, True):
     total, each = sp.sp_triangle_count(g, per_vertex=per)
@@ -115,7 +115,7 @@ def test_routes_against_the_oracle(name, first):
 
 
 def test_index_that_does_not_fit():
-    """No allocation over 2.5 MB: the rows alone (1.8 MB) serve where the index (4 MB) does not fit."""
-    env = dict(os.environ, SP_TEST_FAIL_ALLOC_OVER="2500000")
+    """No allocation over 9 MB: the rows alone (6.4 MB) serve where the index (12.8 MB) does not fit."""
+    env = dict(os.environ, SP_TEST_FAIL_ALLOC_OVER="9000000")
     r = subprocess.run([sys.executable, "-c", CHILD], env=env, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and r.stdout.startswith("ok"), (r.stdout, r.stderr)
