@@ -614,7 +614,7 @@ constexpr double kPrDiffUnit = 0x1p62;
 // renumbered by degree rank ("ids" below; the vertex of id x is old[x]).
 constexpr int kPrRowClasses = 6;
 struct PrView {
-    const int32_t *col;      // row entries, as ids
+    const int32_t *col;      // row entries, as ids: the graph's, rank_ci, or a directed graph's renumbered ones
     const int2 *rows;        // n: {first entry, entries} of the i-th row; null: from rp
     const int32_t *rp;       // n + 1: the graph's offsets of the rows gathered
     const int32_t *order;    // n: id of the i-th row; null: i
@@ -628,16 +628,16 @@ struct PrView {
 };
 struct PrPlan {
     PrView view{};           // tile0 is filled per launch (it depends on the block size)
-    void *rows = nullptr;    // device allocation of view.rows, .order, .out_deg
-    int32_t *col = nullptr;  // device: the renumbered entries of a directed graph; null: rank_ci or the graph's own
+    std::vector<void *> blocks;  // the device memory of view's arrays but rp and (when the graph's or rank_ci) col
+    size_t bytes = 0;        // of blocks
     const int32_t *old_id = nullptr, *new_id = nullptr;  // device, null when not renumbered
-    void *split = nullptr;   // device allocation of view.split, .pieces, .piece_row
     int32_t n_split = 0;     // rows of class 0
 };
 void pr_plan_free(PrPlan *p);
 
 struct PrWorkspace {
     int device = -1;
+    std::vector<void *> blocks;             // the device memory of the arrays below
     double *pr[2] = {nullptr, nullptr};     // V each: PageRank by iteration parity
     double *share[2] = {nullptr, nullptr};  // V each: pr / out-degree (0 without out-edges)
     double *partial = nullptr;              // pieces + 1: sums of the split rows' pieces

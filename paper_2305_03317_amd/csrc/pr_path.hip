@@ -36,6 +36,7 @@
 // device reports done.
 #include <type_traits>
 
+#include "blocks.h"
 #include "capture.h"
 #include "common.h"
 #include "devutil.h"
@@ -309,9 +310,7 @@ constexpr int32_t kPrPiece = 8192;  // rows from here on are split into pieces (
 
 void pr_plan_free(PrPlan *p) {
     if (!p) return;
-    dev_free(p->rows);
-    dev_free(p->col);
-    dev_free(p->split);
+    for (void *b : p->blocks) dev_free(b);
     delete p;
 }
 
@@ -322,14 +321,11 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     const int32_t *rp = g->rp_in, *ci = g->ci_in;
     struct Guard {
         PrPlan *p = new PrPlan;
-        int32_t *tmp = nullptr;
-        ~Guard() {
-            pr_plan_free(p);
-            dev_free(tmp);
-        }
+        ~Guard() { pr_plan_free(p); }
     } gd;
     PrPlan &pl = *gd.p;
     constexpr int32_t longest = kPrPiece - 1;
+    const size_t vn = (size_t)n;
     // renumbered when it pays and its copy fits; the graph's own rows do otherwise
     bool renum = false;
     const bool large = n > kPrRenumberFrom && g->max_degree > 8 && may_be_skewed(g);
@@ -341,27 +337,38 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
             ci = g->rank_ci;
         }
     } else if (large) {
-        sp_status st = ensure_rank_locked(g, s);
-        if (st == SP_OK && rank_skewed(g)) st = dev_alloc((void **)&pl.col, sizeof(int32_t) * (size_t)std::max<int64_t>(g->nnz, 1));
+        const sp_status st = ensure_rank_locked(g, s);
         if (st != SP_OK && st != SP_ERR_OUT_OF_MEMORY) return st;
         if (st != SP_OK) clear_error();
-        renum = pl.col != nullptr;
+        renum = st == SP_OK && rank_skewed(g);
+    }
+    // undirected ranks list the rows by length already, and rows of one class need no list: rows of up to 8
+    // entries, and those of flat graphs, four lanes each (a list costs their first call 0.3 ms and more)
+    int2 *rows = nullptr;  // null: the rows' own offsets serve
+    int32_t *order = nullptr, *out_deg = nullptr, *col = nullptr;
+    bool listed;
+    for (;; renum = false) {
+        listed = renum ? g->directed : g->max_degree > kPrFlat;
+        DevBlocks keep;
+        if (listed) {
+            keep.add(&rows, vn);
+            keep.add(&order, vn);
+        }
+        if (g->directed) keep.add(&out_deg, vn + 1 + (size_t)scan_tiles(n));  // the copied rows' offsets first
+        if (g->directed && renum) keep.add(&col, (size_t)std::max<int64_t>(g->nnz, 1));
+        const sp_status st = keep.alloc();
+        if (st == SP_ERR_OUT_OF_MEMORY && g->directed && renum) {
+            clear_error();
+            continue;
+        }
+        if (st != SP_OK) return st;
+        pl.bytes = keep.give_to(pl.blocks);
+        break;
     }
     if (renum) {
         pl.old_id = g->rank_old;
         pl.new_id = g->rank_new;
     }
-    // undirected ranks list the rows by length already, and rows of one class need no list: rows of up to 8
-    // entries, and those of flat graphs, four lanes each (a list costs their first call 0.3 ms and more)
-    const bool listed = renum ? g->directed : g->max_degree > kPrFlat;
-    const bool plain = !listed;  // the rows' own offsets serve
-    const size_t vn = (size_t)n;
-    const size_t row_bytes = (plain ? 0 : sizeof(int2) * vn) + sizeof(int32_t) * vn * (size_t)(listed + g->directed);
-    if (row_bytes) SP_TRY(dev_alloc(&pl.rows, row_bytes));
-    int2 *rows = plain ? nullptr : (int2 *)pl.rows;
-    int32_t *at = (int32_t *)pl.rows + (plain ? 0 : 2 * vn);
-    int32_t *order = listed ? at : nullptr;
-    int32_t *out_deg = g->directed ? at + (listed ? vn : 0) : nullptr;
     int32_t *row0 = pl.view.row0;
     if (listed) {
         SP_TRY(sort_rows_by_class(rp, pl.old_id, n, longest, order, row0, s));
@@ -376,21 +383,19 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
     }
     const int maxb = device_cu_count() * 8;
     const int vgrid = grid_for(n, 256, maxb);
-    if (out_deg)
-        hipLaunchKernelGGL(k_pr_out_deg, dim3(vgrid), dim3(256), 0, s, (const int32_t *)g->row_ptr, pl.old_id, n,
-                           out_deg);
     int32_t *off = nullptr;
-    if (pl.col) {
-        SP_TRY(dev_alloc((void **)&gd.tmp, sizeof(int32_t) * (size_t)(n + 1 + scan_tiles(n))));
-        off = gd.tmp;
+    if (col) {
+        off = out_deg;
         launch_row_offsets(rp, order, pl.old_id, n, off, off + n + 1, s);
-        launch_renumber(rp, ci, order, pl.old_id, pl.new_id, off, row0[2], n, pl.col, s);
+        launch_renumber(rp, ci, order, pl.old_id, pl.new_id, off, row0[2], n, col, s);
     }
     if (rows)
         hipLaunchKernelGGL(k_pr_rows, dim3(vgrid), dim3(256), 0, s, rp, (const int32_t *)order, pl.old_id,
                            (const int32_t *)off, n, rows);
+    if (out_deg)
+        hipLaunchKernelGGL(k_pr_out_deg, dim3(vgrid), dim3(256), 0, s, (const int32_t *)g->row_ptr, pl.old_id, n,
+                           out_deg);
     SP_HIP(hipGetLastError());
-    size_t split_bytes = 0;
     const int32_t ns = row0[1];  // a row per kPrPiece entries at most
     if (ns > 0) {
         std::vector<int2> srow((size_t)ns), split((size_t)ns), pieces;
@@ -412,27 +417,31 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
             }
             split[j].y = (int32_t)pieces.size() - split[j].x;
         }
-        const size_t sb = sizeof(int2) * (size_t)ns, pb = sizeof(int2) * pieces.size(), ob = sizeof(int32_t) * owner.size();
-        split_bytes = sb + pb + ob;
-        SP_TRY(dev_alloc(&pl.split, split_bytes));
-        char *d = (char *)pl.split;
-        SP_HIP(hipMemcpyAsync(d, split.data(), sb, hipMemcpyHostToDevice, s));
-        SP_HIP(hipMemcpyAsync(d + sb, pieces.data(), pb, hipMemcpyHostToDevice, s));
-        SP_HIP(hipMemcpyAsync(d + sb + pb, owner.data(), ob, hipMemcpyHostToDevice, s));
+        int2 *d_split, *d_pieces;
+        int32_t *d_owner;
+        DevBlocks keep;
+        keep.add(&d_split, split.size());
+        keep.add(&d_pieces, pieces.size());
+        keep.add(&d_owner, owner.size());
+        SP_TRY(keep.alloc());
+        SP_HIP(hipMemcpyAsync(d_split, split.data(), sizeof(int2) * split.size(), hipMemcpyHostToDevice, s));
+        SP_HIP(hipMemcpyAsync(d_pieces, pieces.data(), sizeof(int2) * pieces.size(), hipMemcpyHostToDevice, s));
+        SP_HIP(hipMemcpyAsync(d_owner, owner.data(), sizeof(int32_t) * owner.size(), hipMemcpyHostToDevice, s));
         SP_HIP(hipStreamSynchronize(s));
-        pl.view.split = (const int2 *)d;
-        pl.view.pieces = (const int2 *)(d + sb);
-        pl.view.piece_row = (const int32_t *)(d + sb + pb);
+        pl.view.split = d_split;
+        pl.view.pieces = d_pieces;
+        pl.view.piece_row = d_owner;
+        pl.bytes += keep.give_to(pl.blocks);
         pl.view.n_pieces = (int32_t)pieces.size();
         pl.n_split = ns;
     }
     SP_HIP(hipStreamSynchronize(s));
-    pl.view.col = pl.col ? pl.col : ci;
+    pl.view.col = col ? col : ci;
     pl.view.rows = rows;
     pl.view.rp = rp;
     pl.view.order = order;
     pl.view.out_deg = out_deg;
-    g->bytes += row_bytes + split_bytes + (pl.col ? sizeof(int32_t) * (size_t)g->nnz : 0);
+    g->bytes += pl.bytes;
     g->pr_plan = gd.p;
     gd.p = nullptr;
     return SP_OK;
@@ -444,18 +453,16 @@ sp_status ensure_pr_plan(sp_graph g, hipStream_t s) {
 sp_status pr_ws_create(sp_graph g, PrWorkspace &ws) {
     const size_t n = (size_t)std::max(g->n, 1);
     SP_HIP(hipGetDevice(&ws.device));
-    sp_status st = SP_OK;
-    for (int p = 0; p < 2 && st == SP_OK; ++p) {
-        st = dev_alloc((void **)&ws.pr[p], sizeof(double) * n);
-        if (st == SP_OK) st = dev_alloc((void **)&ws.share[p], sizeof(double) * n);
+    DevBlocks keep;
+    for (int p = 0; p < 2; ++p) {
+        keep.add(&ws.pr[p], n);
+        keep.add(&ws.share[p], n);
     }
-    if (st == SP_OK) st = dev_alloc((void **)&ws.partial, sizeof(double) * ((size_t)g->pr_plan->view.n_pieces + 1));
-    if (st == SP_OK) st = dev_alloc((void **)&ws.arrived, sizeof(int32_t) * ((size_t)g->pr_plan->n_split + 1));
-    if (st == SP_OK) st = dev_alloc((void **)&ws.ctl, sizeof(PrCtl));
-    if (st != SP_OK) {
-        pr_ws_destroy(ws);
-        return st;
-    }
+    keep.add(&ws.partial, (size_t)g->pr_plan->view.n_pieces + 1);
+    keep.add(&ws.arrived, (size_t)g->pr_plan->n_split + 1);
+    keep.add(&ws.ctl, 1);
+    SP_TRY(keep.alloc());
+    keep.give_to(ws.blocks);
     if (hipHostMalloc((void **)&ws.ctl_host, sizeof(PrCtl), hipHostMallocDefault) != hipSuccess) {
         ws.ctl_host = nullptr;
         pr_ws_destroy(ws);
@@ -473,13 +480,7 @@ sp_status pr_ws_create(sp_graph g, PrWorkspace &ws) {
 void pr_ws_destroy(PrWorkspace &ws) {
     if (ws.iters.exec) (void)hipGraphExecDestroy(ws.iters.exec);
     if (ws.cap_stream) (void)hipStreamDestroy(ws.cap_stream);
-    for (int p = 0; p < 2; ++p) {
-        dev_free(ws.pr[p]);
-        dev_free(ws.share[p]);
-    }
-    dev_free(ws.partial);
-    dev_free(ws.arrived);
-    dev_free(ws.ctl);
+    for (void *b : ws.blocks) dev_free(b);
     if (ws.ctl_host) (void)hipHostFree(ws.ctl_host);
     if (ws.ev0) (void)hipEventDestroy(ws.ev0);
     if (ws.ev1) (void)hipEventDestroy(ws.ev1);

@@ -37,9 +37,10 @@ inline int32_t rank_count(sp_graph g, int32_t deg) { return g->rank_first[rank_b
 // to replace the weights 97 and 71, 414 and 347, 501 and 402, 714 and 494, 1,117
 // and 726.
 constexpr int32_t kRenumberFrom = 1 << 20;
-// PageRank (once a graph): from here on 20 iterations win back what the copy
-// takes (first call, rmat, edge factor 16, with and without: 420,000 vertices
-// 2.7 and 2.7 ms, 600,000 3.0 and 3.5, 4,000,000 12.5 and 21.1).
+// PageRank (once a graph): from here on two calls of 20 iterations, and soon one,
+// win back what the copy takes (rmat, edge factor 16, with and without: 410,000
+// vertices first 2.4 and 2.0 ms, then 1.24 and 1.78; first, 600,000 vertices 3.0
+// and 3.5, 4,000,000 12.5 and 21.1).
 constexpr int32_t kPrRenumberFrom = 400000;
 // Per-source passes: four sources, copy made, with and without: 600,000
 // vertices 2.2 and 1.9 ms, 1,000,000 3.29 and 3.33, 2,000,000 5.4 and 6.4,

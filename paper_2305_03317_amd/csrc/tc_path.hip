@@ -26,6 +26,7 @@
 // it saves: they are counted by binary searches, entry by entry (tc_by_pairs).
 #include <utility>
 
+#include "blocks.h"
 #include "common.h"
 #include "devutil.h"
 #include "levels.h"
@@ -728,64 +729,6 @@ __global__ void k_tc_zero(unsigned long long *p, int64_t n) {
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-namespace {
-// Arrays carved from few device allocations; freed unless kept.  One of under 2
-// MB takes 1 us, a larger one 250 to 490 (3 MB in one 284, in three 4): arrays
-// below that share blocks that stay below it, the others one block of their own.
-constexpr size_t kTcBlockLess = 2000 << 10;
-
-struct TcBlock {
-    struct Part {
-        void **at;
-        size_t bytes;
-        bool beside;  // in the block of the array before it, right behind
-    };
-    std::vector<Part> parts;
-    std::vector<void *> blocks;
-    size_t bytes = 0;
-    template <class T>
-    void add(T **p, size_t count, bool beside = false) {
-        parts.push_back({(void **)p, (sizeof(T) * count + 255) & ~(size_t)255, beside});
-    }
-    sp_status alloc() {
-        struct Block {
-            size_t used;
-            bool small;
-        };
-        std::vector<Block> plan;
-        std::vector<std::pair<size_t, size_t>> place;  // block, offset
-        for (size_t i = 0; i < parts.size(); ++i) {
-            size_t b = parts[i].beside ? place.back().first : plan.size();
-            if (!parts[i].beside) {
-                size_t need = parts[i].bytes;
-                for (size_t j = i + 1; j < parts.size() && parts[j].beside; ++j) need += parts[j].bytes;
-                const bool small = need <= kTcBlockLess;
-                for (size_t j = 0; j < plan.size(); ++j)
-                    if (plan[j].small == small && (!small || plan[j].used + need <= kTcBlockLess)) b = j;
-                if (b == plan.size()) plan.push_back({0, small});
-            }
-            place.emplace_back(b, plan[b].used);
-            plan[b].used += parts[i].bytes;
-        }
-        blocks.assign(plan.size(), nullptr);
-        for (size_t b = 0; b < plan.size(); ++b) {
-            SP_TRY(dev_alloc(&blocks[b], plan[b].used));
-            bytes += plan[b].used;
-        }
-        for (size_t i = 0; i < parts.size(); ++i) *parts[i].at = (char *)blocks[place[i].first] + place[i].second;
-        return SP_OK;
-    }
-    void keep_with(sp_graph g) {
-        g->tc_blocks.insert(g->tc_blocks.end(), blocks.begin(), blocks.end());
-        blocks.clear();
-        g->bytes += bytes;
-    }
-    ~TcBlock() {
-        for (void *b : blocks) dev_free(b);
-    }
-};
-}  // namespace
-
 // Which graphs are counted by pairs rather than by bitmaps: flat ones (rows of
 // at most kTcFlat entries); others without an index yet, that are small (entries
 // x average row at most kTcSmall; a 32nd of it where the vertices' shares are
@@ -834,7 +777,7 @@ static sp_status ensure_pairs(sp_graph g, bool *mixed, hipStream_t s) {
     const int maxb = device_cu_count() * 8;
     int32_t *orp, *oci, *osrc, *tiles;
     unsigned long long *found;
-    TcBlock keep, work;
+    DevBlocks keep, work;
     keep.add(&orp, vn + 1);
     keep.add(&found, 2, true);  // right behind orp: both come back in one copy
     keep.add(&oci, me + 1);
@@ -868,7 +811,7 @@ static sp_status ensure_pairs(sp_graph g, bool *mixed, hipStream_t s) {
                            (const int32_t *)orp, oci, osrc);
     SP_HIP(hipGetLastError());
     SP_HIP(hipStreamSynchronize(s));
-    keep.keep_with(g);
+    g->bytes += keep.give_to(g->tc_blocks);
     g->tc_pair_oci = oci;
     g->tc_pair_osrc = osrc;
     g->tc_m = m;
@@ -896,7 +839,7 @@ static sp_status ensure_index(sp_graph g, hipStream_t s) {
     const int32_t lows = std::min(nu, kTcLow), rest = (int32_t)std::min<int64_t>(nu, (int64_t)me / 8);
     const int32_t lo_cap = (int32_t)(me / kTcUnit) + std::min(lows, rest) + 1;
     const int32_t hi_cap = nu > lows ? (int32_t)(me / kTcUnit) + std::min(nu - lows, rest) + 1 : 0;
-    TcBlock keep, work;
+    DevBlocks keep, work;
     keep.add(&orp, vn + 1);
     keep.add(&ctl, 3, true);  // right behind orp: both come back in one copy
     keep.add(&iptr, vn + 1);
@@ -970,7 +913,7 @@ static sp_status ensure_index(sp_graph g, hipStream_t s) {
         SP_HIP(hipMemcpyAsync(un, count, sizeof(un), hipMemcpyDeviceToHost, s));
     }
     SP_HIP(hipStreamSynchronize(s));
-    keep.keep_with(g);
+    g->bytes += keep.give_to(g->tc_blocks);
     g->tc_oci = oci;
     g->tc_olo = olo;
     g->tc_osrc = osrc;
